@@ -59,6 +59,17 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
 
 def _hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
+    # codes-only builds (no fp32 output: epilogue on the transposed product)
+    ("gemm_mid.hip", "gemm_mid_w4_co", ["-DDYBIT_MID_W=0", "-DDYBIT_WB=2"]),
+    ("gemm_mid.hip", "gemm_mid_w8_co", ["-DDYBIT_MID_W=2", "-DDYBIT_WB=2"]),
+    ("gemm_mid.hip", "gemm_mid_w6_co", ["-DDYBIT_MID_W=4", "-DDYBIT_WB=2"]),
+    ("gemm_mid.hip", "gemm_mid_w2_co", ["-DDYBIT_MID_W=6", "-DDYBIT_WB=2"]),
+    ("gemm_f8.hip", "gemm_f8_w4_co", ["-DDYBIT_F8_W=0", "-DDYBIT_WB=2"]),
+    ("gemm_f8.hip", "gemm_f8_w2_co", ["-DDYBIT_F8_W=6", "-DDYBIT_WB=2"]),
+    ("gemm_ws.hip", "gemm_ws_w4_co", ["-DDYBIT_WS_W=0", "-DDYBIT_WB=2"]),
+    ("gemm_ws.hip", "gemm_ws_w8_co", ["-DDYBIT_WS_W=2", "-DDYBIT_WB=2"]),
+    ("gemm_ws.hip", "gemm_ws_w6_co", ["-DDYBIT_WS_W=4", "-DDYBIT_WB=2"]),
+    ("gemm_ws.hip", "gemm_ws_w2_co", ["-DDYBIT_WS_W=6", "-DDYBIT_WB=2"]),
         if cand and (os.path.sep not in cand or os.path.exists(cand)):
             return cand
     return "hipcc"

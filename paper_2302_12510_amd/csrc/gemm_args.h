@@ -6,7 +6,9 @@
 #ifndef DYBIT_WB
 #define DYBIT_WB 0
 #endif
-#if DYBIT_WB
+#if DYBIT_WB == 2
+#define DYBIT_WB_NAME(name) name##_co
+#elif DYBIT_WB
 #define DYBIT_WB_NAME(name) name##_wb
 #else
 #define DYBIT_WB_NAME(name) name
@@ -14,6 +16,10 @@
 
 namespace dybit {
 
+// The builds of a kernel source, by what its epilogue writes: fp32 results; fp32 results and / or their DyBit codes;
+// codes only (codes_epilogue.h: the three kernel families that the codes-only chain runs on).
+enum : int { OUT_FP32 = 0, OUT_WRITE_BACK = 1, OUT_CODES = 2 };
+constexpr int kOut = DYBIT_WB;
 constexpr bool kWriteBack = DYBIT_WB != 0;
 
 struct GemmArgs {
@@ -46,6 +52,15 @@ struct GemmArgs {
     int64_t a_bytes, w_bytes;        // sizes of the two code buffers
 };
 
+// Whether a write-back call can take the codes-only build (codes_epilogue.h): no fp32 output or shortcut; results that
+// an unsigned format can hold (that epilogue encodes magnitudes); a shortcut given as codes in whole, aligned words
+// per row (rows of codes out are whole words by the entry points' checks).
+inline bool codes_only(const GemmArgs &g)
+{
+    return g.q_out && !g.C && !g.residual && (g.relu || g.q_signed) &&
+           (!g.res_codes || (g.res_row_bytes % 4 == 0 && (reinterpret_cast<uintptr_t>(g.res_codes) & 3u) == 0));
+}
+
 // Overrides of the automatic kernel choice (0 = automatic everywhere).  They start from the
 // environment, read once when the library is first used (DYBIT_GEMM_KERNEL, DYBIT_GEMM_MFMA,
 // DYBIT_MID_TILE, DYBIT_MID_KGROUPS, DYBIT_GEMM_WS), and change only through dybit_set_option.
@@ -69,7 +84,9 @@ hipError_t take_hip_error();       // ... and this last: the first error noted s
 // (gemm_fast.hip, 256 x 256) and the mid-size-tile kernel (gemm_mid.hip, 128 x 128), one
 // translation unit per weight format.  a_bits is 4 or 8; signedness comes from g.
 // Every kernel source is compiled twice: plain, and with DYBIT_WB=1 as the write-back build whose
-// epilogue also encodes the results (g.q_out must then be set); those entry points end in _wb.
+// epilogue also encodes the results (g.q_out must then be set); those entry points end in _wb.  The
+// weight-stationary, 128 x 128 and e4m3 kernels are compiled a third time (DYBIT_WB=2, _co) for calls that want
+// codes only (codes_only() below).
 bool launch_gemm_fast_w0(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 4-bit signed
 bool launch_gemm_fast_w2(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 8-bit signed
 bool launch_gemm_fast_w4(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 6-bit signed
@@ -87,6 +104,10 @@ bool launch_gemm_mid_w0_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t
 bool launch_gemm_mid_w2_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 bool launch_gemm_mid_w4_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 bool launch_gemm_mid_w6_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_mid_w0_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_mid_w2_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_mid_w4_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_mid_w6_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 
 // Weight-stationary kernel (gemm_ws.hip) for layers whose decoded weight matrix fits the LDS of a
 // compute unit (N <= 128, N rounded up to 64 or 128 rows of 2 K + 16 bytes within 160 KiB); one
@@ -99,6 +120,10 @@ bool launch_gemm_ws_w0_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t 
 bool launch_gemm_ws_w2_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 bool launch_gemm_ws_w4_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 bool launch_gemm_ws_w6_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_ws_w0_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_ws_w2_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_ws_w4_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+bool launch_gemm_ws_w6_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 
 // fp8 matrix path for pairs of 4-bit formats with signed weights (gemm_f8.hip): the 256 x 256 tile
 // when `large`, else the 128 x 128 tile.
@@ -120,6 +145,8 @@ void launch_gemm_general_a8_wb(const GemmArgs &g, int w_bits, bool conv, int mod
 
 // Picks a tiled kernel for the problem (gemm_dispatch.cpp).  Returns false when the problem does
 // not meet their preconditions; the caller then uses the general kernel.
+bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
+bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st);
 
 // Folds a lane's maximum of |c| into the running maximum: wave reduction, then at most one atomic

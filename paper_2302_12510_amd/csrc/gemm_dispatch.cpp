@@ -129,15 +129,19 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     // it is taken where it was measured faster than the 128 x 128 kernel (M x N x K from 401408 x 256 x 64 to
     // 25088 x 1024 x 256): with the write-back epilogue and a short K, 1.05 to 1.25 times; with fp32 results
     // only its 256-byte row segments lose to the tile's 512-byte ones.
+    // which build of a kernel family writes what the call asks for
+    const bool wb = g.q_out != nullptr, codes = codes_only(g);
+#define DYBIT_BUILD_OF(name) (codes ? name##_co : wb ? name##_wb : name)
+
     const bool ws_wide = g.q_out != nullptr && g.K <= 256 && (g.C == nullptr || g.K >= 128);
     if (force == DYBIT_FORCE_WS || (!force && !opt.ws_off && g.M >= 16384 && (g.N <= 128 || ws_wide))) {
         const bool wb_ = g.q_out != nullptr;
         bool done = false;
         switch (w_bits) {
-            case 4: done = (wb_ ? launch_gemm_ws_w0_wb : launch_gemm_ws_w0)(g, a_bits, conv, st); break;
-            case 8: done = (wb_ ? launch_gemm_ws_w2_wb : launch_gemm_ws_w2)(g, a_bits, conv, st); break;
-            case 6: done = (wb_ ? launch_gemm_ws_w4_wb : launch_gemm_ws_w4)(g, a_bits, conv, st); break;
-            case 2: done = (wb_ ? launch_gemm_ws_w6_wb : launch_gemm_ws_w6)(g, a_bits, conv, st); break;
+            case 4: done = DYBIT_BUILD_OF(launch_gemm_ws_w0)(g, a_bits, conv, st); break;
+            case 8: done = DYBIT_BUILD_OF(launch_gemm_ws_w2)(g, a_bits, conv, st); break;
+            case 6: done = DYBIT_BUILD_OF(launch_gemm_ws_w4)(g, a_bits, conv, st); break;
+            case 2: done = DYBIT_BUILD_OF(launch_gemm_ws_w6)(g, a_bits, conv, st); break;
         }
         if (done) return true;
     }
@@ -157,10 +161,9 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     }
     // two operands of 4 or 2 bits: every value is exact in e4m3, so the fp8 matrix path (twice the
     // fp16 rate, byte decoders) takes them unless the "gemm_mfma" option asks for the fp16 kernels
-    const bool wb = g.q_out != nullptr;                             // write-back builds of the same kernels
     if (low_pair && !rows && !opt.mfma_f16) {
-        if (w_bits == 4) return (wb ? launch_gemm_f8_w0_wb : launch_gemm_f8_w0)(g, a_bits, conv, large, st);
-        return (wb ? launch_gemm_f8_w6_wb : launch_gemm_f8_w6)(g, a_bits, conv, large, st);
+        if (w_bits == 4) return DYBIT_BUILD_OF(launch_gemm_f8_w0)(g, a_bits, conv, large, st);
+        return DYBIT_BUILD_OF(launch_gemm_f8_w6)(g, a_bits, conv, large, st);
     }
     if (rows) large = false;
     if (large) {                                                   // declines a 2- or 6-bit operand unless K (Cin) is a multiple of 128
@@ -171,10 +174,11 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
         else done = (wb ? launch_gemm_fast_w2_wb : launch_gemm_fast_w2)(g, a_bits, conv, st);
         if (done) return true;
     }
-    if (w_bits == 4) return (wb ? launch_gemm_mid_w0_wb : launch_gemm_mid_w0)(g, a_bits, conv, st);
-    if (w_bits == 6) return (wb ? launch_gemm_mid_w4_wb : launch_gemm_mid_w4)(g, a_bits, conv, st);
-    if (w_bits == 2) return (wb ? launch_gemm_mid_w6_wb : launch_gemm_mid_w6)(g, a_bits, conv, st);
-    return (wb ? launch_gemm_mid_w2_wb : launch_gemm_mid_w2)(g, a_bits, conv, st);
+    if (w_bits == 4) return DYBIT_BUILD_OF(launch_gemm_mid_w0)(g, a_bits, conv, st);
+    if (w_bits == 6) return DYBIT_BUILD_OF(launch_gemm_mid_w4)(g, a_bits, conv, st);
+    if (w_bits == 2) return DYBIT_BUILD_OF(launch_gemm_mid_w6)(g, a_bits, conv, st);
+    return DYBIT_BUILD_OF(launch_gemm_mid_w2)(g, a_bits, conv, st);
+#undef DYBIT_BUILD_OF
 }
 
 }  // namespace dybit

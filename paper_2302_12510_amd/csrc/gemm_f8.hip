@@ -28,6 +28,7 @@
 
 #include <type_traits>
 
+#include "codes_epilogue.h"
 #include "dybit_codec.h"
 #include "dybit_codec8.h"
 #include "gemm_args.h"
@@ -49,7 +50,7 @@ template <int NWM, int KG> struct Geom {
     static constexpr int THREADS = 64 * NWM * KG;
 };
 
-template <int FMT_A, int FMT_W, bool CONV, int NWM, int KG, bool WB>
+template <int FMT_A, int FMT_W, bool CONV, int NWM, int KG, int OUT>
 __global__ __launch_bounds__(64 * NWM * KG, NWM == 2 ? 4 : (NWM == 4 && KG == 1) ? 3 : 2)
 void gemm_f8_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
 {
@@ -71,6 +72,9 @@ void gemm_f8_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
     int tile_m, tile_n;
     if (!panel_order_tile(xcd_contiguous_index(), tiles_m, tiles_n, tile_m, tile_n)) return;   // uniform per workgroup
     const int64_t m0 = (int64_t)tile_m * T, n0 = (int64_t)tile_n * T;
+
+    float *const cols = reinterpret_cast<float *>(lds + G::LDS_BYTES);   // codes only: factors and biases of the tile's columns
+    if constexpr (OUT == OUT_CODES) stage_columns<CB, 0>(g, n0, cols);
 
     const __amdgpu_buffer_rsrc_t rsrcA = code_descriptor(g.A, g.a_bytes), rsrcW = code_descriptor(g.W, g.w_bytes);
 
@@ -181,7 +185,8 @@ void gemm_f8_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
             for (int j = 0; j < CB; ++j) {
                 const int q = b * CB + j;
                 if (q == NQ - R) __syncthreads();
-                acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[q % R], acc[j], 0, 0, 0, 0, 0, 0);
+                acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[q % R], fa_cur, acc[j], 0, 0, 0, 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[q % R], acc[j], 0, 0, 0, 0, 0, 0);
                 const int qn = q + R;
                 fw[q % R] = qn < NQ ? read_W(cur, qn / CB, qn % CB) : read_W(nxt, (qn - NQ) / CB, (qn - NQ) % CB);
                 if (q == 0) stage_W(rawW[s ^ 1], 0, nxt);
@@ -223,24 +228,30 @@ void gemm_f8_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
     }
 
     // ---- epilogue: C = acc * (sA sW) (+ bias) (ReLU), running maximum
-    epilogue_strip<CB, WB>(g, acc, m0 + wr * 32, n0);
+    if constexpr (OUT == OUT_CODES) {
+        const float mx = epilogue_strip_codes<CB, 0>(g, acc, m0 + wr * 32, n0, cols, false, out_scale(g));
+        if (g.absmax_bits) fold_absmax(g.absmax_bits, mx);
+    } else {
+        epilogue_strip<CB, OUT != OUT_FP32>(g, acc, m0 + wr * 32, n0);
+    }
 }
 
 template <int FA, int FW, int NWM, int KG>
 static void launch_cfg(const GemmArgs &g, bool conv, hipStream_t st)
 {
     using G = Geom<NWM, KG>;
+    constexpr int lds_bytes = G::LDS_BYTES + (kOut == OUT_CODES ? column_bytes<NWM>() : 0);
     const int tiles_m = (int)((g.M + G::T - 1) / G::T), tiles_n = (int)((g.N + G::T - 1) / G::T);
     const dim3 grid((unsigned)((tiles_m * tiles_n + 7) / 8 * 8)), block(G::THREADS);
     note_kernel(NWM == 8 ? DYBIT_KERNEL_F8_256 : NWM == 2 ? DYBIT_KERNEL_F8_64 : KG == 1 ? DYBIT_KERNEL_F8_128_KG1 : DYBIT_KERNEL_F8_128_KG2);
     if (conv) {
-        auto k = gemm_f8_kernel<FA, FW, true, NWM, KG, kWriteBack>;
-        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES));
-        hipLaunchKernelGGL(k, grid, block, G::LDS_BYTES, st, g, tiles_m, tiles_n);
+        auto k = gemm_f8_kernel<FA, FW, true, NWM, KG, kOut>;
+        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        hipLaunchKernelGGL(k, grid, block, lds_bytes, st, g, tiles_m, tiles_n);
     } else {
-        auto k = gemm_f8_kernel<FA, FW, false, NWM, KG, kWriteBack>;
-        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES));
-        hipLaunchKernelGGL(k, grid, block, G::LDS_BYTES, st, g, tiles_m, tiles_n);
+        auto k = gemm_f8_kernel<FA, FW, false, NWM, KG, kOut>;
+        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        hipLaunchKernelGGL(k, grid, block, lds_bytes, st, g, tiles_m, tiles_n);
     }
 }
 

@@ -26,6 +26,7 @@
 
 #include <type_traits>
 
+#include "codes_epilogue.h"
 #include "dybit_codec.h"
 #include "gemm_args.h"
 #include "tile_common.h"
@@ -59,7 +60,7 @@ static_assert(Geom<2>::LDS_BYTES >= 4 * 4 * 16 * 64 * 4, "reduction buffer must 
 // right of the image are masked to code 0.
 constexpr int ROWS = 2;
 
-template <int FMT_A, int FMT_W, int CONV, int KG, bool WB>
+template <int FMT_A, int FMT_W, int CONV, int KG, int OUT>
 __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
 {
     using CA = Codec<FMT_A>;
@@ -85,6 +86,10 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     // ROWS reads aligned words; the dispatcher takes it only for tensors of a whole number of words, so
     // the descriptor ends exactly with the tensor and no word reaches past it
     const __amdgpu_buffer_rsrc_t rsrcA = code_descriptor(g.A, g.a_bytes), rsrcW = code_descriptor(g.W, g.w_bytes);
+
+    float *const cols = reinterpret_cast<float *>(lds + Geom<KG>::LDS_BYTES);   // codes only: factors and biases of the tile's columns
+    bool big = false;
+    if constexpr (OUT == OUT_CODES) big = stage_columns<4, CA::ACC_EXP + CW::ACC_EXP>(g, n0, cols);
 
     // ---- A: the lane's own row, the 32 codes kq of its k-group's 64
     const int a_row_bytes = (int)(g.K * CA::BITS / 8), w_row_bytes = (int)(g.K * CW::BITS / 8);
@@ -238,7 +243,8 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
             const f16x8 fa_cur = fa;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
+                acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[j], fa_cur, acc[j], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
                 fw[j] = kk < 3 ? read_W(cur, kk + 1, j) : read_W(nxt, 0, j);
             }
             fa = kk < 3 ? decode_A(rawA[s], kk + 1) : decode_A(rawA[s ^ 1], 0);
@@ -280,15 +286,20 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     }
 
     // ---- epilogue: C = acc * (sA sW) (+ bias) (ReLU), running maximum
-    epilogue_strip<4, WB, true, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m0 + wr * 32, n0);
+    if constexpr (OUT == OUT_CODES) {
+        const float mx = epilogue_strip_codes<4, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m0 + wr * 32, n0, cols, big, out_scale(g));
+        if (g.absmax_bits) fold_absmax(g.absmax_bits, mx);
+    } else {
+        epilogue_strip<4, OUT != OUT_FP32, true, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m0 + wr * 32, n0);
+    }
 }
 
 template <int FA, int FW, int CONV, int KG>
 static void launch_one(const GemmArgs &g, hipStream_t st, int tiles_m, int tiles_n)
 {
     const dim3 grid((unsigned)((tiles_m * tiles_n + 7) / 8 * 8), 1, 1), block(256 * KG);
-    constexpr int lds_bytes = Geom<KG>::LDS_BYTES;
-    auto k = gemm_mid_kernel<FA, FW, CONV, KG, kWriteBack>;
+    constexpr int lds_bytes = Geom<KG>::LDS_BYTES + (kOut == OUT_CODES ? column_bytes<4>() : 0);
+    auto k = gemm_mid_kernel<FA, FW, CONV, KG, kOut>;
     note_kernel(CONV == ROWS ? DYBIT_KERNEL_F16_128_ROWS : KG == 1 ? DYBIT_KERNEL_F16_128_KG1 : DYBIT_KERNEL_F16_128_KG2);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     hipLaunchKernelGGL(k, grid, block, lds_bytes, st, g, tiles_m, tiles_n);

@@ -22,6 +22,7 @@
 
 #include <type_traits>
 
+#include "codes_epilogue.h"
 #include "dybit_codec.h"
 #include "dybit_codec8.h"
 #include "gemm_args.h"
@@ -40,14 +41,14 @@ using namespace fast;
 // Waves per workgroup (32 rows each).  Eight; four in the write-back build of the two-block form, whose
 // epilogue needs about 170 registers: three four-wave workgroups then share a compute unit (three waves per
 // SIMD) where a single eight-wave one would fit, and the encoder of one overlaps the K loops of the others.
-template <int CB, bool WB> constexpr int waves_of() { return (WB && CB == 2) ? 4 : 8; }
+template <int CB, int OUT> constexpr int waves_of() { return (OUT != OUT_FP32 && CB == 2) ? 4 : 8; }
 // Workgroups of the persistent grid per compute unit: what the weight tiles in LDS (160 KiB) and the registers
 // allow (two-block form: two eight-wave workgroups at 128 registers, three four-wave ones at 168 in the
 // write-back build; four-block form: one).
 template <int CB> inline int workgroups_per_cu(int lds_bytes)
 {
     const int by_lds = (160 * 1024) / lds_bytes;
-    const int by_regs = CB == 2 ? (kWriteBack ? 3 : 2) : 1;
+    const int by_regs = CB == 2 ? (kOut == OUT_CODES ? 4 : kOut == OUT_WRITE_BACK ? 3 : 2) : 1;
     return by_lds < by_regs ? (by_lds < 1 ? 1 : by_lds) : by_regs;
 }
 
@@ -81,6 +82,22 @@ inline int grid_for_groups(int slabs, int groups, int resident)
     return walkers * groups;
 }
 
+// The kernel's arguments, read again from the kernel-argument segment by each call: the persistent loop's epilogue has a
+// variant per format of its codes, and the compiler otherwise computes the uniform values of all of them once, before the
+// loop, where they exceed the scalar registers (157 spilled, each a v_readlane per slab) -- the scalar loads are cheaper.
+__device__ __forceinline__ GemmArgs reload_args()
+{
+    struct Words { uint64_t w[sizeof(GemmArgs) / 8]; } words;
+    static_assert(sizeof(Words) == sizeof(GemmArgs), "whole 64-bit words");
+    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();     // GemmArgs is the kernels' first argument
+    asm volatile("" : "+s"(at));
+    const auto *p = (const __attribute__((address_space(4))) uint64_t *)at;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(GemmArgs) / 8; ++i) words.w[i] = p[i];
+    const GemmArgs a = __builtin_bit_cast(GemmArgs, words);
+    return a;
+}
+
 // CONV: 0 matrix product; 1 convolution whose 64-code k groups lie inside one filter tap (Cin a
 // multiple of 64); 2 (ROWS) convolution with few channels where one filter row is exactly one 32-code
 // run (kw * Cin = 32): the run of lane-half kq in K step t is filter row 2 t + kq of the lane's output
@@ -89,10 +106,10 @@ inline int grid_for_groups(int slabs, int groups, int resident)
 // workgroups share a compute unit (four waves per SIMD) when their weight tiles both fit its LDS.
 constexpr int ROWS = 2;
 
-template <int FMT_A, int FMT_W, int CONV, int CB, bool WB>
-__global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) : 2)) void gemm_ws_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
+template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
+__global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
-    constexpr int THREADS = 64 * waves_of<CB, WB>(), SLAB = 32 * waves_of<CB, WB>();
+    constexpr int THREADS = 64 * waves_of<CB, OUT>(), SLAB = 32 * waves_of<CB, OUT>();
     using CA = Codec<FMT_A>;
     using CW = Codec<FMT_W>;
     constexpr int WORDS_A = CA::BITS;                               // 32-bit words in a run of 32 codes
@@ -126,7 +143,16 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
             }
         }
     }
-    __syncthreads();
+    // codes only: the columns' factors and biases go behind the weight tile (its barrier is the one that ends the staging)
+    float *const cols = reinterpret_cast<float *>(lds + CB * 32 * row_bytes);
+    bool big = false;
+    OutScale os{};
+    if constexpr (OUT == OUT_CODES) {
+        big = stage_columns<CB, CA::ACC_EXP + CW::ACC_EXP>(g, cg.n0, cols);
+        os = out_scale(g);
+    } else {
+        __syncthreads();
+    }
 
     const int a_row_bytes = (int)(g.K * CA::BITS / 8);
     const int pix_bytes = CONV ? g.pix_bytes : 0;
@@ -249,7 +275,9 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
                 for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const f16x8 *>(wk + kk * 16 + j * 32 * row_bytes);
                 fa = kk < 3 ? decode_A(rawA[s], kk + 1) : decode_A(rawA[s ^ 1], 0);
 #pragma unroll
-                for (int j = 0; j < CB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
+                for (int j = 0; j < CB; ++j)
+                    acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[j], fa_cur, acc[j], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
                 if (kk == 3) load_A(rawA[s]);
             }
         };
@@ -257,7 +285,10 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
             step(kt, std::integral_constant<int, 0>{});
             if (kt + 1 < ktiles) step(kt + 1, std::integral_constant<int, 1>{});
         }
-        run_max = fmaxf(run_max, epilogue_strip<CB, WB, false, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m_strip, cg.n0));
+        if constexpr (OUT == OUT_CODES)
+            run_max = fmaxf(run_max, epilogue_strip_codes<CB, CA::ACC_EXP + CW::ACC_EXP>(reload_args(), acc, m_strip, cg.n0, cols, big, os));
+        else
+            run_max = fmaxf(run_max, epilogue_strip<CB, OUT != OUT_FP32, false, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m_strip, cg.n0));
     }
 
     // ---- running maximum: one merge per workgroup.  The persistent waves finish their strips in step,
@@ -289,10 +320,10 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
 // CONV: 0 matrix product, 1 convolution with Cin a multiple of 64.
 // ---------------------------------------------------------------------------
 #if DYBIT_WS_W == 0 || DYBIT_WS_W == 6
-template <int FMT_A, int FMT_W, int CONV, int CB, bool WB>
-__global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) : 2)) void gemm_ws8_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
+template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
+__global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws8_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
-    constexpr int THREADS = 64 * waves_of<CB, WB>(), SLAB = 32 * waves_of<CB, WB>();
+    constexpr int THREADS = 64 * waves_of<CB, OUT>(), SLAB = 32 * waves_of<CB, OUT>();
     using f8::i32x8;
     constexpr int BA = f8::bits_of<FMT_A>(), BW = f8::bits_of<FMT_W>();
     constexpr int RUN_A = 4 * BA, RUN_W = 4 * BW;                    // bytes of a run of 32 codes
@@ -326,7 +357,14 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
             *reinterpret_cast<u32x4 *>(dst + 16) = u32x4{(u32)f[4], (u32)f[5], (u32)f[6], (u32)f[7]};
         }
     }
-    __syncthreads();
+    float *const cols = reinterpret_cast<float *>(lds + CB * 32 * row_bytes);
+    OutScale os{};
+    if constexpr (OUT == OUT_CODES) {
+        stage_columns<CB, 0>(g, cg.n0, cols);
+        os = out_scale(g);
+    } else {
+        __syncthreads();
+    }
 
     const int a_row_bytes = (int)(g.K * BA / 8);
     const int pix_bytes = CONV ? g.pix_bytes : 0;
@@ -389,14 +427,16 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
             fa = f8::decode_fragment<FMT_A, true>(rawA[s ^ 1]);
 #pragma unroll
             for (int j = 0; j < CB; ++j)
-                acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[j], acc[j], 0, 0, 0, 0, 0, 0);
+                acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[j], fa_cur, acc[j], 0, 0, 0, 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[j], acc[j], 0, 0, 0, 0, 0, 0);
             rawA[s] = load_A();
         };
         for (int kt = 0; kt < ktiles; kt += 2) {
             step(kt, std::integral_constant<int, 0>{});
             if (kt + 1 < ktiles) step(kt + 1, std::integral_constant<int, 1>{});
         }
-        run_max = fmaxf(run_max, epilogue_strip<CB, WB, false, 0>(g, acc, m_strip, cg.n0));
+        if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, 0>(reload_args(), acc, m_strip, cg.n0, cols, false, os));
+        else run_max = fmaxf(run_max, epilogue_strip<CB, OUT != OUT_FP32, false, 0>(g, acc, m_strip, cg.n0));
     }
 
     if (g.absmax_bits) {                                            // one merge per workgroup, as in the fp16 form
@@ -419,12 +459,12 @@ __global__ __launch_bounds__((64 * waves_of<CB, WB>()), (CB == 2 ? (WB ? 3 : 4) 
 template <int FA, int FW, int CONV, int CB>
 static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_bytes)
 {
-    constexpr int THREADS = 64 * waves_of<CB, kWriteBack>(), SLAB = 32 * waves_of<CB, kWriteBack>();
+    constexpr int THREADS = 64 * waves_of<CB, kOut>(), SLAB = 32 * waves_of<CB, kOut>();
     const int slabs = (int)((g.M + SLAB - 1) / SLAB);
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));
     if (grid < 1) return false;
-    auto k = gemm_ws8_kernel<FA, FW, CONV, CB, kWriteBack>;
+    auto k = gemm_ws8_kernel<FA, FW, CONV, CB, kOut>;
     note_kernel(DYBIT_KERNEL_F8_WS);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
@@ -435,12 +475,12 @@ static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds
 template <int FA, int FW, int CONV, int CB>
 static bool launch_cb(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_bytes)
 {
-    constexpr int THREADS = 64 * waves_of<CB, kWriteBack>(), SLAB = 32 * waves_of<CB, kWriteBack>();
+    constexpr int THREADS = 64 * waves_of<CB, kOut>(), SLAB = 32 * waves_of<CB, kOut>();
     const int slabs = (int)((g.M + SLAB - 1) / SLAB);
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));
     if (grid < 1) return false;
-    auto k = gemm_ws_kernel<FA, FW, CONV, CB, kWriteBack>;
+    auto k = gemm_ws_kernel<FA, FW, CONV, CB, kOut>;
     note_kernel(DYBIT_KERNEL_F16_WS);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
@@ -454,11 +494,12 @@ static bool launch(const GemmArgs &g, bool conv, hipStream_t st)
     // leave no registers for the epilogue.  Beyond that the columns go in groups of 64, one group per workgroup.
     const int cb = (g.N <= 64 || g.N > 128) ? 2 : 4;
     const bool rows = conv && g.Cin < 64;                            // kw * Cin = 32 (checked by the dispatcher)
+    const int extra = kOut == OUT_CODES ? (cb == 2 ? column_bytes<2>() : column_bytes<4>()) : 0;
     if (g.M > 0x7fffffff) return false;
 #if DYBIT_WS_W == 0 || DYBIT_WS_W == 6
     // both operands 4- or 2-bit: the fp8 matrix path, unless the "gemm_mfma" option asks for fp16
     if constexpr (FA == F4S || FA == F4U || FA == F2S || FA == F2U) {
-        const int row8 = (int)g.K + 16, lds8 = cb * 32 * row8;
+        const int row8 = (int)g.K + 16, lds8 = cb * 32 * row8 + extra;
         if (!rows && !dispatch_options().mfma_f16 && lds8 <= 160 * 1024) {
             if (cb == 2) return conv ? launch_cb8<FA, FW, 1, 2>(g, st, row8, lds8) : launch_cb8<FA, FW, 0, 2>(g, st, row8, lds8);
             return conv ? launch_cb8<FA, FW, 1, 4>(g, st, row8, lds8) : launch_cb8<FA, FW, 0, 4>(g, st, row8, lds8);
@@ -466,7 +507,7 @@ static bool launch(const GemmArgs &g, bool conv, hipStream_t st)
     }
 #endif
     const int row_bytes = (int)g.K * 2 + 16;
-    const int lds_bytes = cb * 32 * row_bytes;
+    const int lds_bytes = cb * 32 * row_bytes + extra;
     if (lds_bytes > 160 * 1024) return false;
 #define DYBIT_WS_CB(C_) \
     return rows ? launch_cb<FA, FW, ROWS, C_>(g, st, row_bytes, lds_bytes) \

@@ -47,13 +47,12 @@ struct Requant {
     bool ok;            // scale is positive, finite and within [2^-100, 2^100]
 };
 
-__device__ __forceinline__ Requant make_requant(const float *scale, int bits, int is_signed)
+__device__ __forceinline__ Requant make_requant(float s, float rinv, int bits, int is_signed)
 {
     Requant r;
-    const float s = *scale;
     const uint32_t e = (__float_as_uint(s) >> 23) & 0xffu;
     r.ok = s > 0.0f && e >= 27u && e <= 227u;
-    r.rinv = 1.0f / s;
+    r.rinv = rinv;
     r.p = __uint_as_float((254u - e) << 23);
     r.s2 = s * r.p;
     const int m = is_signed ? bits - 1 : bits;
@@ -70,6 +69,11 @@ __device__ __forceinline__ Requant make_requant(const float *scale, int bits, in
     r.sign_mask = is_signed ? (1u << m) : 0u;
     r.sign_shift = (uint32_t)(31 - m);
     return r;
+}
+
+__device__ __forceinline__ Requant make_requant(const float *scale, int bits, int is_signed)
+{
+    return make_requant(*scale, 1.0f / *scale, bits, is_signed);
 }
 
 // Fast path, first half: the bit pattern of (2^m - c) + magic for the value x.  The G low bits are the
@@ -100,6 +104,22 @@ __device__ __forceinline__ uint32_t requant_settle_key(uint32_t zb)
 __device__ __forceinline__ uint32_t requant_magnitude(uint32_t zb, const Requant &r)
 {
     return __builtin_amdgcn_ubfe(Requant::kRound - zb, Requant::G, r.m);
+}
+
+// The same two halves for an epilogue that packs several codes before it complements them (codes_epilogue.h):
+// n = 2^m - c minus one half, on the magic number without the half, so that the bits above the G fraction bits are
+// floor(n - 1/2) = 2^m - 1 - c rounded half down: the complement of the code, in one bit-field extraction.  The fraction
+// bits are zero exactly where those of requant_rounded() are.  x is not negative where the format is unsigned.
+__device__ __forceinline__ uint32_t requant_lower(float x, const Requant &r)
+{
+    const float q = __builtin_amdgcn_fmed3f(fabsf(x) * r.rinv, 0.0f, r.vmax);
+    const float qs = q * __uint_as_float(1u << 23);
+    const float n = __uint_as_float(r.recip_sub - __float_as_uint(qs));
+    return __float_as_uint(n + __uint_as_float(Requant::kMagic - (1u << Requant::G)));
+}
+__device__ __forceinline__ uint32_t requant_complement(uint32_t zb, const Requant &r)
+{
+    return __builtin_amdgcn_ubfe(zb, Requant::G, r.m);
 }
 
 // Exact decision at the midpoint between magnitude codes `code - 1` and `code`, for a value whose
