@@ -51,14 +51,6 @@ SOURCES = [
     ("gemm_ws.hip", "gemm_ws_w8_wb", ["-DDYBIT_WS_W=2", "-DDYBIT_WB=1"]),
     ("gemm_ws.hip", "gemm_ws_w6_wb", ["-DDYBIT_WS_W=4", "-DDYBIT_WB=1"]),
     ("gemm_ws.hip", "gemm_ws_w2_wb", ["-DDYBIT_WS_W=6", "-DDYBIT_WB=1"]),
-    ("diag.hip", "diag", []),
-]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-
-
-def _hipcc() -> str:
-    for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
     # codes-only builds (no fp32 output: epilogue on the transposed product)
     ("gemm_mid.hip", "gemm_mid_w4_co", ["-DDYBIT_MID_W=0", "-DDYBIT_WB=2"]),
     ("gemm_mid.hip", "gemm_mid_w8_co", ["-DDYBIT_MID_W=2", "-DDYBIT_WB=2"]),
@@ -89,7 +81,7 @@ def _compile(item) -> str:
 
 
 # Longest compilations first, so that the pool's last jobs are short ones.
-_ORDER = ("gemm", "gemm_wb", "gemm_mid", "gemm_ws", "gemm_f8", "gemm_fast", "quantize")
+_ORDER = ("gemm", "gemm_wb", "gemm_mid", "gemm_ws", "gemm_f8", "gemm_fast", "gemm_small", "quantize")
 
 
 def _rank(item) -> int:

@@ -71,7 +71,7 @@ struct DispatchOptions {
     int mid_kgroups;   // 0 automatic, 1 or 2: k-groups of the 128 x 128 kernels
     int ws_off;        // 1: the weight-stationary kernel is left out of the automatic choice
 };
-enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4 };
+enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5 };
 DispatchOptions dispatch_options();
 // Record of the kernel a launch function started, per host thread (dybit_last_gemm_kernel reads it),
 // and of a HIP error met on the way (hipFuncSetAttribute, ...), which the entry point then reports.
@@ -145,10 +145,10 @@ void launch_gemm_general_a8_wb(const GemmArgs &g, int w_bits, bool conv, int mod
 
 // Picks a tiled kernel for the problem (gemm_dispatch.cpp).  Returns false when the problem does
 // not meet their preconditions; the caller then uses the general kernel.
-bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
-bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st);
 
+bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
+bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 // Folds a lane's maximum of |c| into the running maximum: wave reduction, then at most one atomic
 // per wave.  Non-negative floats order like their bit patterns; fmaxf has already dropped NaNs.
 // Atomics on one address serialise (about 10 ns each), and a large layer has tens of thousands of

@@ -2,7 +2,8 @@
 //
 // All need signed weights, K (convolution: Cin) a multiple of 64 (2- and 6-bit operands on the 256 x 256 kernel: of 128) so that
 // a 64-wide k group is one run of whole 128-bit loads inside one filter tap, 16-byte aligned
-// code buffers, and buffers below 2 GiB (32-bit buffer offsets).  The 256 x 256 kernel does the
+// code buffers, and buffers below 2 GiB (32-bit buffer offsets).  A matrix product with any other K from 64 on (rows that
+// start at any byte, ragged.h) runs on the small-output and the 128 x 128 fp16 kernel.  The 256 x 256 kernel does the
 // least decode work per MFMA and is used when its tiles can fill the 256 compute units, N is
 // wide enough for them and K is long enough for the main loop to outweigh the epilogue; the
 // 128 x 128 kernel takes the rest.  dybit_set_option (initial values: the environment, read once)
@@ -31,7 +32,8 @@ bool apply_option(const char *name, const char *value)
     const bool is_auto = !strcmp(value, "auto");
     if (!strcmp(name, "gemm_kernel")) {
         const int v = is_auto ? 0 : !strcmp(value, "general") ? DYBIT_FORCE_GENERAL : !strcmp(value, "mid") ? DYBIT_FORCE_MID
-                    : !strcmp(value, "large") ? DYBIT_FORCE_LARGE : !strcmp(value, "ws") ? DYBIT_FORCE_WS : -1;
+                    : !strcmp(value, "large") ? DYBIT_FORCE_LARGE : !strcmp(value, "ws") ? DYBIT_FORCE_WS
+                    : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : -1;
         if (v < 0) return false;
         opt_kernel = v;
     } else if (!strcmp(name, "gemm_mfma")) {
@@ -106,10 +108,25 @@ void launch_gemm_general_wb(const GemmArgs &g, int a_bits, int w_bits, bool conv
     }
 }
 
+// Whether the small-output kernel is the faster one: it decodes each code for 32 rows or columns of use where a tile of the
+// others decodes it for 64 to 256, so it wins as long as those leave most of the device idle.  The line is drawn in tiles of
+// 64 x 64.  Measured over M from 1 to 12544, N from 32 to 4096, K from 256 to 4608 (us, the kernel it replaces -> this one):
+// against the 128 x 128 fp16 kernel (8-bit pair) 128 x 1000 x 1024 (32 tiles) 13.4 -> 7.4, 3136 x 256 x 1024 (196) 15.4 -> 13.7,
+// 1024 x 1024 x 4096 (256) 35.4 -> 29.1, but 12544 x 128 x 1152 (392) 17.5 -> 20.8; against the 64 x 64 e4m3 kernel (4-bit
+// pair) 512 x 512 x 4096 (64) 13.9 -> 9.2, 784 x 512 x 4608 (104) 17.5 -> 15.9, but 128 x 4096 x 1024 (128) 6.9 -> 7.8.  Rows
+// that start at any byte: 1200 x 1200 x 1532 (361) 17.9 -> 20.6 against the 128 x 128 kernel.  Long and narrow products stay
+// on the weight-stationary kernel.
+static bool small_output(const GemmArgs &g, bool ragged, bool e4m3)
+{
+    if (!ragged && g.M >= 16384) return false;
+    return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= (e4m3 ? 104 : 256);
+}
+
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st)
 {
     if (!g.w_signed) return false;                                  // every width 2, 4, 6, 8 has a decoder; weights are signed
-    if (g.M < 1 || g.N < 1 || g.K < 64 || g.K % 64) return false;
+    if (g.M < 1 || g.N < 1 || g.K < 64 || (conv && g.K % 64)) return false;
+    const bool ragged = g.K % 64 != 0;                              // a matrix product whose rows start at any byte
     // a convolution needs whole 64-code k groups inside a filter tap, or (few channels) filter rows of
     // exactly 32 codes, which the 128 x 128 kernel fetches row by row
     const bool dense = conv && (int64_t)g.pix_bytes * 8 == (int64_t)g.Cin * a_bits;   // not one channel group of a wider image
@@ -117,6 +134,10 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     if (conv && g.Cin % 64 && !rows) return false;
     if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 15) return false;
     if (g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff) return false;
+
+    // which build of a kernel family writes what the call asks for
+    const bool wb = g.q_out != nullptr, codes = codes_only(g);
+#define DYBIT_BUILD_OF(name) (codes ? name##_co : wb ? name##_wb : name)
 
     bool large;
     const bool low_pair = (a_bits == 4 || a_bits == 2) && (w_bits == 4 || w_bits == 2);
@@ -129,13 +150,8 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     // it is taken where it was measured faster than the 128 x 128 kernel (M x N x K from 401408 x 256 x 64 to
     // 25088 x 1024 x 256): with the write-back epilogue and a short K, 1.05 to 1.25 times; with fp32 results
     // only its 256-byte row segments lose to the tile's 512-byte ones.
-    // which build of a kernel family writes what the call asks for
-    const bool wb = g.q_out != nullptr, codes = codes_only(g);
-#define DYBIT_BUILD_OF(name) (codes ? name##_co : wb ? name##_wb : name)
-
     const bool ws_wide = g.q_out != nullptr && g.K <= 256 && (g.C == nullptr || g.K >= 128);
-    if (force == DYBIT_FORCE_WS || (!force && !opt.ws_off && g.M >= 16384 && (g.N <= 128 || ws_wide))) {
-        const bool wb_ = g.q_out != nullptr;
+    if (!ragged && (force == DYBIT_FORCE_WS || (!force && !opt.ws_off && g.M >= 16384 && (g.N <= 128 || ws_wide)))) {
         bool done = false;
         switch (w_bits) {
             case 4: done = DYBIT_BUILD_OF(launch_gemm_ws_w0)(g, a_bits, conv, st); break;
@@ -161,11 +177,11 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     }
     // two operands of 4 or 2 bits: every value is exact in e4m3, so the fp8 matrix path (twice the
     // fp16 rate, byte decoders) takes them unless the "gemm_mfma" option asks for the fp16 kernels
-    if (low_pair && !rows && !opt.mfma_f16) {
+    if (low_pair && !rows && !ragged && !opt.mfma_f16) {
         if (w_bits == 4) return DYBIT_BUILD_OF(launch_gemm_f8_w0)(g, a_bits, conv, large, st);
         return DYBIT_BUILD_OF(launch_gemm_f8_w6)(g, a_bits, conv, large, st);
     }
-    if (rows) large = false;
+    if (rows || ragged) large = false;
     if (large) {                                                   // declines a 2- or 6-bit operand unless K (Cin) is a multiple of 128
         bool done;
         if (w_bits == 4) done = (wb ? launch_gemm_fast_w0_wb : launch_gemm_fast_w0)(g, a_bits, conv, st);

@@ -29,6 +29,7 @@
 #include "codes_epilogue.h"
 #include "dybit_codec.h"
 #include "gemm_args.h"
+#include "ragged.h"
 #include "tile_common.h"
 #include "tile_epilogue.h"
 
@@ -58,7 +59,8 @@ static_assert(Geom<2>::LDS_BYTES >= 4 * 4 * 16 * 64 * 4, "reduction buffer must 
 // the image from any byte on.  It is fetched as aligned words (one more than the run holds; a word
 // before or past the tensor reads 0) and, when it is decoded, shifted into place and the taps left or
 // right of the image are masked to code 0.
-constexpr int ROWS = 2;
+// 3 (RAGGED) matrix product whose K is not a multiple of 64: rows start at any byte (ragged.h).
+constexpr int ROWS = 2, RAGGED = 3;
 
 template <int FMT_A, int FMT_W, int CONV, int KG, int OUT>
 __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(const GemmArgs g, const int tiles_m, const int tiles_n)
@@ -67,8 +69,10 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     using CW = Codec<FMT_W>;
     constexpr int TK = Geom<KG>::TK, ROW_BYTES = Geom<KG>::ROW_BYTES, STAGE_BYTES = Geom<KG>::STAGE_BYTES;
     constexpr int WORDS_A = CA::BITS;                               // 32-bit words in a run of 32 codes
-    constexpr int NA = CONV == ROWS ? (WORDS_A + 1 + 3) / 4 : (CA::BITS + 3) / 4;   // 128-bit registers per lane and K step
-    constexpr int NW = (CW::BITS + 3) / 4;
+    constexpr int NA = CONV == ROWS ? (WORDS_A + 1 + 3) / 4                          // 128-bit registers per lane and K step
+                     : CONV == RAGGED ? ragged_regs<CA::BITS>() : (CA::BITS + 3) / 4;
+    constexpr int NW = CONV == RAGGED ? ragged_regs<CW::BITS>() : (CW::BITS + 3) / 4;
+    constexpr bool IMAGE = CONV == 1 || CONV == ROWS;
     constexpr int RUN_A = 4 * CA::BITS, RUN_W = 4 * CW::BITS;       // bytes of a run of 32 codes
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
@@ -83,17 +87,20 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     if (!row_order_tile(xcd_contiguous_index(), tiles_m, tiles_n, tile_m, tile_n)) return;   // uniform per workgroup
     const int64_t m0 = (int64_t)tile_m * TM, n0 = (int64_t)tile_n * TN;
 
-    // ROWS reads aligned words; the dispatcher takes it only for tensors of a whole number of words, so
-    // the descriptor ends exactly with the tensor and no word reaches past it
-    const __amdgpu_buffer_rsrc_t rsrcA = code_descriptor(g.A, g.a_bytes), rsrcW = code_descriptor(g.W, g.w_bytes);
-
     float *const cols = reinterpret_cast<float *>(lds + Geom<KG>::LDS_BYTES);   // codes only: factors and biases of the tile's columns
     bool big = false;
     if constexpr (OUT == OUT_CODES) big = stage_columns<4, CA::ACC_EXP + CW::ACC_EXP>(g, n0, cols);
 
+    // ROWS reads aligned words; the dispatcher takes it only for tensors of a whole number of words, so
+    // the descriptor ends exactly with the tensor and no word reaches past it
+    const __amdgpu_buffer_rsrc_t rsrcA = CONV == RAGGED ? word_descriptor(g.A, g.a_bytes) : code_descriptor(g.A, g.a_bytes);
+    const __amdgpu_buffer_rsrc_t rsrcW = CONV == RAGGED ? word_descriptor(g.W, g.w_bytes) : code_descriptor(g.W, g.w_bytes);
+
     // ---- A: the lane's own row, the 32 codes kq of its k-group's 64
     const int a_row_bytes = (int)(g.K * CA::BITS / 8), w_row_bytes = (int)(g.K * CW::BITS / 8);
-    const int pix_bytes = CONV ? g.pix_bytes : 0;
+    const int pix_bytes = IMAGE ? g.pix_bytes : 0;
+    const int64_t ktiles = (g.K + TK - 1) / TK;
+    const int head = (int)(g.K - (ktiles - 1) * TK);                 // RAGGED: codes of K step 0, the later ones are whole
     u32 offA;
     int hi0 = 0, wi0 = 0;
     bool okA;
@@ -103,7 +110,7 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     {
         const int64_t m = m0 + wr * 32 + (lane & 31);
         okA = m < g.M;
-        if (CONV) {
+        if (IMAGE) {
             const PixelOrigin o = pixel_origin(g, okA ? m : 0);
             hi0 = o.hi0;
             wi0 = o.wi0;
@@ -162,6 +169,13 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
             a_k0 += TK;
             return;
         }
+        if constexpr (CONV == RAGGED) {
+            const int64_t kt = (a_k0 - kgp * 64) / TK;
+            load_run_ragged<CA::BITS>(rsrcA, kt < ktiles ? offA + (u32)(((kt ? head - TK : 0) + a_k0) * CA::BITS / 8) : kOob,
+                                      *reinterpret_cast<u32x4(*)[NA]>(raw));
+            a_k0 += TK;
+            return;
+        }
         u32 off;
         if (CONV) {
             const bool in = okA && a_k0 < g.K && tap.inside(g, hi0, wi0);
@@ -174,6 +188,11 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
         if (CONV == 1) tap.advance(TK, g);
     };
     auto load_W = [&](int64_t kt, u32x4 *raw) {
+        if constexpr (CONV == RAGGED) {
+            load_run_ragged<CW::BITS>(rsrcW, kt < ktiles ? offW + (u32)((kt ? head + (kt - 1) * TK : 0) * CW::BITS / 8) : kOob,
+                                      *reinterpret_cast<u32x4(*)[NW]>(raw));
+            return;
+        }
         const int64_t k0 = kt * TK + wq * 32;
         const u32 off = k0 < g.K ? offW + (u32)(kt * TK * CW::BITS / 8) : kOob;
         load_run<CW::BITS>(rsrcW, off, raw);
@@ -189,14 +208,25 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
             for (int i = 0; i < WORDS_A; ++i)
                 t[i >> 2][i & 3] = __builtin_amdgcn_alignbyte(raw[(i + 1) >> 2][(i + 1) & 3], raw[i >> 2][i & 3], shift) & row_keep[i];
             decode_eight<FMT_A>(t, q, d);
+        } else if constexpr (CONV == RAGGED) {
+            u32x4 t[(CA::BITS + 3) / 4];
+            align_run<CA::BITS>(raw, t);
+            decode_eight<FMT_A>(t, q, d);
         } else {
             decode_eight<FMT_A>(raw, q, d);
         }
         return __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]});
     };
-    auto stage_W = [&](const u32x4 *raw, int q, char *tile) {
+    auto stage_W = [&](const u32x4 *raw, int q, char *tile, bool first = false) {
         u32 d[4];
-        decode_eight<FMT_W>(raw, q, d);
+        if constexpr (CONV == RAGGED) {
+            u32x4 t[(CW::BITS + 3) / 4];
+            align_run<CW::BITS>(raw, t);
+            if (first) keep_codes<CW::BITS>(t, head - wq * 32);      // K step 0: the odd part of K
+            decode_eight<FMT_W>(t, q, d);
+        } else {
+            decode_eight<FMT_W>(raw, q, d);
+        }
         *reinterpret_cast<u32x4 *>(tile + wrW + q * 16) = u32x4{d[0], d[1], d[2], d[3]};
     };
     auto read_W = [&](const char *tile, int kk, int j) -> f16x8 {
@@ -220,7 +250,7 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     load_A(rawA[1]);
     load_W(1, rawW[1]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) stage_W(rawW[0], q, lds);
+    for (int q = 0; q < 4; ++q) stage_W(rawW[0], q, lds, true);
     fa = decode_A(rawA[0], 0);
     __syncthreads();
 #pragma unroll
@@ -261,7 +291,6 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const int64_t ktiles = (g.K + TK - 1) / TK;
     for (int64_t kt = 0; kt < ktiles; kt += 2) {                   // an odd number of K steps is padded with a step of zeros
         step(kt, std::integral_constant<int, 0>{});
         step(kt + 1, std::integral_constant<int, 1>{});

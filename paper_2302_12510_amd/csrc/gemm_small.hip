@@ -1,0 +1,204 @@
+// DyBit matrix product for small outputs: 32 rows by 32 or 64 columns of C per workgroup, K split over its waves.
+//
+// The tiled kernels put one workgroup on a 64 x 64 or 128 x 128 tile and walk K serially; a product with few
+// rows (the classifier of a network, a small batch, a narrow layer) then leaves most compute units idle and takes as
+// long as the K loop of one workgroup: 128 x 1000 x 2048 ran on 8 of 256 compute units.  Here a tile is as small as the
+// matrix instruction allows and up to 16 waves share its K: wave w takes K steps w, w + S, w + 2 S, ... (64 codes each),
+// fetches and decodes the codes of both operands itself, straight into fragments (there is nothing to share between waves
+// that work on different k, so no LDS and no barrier inside the loop), and the partial sums are added through LDS in
+// log2 S rounds at the end.  The price is decoding: every code of A is decoded once per column tile and every code of
+// W once per row tile, at 1/32 of the reuse a full tile would have, which is what bounds the kernel once the
+// device is full; the dispatcher takes it below that.
+//
+// Rows of any length (RAGGED) and convolutions with Cin a multiple of 64 as in the other kernels.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "dybit_codec.h"
+#include "gemm_args.h"
+#include "ragged.h"
+#include "tile_common.h"
+#include "tile_epilogue.h"
+
+#ifndef DYBIT_SMALL_W
+#error "compile with -DDYBIT_SMALL_W=<weight format id> (0: 4-bit, 2: 8-bit, 4: 6-bit, 6: 2-bit; signed)"
+#endif
+
+namespace dybit {
+namespace small {
+
+using namespace fast;
+
+enum : int { ROWS_ALIGNED = 0, CONVOLUTION = 1, RAGGED = 3 };   // how the operands' rows are reached
+constexpr int kMaxWaves = 16;
+
+template <int FMT_A, int FMT_W, int MODE, int CB, int OUT>
+__global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_columns)
+{
+    using CA = Codec<FMT_A>;
+    using CW = Codec<FMT_W>;
+    constexpr int BA = CA::BITS, BW = CW::BITS;
+    constexpr int NA = MODE == RAGGED ? ragged_regs<BA>() : (BA + 3) / 4, NW = MODE == RAGGED ? ragged_regs<BW>() : (BW + 3) / 4;
+    extern __shared__ __attribute__((aligned(16))) float red[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = (int)blockDim.x >> 6, kq = lane >> 5;
+    // neighbouring tiles, which share an operand strip, go to the same XCD: by columns when W is the larger operand
+    const int l = xcd_contiguous_index();
+    if (l >= tiles_m * tiles_n) return;                              // uniform per workgroup
+    const int tile_m = by_columns ? l % tiles_m : l / tiles_n, tile_n = by_columns ? l / tiles_m : l % tiles_n;
+    const int64_t m0 = (int64_t)tile_m * 32, n0 = (int64_t)tile_n * (32 * CB);
+
+    const __amdgpu_buffer_rsrc_t rsrcA = MODE == RAGGED ? word_descriptor(g.A, g.a_bytes) : code_descriptor(g.A, g.a_bytes);
+    const __amdgpu_buffer_rsrc_t rsrcW = MODE == RAGGED ? word_descriptor(g.W, g.w_bytes) : code_descriptor(g.W, g.w_bytes);
+    const int a_row_bytes = (int)(g.K * BA / 8), w_row_bytes = (int)(g.K * BW / 8), K = (int)g.K;
+    const int pix_bytes = MODE == CONVOLUTION ? g.pix_bytes : 0;
+    const int64_t m = m0 + (lane & 31);
+    const bool okA = m < g.M;
+    u32 offA, offW[CB];
+    int hi0 = 0, wi0 = 0;
+    TapCounter tap;
+    if (MODE == CONVOLUTION) {
+        const PixelOrigin o = pixel_origin(g, okA ? m : 0);
+        hi0 = o.hi0;
+        wi0 = o.wi0;
+        offA = (u32)(o.first_pixel * pix_bytes + kq * 4 * BA);
+        tap.advance(wave * 64, g);
+    } else {
+        offA = okA ? (u32)(m * a_row_bytes + kq * 4 * BA) : kOob;
+    }
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+        const int64_t n = n0 + j * 32 + (lane & 31);
+        offW[j] = n < g.N ? (u32)(n * w_row_bytes + kq * 4 * BW) : kOob;
+    }
+    const int steps = (K + 63) / 64, head = MODE == RAGGED ? K - (steps - 1) * 64 : 64;   // codes of K step 0
+    auto first_code = [&](int t) { return t == 0 ? 0 : head + (t - 1) * 64; };
+
+    auto load = [&](int t, u32x4 (&a)[NA], u32x4 (&w)[CB][NW]) {
+        const bool in = t < steps;
+        const int k0 = first_code(t);
+        u32 oa;
+        if (MODE == CONVOLUTION) {
+            oa = in && okA && tap.inside(g, hi0, wi0) ? offA + (u32)tap.byte_offset(g, pix_bytes, BA) : kOob;   // padding reads code 0
+            tap.advance(64 * waves, g);
+        } else {
+            oa = in ? offA + (u32)(k0 * BA / 8) : kOob;
+        }
+        if constexpr (MODE == RAGGED) load_run_ragged<BA>(rsrcA, oa, a);
+        else load_run<BA>(rsrcA, oa, a);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const u32 ow = in ? offW[j] + (u32)(k0 * BW / 8) : kOob;
+            if constexpr (MODE == RAGGED) load_run_ragged<BW>(rsrcW, ow, w[j]);
+            else load_run<BW>(rsrcW, ow, w[j]);
+        }
+    };
+
+    f32x16 acc[CB];
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
+
+    auto contract = [&](int t, const u32x4 (&a)[NA], const u32x4 (&w)[CB][NW]) {
+        u32x4 ta[(BA + 3) / 4], tw[CB][(BW + 3) / 4];
+        if constexpr (MODE == RAGGED) {
+            align_run<BA>(a, ta);
+#pragma unroll
+            for (int j = 0; j < CB; ++j) {
+                align_run<BW>(w[j], tw[j]);
+                if (t == 0) keep_codes<BW>(tw[j], head - 32 * kq);   // uniform: the odd part of K
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32 d[4];
+            decode_eight<FMT_A>(MODE == RAGGED ? ta : a, q, d);
+            const f16x8 fa = __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]});
+#pragma unroll
+            for (int j = 0; j < CB; ++j) {
+                decode_eight<FMT_W>(MODE == RAGGED ? tw[j] : w[j], q, d);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]}), acc[j], 0, 0, 0);
+            }
+        }
+    };
+
+    // the codes of two further steps are in flight while one is decoded
+    u32x4 a0[NA], a1[NA], w0[CB][NW], w1[CB][NW];
+    load(wave, a0, w0);
+    load(wave + waves, a1, w1);
+    for (int t = wave; t < steps; t += 2 * waves) {
+        contract(t, a0, w0);
+        load(t + 2 * waves, a0, w0);
+        if (t + waves < steps) contract(t + waves, a1, w1);
+        load(t + 3 * waves, a1, w1);
+    }
+
+    // ---- add the waves' partial sums: in each round the upper half hands its sums to the lower half
+    for (int half = waves >> 1; half > 0; half >>= 1) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) red[(((wave - half) * CB + j) * 16 + v) * 64 + lane] = acc[j][v];
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] += red[((wave * CB + j) * 16 + v) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) epilogue_strip<CB, OUT != OUT_FP32, true, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m0, n0);
+}
+
+template <int FA, int FW, int MODE, int CB>
+static void launch_one(const GemmArgs &g, hipStream_t st)
+{
+    const int tiles_m = (int)((g.M + 31) / 32), tiles_n = (int)((g.N + 32 * CB - 1) / (32 * CB));
+    const int64_t tiles = (int64_t)tiles_m * tiles_n;
+    const int steps = (int)((g.K + 63) / 64);
+    // waves per tile: at most 16 per compute unit in all (what fits at once), and at least one K step each
+    int waves = 1;
+    while (waves < kMaxWaves && waves * 2 <= steps && tiles * waves * 2 <= 4096) waves *= 2;
+    const int lds_bytes = waves / 2 * CB * 16 * 64 * 4;
+    auto k = gemm_small_kernel<FA, FW, MODE, CB, kOut>;
+    note_kernel(DYBIT_KERNEL_F16_SMALL);
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxWaves / 2 * CB * 16 * 64 * 4));
+    hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), lds_bytes, st, g, tiles_m, tiles_n, g.N > g.M ? 1 : 0);
+}
+
+template <int FA, int FW>
+static void launch(const GemmArgs &g, bool conv, hipStream_t st)
+{
+    // 64 columns per tile (half the decoding of A) once that still gives every compute unit a workgroup
+    const bool two = ((g.M + 31) / 32) * ((g.N + 63) / 64) >= 256;
+    if (conv) return two ? launch_one<FA, FW, CONVOLUTION, 2>(g, st) : launch_one<FA, FW, CONVOLUTION, 1>(g, st);
+    if (g.K % 64) return two ? launch_one<FA, FW, RAGGED, 2>(g, st) : launch_one<FA, FW, RAGGED, 1>(g, st);
+    return two ? launch_one<FA, FW, ROWS_ALIGNED, 2>(g, st) : launch_one<FA, FW, ROWS_ALIGNED, 1>(g, st);
+}
+
+}  // namespace small
+
+#define DYBIT_SMALL_NAME2(w) DYBIT_WB_NAME(launch_gemm_small_w##w)
+#define DYBIT_SMALL_NAME(w) DYBIT_SMALL_NAME2(w)
+void DYBIT_SMALL_NAME(DYBIT_SMALL_W)(const GemmArgs &g, int a_bits, bool conv, hipStream_t st)
+{
+    using namespace fast;
+    const int fa = (a_bits == 8 ? F8S : a_bits == 6 ? F6S : a_bits == 2 ? F2S : F4S) + (g.a_signed ? 0 : 1);
+    switch (fa) {
+        case F2S: return small::launch<F2S, DYBIT_SMALL_W>(g, conv, st);
+        case F2U: return small::launch<F2U, DYBIT_SMALL_W>(g, conv, st);
+        case F4S: return small::launch<F4S, DYBIT_SMALL_W>(g, conv, st);
+        case F4U: return small::launch<F4U, DYBIT_SMALL_W>(g, conv, st);
+        case F6S: return small::launch<F6S, DYBIT_SMALL_W>(g, conv, st);
+        case F6U: return small::launch<F6U, DYBIT_SMALL_W>(g, conv, st);
+        case F8S: return small::launch<F8S, DYBIT_SMALL_W>(g, conv, st);
+        case F8U: return small::launch<F8U, DYBIT_SMALL_W>(g, conv, st);
+    }
+}
+
+}  // namespace dybit
