@@ -32,6 +32,18 @@ SOURCES = [
     ("gemm_ws.hip", "gemm_ws_w8", ["-DDYBIT_WS_W=2"]),
     ("gemm_ws.hip", "gemm_ws_w6", ["-DDYBIT_WS_W=4"]),
     ("gemm_ws.hip", "gemm_ws_w2", ["-DDYBIT_WS_W=6"]),
+    ("gemm_small.hip", "gemm_small_w4", ["-DDYBIT_SMALL_W=0"]),
+    ("gemm_small.hip", "gemm_small_w4_wb", ["-DDYBIT_SMALL_W=0", "-DDYBIT_WB=1"]),
+    ("gemm_small.hip", "gemm_small_w8", ["-DDYBIT_SMALL_W=2"]),
+    ("gemm_small.hip", "gemm_small_w8_wb", ["-DDYBIT_SMALL_W=2", "-DDYBIT_WB=1"]),
+    ("gemm_small.hip", "gemm_small_w6", ["-DDYBIT_SMALL_W=4"]),
+    ("gemm_small.hip", "gemm_small_w6_wb", ["-DDYBIT_SMALL_W=4", "-DDYBIT_WB=1"]),
+    ("gemm_small.hip", "gemm_small_w2", ["-DDYBIT_SMALL_W=6"]),
+    ("gemm_small.hip", "gemm_small_w2_wb", ["-DDYBIT_SMALL_W=6", "-DDYBIT_WB=1"]),
+    ("gemm_group.hip", "gemm_group_w4", ["-DDYBIT_GROUP_W=0"]),
+    ("gemm_group.hip", "gemm_group_w8", ["-DDYBIT_GROUP_W=2"]),
+    ("gemm_group.hip", "gemm_group_w6", ["-DDYBIT_GROUP_W=4"]),
+    ("gemm_group.hip", "gemm_group_w2", ["-DDYBIT_GROUP_W=6"]),
     # write-back builds of the same kernels (epilogue also encodes the results as DyBit codes)
     ("gemm.hip", "gemm_wb_a2", ["-DDYBIT_WB=1", "-DDYBIT_GEN_A=2"]),
     ("gemm.hip", "gemm_wb_a4", ["-DDYBIT_WB=1", "-DDYBIT_GEN_A=4"]),
@@ -62,6 +74,14 @@ SOURCES = [
     ("gemm_ws.hip", "gemm_ws_w8_co", ["-DDYBIT_WS_W=2", "-DDYBIT_WB=2"]),
     ("gemm_ws.hip", "gemm_ws_w6_co", ["-DDYBIT_WS_W=4", "-DDYBIT_WB=2"]),
     ("gemm_ws.hip", "gemm_ws_w2_co", ["-DDYBIT_WS_W=6", "-DDYBIT_WB=2"]),
+    ("diag.hip", "diag", []),
+]
+FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+
+
+def _hipcc() -> str:
+    for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if cand and (os.path.sep not in cand or os.path.exists(cand)):
             return cand
     return "hipcc"

@@ -542,11 +542,14 @@ dybit_status conv2d_impl(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t C
                          const uint8_t *X_codes, dybit_fmt x_fmt, const float *x_scale,
                          const uint8_t *Wt_codes, dybit_fmt w_fmt, const float *w_scale,
                          const Epilogue &e, float *Y, dybit_stream stream,
-                         int64_t ldy = 0, int64_t image_channels = 0, int64_t x_bytes_left = 0)
+                         int64_t ldy = 0, int64_t image_channels = 0, int64_t x_bytes_left = 0, int all_groups = 0,
+                         bool *launched = nullptr)
 {
     // ldy / image_channels / x_bytes_left (grouped convolution): X_codes and Y point at one channel group of
     // tensors with image_channels input and ldy output channels per pixel; x_bytes_left bytes of the image
     // tensor remain from X_codes on.  0: dense tensors of Cin and Cout channels.
+    // all_groups: the pointers are those of the first of so many groups; one launch for all of them, if there is
+    // a kernel for it (*launched).
     clear_call_record();
     dybit_status st = check_fmt(x_fmt);
     if (st == DYBIT_OK) st = check_fmt(w_fmt);
@@ -575,6 +578,13 @@ dybit_status conv2d_impl(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t C
     const bool dense = image_channels == Cin;
     g.a_bytes = dense ? B * H * W * (Cin * x_fmt.bits / 8) : x_bytes_left;
     g.w_bytes = Cout * (g.K * w_fmt.bits / 8);
+    if (all_groups) {
+        g.N *= all_groups;
+        g.Cin *= all_groups;
+        g.w_bytes *= all_groups;
+        *launched = launch_group_conv(g, x_fmt.bits, w_fmt.bits, all_groups, (hipStream_t)stream);
+        return *launched ? launch_status() : DYBIT_OK;
+    }
     if (launch_gemm_tiled(g, x_fmt.bits, w_fmt.bits, true, (hipStream_t)stream)) return launch_status();
     // operand access of the general kernel: whole 16-channel vectors, runs of neighbouring taps
     // when there are few channels (the first layer of an image network), else code by code
@@ -740,6 +750,13 @@ extern "C" dybit_status dybit_group_conv2d(int64_t B, int64_t H, int64_t W, int6
     const int64_t group_x = Cg * x_fmt.bits / 8, group_w = Cog * ((int64_t)kh * kw * Cg * w_fmt.bits / 8);
     Epilogue e;
     e.relu = relu; e.absmax = y_absmax; e.w_per_channel = w_per_channel != 0;
+    if (groups > 1) {
+        e.bias = bias; e.residual = residual;
+        bool launched = false;
+        st = conv2d_impl(B, H, W, Cg, Cog, kh, kw, stride, pad, X_codes, x_fmt, x_scale, Wt_codes, w_fmt, w_scale, e, Y, stream,
+                         Cout, Cin, x_bytes, groups, &launched);
+        if (st != DYBIT_OK || launched) return st;
+    }
     for (int64_t gi = 0; gi < groups; ++gi) {
         e.bias = bias ? bias + gi * Cog : nullptr;
         e.residual = residual ? residual + gi * Cog : nullptr;

@@ -125,12 +125,32 @@ bool launch_gemm_ws_w2_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t 
 bool launch_gemm_ws_w4_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 bool launch_gemm_ws_w6_co(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 
+// Small-output kernel (gemm_small.hip): 32-row tiles, K split over the waves of a workgroup; also K not a multiple of 64.
+void launch_gemm_small_w0(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w2(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w4(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w6(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w0_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w2_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w4_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+void launch_gemm_small_w6_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
+
+// Grouped convolution in one launch (gemm_group.hip): g describes the whole layer (Cin and N of all groups, K of one).  false:
+// a group's channels are not whole words, or its weights do not fit the LDS of a compute unit.
+bool launch_group_conv_w0(const GemmArgs &g, int a_bits, int groups, hipStream_t st);
+bool launch_group_conv_w2(const GemmArgs &g, int a_bits, int groups, hipStream_t st);
+bool launch_group_conv_w4(const GemmArgs &g, int a_bits, int groups, hipStream_t st);
+bool launch_group_conv_w6(const GemmArgs &g, int a_bits, int groups, hipStream_t st);
+bool launch_group_conv(const GemmArgs &g, int a_bits, int w_bits, int groups, hipStream_t st);   // gemm_dispatch.cpp
+
 // fp8 matrix path for pairs of 4-bit formats with signed weights (gemm_f8.hip): the 256 x 256 tile
 // when `large`, else the 128 x 128 tile.
 bool launch_gemm_f8_w0(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);      // W 4-bit signed
 bool launch_gemm_f8_w6(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);      // W 2-bit signed
 bool launch_gemm_f8_w0_wb(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 bool launch_gemm_f8_w6_wb(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
+bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
+bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 
 // General kernel (gemm.hip): any format pair and shape.  mode: 0 operands fetched code by code;
 // 1 operands are 16-byte aligned and K (convolution: Cin) is a multiple of 16; 2 (convolution
@@ -147,8 +167,6 @@ void launch_gemm_general_a8_wb(const GemmArgs &g, int w_bits, bool conv, int mod
 // not meet their preconditions; the caller then uses the general kernel.
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st);
 
-bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
-bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 // Folds a lane's maximum of |c| into the running maximum: wave reduction, then at most one atomic
 // per wave.  Non-negative floats order like their bit patterns; fmaxf has already dropped NaNs.
 // Atomics on one address serialise (about 10 ns each), and a large layer has tens of thousands of

@@ -145,6 +145,16 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     const int force = opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
 
+    // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.
+    if (!rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !ragged && !opt.mfma_f16)))) {
+        switch (w_bits) {
+            case 4: (wb ? launch_gemm_small_w0_wb : launch_gemm_small_w0)(g, a_bits, conv, st); return true;
+            case 8: (wb ? launch_gemm_small_w2_wb : launch_gemm_small_w2)(g, a_bits, conv, st); return true;
+            case 6: (wb ? launch_gemm_small_w4_wb : launch_gemm_small_w4)(g, a_bits, conv, st); return true;
+            default: (wb ? launch_gemm_small_w6_wb : launch_gemm_small_w6)(g, a_bits, conv, st); return true;
+        }
+    }
+
     // Weight-stationary kernel: the decoded weights of up to 128 columns (N > 128: of a group of 64) stay in
     // LDS, for many rows against few weights (it declines when the weights do not fit).  Wider than 128 columns
     // it is taken where it was measured faster than the 128 x 128 kernel (M x N x K from 401408 x 256 x 64 to
@@ -195,6 +205,22 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     if (w_bits == 2) return DYBIT_BUILD_OF(launch_gemm_mid_w6)(g, a_bits, conv, st);
     return DYBIT_BUILD_OF(launch_gemm_mid_w2)(g, a_bits, conv, st);
 #undef DYBIT_BUILD_OF
+}
+
+bool launch_group_conv(const GemmArgs &g, int a_bits, int w_bits, int groups, hipStream_t st)
+{
+    const int Cg = g.Cin / groups;
+    // pieces of 8, 16 or 32 codes, whole words, inside one filter tap; 32-bit buffer offsets; no kernel forced
+    if (!g.w_signed || Cg % 8 || (Cg * a_bits) % 32 || g.M > 0x7fffffff || g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff) return false;
+    if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 3) return false;
+    if (dispatch_options().kernel) return false;
+    switch (w_bits) {
+        case 4: return launch_group_conv_w0(g, a_bits, groups, st);
+        case 8: return launch_group_conv_w2(g, a_bits, groups, st);
+        case 6: return launch_group_conv_w4(g, a_bits, groups, st);
+        case 2: return launch_group_conv_w6(g, a_bits, groups, st);
+        default: return false;
+    }
 }
 
 }  // namespace dybit
