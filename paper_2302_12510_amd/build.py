@@ -76,7 +76,7 @@ SOURCES = [
     ("gemm_ws.hip", "gemm_ws_w2_co", ["-DDYBIT_WS_W=6", "-DDYBIT_WB=2"]),
     ("diag.hip", "diag", []),
 ]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
+FLAGS = ["--offload-arch=gfx950", "--offload-compress", "-O3", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
