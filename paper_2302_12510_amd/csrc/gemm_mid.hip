@@ -349,7 +349,9 @@ static void launch(const GemmArgs &g, bool conv, hipStream_t st)
     const int tiles_m = (int)((g.M + TM - 1) / TM), tiles_n = (int)((g.N + TN - 1) / TN);
     if (conv && g.Cin < 64) return launch_one<FA, FW, ROWS, 1>(g, st, tiles_m, tiles_n);   // kw * Cin = 32 (checked by the dispatcher)
     const int force = dispatch_options().mid_kgroups;
-    const bool one = force ? force == 1 : (int64_t)tiles_m * tiles_n > 256;
+    const bool one = (force ? force == 1 : (int64_t)tiles_m * tiles_n > 256);
+    if (!conv && g.K % 64)                                          // a run of every k-group must lie inside its row
+        return one || g.K < 128 ? launch_one<FA, FW, RAGGED, 1>(g, st, tiles_m, tiles_n) : launch_one<FA, FW, RAGGED, 2>(g, st, tiles_m, tiles_n);
     if (one) launch_kg<FA, FW, 1>(g, conv, st, tiles_m, tiles_n);
     else launch_kg<FA, FW, 2>(g, conv, st, tiles_m, tiles_n);
 }
