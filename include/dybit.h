@@ -69,6 +69,12 @@ const char *dybit_status_string(dybit_status s);
 dybit_status dybit_absmax_scale(const float *x, size_t n, dybit_fmt f, float *scale_out,
                                 dybit_stream stream);
 
+/* The same with a workspace of DYBIT_ABSMAX_WORKSPACE floats [device] that is the call's own until it has run; its
+ * contents do not matter before or after.  One launch fewer for tensors of more than a few ten thousand floats. */
+#define DYBIT_ABSMAX_WORKSPACE 1024
+dybit_status dybit_absmax_scale_ws(const float *x, size_t n, dybit_fmt f, float *scale_out,
+                                   float *workspace, dybit_stream stream);
+
 /* Encoder (Sec. III-B) with round-to-nearest: codes_out[j] is the code whose value times
  * *scale is nearest to x[j] in exact arithmetic, ties to the even magnitude code.  NaN -> code 0;
  * |x| >= scale * 2^(m-1) (and +-Inf) -> all-ones magnitude; negative x in an unsigned format -> 0;

@@ -45,6 +45,7 @@ def lib() -> C.CDLL:
         L.dybit_status_string.argtypes = [C.c_int]
         L.dybit_status_string.restype = C.c_char_p
         L.dybit_absmax_scale.argtypes = [vp, sz, Fmt, vp, vp]
+        L.dybit_absmax_scale_ws.argtypes = [vp, sz, Fmt, vp, vp, vp]
         L.dybit_quantize.argtypes = [vp, sz, Fmt, vp, vp, vp]
         L.dybit_dequantize.argtypes = [vp, sz, Fmt, vp, vp, vp]
         L.dybit_quantize_absmax.argtypes = [vp, sz, Fmt, vp, vp, vp, vp]
@@ -171,12 +172,20 @@ def dybit_rmse(x: torch.Tensor, scale: torch.Tensor, bits: int, signed: bool, ou
     return out
 
 
+ABSMAX_WORKSPACE = 1024          # floats (dybit_absmax_scale_ws)
+_SMALL_ABSMAX = 1 << 16          # up to here the library needs no workspace
+
+
 def dybit_absmax_scale(x: torch.Tensor, bits: int, signed: bool, out: torch.Tensor | None = None, stream=None):
     assert x.dtype == torch.float32
     if out is None:
         out = torch.empty(1, dtype=torch.float32, device=x.device)
-    _check(lib().dybit_absmax_scale(_ptr(x), x.numel(), fmt(bits, signed), _ptr(out), _stream(stream)),
-           "dybit_absmax_scale")
+    n = x.numel()
+    if n > _SMALL_ABSMAX and stream is None:                # on the current stream, whose allocator the workspace comes from
+        work = torch.empty(ABSMAX_WORKSPACE, dtype=torch.float32, device=x.device)
+        _check(lib().dybit_absmax_scale_ws(_ptr(x), n, fmt(bits, signed), _ptr(out), _ptr(work), _stream()), "dybit_absmax_scale")
+    else:
+        _check(lib().dybit_absmax_scale(_ptr(x), n, fmt(bits, signed), _ptr(out), _stream(stream)), "dybit_absmax_scale")
     return out
 
 

@@ -22,10 +22,19 @@ constexpr int kThreads = 256;
 #define DYBIT_QUANT_UNROLL 4
 #endif
 #define DYBIT_QUANT_UNROLL_SMALL 2
+#ifndef DYBIT_FQ_UNROLL_SMALL
+#define DYBIT_FQ_UNROLL_SMALL 1
+#endif
 constexpr size_t kQuantSmall = (size_t)1 << 21;     // in groups of four elements
 #ifndef DYBIT_QUANT_BLOCKS_PER_CU
 #define DYBIT_QUANT_BLOCKS_PER_CU 128
 #endif
+// Tensors up to this size are read through the last-level cache (256 MB), so that the pass that follows on the same
+// tensor (scale, then encode) finds them there; larger ones stream past it.  Scale + encode + decode of 2^26 floats
+// 150.8 -> 146.2 us, of 23 M floats 70 -> 66 us; at 2^28 the scale alone would go 162 -> 181 us.
+constexpr size_t kStreamBytes = (size_t)256 << 20;
+// One workgroup finds the maximum of so many floats in the time of two launches (absmax_small_kernel).
+constexpr size_t kSmallAbsmax = (size_t)1 << 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
@@ -35,12 +44,33 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // integer atomicMax directly in the output word; NaNs are dropped by fmaxf before that.
 __global__ void absmax_init_kernel(float *scale_out) { *scale_out = 0.0f; }
 
-__global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restrict__ x, size_t n,
-                                                          float *scale_out)
+__device__ __forceinline__ float scale_of_max(float mx, float inv_vmax)
 {
-    // A workgroup reads contiguous chunks of 4 x kThreads 128-bit words (16 KiB), four loads in flight per
-    // lane.  (A lane whose four loads are a whole grid apart -- a large power of two -- keeps hitting
-    // the same memory channels: that form measured 5.4 TB/s against 7.0 TB/s for this one.)
+    return (mx == 0.0f) ? 1.0f : mx * inv_vmax;         // division by 2^(m-1): exact
+}
+
+// Maximum over the workgroup, valid in thread 0.
+template <int THREADS>
+__device__ __forceinline__ float workgroup_max(float mx)
+{
+    __shared__ float wave_max[THREADS / 64];
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < THREADS / 64; ++w) mx = fmaxf(mx, wave_max[w]);
+    }
+    return mx;
+}
+
+// max|x| of the elements this workgroup covers; valid in thread 0.  A workgroup reads contiguous chunks of
+// 4 x kThreads 128-bit words (16 KiB), four loads in flight per lane.  (A lane whose four loads are a whole grid
+// apart -- a large power of two -- keeps hitting the same memory channels: that form measured 5.4 TB/s against 7.0 TB/s
+// for this one.)  STREAM: past the last-level cache; see kStreamBytes.
+template <bool STREAM>
+__device__ __forceinline__ float absmax_of_chunks(const float *__restrict__ x, size_t n)
+{
     const size_t n4 = n >> 2;
     const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     float mx = 0.0f;
@@ -50,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
         f32x4 v[4];
         if (base + per_block <= n4) {                                  // uniform: a whole chunk
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kThreads);
+            for (int u = 0; u < 4; ++u) v[u] = STREAM ? __builtin_nontemporal_load(x4 + i + u * kThreads) : x4[i + u * kThreads];
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u) v[u] = (i + u * kThreads < n4) ? x4[i + u * kThreads] : f32x4{0.f, 0.f, 0.f, 0.f};
@@ -60,31 +90,73 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
             mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
     }
     if (blockIdx.x == 0 && threadIdx.x < (n & 3)) mx = fmaxf(mx, fabsf(x[(n4 << 2) + threadIdx.x]));
-    // At most one atomic per workgroup, and only when it would raise the word: atomics on a single address
-    // serialise in L2 (about 10 ns each).  A stale read can only cause a needless atomic.
-    __shared__ float wave_max[kThreads / 64];
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = mx;
-    __syncthreads();
+    return workgroup_max<kThreads>(mx);
+}
+
+// Without a workspace: the maximum is kept in the output word (one kernel clears it, one turns it into the scale).
+// At most one atomic per workgroup, and only when it would raise the word: atomics on a single address
+// serialise in L2 (about 10 ns each).  A stale read can only cause a needless atomic.
+template <bool STREAM>
+__global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restrict__ x, size_t n, float *scale_out)
+{
+    const float mx = absmax_of_chunks<STREAM>(x, n);
     if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, wave_max[w]);
         unsigned int *word = reinterpret_cast<unsigned int *>(scale_out);
         const unsigned int bits = __float_as_uint(mx);
         if (bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, bits);
     }
 }
 
+// With a workspace: every workgroup leaves its maximum in a word of its own, and one workgroup makes the scale of
+// them -- two launches instead of three, nothing to clear and no atomics.  Kernel times in a graph, three launches -> these
+// two: 2^18 floats 6.2 -> 4.1 us, 2.4 M 13.3 -> 4.7, 2^24 21.0 -> 14.2, 2^26 43.4 -> 42.9.
+template <bool STREAM>
+__global__ __launch_bounds__(kThreads) void absmax_partial_kernel(const float *__restrict__ x, size_t n, float *__restrict__ partial)
+{
+    const float mx = absmax_of_chunks<STREAM>(x, n);
+    if (threadIdx.x == 0) partial[blockIdx.x] = mx;
+}
+
+__global__ __launch_bounds__(kThreads) void absmax_join_kernel(const float *__restrict__ partial, int count, float *scale_out, float inv_vmax)
+{
+    float mx = 0.0f;
+    for (int i = threadIdx.x; i < count; i += kThreads) mx = fmaxf(mx, partial[i]);
+    mx = workgroup_max<kThreads>(mx);
+    if (threadIdx.x == 0) *scale_out = scale_of_max(mx, inv_vmax);
+}
+
+// Small tensors: one workgroup, one launch.  Eight 128-bit loads in flight per lane, 128 KiB in all.  16384 floats 2.7 us,
+// 65536 floats 3.9 us, where the two launches take as long.
+constexpr int kSmallThreads = 1024;
+__global__ __launch_bounds__(kSmallThreads) void absmax_small_kernel(const float *__restrict__ x, int n, float *scale_out, float inv_vmax)
+{
+    const int n4 = n >> 2;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    float mx = 0.0f;
+    for (int base = 0; base < n4; base += kSmallThreads * 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = base + u * kSmallThreads + (int)threadIdx.x;
+            v[u] = i < n4 ? x4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+    }
+    if (threadIdx.x < (n & 3)) mx = fmaxf(mx, fabsf(x[(n4 << 2) + (int)threadIdx.x]));
+    mx = workgroup_max<kSmallThreads>(mx);
+    if (threadIdx.x == 0) *scale_out = scale_of_max(mx, inv_vmax);
+}
+
 __global__ void absmax_to_scale_kernel(const float *absmax, float *scale_out, float inv_vmax)
 {
-    const float mx = *absmax;
-    *scale_out = (mx == 0.0f) ? 1.0f : mx * inv_vmax;   // division by 2^(m-1): exact
+    *scale_out = scale_of_max(*absmax, inv_vmax);
 }
 
 __global__ void absmax_finish_kernel(float *scale_out, float inv_vmax)
 {
-    const float mx = *scale_out;
-    *scale_out = (mx == 0.0f) ? 1.0f : mx * inv_vmax;   // division by 2^(m-1): exact
+    *scale_out = scale_of_max(*scale_out, inv_vmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -517,7 +589,8 @@ __global__ __launch_bounds__(kThreads) void quantize_pad_kernel(const float *__r
         return;
     }
     for (int64_t gi = (int64_t)blockIdx.x * kThreads + threadIdx.x; gi < groups; gi += (int64_t)gridDim.x * kThreads) {
-        const int64_t row = gi / groups_per_row;
+        // a 64-bit division costs more than the encoder: rows of one group (3 -> 4 channels) need none, and 32 bits do for most
+        const int64_t row = groups_per_row == 1 ? gi : groups <= 0x7fffffff ? (int64_t)((uint32_t)gi / (uint32_t)groups_per_row) : gi / groups_per_row;
         const int c0 = (int)(gi - row * groups_per_row) * 4;
         const float *src = x + row * cols;
         float e[4];
@@ -536,6 +609,48 @@ __global__ __launch_bounds__(kThreads) void quantize_pad_kernel(const float *__r
         else {
 #pragma unroll
             for (int b = 0; b < BITS / 2; ++b) dst[b] = (uint8_t)(w >> (8 * b));
+        }
+    }
+}
+
+// The same for rows of three floats padded to four codes (a colour image) with 16-byte aligned tensors: a thread takes four
+// rows, three 128-bit loads for four groups of codes and one store.  One group per thread, three 32-bit loads each, waited
+// on latency: 64 x 224 x 224 x 3 to 8-bit codes 15.6 -> 11.3 us (4.5 TB/s).
+template <int BITS, bool SIGNED>
+__global__ __launch_bounds__(kThreads) void quantize_pad3_kernel(const float *__restrict__ x, int64_t rows, const float *__restrict__ scale,
+                                                                 uint8_t *__restrict__ out, int *err)
+{
+    const ScaleInfo si = load_scale(scale);
+    if (!si.ok) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
+        return;
+    }
+    auto encode = [&](float a, float b, float c) -> uint32_t {
+        const float e[4] = {a, b, c, 0.0f};
+        bool redo;
+        uint32_t w = quantize_fast4<BITS, SIGNED>(e, si.rinv, redo);
+        if (redo | si.all_exact) {
+            w = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) w |= quantize_exact<BITS, SIGNED>(e[k], si.s) << (k * BITS);
+        }
+        return w;
+    };
+    const int64_t r0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    if (r0 + 4 <= rows) {
+        const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x + r0 * 3);
+        const f32x4 a = x4[0], b = x4[1], c = x4[2];
+        const uint32_t w0 = encode(a.x, a.y, a.z), w1 = encode(a.w, b.x, b.y), w2 = encode(b.z, b.w, c.x), w3 = encode(c.y, c.z, c.w);
+        uint32_t *o = reinterpret_cast<uint32_t *>(out + r0 * (BITS / 2));           // 4 rows are 2 BITS bytes
+        if constexpr (BITS == 8) *reinterpret_cast<uint4 *>(o) = make_uint4(w0, w1, w2, w3);
+        else if constexpr (BITS == 6) {
+            o[0] = w0 | (w1 << 24); o[1] = (w1 >> 8) | (w2 << 16); o[2] = (w2 >> 16) | (w3 << 8);
+        } else if constexpr (BITS == 4) *reinterpret_cast<uint2 *>(o) = make_uint2(w0 | (w1 << 16), w2 | (w3 << 16));
+        else o[0] = w0 | (w1 << 8) | (w2 << 16) | (w3 << 24);
+    } else {
+        for (int64_t r = r0; r < rows; ++r) {
+            const uint32_t w = encode(x[r * 3], x[r * 3 + 1], x[r * 3 + 2]);
+            for (int b = 0; b < BITS / 2; ++b) out[r * (BITS / 2) + b] = (uint8_t)(w >> (8 * b));
         }
     }
 }
@@ -591,9 +706,11 @@ __global__ __launch_bounds__(kThreads) void fake_quant_bwd_kernel(const float *_
 template <int BITS>
 __device__ __forceinline__ uint32_t load_code_group(const uint8_t *__restrict__ codes, size_t g)
 {
-    if (BITS == 8) return __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(codes) + g);
-    if (BITS == 4) return __builtin_nontemporal_load(reinterpret_cast<const uint16_t *>(codes) + g);
-    if (BITS == 2) return __builtin_nontemporal_load(codes + g);
+    // plain loads: codes that a recent pass wrote are still in the last-level cache (2^28 4-bit codes behind their encoder:
+    // 258 -> 206 us together with the grid below)
+    if (BITS == 8) return reinterpret_cast<const uint32_t *>(codes)[g];
+    if (BITS == 4) return reinterpret_cast<const uint16_t *>(codes)[g];
+    if (BITS == 2) return codes[g];
     const uint8_t *p = codes + g * 3;
     return p[0] | (p[1] << 8) | (p[2] << 16);
 }
@@ -688,19 +805,41 @@ static void launch_quantize(const float *x, size_t n, const float *scale, uint8_
 
 using namespace dybit;
 
-extern "C" dybit_status dybit_absmax_scale(const float *x, size_t n, dybit_fmt f, float *scale_out,
-                                           dybit_stream stream)
+static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *scale_out, float *workspace, dybit_stream stream)
 {
     dybit_status st = check_fmt(f);
     if (st != DYBIT_OK) return st;
     if (!scale_out || (!x && n)) return DYBIT_ERR_NULL;
     if (!aligned16(x)) return DYBIT_ERR_ALIGNMENT;
     hipStream_t hs = (hipStream_t)stream;
-    hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, hs, scale_out);
-    if (n) hipLaunchKernelGGL(absmax_kernel, dim3(grid_for(n / 4 + 1, kThreads * 4, 256 * 4)), dim3(kThreads), 0, hs, x, n, scale_out);
-    const int m = mag_bits(f.bits, f.is_signed);
-    hipLaunchKernelGGL(absmax_finish_kernel, dim3(1), dim3(1), 0, hs, scale_out, 1.0f / (float)(1u << (m - 1)));
+    const float inv_vmax = 1.0f / (float)(1u << (mag_bits(f.bits, f.is_signed) - 1));
+    if (n <= kSmallAbsmax) {
+        hipLaunchKernelGGL(absmax_small_kernel, dim3(1), dim3(kSmallThreads), 0, hs, x, (int)n, scale_out, inv_vmax);
+        return launch_status();
+    }
+    const int blocks = grid_for(n / 4 + 1, kThreads * 4, DYBIT_ABSMAX_WORKSPACE);
+    const bool stream_past = n * sizeof(float) > kStreamBytes;
+    if (workspace) {
+        hipLaunchKernelGGL(stream_past ? absmax_partial_kernel<true> : absmax_partial_kernel<false>, dim3(blocks), dim3(kThreads), 0, hs,
+                           x, n, workspace);
+        hipLaunchKernelGGL(absmax_join_kernel, dim3(1), dim3(kThreads), 0, hs, workspace, blocks, scale_out, inv_vmax);
+    } else {
+        hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, hs, scale_out);
+        hipLaunchKernelGGL(stream_past ? absmax_kernel<true> : absmax_kernel<false>, dim3(blocks), dim3(kThreads), 0, hs, x, n, scale_out);
+        hipLaunchKernelGGL(absmax_finish_kernel, dim3(1), dim3(1), 0, hs, scale_out, inv_vmax);
+    }
     return launch_status();
+}
+
+extern "C" dybit_status dybit_absmax_scale(const float *x, size_t n, dybit_fmt f, float *scale_out, dybit_stream stream)
+{
+    return absmax_impl(x, n, f, scale_out, nullptr, stream);
+}
+
+extern "C" dybit_status dybit_absmax_scale_ws(const float *x, size_t n, dybit_fmt f, float *scale_out, float *workspace, dybit_stream stream)
+{
+    if (!workspace && n) return DYBIT_ERR_NULL;
+    return absmax_impl(x, n, f, scale_out, workspace, stream);
 }
 
 extern "C" dybit_status dybit_scale_from_absmax(const float *absmax, dybit_fmt f, float *scale_out, dybit_stream stream)
@@ -825,8 +964,12 @@ extern "C" dybit_status dybit_quantize_pad(const float *x, int64_t rows, int64_t
     if (!err) return DYBIT_ERR_HIP;
     const int64_t groups = rows * (cols_padded / 4);
     const dim3 grid((unsigned)((groups + kThreads - 1) / kThreads < 256 * 64 ? (groups + kThreads - 1) / kThreads : 256 * 64));
-#define DYBIT_QP(B, S) hipLaunchKernelGGL((quantize_pad_kernel<B, S>), grid, dim3(kThreads), 0, (hipStream_t)stream, \
-                                          x, (int)cols, (int)(cols_padded / 4), groups, scale, codes_out, err)
+    const int64_t blocks3 = (rows + 4 * kThreads - 1) / (4 * kThreads);
+    const bool three = cols == 3 && cols_padded == 4 && aligned16(x) && aligned16(codes_out) && blocks3 <= 0x7fffffff;
+#define DYBIT_QP(B, S) \
+    if (three) hipLaunchKernelGGL((quantize_pad3_kernel<B, S>), dim3((unsigned)blocks3), dim3(kThreads), 0, (hipStream_t)stream, x, rows, scale, codes_out, err); \
+    else hipLaunchKernelGGL((quantize_pad_kernel<B, S>), grid, dim3(kThreads), 0, (hipStream_t)stream, \
+                            x, (int)cols, (int)(cols_padded / 4), groups, scale, codes_out, err)
     switch (f.bits * 2 + f.is_signed) {
         case 4: DYBIT_QP(2, false); break;   case 5: DYBIT_QP(2, true); break;
         case 8: DYBIT_QP(4, false); break;   case 9: DYBIT_QP(4, true); break;
@@ -863,10 +1006,13 @@ extern "C" dybit_status dybit_fake_quant(const float *x, size_t n, dybit_fmt f, 
     if (!aligned16(x) || !aligned16(y_out)) return DYBIT_ERR_ALIGNMENT;
     if (n == 0) return DYBIT_OK;
     hipStream_t hs = (hipStream_t)stream;
-    const int grid = grid_for(n / 4 + 1, kThreads * 4, 256 * DYBIT_QUANT_BLOCKS_PER_CU);
+    const bool small = n / 4 < kQuantSmall;                        // as the quantize pass
+    const int grid = grid_for(n / 4 + 1, kThreads * (small ? DYBIT_FQ_UNROLL_SMALL : 4), 256 * DYBIT_QUANT_BLOCKS_PER_CU);
     int *err = async_error_word();
     if (!err) return DYBIT_ERR_HIP;
-#define DYBIT_FQ(B, S) hipLaunchKernelGGL((fake_quant_kernel<B, S, 4>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err)
+#define DYBIT_FQ(B, S) \
+    if (small) hipLaunchKernelGGL((fake_quant_kernel<B, S, DYBIT_FQ_UNROLL_SMALL>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err); \
+    else hipLaunchKernelGGL((fake_quant_kernel<B, S, 4>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err)
     switch (f.bits * 2 + f.is_signed) {
         case 4: DYBIT_FQ(2, false); break;   case 5: DYBIT_FQ(2, true); break;
         case 8: DYBIT_FQ(4, false); break;   case 9: DYBIT_FQ(4, true); break;
@@ -886,7 +1032,7 @@ extern "C" dybit_status dybit_dequantize(const uint8_t *codes, size_t n, dybit_f
     if (!aligned16(codes) || !aligned16(y_out)) return DYBIT_ERR_ALIGNMENT;
     if (n == 0) return DYBIT_OK;
     hipStream_t hs = (hipStream_t)stream;
-    const int grid = grid_for(n / 4 + 1, kThreads * 4, 256 * 16);
+    const int grid = grid_for(n / 4 + 1, kThreads * 4, 1 << 20);   // a chunk per workgroup: the pass is bound by its stores
     switch (f.bits) {
         case 2: hipLaunchKernelGGL((dequantize_kernel<2>), dim3(grid), dim3(kThreads), 0, hs, codes, n, f.is_signed, scale, y_out); break;
         case 4: hipLaunchKernelGGL((dequantize_kernel<4>), dim3(grid), dim3(kThreads), 0, hs, codes, n, f.is_signed, scale, y_out); break;
