@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libdybit.so: argument marshalling only.
+"""Thin binding of libdybit.so: argument marshalling only, through a native module for the calls that launch
+work (csrc/binding_native.cpp) and through ctypes for the rest.
 
 PyTorch-ROCm supplies device memory and streams; every step of the path runs in the
 library's HIP kernels.  Loading fails loudly when the library has not been built: there is
@@ -29,6 +30,18 @@ class DybitError(RuntimeError):
 
 
 _lib = None
+_native_module = None
+
+
+def _n():
+    """The native marshalling module (csrc/binding_native.cpp): the C entry points, called with tensors (None: NULL),
+    (bits, signed) pairs, numbers and a stream (None: the current one) in the order of their prototypes."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        from . import _native                        # built beside the library; there is no fallback
+        _native_module = _native
+    return _native_module
 
 
 def lib() -> C.CDLL:
@@ -168,7 +181,7 @@ def dybit_rmse(x: torch.Tensor, scale: torch.Tensor, bits: int, signed: bool, ou
     if out is None:
         out = torch.empty(4, dtype=torch.float64, device=x.device)
     assert out.dtype == torch.float64 and out.numel() >= 4
-    _check(lib().dybit_rmse(_ptr(x), x.numel(), fmt(bits, signed), _ptr(scale), _ptr(out), _stream(stream)), "dybit_rmse")
+    _check(_n().dybit_rmse(x, x.numel(), (bits, signed), scale, out, stream), "dybit_rmse")
     return out
 
 
@@ -179,13 +192,13 @@ _SMALL_ABSMAX = 1 << 16          # up to here the library needs no workspace
 def dybit_absmax_scale(x: torch.Tensor, bits: int, signed: bool, out: torch.Tensor | None = None, stream=None):
     assert x.dtype == torch.float32
     if out is None:
-        out = torch.empty(1, dtype=torch.float32, device=x.device)
+        out = _n().empty(x, True, 1)
     n = x.numel()
     if n > _SMALL_ABSMAX and stream is None:                # on the current stream, whose allocator the workspace comes from
-        work = torch.empty(ABSMAX_WORKSPACE, dtype=torch.float32, device=x.device)
-        _check(lib().dybit_absmax_scale_ws(_ptr(x), n, fmt(bits, signed), _ptr(out), _ptr(work), _stream()), "dybit_absmax_scale")
+        work = _n().empty(x, True, ABSMAX_WORKSPACE)
+        _check(_n().dybit_absmax_scale_ws(x, n, (bits, signed), out, work, None), "dybit_absmax_scale")
     else:
-        _check(lib().dybit_absmax_scale(_ptr(x), n, fmt(bits, signed), _ptr(out), _stream(stream)), "dybit_absmax_scale")
+        _check(_n().dybit_absmax_scale(x, n, (bits, signed), out, stream), "dybit_absmax_scale")
     return out
 
 
@@ -195,8 +208,8 @@ def dybit_quantize(x: torch.Tensor, scale: torch.Tensor, bits: int, signed: bool
     assert x.dtype == torch.float32 and scale.dtype == torch.float32
     n = x.numel()
     if out is None:
-        out = torch.empty(dybit_packed_bytes(bits, signed, n), dtype=torch.uint8, device=x.device)
-    _check(lib().dybit_quantize(_ptr(x), n, fmt(bits, signed), _ptr(scale), _ptr(out), _stream(stream)),
+        out = _n().empty(x, False, _n().dybit_packed_bytes((bits, signed), n))
+    _check(_n().dybit_quantize(x, n, (bits, signed), scale, out, stream),
            "dybit_quantize")
     return out
 
@@ -207,11 +220,11 @@ def dybit_quantize_absmax(x: torch.Tensor, absmax: torch.Tensor, bits: int, sign
     assert x.dtype == torch.float32 and absmax.dtype == torch.float32
     n = x.numel()
     if out is None:
-        out = torch.empty(dybit_packed_bytes(bits, signed, n), dtype=torch.uint8, device=x.device)
+        out = _n().empty(x, False, _n().dybit_packed_bytes((bits, signed), n))
     if scale_out is None:
-        scale_out = torch.empty(1, dtype=torch.float32, device=x.device)
-    _check(lib().dybit_quantize_absmax(_ptr(x), n, fmt(bits, signed), _ptr(absmax), _ptr(scale_out), _ptr(out),
-                                       _stream(stream)), "dybit_quantize_absmax")
+        scale_out = _n().empty(x, True, 1)
+    _check(_n().dybit_quantize_absmax(x, n, (bits, signed), absmax, scale_out, out,
+                                       stream), "dybit_quantize_absmax")
     return scale_out, out
 
 
@@ -221,7 +234,7 @@ def dybit_fake_quant(x: torch.Tensor, scale: torch.Tensor, bits: int, signed: bo
     if out is None:
         out = torch.empty_like(x)
     assert out.dtype == torch.float32 and out.numel() == x.numel()
-    _check(lib().dybit_fake_quant(_ptr(x), x.numel(), fmt(bits, signed), _ptr(scale), _ptr(out), _stream(stream)),
+    _check(_n().dybit_fake_quant(x, x.numel(), (bits, signed), scale, out, stream),
            "dybit_fake_quant")
     return out
 
@@ -232,8 +245,8 @@ def dybit_fake_quant_bwd(x: torch.Tensor, grad_out: torch.Tensor, scale: torch.T
     assert x.dtype == torch.float32 and grad_out.dtype == torch.float32 and grad_out.numel() == x.numel()
     if out is None:
         out = torch.empty_like(x)
-    _check(lib().dybit_fake_quant_bwd(_ptr(x), _ptr(grad_out), x.numel(), fmt(bits, signed), _ptr(scale), _ptr(out),
-                                      _stream(stream)), "dybit_fake_quant_bwd")
+    _check(_n().dybit_fake_quant_bwd(x, grad_out, x.numel(), (bits, signed), scale, out,
+                                      stream), "dybit_fake_quant_bwd")
     return out
 
 
@@ -241,8 +254,8 @@ def dybit_dequantize(codes: torch.Tensor, n: int, scale: torch.Tensor, bits: int
                      out: torch.Tensor | None = None, stream=None):
     assert codes.dtype == torch.uint8
     if out is None:
-        out = torch.empty(n, dtype=torch.float32, device=codes.device)
-    _check(lib().dybit_dequantize(_ptr(codes), n, fmt(bits, signed), _ptr(scale), _ptr(out), _stream(stream)),
+        out = _n().empty(codes, True, n)
+    _check(_n().dybit_dequantize(codes, n, (bits, signed), scale, out, stream),
            "dybit_dequantize")
     return out
 
@@ -251,12 +264,12 @@ def dybit_gemm(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fmt, 
                bias=None, relu: bool = False, out: torch.Tensor | None = None, ldc: int | None = None, stream=None):
     """C [M][N] float32 = sA sW A W^T (+bias)(ReLU); a_fmt / w_fmt are (bits, signed) pairs."""
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=a_scale.device)
+        out = _n().empty(a_scale, True, M, N)
     if ldc is None:
         ldc = N
-    _check(lib().dybit_gemm(M, N, K, _ptr(a_codes), fmt(*a_fmt), _ptr(a_scale),
-                            _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), int(bool(relu)),
-                            _ptr(out), ldc, _stream(stream)), "dybit_gemm")
+    _check(_n().dybit_gemm(M, N, K, a_codes, a_fmt, a_scale,
+                            w_codes, w_fmt, w_scale, bias, bool(relu),
+                            out, ldc, stream), "dybit_gemm")
     return out
 
 
@@ -267,11 +280,11 @@ def dybit_conv2d(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw: int, 
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
-    _check(lib().dybit_conv2d(B, H, W, Cin, Cout, kh, kw, stride, pad,
-                              _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                              _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), int(bool(relu)),
-                              _ptr(out), _stream(stream)), "dybit_conv2d")
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
+    _check(_n().dybit_conv2d(B, H, W, Cin, Cout, kh, kw, stride, pad,
+                              x_codes, x_fmt, x_scale,
+                              w_codes, w_fmt, w_scale, bias, bool(relu),
+                              out, stream), "dybit_conv2d")
     return out
 
 
@@ -281,12 +294,12 @@ def dybit_gemm_ex(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fm
     """dybit_gemm with the optional shortcut tensor `residual` (laid out like the output) and the
     optional running maximum `absmax` (device float32 scalar, >= 0 on entry)."""
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=a_scale.device)
+        out = _n().empty(a_scale, True, M, N)
     if ldc is None:
         ldc = N
-    _check(lib().dybit_gemm_ex(M, N, K, _ptr(a_codes), fmt(*a_fmt), _ptr(a_scale),
-                               _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), _ptr(residual), int(bool(relu)),
-                               _ptr(out), ldc, _ptr(absmax), _stream(stream)), "dybit_gemm_ex")
+    _check(_n().dybit_gemm_ex(M, N, K, a_codes, a_fmt, a_scale,
+                               w_codes, w_fmt, w_scale, bias, residual, bool(relu),
+                               out, ldc, absmax, stream), "dybit_gemm_ex")
     return out
 
 
@@ -298,11 +311,11 @@ def dybit_conv2d_ex(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw: in
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
-    _check(lib().dybit_conv2d_ex(B, H, W, Cin, Cout, kh, kw, stride, pad,
-                                 _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                 _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), _ptr(residual), int(bool(relu)),
-                                 _ptr(out), _ptr(absmax), _stream(stream)), "dybit_conv2d_ex")
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
+    _check(_n().dybit_conv2d_ex(B, H, W, Cin, Cout, kh, kw, stride, pad,
+                                 x_codes, x_fmt, x_scale,
+                                 w_codes, w_fmt, w_scale, bias, residual, bool(relu),
+                                 out, absmax, stream), "dybit_conv2d_ex")
     return out
 
 
@@ -315,13 +328,13 @@ def dybit_gemm_wb(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fm
     if ldc is None:
         ldc = N
     if fp32 and out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=a_scale.device)
+        out = _n().empty(a_scale, True, M, N)
     if codes_out is None:
-        codes_out = torch.empty((M, N * c_fmt[0] // 8), dtype=torch.uint8, device=a_scale.device)
-    _check(lib().dybit_gemm_wb(M, N, K, _ptr(a_codes), fmt(*a_fmt), _ptr(a_scale),
-                               _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), _ptr(residual), int(bool(relu)),
-                               _ptr(out if fp32 else None), ldc, _ptr(absmax),
-                               fmt(*c_fmt), _ptr(c_scale), _ptr(codes_out), _stream(stream)), "dybit_gemm_wb")
+        codes_out = _n().empty(a_scale, False, M, N * c_fmt[0] // 8)
+    _check(_n().dybit_gemm_wb(M, N, K, a_codes, a_fmt, a_scale,
+                               w_codes, w_fmt, w_scale, bias, residual, bool(relu),
+                               out if fp32 else None, ldc, absmax,
+                               c_fmt, c_scale, codes_out, stream), "dybit_gemm_wb")
     return (out if fp32 else None), codes_out
 
 
@@ -334,14 +347,14 @@ def dybit_conv2d_wb(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw: in
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if fp32 and out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
     if codes_out is None:
-        codes_out = torch.empty((B, Ho, Wo, Cout * y_fmt[0] // 8), dtype=torch.uint8, device=x_scale.device)
-    _check(lib().dybit_conv2d_wb(B, H, W, Cin, Cout, kh, kw, stride, pad,
-                                 _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                 _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), _ptr(residual), int(bool(relu)),
-                                 _ptr(out if fp32 else None), _ptr(absmax),
-                                 fmt(*y_fmt), _ptr(y_scale), _ptr(codes_out), _stream(stream)), "dybit_conv2d_wb")
+        codes_out = _n().empty(x_scale, False, B, Ho, Wo, Cout * y_fmt[0] // 8)
+    _check(_n().dybit_conv2d_wb(B, H, W, Cin, Cout, kh, kw, stride, pad,
+                                 x_codes, x_fmt, x_scale,
+                                 w_codes, w_fmt, w_scale, bias, residual, bool(relu),
+                                 out if fp32 else None, absmax,
+                                 y_fmt, y_scale, codes_out, stream), "dybit_conv2d_wb")
     return (out if fp32 else None), codes_out
 
 
@@ -351,14 +364,14 @@ def dybit_gemm_wb_rc(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w
     """dybit_gemm_wb with the shortcut given as packed DyBit codes `r_codes` ([M][N*bits/8]) of format r_fmt
     and scale r_scale.  Returns (C or None, codes)."""
     if fp32 and out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=a_scale.device)
+        out = _n().empty(a_scale, True, M, N)
     if codes_out is None:
-        codes_out = torch.empty((M, N * c_fmt[0] // 8), dtype=torch.uint8, device=a_scale.device)
-    _check(lib().dybit_gemm_wb_rc(M, N, K, _ptr(a_codes), fmt(*a_fmt), _ptr(a_scale),
-                                  _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias),
-                                  _ptr(r_codes), fmt(*r_fmt), _ptr(r_scale), int(bool(relu)),
-                                  _ptr(out if fp32 else None), N, _ptr(absmax),
-                                  fmt(*c_fmt), _ptr(c_scale), _ptr(codes_out), _stream(stream)), "dybit_gemm_wb_rc")
+        codes_out = _n().empty(a_scale, False, M, N * c_fmt[0] // 8)
+    _check(_n().dybit_gemm_wb_rc(M, N, K, a_codes, a_fmt, a_scale,
+                                  w_codes, w_fmt, w_scale, bias,
+                                  r_codes, r_fmt, r_scale, bool(relu),
+                                  out if fp32 else None, N, absmax,
+                                  c_fmt, c_scale, codes_out, stream), "dybit_gemm_wb_rc")
     return (out if fp32 else None), codes_out
 
 
@@ -371,15 +384,15 @@ def dybit_conv2d_wb_rc(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw:
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if fp32 and out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
     if codes_out is None:
-        codes_out = torch.empty((B, Ho, Wo, Cout * y_fmt[0] // 8), dtype=torch.uint8, device=x_scale.device)
-    _check(lib().dybit_conv2d_wb_rc(B, H, W, Cin, Cout, kh, kw, stride, pad,
-                                    _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                    _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias),
-                                    _ptr(r_codes), fmt(*r_fmt), _ptr(r_scale), int(bool(relu)),
-                                    _ptr(out if fp32 else None), _ptr(absmax),
-                                    fmt(*y_fmt), _ptr(y_scale), _ptr(codes_out), _stream(stream)), "dybit_conv2d_wb_rc")
+        codes_out = _n().empty(x_scale, False, B, Ho, Wo, Cout * y_fmt[0] // 8)
+    _check(_n().dybit_conv2d_wb_rc(B, H, W, Cin, Cout, kh, kw, stride, pad,
+                                    x_codes, x_fmt, x_scale,
+                                    w_codes, w_fmt, w_scale, bias,
+                                    r_codes, r_fmt, r_scale, bool(relu),
+                                    out if fp32 else None, absmax,
+                                    y_fmt, y_scale, codes_out, stream), "dybit_conv2d_wb_rc")
     return (out if fp32 else None), codes_out
 
 
@@ -389,8 +402,8 @@ def dybit_maxpool2d_codes(B: int, H: int, W: int, C: int, k: int, stride: int, p
     Ho = (H + 2 * pad - k) // stride + 1
     Wo = (W + 2 * pad - k) // stride + 1
     if out is None:
-        out = torch.empty((B, Ho, Wo, C * x_fmt[0] // 8), dtype=torch.uint8, device=x_codes.device)
-    _check(lib().dybit_maxpool2d_codes(B, H, W, C, k, stride, pad, _ptr(x_codes), fmt(*x_fmt), _ptr(out), _stream(stream)),
+        out = _n().empty(x_codes, False, B, Ho, Wo, C * x_fmt[0] // 8)
+    _check(_n().dybit_maxpool2d_codes(B, H, W, C, k, stride, pad, x_codes, x_fmt, out, stream),
            "dybit_maxpool2d_codes")
     return out
 
@@ -402,10 +415,10 @@ def dybit_dwconv2d(B: int, H: int, W: int, C: int, kh: int, kw: int, stride: int
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if out is None:
-        out = torch.empty((B, Ho, Wo, C), dtype=torch.float32, device=x_scale.device)
-    _check(lib().dybit_dwconv2d(B, H, W, C, kh, kw, stride, pad, _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), _ptr(bias), int(bool(relu)),
-                                _ptr(out), _ptr(absmax), _stream(stream)), "dybit_dwconv2d")
+        out = _n().empty(x_scale, True, B, Ho, Wo, C)
+    _check(_n().dybit_dwconv2d(B, H, W, C, kh, kw, stride, pad, x_codes, x_fmt, x_scale,
+                                w_codes, w_fmt, w_scale, bias, bool(relu),
+                                out, absmax, stream), "dybit_dwconv2d")
     return out
 
 
@@ -418,14 +431,14 @@ def dybit_dwconv2d_wb(B: int, H: int, W: int, C: int, kh: int, kw: int, stride: 
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if fp32 and out is None:
-        out = torch.empty((B, Ho, Wo, C), dtype=torch.float32, device=x_scale.device)
+        out = _n().empty(x_scale, True, B, Ho, Wo, C)
     codes = None
     if y_fmt is not None:
-        codes = torch.empty((B, Ho, Wo, C * y_fmt[0] // 8), dtype=torch.uint8, device=x_scale.device)
-    _check(lib().dybit_dwconv2d_wb(B, H, W, C, kh, kw, stride, pad, _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                   _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), int(bool(per_channel)), _ptr(bias), int(bool(relu)),
-                                   _ptr(out) if fp32 else None, _ptr(absmax), fmt(*(y_fmt or (4, False))), _ptr(y_scale),
-                                   _ptr(codes), _stream(stream)), "dybit_dwconv2d_wb")
+        codes = _n().empty(x_scale, False, B, Ho, Wo, C * y_fmt[0] // 8)
+    _check(_n().dybit_dwconv2d_wb(B, H, W, C, kh, kw, stride, pad, x_codes, x_fmt, x_scale,
+                                   w_codes, w_fmt, w_scale, bool(per_channel), bias, bool(relu),
+                                   out if fp32 else None, absmax, y_fmt or (4, False), y_scale,
+                                   codes, stream), "dybit_dwconv2d_wb")
     return (out if fp32 else None), codes
 
 
@@ -436,10 +449,10 @@ def dybit_group_conv2d(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw:
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
-    _check(lib().dybit_group_conv2d(B, H, W, Cin, Cout, kh, kw, stride, pad, groups, _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                    _ptr(w_codes), fmt(*w_fmt), _ptr(w_scale), int(bool(per_channel)), _ptr(bias), _ptr(residual),
-                                    int(bool(relu)), _ptr(out), _ptr(absmax), _stream(stream)), "dybit_group_conv2d")
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
+    _check(_n().dybit_group_conv2d(B, H, W, Cin, Cout, kh, kw, stride, pad, groups, x_codes, x_fmt, x_scale,
+                                    w_codes, w_fmt, w_scale, bool(per_channel), bias, residual,
+                                    bool(relu), out, absmax, stream), "dybit_group_conv2d")
     return out
 
 
@@ -448,9 +461,9 @@ def dybit_quantize_cols(x: torch.Tensor, bits: int, signed: bool, stream=None):
     its own max-abs scale (a depthwise filter [kh*kw][C] with one scale per channel)."""
     assert x.dtype == torch.float32 and x.dim() == 2
     rows, cols = x.shape
-    scales = torch.empty(cols, dtype=torch.float32, device=x.device)
-    codes = torch.empty((rows, cols * bits // 8), dtype=torch.uint8, device=x.device)
-    _check(lib().dybit_quantize_cols(_ptr(x), rows, cols, fmt(bits, signed), _ptr(scales), _ptr(codes), _stream(stream)),
+    scales = _n().empty(x, True, cols)
+    codes = _n().empty(x, False, rows, cols * bits // 8)
+    _check(_n().dybit_quantize_cols(x, rows, cols, (bits, signed), scales, codes, stream),
            "dybit_quantize_cols")
     return scales, codes
 
@@ -458,8 +471,8 @@ def dybit_quantize_cols(x: torch.Tensor, bits: int, signed: bool, stream=None):
 def dybit_quantize_pad(x: torch.Tensor, cols_padded: int, scale: torch.Tensor, bits: int, signed: bool, stream=None):
     """Codes of the [rows][cols] matrix x with every row padded to cols_padded codes (zero codes)."""
     rows, cols = x.shape
-    out = torch.empty((rows, cols_padded * bits // 8), dtype=torch.uint8, device=x.device)
-    _check(lib().dybit_quantize_pad(_ptr(x), rows, cols, cols_padded, fmt(bits, signed), _ptr(scale), _ptr(out), _stream(stream)),
+    out = _n().empty(x, False, rows, cols_padded * bits // 8)
+    _check(_n().dybit_quantize_pad(x, rows, cols, cols_padded, (bits, signed), scale, out, stream),
            "dybit_quantize_pad")
     return out
 
@@ -469,9 +482,9 @@ def dybit_quantize_rows(x: torch.Tensor, bits: int, signed: bool, stream=None):
     its own max-abs scale."""
     assert x.dtype == torch.float32 and x.dim() == 2
     rows, cols = x.shape
-    scales = torch.empty(rows, dtype=torch.float32, device=x.device)
-    codes = torch.empty((rows, cols * bits // 8), dtype=torch.uint8, device=x.device)
-    _check(lib().dybit_quantize_rows(_ptr(x), rows, cols, fmt(bits, signed), _ptr(scales), _ptr(codes), _stream(stream)),
+    scales = _n().empty(x, True, rows)
+    codes = _n().empty(x, False, rows, cols * bits // 8)
+    _check(_n().dybit_quantize_rows(x, rows, cols, (bits, signed), scales, codes, stream),
            "dybit_quantize_rows")
     return scales, codes
 
@@ -484,14 +497,14 @@ def dybit_gemm_pc(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fm
     if ldc is None:
         ldc = N
     if fp32 and out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=a_scale.device)
+        out = _n().empty(a_scale, True, M, N)
     codes = None
     if c_fmt is not None:
-        codes = torch.empty((M, N * c_fmt[0] // 8), dtype=torch.uint8, device=a_scale.device)
-    _check(lib().dybit_gemm_pc(M, N, K, _ptr(a_codes), fmt(*a_fmt), _ptr(a_scale),
-                               _ptr(w_codes), fmt(*w_fmt), _ptr(w_scales), _ptr(bias), _ptr(residual), int(bool(relu)),
-                               _ptr(out if fp32 else None), ldc, _ptr(absmax),
-                               fmt(*(c_fmt or (8, False))), _ptr(c_scale), _ptr(codes), _stream(stream)), "dybit_gemm_pc")
+        codes = _n().empty(a_scale, False, M, N * c_fmt[0] // 8)
+    _check(_n().dybit_gemm_pc(M, N, K, a_codes, a_fmt, a_scale,
+                               w_codes, w_fmt, w_scales, bias, residual, bool(relu),
+                               out if fp32 else None, ldc, absmax,
+                               c_fmt or (8, False), c_scale, codes, stream), "dybit_gemm_pc")
     return (out if fp32 else None), codes
 
 
@@ -503,23 +516,23 @@ def dybit_conv2d_pc(B: int, H: int, W: int, Cin: int, Cout: int, kh: int, kw: in
     Ho = (H + 2 * pad - kh) // stride + 1
     Wo = (W + 2 * pad - kw) // stride + 1
     if fp32 and out is None:
-        out = torch.empty((B, Ho, Wo, Cout), dtype=torch.float32, device=x_scale.device)
+        out = _n().empty(x_scale, True, B, Ho, Wo, Cout)
     codes = None
     if y_fmt is not None:
-        codes = torch.empty((B, Ho, Wo, Cout * y_fmt[0] // 8), dtype=torch.uint8, device=x_scale.device)
-    _check(lib().dybit_conv2d_pc(B, H, W, Cin, Cout, kh, kw, stride, pad,
-                                 _ptr(x_codes), fmt(*x_fmt), _ptr(x_scale),
-                                 _ptr(w_codes), fmt(*w_fmt), _ptr(w_scales), _ptr(bias), _ptr(residual), int(bool(relu)),
-                                 _ptr(out if fp32 else None), _ptr(absmax),
-                                 fmt(*(y_fmt or (8, False))), _ptr(y_scale), _ptr(codes), _stream(stream)), "dybit_conv2d_pc")
+        codes = _n().empty(x_scale, False, B, Ho, Wo, Cout * y_fmt[0] // 8)
+    _check(_n().dybit_conv2d_pc(B, H, W, Cin, Cout, kh, kw, stride, pad,
+                                 x_codes, x_fmt, x_scale,
+                                 w_codes, w_fmt, w_scales, bias, residual, bool(relu),
+                                 out if fp32 else None, absmax,
+                                 y_fmt or (8, False), y_scale, codes, stream), "dybit_conv2d_pc")
     return (out if fp32 else None), codes
 
 
 def dybit_scale_from_absmax(absmax: torch.Tensor, bits: int, signed: bool, out: torch.Tensor | None = None, stream=None):
     """scale = absmax / 2^(m-1) (1.0 for 0) on the device; returns the 1-element scale tensor."""
     if out is None:
-        out = torch.empty(1, dtype=torch.float32, device=absmax.device)
-    _check(lib().dybit_scale_from_absmax(_ptr(absmax), fmt(bits, signed), _ptr(out), _stream(stream)), "dybit_scale_from_absmax")
+        out = _n().empty(absmax, True, 1)
+    _check(_n().dybit_scale_from_absmax(absmax, (bits, signed), out, stream), "dybit_scale_from_absmax")
     return out
 
 

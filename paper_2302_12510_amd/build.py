@@ -1,13 +1,16 @@
 """Builds libdybit.so (HIP, gfx950) in-tree with hipcc."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdybit.so")
+NATIVE = os.path.join(HERE, "_native.so")         # the binding's argument marshalling (needs torch's headers)
 # (source, object stem, extra flags): the tiled kernels are compiled once per weight format
 SOURCES = [
     ("host.cpp", "host", []),
@@ -112,6 +115,19 @@ def _rank(item) -> int:
     return len(_ORDER)
 
 
+def _build_native() -> None:
+    spec = importlib.util.find_spec("torch")
+    torch_dir = spec.submodule_search_locations[0]
+    inc, libs = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-I{inc}", f"-I{inc}/torch/csrc/api/include", "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}",
+           os.path.join(CSRC, "binding_native.cpp"), "-o", NATIVE, f"-L{HERE}", "-l:libdybit.so",
+           f"-L{libs}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    if p.returncode:
+        raise RuntimeError("g++ failed on binding_native.cpp:\n" + p.stderr)
+
+
 def build(verbose: bool = True) -> str:
     jobs = sorted(SOURCES, key=_rank)
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 8)) as ex:
@@ -120,6 +136,7 @@ def build(verbose: bool = True) -> str:
     p = subprocess.run(cmd, capture_output=True, text=True)
     if p.returncode:
         raise RuntimeError("link failed:\n" + p.stderr)
+    _build_native()
     if verbose:
         print("built", LIB)
     return LIB
