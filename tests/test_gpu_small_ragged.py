@@ -11,18 +11,18 @@ from test_gpu_gemm import random_codes
 
 pytestmark = pytest.mark.gpu
 
-PAIRS = [((8, True), (4, True)), ((8, False), (8, True)), ((6, True), (6, True)), ((4, False), (2, True)), ((2, True), (8, True)),
+PAIRS = [((4, False), (4, True)), ((2, True), (4, True)), ((8, True), (4, True)), ((8, False), (8, True)), ((6, True), (6, True)), ((4, False), (2, True)), ((2, True), (8, True)),
          ((4, True), (6, True)), ((6, False), (4, True)), ((2, False), (2, True))]
 # K: one step; an odd part of 4 codes; one code group short of a step; odd parts of every k-group; more steps than waves
 SHAPES = [(1, 7, 64), (33, 70, 68), (32, 32, 124), (65, 33, 128), (5, 129, 132), (130, 65, 196), (31, 257, 1148), (290, 130, 1216)]
 
 
-@pytest.fixture(params=["small", "mid1", "mid2", "auto"])
+@pytest.fixture(params=["small", "small-e4m3", "mid1", "mid2", "auto"])
 def kernel(request):
     name = request.param
-    B.dybit_set_option("gemm_kernel", name[:3] if name.startswith("mid") else name)
+    B.dybit_set_option("gemm_kernel", name[:3] if name.startswith("mid") else name.split("-")[0])
     B.dybit_set_option("mid_kgroups", name[3:] or "auto" if name.startswith("mid") else "auto")
-    B.dybit_set_option("gemm_mfma", "f16")
+    B.dybit_set_option("gemm_mfma", "auto" if name == "small-e4m3" else "f16")
     yield name
     for k in ("gemm_kernel", "mid_kgroups", "gemm_mfma"):
         B.dybit_set_option(k, "auto")
@@ -42,7 +42,8 @@ def test_products(kernel, a_fmt, w_fmt, shape):
                         dev(bias), dev(res), True, mx)
     ran = B.dybit_last_gemm_kernel()
     torch.cuda.synchronize()
-    assert ran == {"small": "f16_small", "mid1": "f16_128_kg1", "auto": "f16_small",
+    low = a_fmt[0] <= 4 and w_fmt[0] <= 4
+    assert ran == {"small": "f16_small", "small-e4m3": "f8_small" if low else "f16_small", "mid1": "f16_128_kg1", "auto": "f16_small",
                    "mid2": "f16_128_kg1" if K % 64 and K < 128 else "f16_128_kg2"}[kernel]
     got = c.cpu().numpy()
     assert_within(got, want, den, shortcut=True)
