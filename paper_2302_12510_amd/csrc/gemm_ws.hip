@@ -41,14 +41,22 @@ using namespace fast;
 // Waves per workgroup (32 rows each).  Eight; four in the write-back build of the two-block form, whose
 // epilogue needs about 170 registers: three four-wave workgroups then share a compute unit (three waves per
 // SIMD) where a single eight-wave one would fit, and the encoder of one overlaps the K loops of the others.
-template <int CB, int OUT> constexpr int waves_of() { return (OUT != OUT_FP32 && CB == 2) ? 4 : 8; }
+// The codes-only build of the two-block form runs at 128 registers, four waves per SIMD, however many workgroups' weights
+// fit the LDS: 16 waves of one, two of eight, or four of four (waves_for; the kernel takes it from blockDim).
+template <int CB, int OUT> constexpr int waves_of() { return OUT == OUT_CODES && CB == 2 ? 16 : (OUT != OUT_FP32 && CB == 2) ? 4 : 8; }
+template <int CB, int OUT> inline int waves_for(int lds_bytes)
+{
+    if (OUT != OUT_CODES || CB != 2) return waves_of<CB, OUT>();
+    const int by_lds = (160 * 1024) / lds_bytes;
+    return by_lds >= 4 ? 4 : by_lds >= 2 ? 8 : 16;
+}
 // Workgroups of the persistent grid per compute unit: what the weight tiles in LDS (160 KiB) and the registers
 // allow (two-block form: two eight-wave workgroups at 128 registers, three four-wave ones at 168 in the
 // write-back build; four-block form: one).
 template <int CB> inline int workgroups_per_cu(int lds_bytes)
 {
     const int by_lds = (160 * 1024) / lds_bytes;
-    const int by_regs = CB == 2 ? (kOut == OUT_CODES ? 4 : kOut == OUT_WRITE_BACK ? 3 : 2) : 1;
+    const int by_regs = CB == 2 ? (kOut == OUT_CODES ? 16 / waves_for<CB, kOut>(lds_bytes) : kOut == OUT_WRITE_BACK ? 3 : 2) : 1;
     return by_lds < by_regs ? (by_lds < 1 ? 1 : by_lds) : by_regs;
 }
 
@@ -109,7 +117,7 @@ constexpr int ROWS = 2;
 template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
 __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
-    constexpr int THREADS = 64 * waves_of<CB, OUT>(), SLAB = 32 * waves_of<CB, OUT>();
+    const int THREADS = OUT == OUT_CODES ? (int)blockDim.x : 64 * waves_of<CB, OUT>(), SLAB = THREADS / 2;
     using CA = Codec<FMT_A>;
     using CW = Codec<FMT_W>;
     constexpr int WORDS_A = CA::BITS;                               // 32-bit words in a run of 32 codes
@@ -323,7 +331,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
 template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
 __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws8_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
-    constexpr int THREADS = 64 * waves_of<CB, OUT>(), SLAB = 32 * waves_of<CB, OUT>();
+    const int THREADS = OUT == OUT_CODES ? (int)blockDim.x : 64 * waves_of<CB, OUT>(), SLAB = THREADS / 2;
     using f8::i32x8;
     constexpr int BA = f8::bits_of<FMT_A>(), BW = f8::bits_of<FMT_W>();
     constexpr int RUN_A = 4 * BA, RUN_W = 4 * BW;                    // bytes of a run of 32 codes
@@ -459,7 +467,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
 template <int FA, int FW, int CONV, int CB>
 static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_bytes)
 {
-    constexpr int THREADS = 64 * waves_of<CB, kOut>(), SLAB = 32 * waves_of<CB, kOut>();
+    const int waves = waves_for<CB, kOut>(lds_bytes), THREADS = 64 * waves, SLAB = 32 * waves;
     const int slabs = (int)((g.M + SLAB - 1) / SLAB);
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));
@@ -475,7 +483,7 @@ static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds
 template <int FA, int FW, int CONV, int CB>
 static bool launch_cb(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_bytes)
 {
-    constexpr int THREADS = 64 * waves_of<CB, kOut>(), SLAB = 32 * waves_of<CB, kOut>();
+    const int waves = waves_for<CB, kOut>(lds_bytes), THREADS = 64 * waves, SLAB = 32 * waves;
     const int slabs = (int)((g.M + SLAB - 1) / SLAB);
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));

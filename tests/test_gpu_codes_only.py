@@ -82,3 +82,16 @@ def test_codes_only_extreme_scales(force_kernel, sa, sw, sc):
         codes.append(out)
     assert torch.equal(codes[0], codes[1])
     assert (sc == sc) or bool((codes[1] == 7).all())
+
+
+@pytest.mark.parametrize("force_kernel", ["ws"], indirect=True)
+@pytest.mark.parametrize("K", [192, 576, 704, 1216])                            # four, two and one workgroup's weights in a compute unit's LDS
+@pytest.mark.parametrize("M", [31, 513, 1030])
+def test_codes_only_by_lds_share(force_kernel, K, M):
+    rng = np.random.default_rng(K)
+    a_fmt, w_fmt, N = (8, False), (4, True), 64
+    qa, qw = random_codes(rng, (M, K), a_fmt), random_codes(rng, (N, K), w_fmt)
+    want, _ = R.gemm(qa, a_fmt, 0.37, qw, w_fmt, 0.011, None, True)
+    args = (M, N, K, pack_rows_dev(qa, 8), a_fmt, scalar(0.37), pack_rows_dev(qw, 4), w_fmt, scalar(0.011), (6, False),
+            scalar(np.abs(want).max() / R.vmax(6, False)))
+    both(args, {"relu": True})
