@@ -442,7 +442,8 @@ typedef enum {
     DYBIT_KERNEL_F8_WS = 11,         /* e4m3 MFMA, weight-stationary                                    */
     DYBIT_KERNEL_F16_SMALL = 12,     /* fp16 MFMA, 32-row tile, K split over the waves of a workgroup   */
     DYBIT_KERNEL_F16_GROUP = 13,     /* fp16 MFMA, weight-stationary grouped convolution                */
-    DYBIT_KERNEL_F8_SMALL = 14       /* e4m3 MFMA, 32-row tile, K split over the waves of a workgroup   */
+    DYBIT_KERNEL_F8_SMALL = 14,      /* e4m3 MFMA, 32-row tile, K split over the waves of a workgroup   */
+    DYBIT_KERNEL_F16_FEW = 15        /* fp16 MFMA, few-channel convolution, input decoded once          */
 } dybit_kernel_id;
 int32_t dybit_last_gemm_kernel(void);
 dybit_status dybit_set_option(const char *name, const char *value);

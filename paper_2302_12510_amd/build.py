@@ -77,6 +77,14 @@ SOURCES = [
     ("gemm_ws.hip", "gemm_ws_w8_co", ["-DDYBIT_WS_W=2", "-DDYBIT_WB=2"]),
     ("gemm_ws.hip", "gemm_ws_w6_co", ["-DDYBIT_WS_W=4", "-DDYBIT_WB=2"]),
     ("gemm_ws.hip", "gemm_ws_w2_co", ["-DDYBIT_WS_W=6", "-DDYBIT_WB=2"]),
+    ("conv_few.hip", "conv_few_w4", ["-DDYBIT_FEW_W=0"]),
+    ("conv_few.hip", "conv_few_w4_co", ["-DDYBIT_FEW_W=0", "-DDYBIT_WB=2"]),
+    ("conv_few.hip", "conv_few_w8", ["-DDYBIT_FEW_W=2"]),
+    ("conv_few.hip", "conv_few_w8_co", ["-DDYBIT_FEW_W=2", "-DDYBIT_WB=2"]),
+    ("conv_few.hip", "conv_few_w6", ["-DDYBIT_FEW_W=4"]),
+    ("conv_few.hip", "conv_few_w6_co", ["-DDYBIT_FEW_W=4", "-DDYBIT_WB=2"]),
+    ("conv_few.hip", "conv_few_w2", ["-DDYBIT_FEW_W=6"]),
+    ("conv_few.hip", "conv_few_w2_co", ["-DDYBIT_FEW_W=6", "-DDYBIT_WB=2"]),
     ("diag.hip", "diag", []),
 ]
 FLAGS = ["--offload-arch=gfx950", "--offload-compress", "-O3", "-fPIC", "-std=c++17",
@@ -104,7 +112,7 @@ def _compile(item) -> str:
 
 
 # Longest compilations first, so that the pool's last jobs are short ones.
-_ORDER = ("gemm", "gemm_wb", "gemm_mid", "gemm_ws", "gemm_f8", "gemm_fast", "gemm_small", "quantize")
+_ORDER = ("gemm", "gemm_wb", "gemm_mid", "gemm_ws", "gemm_f8", "gemm_fast", "conv_few", "gemm_small", "quantize")
 
 
 def _rank(item) -> int:

@@ -135,6 +135,17 @@ void launch_gemm_small_w2_wb(const GemmArgs &g, int a_bits, bool conv, hipStream
 void launch_gemm_small_w4_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 void launch_gemm_small_w6_wb(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);
 
+// Few-channel convolution with its input decoded once (conv_few.hip); plain and codes-only builds.  false: no unit of output
+// rows fits the LDS.
+bool launch_conv_few_w0(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w2(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w4(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w6(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w0_co(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w2_co(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w4_co(const GemmArgs &g, int a_bits, hipStream_t st);
+bool launch_conv_few_w6_co(const GemmArgs &g, int a_bits, hipStream_t st);
+
 // Grouped convolution in one launch (gemm_group.hip): g describes the whole layer (Cin and N of all groups, K of one).  false:
 // a group's channels are not whole words, or its weights do not fit the LDS of a compute unit.
 bool launch_group_conv_w0(const GemmArgs &g, int a_bits, int groups, hipStream_t st);

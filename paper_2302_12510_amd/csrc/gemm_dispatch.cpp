@@ -123,9 +123,33 @@ static bool small_output(const GemmArgs &g, bool ragged, bool low_pair)
     return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= (!low_pair ? 256 : ragged ? 384 : 104);
 }
 
+// The few-channel kernel takes a convolution whose filter rows fit 32 codes with at least two taps (with one, no code would be
+// decoded twice) and whose fragments start on groups of eight codes.  Filters that the weight-stationary kernel's row mode
+// takes as well (rows of exactly 32 codes, an even number of them) go there while the outputs are few: 8 x 8 taps of 4 channels,
+// stride 2, 64 channels out, 8-bit operands, row mode -> this kernel (us): codes out at 50176 outputs 11.5 -> 11.6, 100352
+// 16.5 -> 13.7, 802816 74.4 -> 50.6; fp32 out at 200704 24.8 -> 25.5, 401408 41.0 -> 40.0, 802816 79.3 -> 65.6.  Others would run
+// on the general kernel (7 x 7 taps at 9409 outputs 28.8 -> 8.9); below 2048 outputs they stay there.
+static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, hipStream_t st)
+{
+    const bool dense = (int64_t)g.pix_bytes * 8 == (int64_t)g.Cin * a_bits, codes = codes_only(g);
+    if (!dense || a_bits == 2 || (g.Cin != 4 && g.Cin != 8 && g.Cin != 16) || g.kw < 2 || g.kw * g.Cin > 32 || g.stride * (int64_t)g.Cin % 8) return false;
+    const bool row_mode = g.kw * g.Cin == 32 && g.kh % 2 == 0 && g.N <= 128 && g.a_bytes % 4 == 0;
+    if (g.N > 256 || g.M < (!row_mode ? 2048 : codes ? 1 << 16 : 1 << 18) || g.M > 0x7fffffff || (g.q_out && !codes)) return false;
+    if (g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff || ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 3)) return false;
+    switch (w_bits) {
+        case 4: return (codes ? launch_conv_few_w0_co : launch_conv_few_w0)(g, a_bits, st);
+        case 8: return (codes ? launch_conv_few_w2_co : launch_conv_few_w2)(g, a_bits, st);
+        case 6: return (codes ? launch_conv_few_w4_co : launch_conv_few_w4)(g, a_bits, st);
+        case 2: return (codes ? launch_conv_few_w6_co : launch_conv_few_w6)(g, a_bits, st);
+        default: return false;
+    }
+}
+
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st)
 {
     if (!g.w_signed) return false;                                  // every width 2, 4, 6, 8 has a decoder; weights are signed
+    const DispatchOptions opt = dispatch_options();
+    if (conv && !opt.kernel && !opt.mid_tile && !opt.mid_kgroups && g.M >= 1 && g.N >= 1 && launch_conv_few(g, a_bits, w_bits, st)) return true;
     if (g.M < 1 || g.N < 1 || g.K < 64 || (conv && g.K % 64)) return false;
     const bool ragged = g.K % 64 != 0;                              // a matrix product whose rows start at any byte
     // a convolution needs whole 64-code k groups inside a filter tap, or (few channels) filter rows of
@@ -142,7 +166,6 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 
     bool large;
     const bool low_pair = (a_bits == 4 || a_bits == 2) && (w_bits == 4 || w_bits == 2);
-    const DispatchOptions opt = dispatch_options();
     const int force = opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
 

@@ -90,22 +90,6 @@ inline int grid_for_groups(int slabs, int groups, int resident)
     return walkers * groups;
 }
 
-// The kernel's arguments, read again from the kernel-argument segment by each call: the persistent loop's epilogue has a
-// variant per format of its codes, and the compiler otherwise computes the uniform values of all of them once, before the
-// loop, where they exceed the scalar registers (157 spilled, each a v_readlane per slab) -- the scalar loads are cheaper.
-__device__ __forceinline__ GemmArgs reload_args()
-{
-    struct Words { uint64_t w[sizeof(GemmArgs) / 8]; } words;
-    static_assert(sizeof(Words) == sizeof(GemmArgs), "whole 64-bit words");
-    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();     // GemmArgs is the kernels' first argument
-    asm volatile("" : "+s"(at));
-    const auto *p = (const __attribute__((address_space(4))) uint64_t *)at;
-#pragma unroll
-    for (unsigned i = 0; i < sizeof(GemmArgs) / 8; ++i) words.w[i] = p[i];
-    const GemmArgs a = __builtin_bit_cast(GemmArgs, words);
-    return a;
-}
-
 // CONV: 0 matrix product; 1 convolution whose 64-code k groups lie inside one filter tap (Cin a
 // multiple of 64); 2 (ROWS) convolution with few channels where one filter row is exactly one 32-code
 // run (kw * Cin = 32): the run of lane-half kq in K step t is filter row 2 t + kq of the lane's output

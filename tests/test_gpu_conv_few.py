@@ -1,0 +1,70 @@
+"""Few-channel convolutions on the kernel that decodes its input once per unit of output rows, against the oracle: filter rows
+of 28 and 32 codes, odd filter heights, last units of fewer rows, output widths that are no multiple of 32, several images,
+groups of 64 output channels with a partial last one; fp32 results with shortcut and maximum, and codes only."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dybit_ref as R
+from paper_2302_12510_amd import binding as B
+from gpu_util import dev, scalar, pack_rows_dev, assert_within
+from test_gpu_gemm import random_codes
+
+pytestmark = pytest.mark.gpu
+
+#        B  H   W   Cin Cout kh kw s  p
+GEOMS = [(1, 97, 103, 4, 64, 7, 7, 2, 3), (2, 64, 70, 4, 64, 9, 8, 2, 3), (3, 31, 27, 8, 70, 3, 3, 1, 1), (1, 50, 49, 16, 19, 3, 2, 1, 0),
+         (5, 23, 21, 8, 150, 5, 4, 1, 2), (1, 400, 9, 4, 40, 2, 5, 2, 8)]
+
+
+@pytest.mark.parametrize("x_fmt,w_fmt", [((8, True), (8, True)), ((6, False), (4, True)), ((4, False), (6, True)), ((6, True), (2, True))])
+@pytest.mark.parametrize("geom", GEOMS)
+def test_few_channel_kernel(x_fmt, w_fmt, geom):
+    Bn, H, W, Cin, Cout, kh, kw, stride, pad = geom
+    if (kh * kw * Cin * w_fmt[0]) % 8 or (Cin * w_fmt[0]) % 8:
+        pytest.skip("filters of whole bytes")
+    rng = np.random.default_rng(Cin + Cout)
+    qx, qw = random_codes(rng, (Bn, H, W, Cin), x_fmt), random_codes(rng, (Cout, kh, kw, Cin), w_fmt)
+    bias = rng.normal(0, 1, Cout).astype(np.float32)
+    Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kw) // stride + 1
+    res = rng.normal(0, 3, (Bn, Ho, Wo, Cout)).astype(np.float32)
+    want, den = R.conv2d(qx, x_fmt, 0.21, qw, w_fmt, 0.05, stride, pad, bias, True, res)
+    args = (Bn, H, W, Cin, Cout, kh, kw, stride, pad, pack_rows_dev(qx.reshape(-1, Cin), x_fmt[0]), x_fmt, scalar(0.21),
+            pack_rows_dev(qw.reshape(Cout, -1), w_fmt[0]), w_fmt, scalar(0.05))
+    mx = torch.zeros(2, dtype=torch.float32, device="cuda")
+    y = B.dybit_conv2d_ex(*args, dev(bias), dev(res), True, mx[0:1])
+    ran = B.dybit_last_gemm_kernel()
+    torch.cuda.synchronize()
+    assert ran == "f16_few"
+    got = y.cpu().numpy()
+    assert_within(got, want, den, shortcut=True)
+    assert mx[0].item() == np.abs(got).max()
+    if Cout % 8:
+        return
+    # codes only: those of the fp32 results the same kernel writes
+    y = B.dybit_conv2d_ex(*args, dev(bias), None, True, mx[0:1].zero_())
+    for y_fmt in ((4, False), (8, False)):
+        s = np.float32(y.max().item() * 0.8 / R.vmax(*y_fmt))
+        codes = torch.full((Bn * Ho * Wo * Cout * y_fmt[0] // 8 + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        B.dybit_conv2d_wb(*args, y_fmt, scalar(s), dev(bias), None, True, mx[1:2].zero_(), fp32=False, codes_out=codes[:-64])
+        assert B.dybit_last_gemm_kernel() == "f16_few"
+        torch.cuda.synchronize()
+        assert bool((codes[-64:] == 0xA5).all()) and mx[0].item() == mx[1].item()
+        want_codes = R.pack_rows(R.quantize(y.cpu().numpy().reshape(-1, Cout), s, *y_fmt), y_fmt[0])
+        assert np.array_equal(codes[:-64].cpu().numpy(), want_codes.ravel())
+
+
+def test_every_tap_reaches_its_pixel():
+    """A single non-zero filter code: the result is the input pixel that tap sees (zero outside the image)."""
+    x_fmt, w_fmt = (8, False), (4, True)
+    rng = np.random.default_rng(3)
+    qx = random_codes(rng, (1, 96, 98, 4), x_fmt)
+    qw = np.zeros((7 * 7, 7, 7, 4), dtype=np.uint8)
+    one = int(np.argmax(R.codebook(*w_fmt) == 1.0))
+    for t in range(49):
+        qw[t, t // 7, t % 7, t % 4] = one
+    y = B.dybit_conv2d(1, 96, 98, 4, 49, 7, 7, 2, 3, pack_rows_dev(qx.reshape(-1, 4), 8), x_fmt, scalar(1.0), pack_rows_dev(qw.reshape(49, -1), 4), w_fmt, scalar(1.0))
+    assert B.dybit_last_gemm_kernel() == "f16_few"
+    torch.cuda.synchronize()
+    want, _ = R.conv2d(qx, x_fmt, 1.0, qw, w_fmt, 1.0, 2, 3)
+    assert np.array_equal(y.cpu().numpy(), want.astype(np.float32))
