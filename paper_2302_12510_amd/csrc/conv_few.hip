@@ -70,16 +70,12 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
     // ---- weights: filter row by filter row, 32 codes each with zeros behind the row's own
     {
         const __amdgpu_buffer_rsrc_t rsrcW = word_descriptor(g.W, g.w_bytes);
+        const u32 w_end = (u32)whole_words(g.w_bytes), w_last = last_bytes(g.W, g.w_bytes);
         for (int r = tid; r < CB * 32 * g.kh; r += threads) {
             const int n = r / g.kh, fr = r - n * g.kh;
             const u32 off = n0 + n < g.N ? (u32)(((int64_t)(n0 + n) * K + fr * row_codes) * BW / 8) : kOob;
-            u32 w[4 * ragged_regs<BW>()];
-#pragma unroll
-            for (int i = 0; i < 4 * ragged_regs<BW>(); ++i) w[i] = i <= BW ? __builtin_amdgcn_raw_buffer_load_b32(rsrcW, (off & ~3u) + 4 * i, 0, 0) : 0u;
-            w[4 * ragged_regs<BW>() - 1] = off & 3u;
             u32x4 raw[ragged_regs<BW>()], t[(BW + 3) / 4];
-#pragma unroll
-            for (int p = 0; p < ragged_regs<BW>(); ++p) raw[p] = u32x4{w[4 * p], w[4 * p + 1], w[4 * p + 2], w[4 * p + 3]};
+            load_run_bounded<BW>(rsrcW, off, w_end, w_last, raw);
             align_run<BW>(raw, t);
             keep_codes<BW>(t, row_codes);
 #pragma unroll
@@ -113,13 +109,18 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
         u.runs = unit < f.units ? ((u.rows - 1) * g.stride + g.kh) * row_runs : 0;
         return u;
     };
-    auto fetch = [&](const Unit &u, int it, u32x4 (&raw)[ragged_regs<BA>()]) {
+    auto run_offset = [&](const Unit &u, int it) {
         const int iy = (int)((u32)it / (u32)row_runs), run = it - iy * row_runs, hi = u.hi_first + iy;
         const bool in = it < u.runs && (unsigned)hi < (unsigned)g.H;   // a row above or below the image: zeros
-        load_run_ragged<BA>(rsrcA, in ? (u32)((u.b * g.H + hi) * g.Wd * g.pix_bytes + run * 4 * BA) : kOob, raw);
+        return in ? (u32)((u.b * g.H + hi) * g.Wd * g.pix_bytes + run * 4 * BA) : kOob;
     };
-    auto decode = [&](int it, const u32x4 (&raw)[ragged_regs<BA>()]) {
+    auto fetch = [&](const Unit &u, int it, u32x4 (&raw)[ragged_regs<BA>()]) { load_run_ragged<BA>(rsrcA, run_offset(u, it), raw); };
+    auto decode = [&](const Unit &u, int it, u32x4 (&raw)[ragged_regs<BA>()]) {
         const int iy = (int)((u32)it / (u32)row_runs), run = it - iy * row_runs;
+        if (g.a_bytes & 3) {                                           // the tensor ends inside a word: the lanes whose runs hold its last bytes
+            const u32 off = run_offset(u, it), end = (u32)whole_words(g.a_bytes);
+            if (end - (off & ~3u) <= 4u * BA) join_last_bytes<BA>(off, end, last_bytes(g.A, g.a_bytes), raw);
+        }
         u32x4 t[(BA + 3) / 4];
         align_run<BA>(raw, t);
         if (last_codes != 32 && run == row_runs - 1) keep_codes<BA>(t, last_codes);   // behind the image: the next row
@@ -140,11 +141,11 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
         const int b = u.b, ho0 = u.ho0, rows = u.rows;
         // ---- the unit's input rows, decoded
         __syncthreads();                                               // the previous unit's fragments have been read (first: weights and zeros are written)
-        if (tid < u.runs) decode(tid, ahead);
+        if (tid < u.runs) decode(u, tid, ahead);
         for (int it = tid + threads; it < u.runs; it += threads) {
             u32x4 raw[ragged_regs<BA>()];
             fetch(u, it, raw);
-            decode(it, raw);
+            decode(u, it, raw);
         }
         fetch(unit_of(unit + walkers), tid, ahead);
         __syncthreads();

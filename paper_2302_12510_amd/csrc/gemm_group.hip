@@ -59,18 +59,14 @@ __global__ __launch_bounds__(kThreads, 4) void group_conv_kernel(const GemmArgs 
     // ---- weights of the group's columns, decoded once; rows are K codes, which may start at any byte: fetched word by word
     {
         const __amdgpu_buffer_rsrc_t rsrcW = word_descriptor(g.W, g.w_bytes);
+        const u32 w_end = (u32)whole_words(g.w_bytes), w_last = last_bytes(g.W, g.w_bytes);
         const int runs = c.ktiles * 2;
         for (int r = tid; r < CB * 32 * runs; r += kThreads) {
             const int row = r / runs, run = r - row * runs;
             const u32 first = (u32)(((int64_t)(n0 + row) * K + run * 32) * BW / 8);
             const u32 off = n0 + row < n_end && run * 32 < K ? first : kOob;
             u32x4 raw[ragged_regs<BW>()], t[(BW + 3) / 4];
-            u32 w[4 * ragged_regs<BW>()];
-#pragma unroll
-            for (int i = 0; i < 4 * ragged_regs<BW>(); ++i) w[i] = i <= BW ? __builtin_amdgcn_raw_buffer_load_b32(rsrcW, (off & ~3u) + 4 * i, 0, 0) : 0u;
-            w[4 * ragged_regs<BW>() - 1] = off & 3u;
-#pragma unroll
-            for (int p = 0; p < ragged_regs<BW>(); ++p) raw[p] = u32x4{w[4 * p], w[4 * p + 1], w[4 * p + 2], w[4 * p + 3]};
+            load_run_bounded<BW>(rsrcW, off, w_end, w_last, raw);
             align_run<BW>(raw, t);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {

@@ -140,6 +140,13 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     const u32 wrW = (u32)wrow * ROW_BYTES + (u32)wq * 64;
     const u32 rdW = (u32)(lane & 31) * ROW_BYTES + (u32)kgp * 128 + (u32)kq * 64;   // block kk adds 16 B, column block j adds 32 rows
 
+    // RAGGED: the last bytes of the operands, in the threads whose runs they end
+    u32 last_a = 0, last_w = 0;
+    if constexpr (CONV == RAGGED) {
+        if (m0 + wr * 32 + (lane & 31) == g.M - 1 && kgp == KG - 1 && kq == 1) last_a = last_bytes(g.A, g.a_bytes);
+        if (nrow == g.N - 1 && wq == 2 * KG - 1) last_w = last_bytes(g.W, g.w_bytes);
+    }
+
     // K steps are loaded in order, so the position of the next one is counted up instead of being
     // divided out of k every time: first k of the wave's k-group, and for a convolution its filter
     // row, filter column and first channel (all uniform over the wave, hence the readfirstlane above).
@@ -197,7 +204,7 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
         const u32 off = k0 < g.K ? offW + (u32)(kt * TK * CW::BITS / 8) : kOob;
         load_run<CW::BITS>(rsrcW, off, raw);
     };
-    auto decode_A = [&](const u32x4 *raw, int q) -> f16x8 {
+    auto decode_A = [&](const u32x4 *raw, int q, bool last) -> f16x8 {                      // last: the last K step
         u32 d[4];
         if constexpr (CONV == ROWS) {
             // shift the run into place and drop the taps outside the image (only the words group q
@@ -210,18 +217,18 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
             decode_eight<FMT_A>(t, q, d);
         } else if constexpr (CONV == RAGGED) {
             u32x4 t[(CA::BITS + 3) / 4];
-            align_run<CA::BITS>(raw, t);
+            align_run<CA::BITS>(raw, t, last ? last_a : 0u);
             decode_eight<FMT_A>(t, q, d);
         } else {
             decode_eight<FMT_A>(raw, q, d);
         }
         return __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]});
     };
-    auto stage_W = [&](const u32x4 *raw, int q, char *tile, bool first = false) {
+    auto stage_W = [&](const u32x4 *raw, int q, char *tile, bool first, bool last) {         // first, last: K step 0; the last one
         u32 d[4];
         if constexpr (CONV == RAGGED) {
             u32x4 t[(CW::BITS + 3) / 4];
-            align_run<CW::BITS>(raw, t);
+            align_run<CW::BITS>(raw, t, last ? last_w : 0u);
             if (first) keep_codes<CW::BITS>(t, head - wq * 32);      // K step 0: the odd part of K
             decode_eight<FMT_W>(t, q, d);
         } else {
@@ -250,8 +257,8 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
     load_A(rawA[1]);
     load_W(1, rawW[1]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) stage_W(rawW[0], q, lds, true);
-    fa = decode_A(rawA[0], 0);
+    for (int q = 0; q < 4; ++q) stage_W(rawW[0], q, lds, true, false);   // a ragged K is two steps at least
+    fa = decode_A(rawA[0], 0, false);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 4; ++j) fw[j] = read_W(lds, 0, j);
@@ -266,6 +273,7 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
         constexpr int s = decltype(stage_tag)::value;
         const char *cur = lds + s * STAGE_BYTES;
         char *nxt = lds + (s ^ 1) * STAGE_BYTES;
+        const bool last_next = kt + 1 == ktiles - 1;
         load_W(kt + 2, rawW[s]);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -277,10 +285,10 @@ __global__ __launch_bounds__(256 * KG, (KG == 1) ? 3 : 2) void gemm_mid_kernel(c
                                           : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
                 fw[j] = kk < 3 ? read_W(cur, kk + 1, j) : read_W(nxt, 0, j);
             }
-            fa = kk < 3 ? decode_A(rawA[s], kk + 1) : decode_A(rawA[s ^ 1], 0);
-            if (kk == 0) { stage_W(rawW[s ^ 1], 0, nxt); stage_W(rawW[s ^ 1], 1, nxt); }
-            if (kk == 1) stage_W(rawW[s ^ 1], 2, nxt);
-            if (kk == 2) stage_W(rawW[s ^ 1], 3, nxt);
+            fa = kk < 3 ? decode_A(rawA[s], kk + 1, kt == ktiles - 1) : decode_A(rawA[s ^ 1], 0, last_next);
+            if (kk == 0) { stage_W(rawW[s ^ 1], 0, nxt, false, last_next); stage_W(rawW[s ^ 1], 1, nxt, false, last_next); }
+            if (kk == 1) stage_W(rawW[s ^ 1], 2, nxt, false, last_next);
+            if (kk == 2) stage_W(rawW[s ^ 1], 3, nxt, false, last_next);
             if (kk == 2) load_A(rawA[s]);                           // K step kt + 2; tile kt's codes are fully decoded by now
 #pragma unroll
             for (int r = 0; r < 4; ++r) {

@@ -77,6 +77,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
         const int64_t n = n0 + j * 32 + (lane & 31);
         offW[j] = n < g.N ? (u32)(n * w_row_bytes + kq * 4 * BW) : kOob;
     }
+    // RAGGED: the last bytes of the operands, in the lanes whose row they end
+    u32 last_a = 0, last_w[CB] = {};
+    if (MODE == RAGGED && kq == 1) {
+        if (m == g.M - 1) last_a = last_bytes(g.A, g.a_bytes);
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+            if (n0 + j * 32 + (lane & 31) == g.N - 1) last_w[j] = last_bytes(g.W, g.w_bytes);
+    }
     const int steps = (K + 63) / 64, head = MODE == RAGGED ? K - (steps - 1) * 64 : 64;   // codes of K step 0
     auto first_code = [&](int t) { return t == 0 ? 0 : head + (t - 1) * 64; };
 
@@ -109,10 +117,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     auto contract = [&](int t, const u32x4 (&a)[NA], const u32x4 (&w)[CB][NW]) {
         u32x4 ta[(BA + 3) / 4], tw[CB][(BW + 3) / 4];
         if constexpr (MODE == RAGGED) {
-            align_run<BA>(a, ta);
+            align_run<BA>(a, ta, t == steps - 1 ? last_a : 0u);
 #pragma unroll
             for (int j = 0; j < CB; ++j) {
-                align_run<BW>(w[j], tw[j]);
+                align_run<BW>(w[j], tw[j], t == steps - 1 ? last_w[j] : 0u);
                 if (t == 0) keep_codes<BW>(tw[j], head - 32 * kq);   // uniform: the odd part of K
             }
         }
