@@ -169,8 +169,10 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     const int force = opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
 
-    // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.
-    if (!rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !opt.mfma_f16)))) {
+    // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.  That kernel counts the codes
+    // of K and the bits of a row in 32 bits (its waves look up to 3072 codes ahead); longer rows go to the others.
+    const bool short_rows = g.K < 0x7fff0000 / (a_bits > w_bits ? a_bits : w_bits);
+    if (!rows && short_rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !opt.mfma_f16)))) {
         switch (w_bits) {
             case 4: (wb ? launch_gemm_small_w0_wb : launch_gemm_small_w0)(g, a_bits, conv, st); return true;
             case 8: (wb ? launch_gemm_small_w2_wb : launch_gemm_small_w2)(g, a_bits, conv, st); return true;
