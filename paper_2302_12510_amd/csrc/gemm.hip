@@ -580,7 +580,6 @@ dybit_status conv2d_impl(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t C
     g.w_bytes = Cout * (g.K * w_fmt.bits / 8);
     if (all_groups) {
         g.N *= all_groups;
-        g.Cin *= all_groups;
         g.w_bytes *= all_groups;
         *launched = launch_group_conv(g, x_fmt.bits, w_fmt.bits, all_groups, (hipStream_t)stream);
         return *launched ? launch_status() : DYBIT_OK;

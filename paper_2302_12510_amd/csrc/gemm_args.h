@@ -146,7 +146,7 @@ bool launch_conv_few_w2_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w4_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w6_co(const GemmArgs &g, int a_bits, hipStream_t st);
 
-// Grouped convolution in one launch (gemm_group.hip): g describes the whole layer (Cin and N of all groups, K of one).  false:
+// Grouped convolution in one launch (gemm_group.hip): g describes the whole layer (N of all groups, Cin and K of one).  false:
 // a group's channels are not whole words, or its weights do not fit the LDS of a compute unit.
 bool launch_group_conv_w0(const GemmArgs &g, int a_bits, int groups, hipStream_t st);
 bool launch_group_conv_w2(const GemmArgs &g, int a_bits, int groups, hipStream_t st);

@@ -235,9 +235,9 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 
 bool launch_group_conv(const GemmArgs &g, int a_bits, int w_bits, int groups, hipStream_t st)
 {
-    const int Cg = g.Cin / groups;
+    const int Cg = g.Cin;
     // pieces of 8, 16 or 32 codes, whole words, inside one filter tap; 32-bit buffer offsets; no kernel forced
-    if (!g.w_signed || Cg % 8 || (Cg * a_bits) % 32 || g.M > 0x7fffffff || g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff) return false;
+    if (!g.w_signed || Cg % 8 || (Cg * a_bits) % 32 || g.N / groups > 0x7fffffff || g.M > 0x7fffffff || g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff) return false;
     if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 3) return false;
     if (dispatch_options().kernel) return false;
     switch (w_bits) {

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kThreads, 4) void group_conv_kernel(const GemmArgs 
         const u32 mm = m_strip + (lane & 31) < g.M ? (u32)m_strip + (lane & 31) : 0u;   // a row past M: pixel 0, not stored
         const u32 b = mm / plane, rem = mm - b * plane, ho = rem / (u32)g.Wo, wo = rem - ho * (u32)g.Wo;
         const int hi0 = (int)ho * g.stride - g.pad, wi0 = (int)wo * g.stride - g.pad;
-        const int offA = (((int)b * g.H + hi0) * g.Wd + wi0) * g.pix_bytes + gi * c.Cg * BA / 8;   // the image is under 2 GiB
+        const int offA = (((int)b * g.H + hi0) * g.Wd + wi0) * g.pix_bytes + gi * (c.Cg * BA / 8);   // the image is under 2 GiB; a group is whole words
 
         auto load_A = [&](int kt, u32x4 (&raw)[NA]) {
             u32 w[4 * NA];
@@ -173,23 +173,27 @@ __global__ __launch_bounds__(kThreads, 4) void group_conv_kernel(const GemmArgs 
     }
 }
 
+// The sizes behind the LDS request and the grid are computed in 64 bits: K goes up to 2^31, groups x columns to as many.
 template <int FA, int FW, int P, int CB>
 static bool launch_p(const GemmArgs &g, GroupArgs c, hipStream_t st)
 {
     if constexpr (P * Codec<FA>::BITS % 32 != 0) {
         return false;
     } else {
+        const int64_t ktiles = (g.K + 63) / 64, row_bytes = ktiles * 128 + 16;
+        const int64_t lds_bytes = CB * 32 * row_bytes + ktiles * 2 * (32 / P) * 8;
+        if (lds_bytes > 160 * 1024) return false;
+        c.ktiles = (int)ktiles;
+        c.row_bytes = (int)row_bytes;
         c.parts = (c.Cog + 32 * CB - 1) / (32 * CB);
         c.slabs = (int)((g.M + kSlab - 1) / kSlab);
-        const int64_t lds_bytes = (int64_t)CB * 32 * c.row_bytes + (int64_t)c.ktiles * 2 * (32 / P) * 8;
-        if (lds_bytes > 160 * 1024) return false;
         // resident: two workgroups per compute unit (512 threads at 128 registers) where their weights fit
-        const int per = 8 * c.groups * c.parts, resident = lds_bytes <= 80 * 1024 ? 512 : 256;
-        int walkers = resident / per * 8;
+        const int64_t columns = (int64_t)c.groups * c.parts, resident = lds_bytes <= 80 * 1024 ? 512 : 256;
+        int64_t walkers = resident / (8 * columns) * 8;
         if (walkers < 8) walkers = 8;
         if (walkers > (c.slabs + 7) / 8 * 8) walkers = (c.slabs + 7) / 8 * 8;
-        const int64_t grid = (int64_t)walkers * c.groups * c.parts;
-        if (grid > 0x7fffffff) return false;
+        const int64_t grid = walkers * columns;
+        if (grid * kThreads > 0xffffffff) return false;               // a launch is less than 2^32 threads
         auto k = group_conv_kernel<FA, FW, P, CB>;
         note_kernel(DYBIT_KERNEL_F16_GROUP);
         note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
@@ -203,10 +207,8 @@ static bool launch(const GemmArgs &g, int groups, hipStream_t st)
 {
     GroupArgs c{};
     c.groups = groups;
-    c.Cg = g.Cin / groups;
+    c.Cg = g.Cin;
     c.Cog = (int)(g.N / groups);
-    c.ktiles = (int)((g.K + 63) / 64);
-    c.row_bytes = c.ktiles * 128 + 16;
     const bool one = c.Cog <= 32;
     if (c.Cg % 32 == 0) return one ? launch_p<FA, FW, 32, 1>(g, c, st) : launch_p<FA, FW, 32, 2>(g, c, st);
     if (c.Cg % 16 == 0) return one ? launch_p<FA, FW, 16, 1>(g, c, st) : launch_p<FA, FW, 16, 2>(g, c, st);

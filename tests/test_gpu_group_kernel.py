@@ -37,3 +37,41 @@ def test_one_launch(x_fmt, w_fmt, geom, per_channel):
     got = y.cpu().numpy()
     assert_within(got, want, den)
     assert mx.item() == np.abs(got).max()
+
+
+def _sparse(n_bytes, at):
+    """A tensor of zero bytes but for {position: value}."""
+    q = torch.zeros(n_bytes, dtype=torch.uint8, device="cuda")
+    for i, v in at.items():
+        q[i] = v
+    return q
+
+
+def test_sizes_past_32_bits():
+    """Sizes whose products leave 32 bits: every group's codes still meet its own filters.  Codes of value 1 in the last channels."""
+    one = scalar(1.0)
+    # filters of 2^30 codes (8 x 8 taps of 2^24 channels): no kernel's LDS holds them, a launch per group
+    cg, fmt = 1 << 24, (2, True)
+    x = _sparse(64 * 2 * cg // 4, {2 * cg // 4 - 1: 0x40, 64 * 2 * cg // 4 - 1: 0x55})     # pixel 0: the last channel; pixel 63: the last four
+    w = _sparse(2 * 64 * cg // 4, {64 * cg // 4 + cg // 4 - 1: 0x40, 2 * 64 * cg // 4 - 1: 0x55})
+    y = B.dybit_group_conv2d(1, 8, 8, 2 * cg, 2, 8, 8, 1, 0, 2, x, fmt, one, w, fmt, one)
+    assert B.dybit_last_gemm_kernel() != "f16_group" and y.flatten().tolist() == [0.0, 5.0]
+    del x, w
+    # a pixel of 2^29 channels: the groups' channels start beyond 2^32 bits
+    groups, cg, fmt = 1 << 19, 1024, (8, False)
+    v = R.codebook(*fmt)
+    x = _sparse(groups * cg, {groups * cg - 1: 200, groups // 2 * cg: 100})
+    w = torch.zeros(groups, cg, dtype=torch.uint8, device="cuda")
+    w[:, 0], w[:, -1] = 3, 5
+    y = B.dybit_group_conv2d(1, 1, 1, groups * cg, groups, 1, 1, 1, 0, groups, x, fmt, one, w.reshape(-1), (8, True), one).flatten()
+    s = R.codebook(8, True)
+    assert B.dybit_last_gemm_kernel() == "f16_group"
+    assert y[-1].item() == np.float32(v[200] * s[5]) and y[groups // 2].item() == np.float32(v[100] * s[3]) and int((y != 0).sum()) == 2
+    del x, w
+    # 2^20 groups: one launch for them would be 2^32 threads
+    groups, cg, fmt = 1 << 20, 8, (4, False)
+    x = _sparse(groups * cg // 2, {groups * cg // 2 - 1: 0x70, 0: 0x07})
+    w = torch.full((groups * cg // 2,), 0x11, dtype=torch.uint8, device="cuda")
+    y = B.dybit_group_conv2d(1, 1, 1, groups * cg, groups, 1, 1, 1, 0, groups, x, fmt, one, w, (4, True), one).flatten()
+    want = np.float32(R.codebook(*fmt)[7] * R.codebook(4, True)[1])
+    assert y[0].item() == want and y[-1].item() == want and int((y != 0).sum()) == 2
