@@ -207,9 +207,11 @@ static bool plan(const GemmArgs &g, FewArgs &f, int &waves, int &lds_bytes, int 
     f.parts = (int)((g.N + 32 * CB - 1) / (32 * CB));
     f.row_bytes = g.kh * 64 + 16;
     const int taps = 32 / g.Cin;
-    f.in_cols = (g.Wo - 1) * g.stride + taps;
-    const int written = g.pad + (g.Wd * g.Cin + 31) / 32 * 32 / g.Cin;  // the last run of a row may reach past the image
-    if (f.in_cols < written) f.in_cols = written;
+    int64_t in_cols = (int64_t)(g.Wo - 1) * g.stride + taps;
+    const int64_t written = g.pad + ((int64_t)g.Wd * g.Cin + 31) / 32 * 32 / g.Cin;   // the last run of a row may reach past the image
+    if (in_cols < written) in_cols = written;
+    if (in_cols * g.Cin * 2 > 160 * 1024) return false;               // no row fits the LDS (padding and stride reach 2^31)
+    f.in_cols = (int)in_cols;
     f.pitch = (f.in_cols * g.Cin * 2 + 15) / 16 * 16;
     const int64_t fixed = (int64_t)CB * 32 * f.row_bytes + (kOut == OUT_CODES ? column_bytes<CB>() : 0);
     double best = 0;

@@ -68,3 +68,18 @@ def test_every_tap_reaches_its_pixel():
     torch.cuda.synchronize()
     want, _ = R.conv2d(qx, x_fmt, 1.0, qw, w_fmt, 1.0, 2, 3)
     assert np.array_equal(y.cpu().numpy(), want.astype(np.float32))
+
+
+def test_padding_and_stride_past_32_bits():
+    """The patch of such a convolution does not fit the LDS by far (its size leaves 32 bits): another kernel takes it."""
+    x_fmt, w_fmt, stride, pad = (8, False), (8, True), 1 << 26, 1 << 30
+    rng = np.random.default_rng(9)
+    qx, qw = random_codes(rng, (2, 8, 8, 4), x_fmt), random_codes(rng, (8, 3, 3, 4), w_fmt)
+    y = B.dybit_conv2d(2, 8, 8, 4, 8, 3, 3, stride, pad, pack_rows_dev(qx.reshape(-1, 4), 8), x_fmt, scalar(0.3), pack_rows_dev(qw.reshape(8, -1), 8), w_fmt,
+                       scalar(0.02))
+    assert y.shape == (2, 33, 33, 8) and B.dybit_last_gemm_kernel() != "f16_few"
+    want, den = R.conv2d(np.ascontiguousarray(qx[:, :3, :3]), x_fmt, 0.3, qw, w_fmt, 0.02, 1, 0)   # output (16, 16) sees the image's corner
+    got = y.cpu().numpy()
+    assert_within(got[:, 16:17, 16:17], want, den)
+    got[:, 16, 16] = 0
+    assert not got.any()
