@@ -455,14 +455,15 @@ static dybit_status dwconv_impl(int64_t B, int64_t H, int64_t W, int64_t C,
     if (blocks > 0x7fffffff || B > 0x7fffffff) return DYBIT_ERR_INVALID_ARG;
     hipStream_t hs = (hipStream_t)stream;
     dim3 grid;
-    if (plan_dw3(a, grid)) {
+    DwArgs a3 = a;                                                                 // the plan fills in its own tiles; the general kernel keeps those of a
+    if (plan_dw3(a3, grid)) {
         using namespace fast;
         auto with_image = [&](auto fa) {
             constexpr int FA = decltype(fa)::value;
             switch (w_fmt.bits * 2 + w_fmt.is_signed) {
-                case 4: launch_dw3<FA, F2U>(a, hs, grid); break;   case 5: launch_dw3<FA, F2S>(a, hs, grid); break;
-                case 8: launch_dw3<FA, F4U>(a, hs, grid); break;   case 9: launch_dw3<FA, F4S>(a, hs, grid); break;
-                case 16: launch_dw3<FA, F8U>(a, hs, grid); break;  case 17: launch_dw3<FA, F8S>(a, hs, grid); break;
+                case 4: launch_dw3<FA, F2U>(a3, hs, grid); break;   case 5: launch_dw3<FA, F2S>(a3, hs, grid); break;
+                case 8: launch_dw3<FA, F4U>(a3, hs, grid); break;   case 9: launch_dw3<FA, F4S>(a3, hs, grid); break;
+                case 16: launch_dw3<FA, F8U>(a3, hs, grid); break;  case 17: launch_dw3<FA, F8S>(a3, hs, grid); break;
             }
         };
         switch (x_fmt.bits * 2 + x_fmt.is_signed) {
