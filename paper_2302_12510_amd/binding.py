@@ -1,5 +1,6 @@
 """Thin binding of libdybit.so: argument marshalling only, through a native module for the calls that launch
-work (csrc/binding_native.cpp) and through ctypes for the rest.
+work (csrc/binding_native.cpp) and through ctypes for the rest.  The module is built against one torch and one Python;
+under another the launching calls go through ctypes too, with a warning (slower by some microseconds each).
 
 PyTorch-ROCm supplies device memory and streams; every step of the path runs in the
 library's HIP kernels.  Loading fails loudly when the library has not been built: there is
@@ -8,7 +9,9 @@ no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
+import warnings
 
 import torch  # imported first so that the library binds to the HIP runtime torch already loaded
 
@@ -39,9 +42,34 @@ def _n():
     global _native_module
     if _native_module is None:
         lib()
-        from . import _native                        # built beside the library; there is no fallback
-        _native_module = _native
+        try:
+            from . import _native                    # built beside the library
+            _native_module = _native
+        except ImportError as e:
+            warnings.warn(f"the native argument marshalling cannot be loaded ({e}): calls go through ctypes; "
+                          "`python -m paper_2302_12510_amd.build` builds it", RuntimeWarning, stacklevel=3)
+            _native_module = _Ctypes()
     return _native_module
+
+
+class _Ctypes:
+    """What _n() offers, through ctypes."""
+
+    def __getattr__(self, name):
+        entry = getattr(lib(), name)
+
+        def call(*args):
+            *args, stream = args
+            return entry(*(fmt(*a) if isinstance(a, (tuple, list)) else _ptr(a) if a is None or hasattr(a, "is_cuda") else operator.index(a)
+                           for a in args), _stream(stream))
+        setattr(self, name, call)
+        return call
+
+    def dybit_packed_bytes(self, pair, n):
+        return int(lib().dybit_packed_bytes(fmt(*pair), n))
+
+    def empty(self, like, floats, *sizes):
+        return torch.empty(sizes, dtype=torch.float32 if floats else torch.uint8, device=like.device)
 
 
 def lib() -> C.CDLL:

@@ -1,5 +1,7 @@
-"""The native argument marshalling of the binding (no GPU needed: every call here is refused before it launches anything)."""
+"""The native argument marshalling of the binding, and ctypes in its place where it cannot be imported (no GPU needed, but for
+the last test: every other call here is refused before it launches anything)."""
 import re
+import sys
 from pathlib import Path
 
 import numpy as np
@@ -54,3 +56,37 @@ def test_allocations():
     assert t.dtype == torch.float32 and t.shape == (3, 5) and t.device == CPU.device
     assert NATIVE.empty(CPU, False, 7).dtype == torch.uint8
     assert NATIVE.dybit_packed_bytes((6, True), 9) == 7
+
+
+@pytest.fixture
+def without_native(monkeypatch):
+    monkeypatch.setattr(B, "_native_module", None)
+    monkeypatch.setitem(sys.modules, B.__package__ + "._native", None)          # its import now fails
+    monkeypatch.delattr(sys.modules[B.__package__], "_native", raising=False)
+
+
+def test_without_the_native_module(without_native):
+    with pytest.warns(RuntimeWarning, match="native argument marshalling"):
+        n = B._n()
+    assert n is not NATIVE and B._n() is n
+    with pytest.raises(ValueError, match="expected a device tensor"):
+        B.dybit_gemm(1, 1, 16, CPU, (4, True), CPU, CPU, (4, True), CPU)
+    for pair, status in (((4, True), B.ERR_NULL), ((5, True), B.ERR_UNSUPPORTED_BITS), ([np.int64(4), np.bool_(True)], B.ERR_NULL)):
+        assert n.dybit_quantize(None, np.int64(16), pair, None, None, _Stream()) == status
+    assert n.empty(CPU, True, 3, 5).shape == (3, 5) and n.empty(CPU, False, 7).dtype == torch.uint8
+    assert n.dybit_packed_bytes((6, True), 9) == 7
+
+
+@pytest.mark.gpu
+@pytest.mark.filterwarnings("ignore:the native argument marshalling")
+def test_results_without_the_native_module(without_native):
+    x = torch.randn(64, 256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    def chain():
+        s = B.dybit_absmax_scale(x.reshape(-1), 4, True)
+        q = B.dybit_quantize(x.reshape(-1), s, 4, True)
+        word = torch.zeros(1, device="cuda")
+        return s, q, B.dybit_gemm_ex(64, 64, 256, q, (4, True), s, q, (4, True), s, absmax=word, relu=True), word
+    by_ctypes = chain()
+    B._native_module = NATIVE
+    for a, b in zip(by_ctypes, chain()):
+        assert torch.equal(a, b)
