@@ -965,7 +965,7 @@ extern "C" dybit_status dybit_quantize_pad(const float *x, int64_t rows, int64_t
     const int64_t groups = rows * (cols_padded / 4);
     const dim3 grid((unsigned)((groups + kThreads - 1) / kThreads < 256 * 64 ? (groups + kThreads - 1) / kThreads : 256 * 64));
     const int64_t blocks3 = (rows + 4 * kThreads - 1) / (4 * kThreads);
-    const bool three = cols == 3 && cols_padded == 4 && aligned16(x) && aligned16(codes_out) && blocks3 <= 0x7fffffff;
+    const bool three = cols == 3 && cols_padded == 4 && aligned16(x) && aligned16(codes_out) && blocks3 * kThreads <= 0x7fffffff;   // one launch's threads
 #define DYBIT_QP(B, S) \
     if (three) hipLaunchKernelGGL((quantize_pad3_kernel<B, S>), dim3((unsigned)blocks3), dim3(kThreads), 0, (hipStream_t)stream, x, rows, scale, codes_out, err); \
     else hipLaunchKernelGGL((quantize_pad_kernel<B, S>), grid, dim3(kThreads), 0, (hipStream_t)stream, \
