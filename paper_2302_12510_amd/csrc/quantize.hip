@@ -22,9 +22,10 @@ constexpr int kThreads = 256;
 #define DYBIT_QUANT_UNROLL 4
 #endif
 #define DYBIT_QUANT_UNROLL_SMALL 2
-#ifndef DYBIT_FQ_UNROLL_SMALL
-#define DYBIT_FQ_UNROLL_SMALL 1
-#endif
+// Fake-quant up to this size takes one load per lane: more workgroups.  Kernel times in a graph, four loads -> one (us): 2^14 floats
+// at 8 bits 5.0 -> 2.4, 2^20 9.4 -> 5.2, 2^22 9.2 -> 8.2, at 4 bits 7.8 -> 6.9, but 6.3 M at 4 bits 8.6 -> 9.6.  The 2-bit form, which
+// computes least, turns earlier: 2.4 M 4.9 -> 4.3, 3.1 M 4.9 -> 5.6.
+constexpr size_t fake_quant_small(int bits) { return bits == 2 ? (size_t)5 << 19 : (size_t)1 << 22; }
 constexpr size_t kQuantSmall = (size_t)1 << 21;     // in groups of four elements
 #ifndef DYBIT_QUANT_BLOCKS_PER_CU
 #define DYBIT_QUANT_BLOCKS_PER_CU 128
@@ -1006,12 +1007,12 @@ extern "C" dybit_status dybit_fake_quant(const float *x, size_t n, dybit_fmt f, 
     if (!aligned16(x) || !aligned16(y_out)) return DYBIT_ERR_ALIGNMENT;
     if (n == 0) return DYBIT_OK;
     hipStream_t hs = (hipStream_t)stream;
-    const bool small = n / 4 < kQuantSmall;                        // as the quantize pass
-    const int grid = grid_for(n / 4 + 1, kThreads * (small ? DYBIT_FQ_UNROLL_SMALL : 4), 256 * DYBIT_QUANT_BLOCKS_PER_CU);
+    const bool small = n <= fake_quant_small(f.bits);
+    const int grid = grid_for(n / 4 + 1, kThreads * (small ? 1 : 4), 256 * DYBIT_QUANT_BLOCKS_PER_CU);
     int *err = async_error_word();
     if (!err) return DYBIT_ERR_HIP;
 #define DYBIT_FQ(B, S) \
-    if (small) hipLaunchKernelGGL((fake_quant_kernel<B, S, DYBIT_FQ_UNROLL_SMALL>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err); \
+    if (small) hipLaunchKernelGGL((fake_quant_kernel<B, S, 1>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err); \
     else hipLaunchKernelGGL((fake_quant_kernel<B, S, 4>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err)
     switch (f.bits * 2 + f.is_signed) {
         case 4: DYBIT_FQ(2, false); break;   case 5: DYBIT_FQ(2, true); break;
