@@ -233,13 +233,28 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 #undef DYBIT_BUILD_OF
 }
 
+// Whether a launch per group beats the one-launch kernel.  For a pair of 4- and 2-bit formats in groups of whole 64-channel k groups
+// the tiled kernels have e4m3 forms, the one-launch kernel is fp16; so with weights of some size (its own advantage on small ones is
+// that it fills the device), more columns than its 32-column form takes and enough multiply-adds per group for the number of
+// groups, they win.  One launch -> one per group (us), 3 x 3, 4-bit pair: 2 groups of 128 -> 128 channels, M = 50176: 44.3 -> 29.4,
+// 4 groups 88.9 -> 71.2; M = 200704, 2 groups 162 -> 111; but 64 -> 64 channels, 4 groups 88.6 <- 109.6, and at M = 12544 128 -> 128
+// channels, 2 groups 20.2 <- 24.1.  Of 700 geometries measured (64 to 512 channels, 1 x 1 to 3 x 3, 2 to 8 groups) the line leaves 30
+// more than 3 % slower than a launch per group (at most 1.34 times) and 17 than one launch (1.25 times).
+static bool launch_per_group(const GemmArgs &g, int a_bits, int w_bits, int groups)
+{
+    if (a_bits > 4 || w_bits > 4 || g.Cin % 64 || dispatch_options().mfma_f16) return false;
+    if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 15) return false;
+    const int64_t Cog = g.N / groups, columns = (Cog + 63) / 64 * 64, weights = columns * g.K;
+    return Cog > 32 && (Cog <= 128 || g.K >= 512) && weights > 64 * 576 && (double)g.M * (double)weights >= 1.25e9 * groups;
+}
+
 bool launch_group_conv(const GemmArgs &g, int a_bits, int w_bits, int groups, hipStream_t st)
 {
     const int Cg = g.Cin;
     // pieces of 8, 16 or 32 codes, whole words, inside one filter tap; 32-bit buffer offsets; no kernel forced
     if (!g.w_signed || Cg % 8 || (Cg * a_bits) % 32 || g.N / groups > 0x7fffffff || g.M > 0x7fffffff || g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff) return false;
     if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 3) return false;
-    if (dispatch_options().kernel) return false;
+    if (dispatch_options().kernel || launch_per_group(g, a_bits, w_bits, groups)) return false;
     switch (w_bits) {
         case 4: return launch_group_conv_w0(g, a_bits, groups, st);
         case 8: return launch_group_conv_w2(g, a_bits, groups, st);
