@@ -116,11 +116,18 @@ void launch_gemm_general_wb(const GemmArgs &g, int a_bits, int w_bits, bool conv
 // pair) 512 x 512 x 4096 (64) 13.9 -> 8.4, 784 x 512 x 4608 (104) 17.7 -> 13.3, but 128 x 4096 x 1024 (128) 6.7 -> 7.6.  Rows
 // that start at any byte, 1200 x 1200 x 1532 (361) against the 128 x 128 fp16 kernel: 8-bit x 4-bit 17.9 -> 20.6, a 4-bit pair
 // (which has its e4m3 form only here) 16.9 -> 14.3, but 2999 x 1999 x 1532 (1504) 34.5 -> 39.9.  Long and narrow products stay
-// on the weight-stationary kernel.
+// on the weight-stationary kernel.  The line was measured for K up to 2^18 (1024 x 1024, 8-bit pair: 467 -> 393 at K = 2^16, 1866 ->
+// 1757 at 2^18), with rows at any byte up to 2^14 (1024 x 1024 x 9220, 8-bit x 4-bit 73.3 -> 59.2, 8-bit pair 78.8 -> 82.0).  A longer
+// K outgrows the caches, which this kernel's tiles lean on most, and the line halves: 1024 x 1024 x 2^20, 8-bit x 4-bit 6890 -> 8009,
+// 784 x 512 with a 4-bit pair 2558 -> 2715, but 512 x 512 2560 -> 1362; at any byte 1024 x 1024 x 65540, 8-bit pair 477 -> 619, and once
+// more from 2^19 on (1024 x 640 x 1048580 10353 -> 12993, 512 x 512 10712 -> 3584).
 static bool small_output(const GemmArgs &g, bool ragged, bool low_pair)
 {
     if (!ragged && g.M >= 16384) return false;
-    return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= (!low_pair ? 256 : ragged ? 384 : 104);
+    int line = !low_pair ? 256 : ragged ? 384 : 104;
+    if (ragged && g.K > 1 << 14) line /= 2;
+    if (g.K > 1 << 19) line /= 2;
+    return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= line;
 }
 
 // The few-channel kernel takes a convolution whose filter rows fit 32 codes with at least two taps (with one, no code would be

@@ -82,3 +82,20 @@ def test_small_kernel_convolutions(x_fmt, w_fmt, geom):
     assert_within(y.cpu().numpy(), want, den)
     assert np.array_equal(codes.cpu().numpy().ravel(), R.quantize(y.cpu().numpy(), y_scale, *y_fmt).ravel())
     assert torch.equal(only, codes)
+
+
+@pytest.mark.parametrize("fmts,shape,small", [(((8, False), (8, True)), (1024, 1024, 4096), True), (((8, False), (8, True)), (1024, 1088, 64), False),
+                                              (((8, False), (8, True)), (1024, 1024, (1 << 14) + 4), False), (((8, False), (8, True)), (512, 1024, (1 << 14) + 4), True),
+                                              (((4, False), (4, True)), (832, 512, 256), True), (((4, False), (4, True)), (832, 576, 256), False),
+                                              (((4, False), (4, True)), (1216, 1216, 132), True), (((4, False), (4, True)), (1216, 1216, (1 << 14) + 4), False),
+                                              (((8, False), (4, True)), (1024, 512, (1 << 19) + 64), True), (((8, False), (4, True)), (1024, 576, (1 << 19) + 64), False)])
+def test_line_of_the_small_kernel(fmts, shape, small):
+    """By tiles of 64 x 64, at half the line for a long K; code 1 everywhere: every sum is K."""
+    M, N, K = shape
+    (a_fmt, w_fmt), one = fmts, scalar(1.0)
+    byte = lambda f: {8: 64 if f[1] else 128, 4: 0x44 if f[1] else 0x88}[f[0]]      # noqa: E731  codes of value 1
+    a = torch.full((M * K * a_fmt[0] // 8,), byte(a_fmt), dtype=torch.uint8, device="cuda")
+    w = torch.full((N * K * w_fmt[0] // 8,), byte(w_fmt), dtype=torch.uint8, device="cuda")
+    c = B.dybit_gemm(M, N, K, a, a_fmt, one, w, w_fmt, one)
+    assert ("small" in B.dybit_last_gemm_kernel()) == small
+    assert bool((c == float(K)).all())
