@@ -417,7 +417,7 @@ dybit_status dybit_set_async_error_word(int32_t *device_word);
  *
  * dybit_set_option: overrides the automatic choice for the whole process, for tests and A/B
  * measurements.  name / value [host, NUL-terminated]:
- *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small"  -- takes the named kernel family whenever
+ *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small" | "few"  -- takes the named kernel family whenever
  *                  the problem meets its preconditions (otherwise the automatic choice continues, which
  *                  dybit_last_gemm_kernel shows)
  *   "gemm_mfma"    "auto" | "f16"   -- "f16" keeps pairs of 4- and 2-bit operands off the e4m3 kernels

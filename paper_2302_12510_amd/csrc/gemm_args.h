@@ -71,7 +71,7 @@ struct DispatchOptions {
     int mid_kgroups;   // 0 automatic, 1 or 2: k-groups of the 128 x 128 kernels
     int ws_off;        // 1: the weight-stationary kernel is left out of the automatic choice
 };
-enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5 };
+enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5, DYBIT_FORCE_FEW = 6 };
 DispatchOptions dispatch_options();
 // Record of the kernel a launch function started, per host thread (dybit_last_gemm_kernel reads it),
 // and of a HIP error met on the way (hipFuncSetAttribute, ...), which the entry point then reports.

@@ -33,7 +33,7 @@ bool apply_option(const char *name, const char *value)
     if (!strcmp(name, "gemm_kernel")) {
         const int v = is_auto ? 0 : !strcmp(value, "general") ? DYBIT_FORCE_GENERAL : !strcmp(value, "mid") ? DYBIT_FORCE_MID
                     : !strcmp(value, "large") ? DYBIT_FORCE_LARGE : !strcmp(value, "ws") ? DYBIT_FORCE_WS
-                    : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : -1;
+                    : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : !strcmp(value, "few") ? DYBIT_FORCE_FEW : -1;
         if (v < 0) return false;
         opt_kernel = v;
     } else if (!strcmp(name, "gemm_mfma")) {
@@ -130,18 +130,45 @@ static bool small_output(const GemmArgs &g, bool ragged, bool low_pair)
     return ((g.M + 63) / 64) * ((g.N + 63) / 64) <= line;
 }
 
+// Whether the few-channel kernel is the faster one (us, the kernel it replaces -> this one; stride 1 or 2, N output channels, M outputs).
+// Filters that the weight-stationary and 128 x 128 kernels' row mode takes as well (rows of exactly 32 codes, an even number of them):
+//   N <= 128: 8 x 8 taps of 4 channels, 64 out, 8-bit: codes out at M = 50176 11.5 -> 11.6, 100352 16.5 -> 13.7, 802816 74.4 -> 50.6;
+//     fp32 out at 200704 24.8 -> 25.5, 401408 41.0 -> 40.0, 802816 79.3 -> 65.6.
+//   N > 128: fp32 out only with K >= 256 and M from 393216 on (8 x 8 taps of 4, 256 out: 401408 123.9 -> 104.8, but 192 out at 12544
+//     10.2 -> 18.1; 4 x 4 of 8, 256 out: 254016 52.5 -> 68.4); codes out with K >= 128 and 3 * 2^30 multiply-adds (8 x 8 of 4, 160 out:
+//     200704 50.6 -> 42.5, but 12544 11.2 -> 12.0, and 2 x 2 of 16, 160 out, 50176: 1.1 to 1.4 times as long).
+// Any other filter would run on the general kernel (below 2048 outputs it does).  Codes out take 0.1 to 0.9 of its time everywhere.  fp32
+// out, with `units` the outputs times the groups of 128 columns that kernel walks over:
+//   where it reads code by code (7 x 7 of 4 at M = 9409 28.8 -> 8.9): with K >= 112 or units from 98304 on (0.2 to 0.95), with K >= 64 but for
+//     8-bit images at 16384 to 40960 units (there 1.0 to 1.1, else 0.3 to 1.0), with less K only small calls of narrower codes (0.8 to 0.95;
+//     8-bit and more columns 1.0 to 1.5);
+//   where it reads 16 codes at a time: with K >= 128 from 98304 units on (0.4 to 1.05); with at most 64 columns in the last 128, K >= 80 and
+//     M from 98304 on (0.5 to 1.0) or less K and M from 2^17 on (0.5 to 1.1); below 1.0 to 1.9.
+static bool few_channels_pay(const GemmArgs &g, int a_bits, bool codes)
+{
+    const bool whole_words = g.a_bytes % 4 == 0;
+    if (g.kw * g.Cin == 32 && g.kh % 2 == 0 && whole_words) {
+        if (g.N <= 128) return g.M >= (codes ? 1 << 16 : 1 << 18);
+        return codes ? g.K >= 128 && (double)g.M * (double)(g.N * g.K) >= 3.0 * (1 << 30) : g.K >= 256 && g.M >= 3 << 17;
+    }
+    if (g.M < 2048) return false;
+    if (codes) return true;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 15) == 0;
+    const int64_t units = g.M * ((g.N + 127) / 128);
+    if (aligned && (g.Cin == 16 || (g.kw * g.Cin % 16 == 0 && whole_words)))
+        return g.K >= 128 ? units >= 3 << 15 : (g.N - 1) % 128 < 64 && g.M >= (g.K >= 80 ? 3 << 15 : 1 << 17);
+    if (g.K >= 112 || units >= 3 << 15) return true;
+    if (g.K >= 64) return a_bits < 8 || units < 1 << 14 || units >= 5 << 13;
+    return a_bits < 8 && g.M < 1 << 14 && g.N <= 128;
+}
+
 // The few-channel kernel takes a convolution whose filter rows fit 32 codes with at least two taps (with one, no code would be
-// decoded twice) and whose fragments start on groups of eight codes.  Filters that the weight-stationary kernel's row mode
-// takes as well (rows of exactly 32 codes, an even number of them) go there while the outputs are few: 8 x 8 taps of 4 channels,
-// stride 2, 64 channels out, 8-bit operands, row mode -> this kernel (us): codes out at 50176 outputs 11.5 -> 11.6, 100352
-// 16.5 -> 13.7, 802816 74.4 -> 50.6; fp32 out at 200704 24.8 -> 25.5, 401408 41.0 -> 40.0, 802816 79.3 -> 65.6.  Others would run
-// on the general kernel (7 x 7 taps at 9409 outputs 28.8 -> 8.9); below 2048 outputs they stay there.
-static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, hipStream_t st)
+// decoded twice) and whose fragments start on groups of eight codes.
+static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forced, hipStream_t st)
 {
     const bool dense = (int64_t)g.pix_bytes * 8 == (int64_t)g.Cin * a_bits, codes = codes_only(g);
     if (!dense || a_bits == 2 || (g.Cin != 4 && g.Cin != 8 && g.Cin != 16) || g.kw < 2 || g.kw * g.Cin > 32 || g.stride * (int64_t)g.Cin % 8) return false;
-    const bool row_mode = g.kw * g.Cin == 32 && g.kh % 2 == 0 && g.N <= 128 && g.a_bytes % 4 == 0;
-    if (g.N > 256 || g.M < (!row_mode ? 2048 : codes ? 1 << 16 : 1 << 18) || g.M > 0x7fffffff || (g.q_out && !codes)) return false;
+    if (g.N > 256 || g.M > 0x7fffffff || (g.q_out && !codes) || (!forced && !few_channels_pay(g, a_bits, codes))) return false;
     if (g.a_bytes >= 0x7fffffff || g.w_bytes >= 0x7fffffff || ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.W)) & 3)) return false;
     switch (w_bits) {
         case 4: return (codes ? launch_conv_few_w0_co : launch_conv_few_w0)(g, a_bits, st);
@@ -156,7 +183,8 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 {
     if (!g.w_signed) return false;                                  // every width 2, 4, 6, 8 has a decoder; weights are signed
     const DispatchOptions opt = dispatch_options();
-    if (conv && !opt.kernel && !opt.mid_tile && !opt.mid_kgroups && g.M >= 1 && g.N >= 1 && launch_conv_few(g, a_bits, w_bits, st)) return true;
+    const bool few = opt.kernel == DYBIT_FORCE_FEW;
+    if (conv && g.M >= 1 && g.N >= 1 && (few || (!opt.kernel && !opt.mid_tile && !opt.mid_kgroups)) && launch_conv_few(g, a_bits, w_bits, few, st)) return true;
     if (g.M < 1 || g.N < 1 || g.K < 64 || (conv && g.K % 64)) return false;
     const bool ragged = g.K % 64 != 0;                              // a matrix product whose rows start at any byte
     // a convolution needs whole 64-code k groups inside a filter tap, or (few channels) filter rows of
@@ -173,7 +201,7 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 
     bool large;
     const bool low_pair = (a_bits == 4 || a_bits == 2) && (w_bits == 4 || w_bits == 2);
-    const int force = opt.kernel;
+    const int force = few ? 0 : opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
 
     // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.  That kernel counts the codes

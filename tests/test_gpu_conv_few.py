@@ -17,9 +17,16 @@ GEOMS = [(1, 97, 103, 4, 64, 7, 7, 2, 3), (2, 64, 70, 4, 64, 9, 8, 2, 3), (3, 31
          (5, 23, 21, 8, 150, 5, 4, 1, 2), (1, 400, 9, 4, 40, 2, 5, 2, 8)]
 
 
+@pytest.fixture
+def few():
+    B.dybit_set_option("gemm_kernel", "few")                                    # also where another kernel is the faster one
+    yield
+    B.dybit_set_option("gemm_kernel", "auto")
+
+
 @pytest.mark.parametrize("x_fmt,w_fmt", [((8, True), (8, True)), ((6, False), (4, True)), ((4, False), (6, True)), ((6, True), (2, True))])
 @pytest.mark.parametrize("geom", GEOMS)
-def test_few_channel_kernel(x_fmt, w_fmt, geom):
+def test_few_channel_kernel(few, x_fmt, w_fmt, geom):
     Bn, H, W, Cin, Cout, kh, kw, stride, pad = geom
     if (kh * kw * Cin * w_fmt[0]) % 8 or (Cin * w_fmt[0]) % 8:
         pytest.skip("filters of whole bytes")
@@ -83,3 +90,28 @@ def test_padding_and_stride_past_32_bits():
     assert_within(got[:, 16:17, 16:17], want, den)
     got[:, 16, 16] = 0
     assert not got.any()
+
+
+# filter, N, side of the output (no padding; stride 2 for four channels, else 1), codes out -> whether the kernel takes it unasked
+@pytest.mark.parametrize("cin,kh,kw,n,side,codes,takes", [
+    (4, 8, 8, 64, 240, True, False), (4, 8, 8, 64, 256, True, True), (4, 8, 8, 64, 511, False, False), (4, 8, 8, 64, 512, False, True),   # row mode takes them as well
+    (4, 8, 8, 160, 512, False, False), (4, 8, 8, 160, 628, False, True), (4, 8, 8, 160, 256, True, False), (4, 8, 8, 160, 300, True, True), (16, 2, 2, 160, 512, True, False),
+    (8, 5, 2, 64, 300, False, False), (8, 5, 2, 64, 320, False, True), (8, 5, 2, 96, 320, False, False), (8, 7, 4, 128, 314, False, True),  # 16 codes at a time
+    (8, 2, 2, 64, 340, False, False), (8, 2, 2, 64, 363, False, True), (8, 2, 2, 64, 46, True, True), (8, 2, 2, 64, 45, True, False),
+    (4, 7, 7, 64, 46, False, True), (8, 3, 3, 64, 46, False, True), (8, 3, 3, 64, 130, False, False), (8, 3, 3, 64, 203, False, True), (8, 3, 1, 64, 200, False, False),
+    (8, 1, 3, 160, 222, False, True), (8, 1, 3, 64, 222, False, False)])
+def test_rule(cin, kh, kw, n, side, codes, takes):
+    """The line between this kernel and those it replaces, from both sides; same values on either."""
+    stride = 8 // min(cin, 8)
+    H, W = (side - 1) * stride + kh, (side - 1) * stride + kw
+    x = torch.randint(0, 256, (H * W * cin,), dtype=torch.uint8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(side))
+    w = torch.randint(0, 256, (n * kh * kw * cin,), dtype=torch.uint8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    args = (1, H, W, cin, n, kh, kw, stride, 0, x, (8, False), scalar(0.3), w, (8, True), scalar(0.02))
+    call = (lambda: B.dybit_conv2d_wb(*args, (8, False), scalar(1.0), relu=True, fp32=False)[1]) if codes else (lambda: B.dybit_conv2d(*args))
+    y = call()
+    assert (B.dybit_last_gemm_kernel() == "f16_few") == takes
+    B.dybit_set_option("gemm_kernel", "few" if not takes else "general")
+    other = call()
+    B.dybit_set_option("gemm_kernel", "auto")
+    a, b = (t.double() if not codes else t.short().double() for t in (y, other))
+    assert (a - b).abs().max() <= (1 if codes else 1e-5 * kh * kw * cin * 0.006 * 128 * 64)   # sums in another order: a code beside, 1e-5 of sum |a b|
