@@ -48,9 +48,8 @@ struct DwArgs {
     int a_bits, a_signed, w_bits, w_signed;
     int in_h, in_w;                                // extent of the input patch, halo included
     int tiles_h, tiles_w, groups;
-    // dw3_kernel: output rows of a thread (tiles_h = strips, tiles_w = column groups).  A grid row covers `images` whole images
-    // (bands = 1) or, of an image too large for 32-bit offsets, one of `bands` bands of band_rows output rows
-    int rows, images, bands, band_rows;
+    int images, rows;                              // dw3_kernel: images of a grid row, output rows of a thread (tiles_h = strips, tiles_w = column groups)
+    int pad_top;                                   // dw3_kernel: padding above the image (pad, but for the later bands of a large image)
 };
 
 // Scale, bias, ReLU, maximum and the stores of four neighbouring channels; elem is the index of the first.
@@ -140,10 +139,8 @@ __global__ __launch_bounds__(kThreads, 4) void dw3_kernel(const DwArgs a)
     constexpr int BA = fast::Codec<FA>::BITS, BW = fast::Codec<FW>::BITS;
     constexpr int DW = cols_of(S), NP = (DW - 1) * S + 3;                          // input columns of a thread
     constexpr float kExp = (float)(1u << fast::Codec<FA>::ACC_EXP) * (float)(1u << fast::Codec<FW>::ACC_EXP);
-    const int b_first = (int)(blockIdx.y / (u32)a.bands) * a.images;   // first image of this grid row, images in it
+    const int b_first = blockIdx.y * a.images;                    // first image of this grid row, images in it
     const int images = min(a.images, a.B - b_first);
-    const int ho_first = (int)(blockIdx.y % (u32)a.bands) * a.band_rows;
-    const int hi_first = max(ho_first * S - a.pad, 0);            // first input row the band reads (the whole image: 0)
     const int quads = a.C / 4;
     int id = blockIdx.x * kThreads + threadIdx.x;
     const int quad = id % quads; id /= quads;
@@ -151,12 +148,10 @@ __global__ __launch_bounds__(kThreads, 4) void dw3_kernel(const DwArgs a)
     const int strip = id % a.tiles_h;
     const int b = id / a.tiles_h;
     const bool live = b < images;
-    const int c = quad * 4, wo = colg * DW, ho = ho_first + strip * a.rows;
-    const u32 pix_bytes = a.C * BA / 8, row_bytes = a.W * pix_bytes, image_bytes = a.H * row_bytes;   // an image in bands: b is 0
-    const int band_in = max(min((ho_first + a.band_rows - 1) * S - a.pad + 3, a.H) - hi_first, 0);    // input rows the band reads
+    const int c = quad * 4, wo = colg * DW, ho = strip * a.rows;
+    const u32 pix_bytes = a.C * BA / 8, row_bytes = a.W * pix_bytes, image_bytes = a.H * row_bytes;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t *>(reinterpret_cast<const uint8_t *>(a.X)) + ((int64_t)b_first * a.H + hi_first) * row_bytes, 0,
-        a.bands > 1 ? band_in * row_bytes : images * image_bytes, 0x00020000);
+        const_cast<uint8_t *>(reinterpret_cast<const uint8_t *>(a.X)) + (int64_t)b_first * image_bytes, 0, images * image_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.Wt), 0, 9u * a.C * BW / 8, 0x00020000);
 
     u32 col_off[NP];                                              // a column outside the image reads zeros: code 0 is 0.0
@@ -165,9 +160,9 @@ __global__ __launch_bounds__(kThreads, 4) void dw3_kernel(const DwArgs a)
         const int wi = wo * S - a.pad + p;
         col_off[p] = (live && (unsigned)wi < (unsigned)a.W) ? wi * pix_bytes + c * BA / 8 : fast::kOob;
     }
-    int hi = ho * S - a.pad;                                      // next input row to read
+    int hi = ho * S - a.pad_top;                                  // next input row to read
     auto load_row = [&](u32 *raw) {
-        const u32 row = (unsigned)hi < (unsigned)a.H ? b * image_bytes + (hi - hi_first) * row_bytes : kRowOob;
+        const u32 row = (unsigned)hi < (unsigned)a.H ? b * image_bytes + hi * row_bytes : kRowOob;
 #pragma unroll
         for (int p = 0; p < NP; ++p) raw[p] = load_quad<FA>(rx, row + col_off[p]);
         ++hi;
@@ -371,14 +366,13 @@ void launch_dw3(const DwArgs &a, hipStream_t st, dim3 grid)
     else hipLaunchKernelGGL((dw3_kernel<FA, FW, 2>), grid, dim3(kThreads), 0, st, a);
 }
 
-// Plans dw3_kernel: the rows of a thread, and the images or the band of a grid row.  Byte offsets with room for the out-of-range ones
-// are 32-bit, so a grid row reads less than 2^30 bytes of the image tensor: an image of 2^30 bytes and more goes in bands of output
-// rows (8192 x 8192 x 16, 8-bit, fp32 results at stride 2: 2258 -> 646 us against the run-time-geometry kernel).  False: not a 3 x 3
-// filter at stride 1 or 2, or three image rows hold 2^30 bytes.
+// Plans dw3_kernel: the rows of a thread and the images of a grid row.  False: the call is outside its range (an image of 2^30
+// bytes or more, see launch_bands: byte offsets with room for the out-of-range ones are 32-bit), or not a 3 x 3 filter at stride 1 or 2.
 bool plan_dw3(DwArgs &a, dim3 &grid)
 {
     if (a.kh != 3 || a.kw != 3 || a.stride > 2 || a.C > (1 << 20)) return false;
-    const int64_t row_bytes = (int64_t)a.W * a.C * a.a_bits / 8, image_bytes = a.H * row_bytes;
+    const int64_t image_bytes = (int64_t)a.H * a.W * a.C * a.a_bits / 8;
+    if (image_bytes >= kRowOob) return false;
     const int64_t quads = a.C / 4, colg = (a.Wo + cols_of(a.stride) - 1) / cols_of(a.stride);
     // Rows: what a thread does once (two rows more to decode, taps, scales, addresses) is worth about 1.2 rows, so long strips do
     // less work, short ones fill the chip.  The longest of 1 .. 16 rows with the least (waves per SIMD, 4 at least) x (rows + 1.2)
@@ -392,30 +386,52 @@ bool plan_dw3(DwArgs &a, dim3 &grid)
         const int64_t cost = waves * (10 * rows + 12);
         if (cost <= best) { best = cost; a.rows = rows; }
     }
-    constexpr int64_t kMaxThreads = 0x7fffff00;
-    int64_t strips = (a.Ho + a.rows - 1) / a.rows, images = 1, bands = 1;
-    if (image_bytes >= kRowOob) {
-        const int64_t out_rows = ((kRowOob - 1) / row_bytes - 3) / a.stride + 1;    // of a band: (out_rows - 1) stride + 3 input rows
-        if ((kRowOob - 1) / row_bytes < 3) return false;
-        if (a.rows > out_rows) a.rows = (int)out_rows;
-        strips = out_rows / a.rows;
-        if (strips * colg * quads > kMaxThreads) strips = kMaxThreads / (colg * quads);
-        if (strips < 1) return false;
-        bands = (a.Ho + strips * a.rows - 1) / (strips * a.rows);
-    } else {
-        images = (kRowOob - 1) / image_bytes;
-        if (images > a.B) images = a.B;
-        if (images * strips * colg * quads > kMaxThreads) images = kMaxThreads / (strips * colg * quads);
-        if (images < 1) return false;
-    }
-    const int64_t grid_rows = (a.B + images - 1) / images * bands;
-    if (grid_rows > 65535) return false;
-    a.tiles_h = (int)strips;
+    a.tiles_h = (a.Ho + a.rows - 1) / a.rows;
     a.tiles_w = (int)colg;
+    const int64_t image_threads = a.tiles_h * colg * quads;
+    int64_t images = image_bytes ? (kRowOob - 1) / image_bytes : 1;
+    if (images > a.B) images = a.B;
+    if (images * image_threads > 0x7fffff00) images = 0x7fffff00 / image_threads;
+    if (images < 1 || (a.B + images - 1) / images > 65535) return false;
     a.images = (int)images;
-    a.bands = (int)bands;
-    a.band_rows = (int)(strips * a.rows);
-    grid = dim3((unsigned)((images * strips * colg * quads + kThreads - 1) / kThreads), (unsigned)grid_rows);
+    grid = dim3((unsigned)((images * image_threads + kThreads - 1) / kThreads), (unsigned)((a.B + images - 1) / images));
+    return true;
+}
+
+// launch(arguments, grid) for a 3 x 3 filter: once, or for images of 2^30 bytes and more once per image and band of output rows that
+// reads less than that.  False, with nothing launched: another kernel has to take the call (a last such case: three rows of the
+// image hold 2^30 bytes).  One image of 8192 x 8192 x 16, 8-bit, fp32 results: run-time-geometry kernel 3446 us at stride 1, 2258 at
+// stride 2; in bands 1529 and 510.
+template <class F>
+bool launch_bands(DwArgs a, F launch)
+{
+    a.pad_top = a.pad;
+    dim3 grid;
+    if (plan_dw3(a, grid)) {
+        launch(a, grid);
+        return true;
+    }
+    if (a.kh != 3 || a.kw != 3 || a.stride > 2) return false;
+    const int64_t row_bytes = (int64_t)a.W * a.C * a.a_bits / 8, in_rows = (kRowOob - 1) / row_bytes;
+    if (a.H * row_bytes < kRowOob || in_rows < 3) return false;
+    const int64_t band = (in_rows - 3) / a.stride + 1;
+    for (int pass = 0; pass < 2; ++pass)                          // every band is planned before the first is launched
+        for (int64_t b = 0; b < a.B; ++b)
+            for (int64_t ho = 0; ho < a.Ho; ho += band) {
+                DwArgs s = a;
+                s.B = 1;
+                s.Ho = (int)(a.Ho - ho < band ? a.Ho - ho : band);
+                const int64_t top = ho * a.stride - a.pad, first = top > 0 ? top : 0, end = top + (s.Ho - 1) * (int64_t)a.stride + 3;
+                s.H = (int)((end < a.H ? end : a.H) - first);
+                if (s.H < 0) s.H = 0;                             // padding only
+                else s.X += (b * a.H + first) * row_bytes / 4;
+                s.pad_top = (int)(first - top);
+                const int64_t elem = (b * a.Ho + ho) * a.Wo * a.C;
+                if (s.Y) s.Y += elem;
+                if (s.q_out) s.q_out += elem * a.q_bits / 8;
+                if (!plan_dw3(s, grid)) return false;
+                if (pass) launch(s, grid);
+            }
     return true;
 }
 
@@ -476,9 +492,8 @@ static dybit_status dwconv_impl(int64_t B, int64_t H, int64_t W, int64_t C,
     const int64_t blocks = B * a.tiles_h * a.tiles_w * a.groups;
     if (blocks > 0x7fffffff || B > 0x7fffffff) return DYBIT_ERR_INVALID_ARG;
     hipStream_t hs = (hipStream_t)stream;
-    dim3 grid;
-    DwArgs a3 = a;                                                                 // the plan fills in its own tiles; the general kernel keeps those of a
-    if (plan_dw3(a3, grid)) {
+    // the plan fills in its own tiles in a copy; the general kernel keeps those of a
+    const bool done = launch_bands(a, [&](const DwArgs &a3, dim3 grid) {
         using namespace fast;
         auto with_image = [&](auto fa) {
             constexpr int FA = decltype(fa)::value;
@@ -493,8 +508,8 @@ static dybit_status dwconv_impl(int64_t B, int64_t H, int64_t W, int64_t C,
             case 8: with_image(std::integral_constant<int, F4U>{}); break;   case 9: with_image(std::integral_constant<int, F4S>{}); break;
             case 16: with_image(std::integral_constant<int, F8U>{}); break;  case 17: with_image(std::integral_constant<int, F8S>{}); break;
         }
-        return launch_status();
-    }
+    });
+    if (done) return launch_status();
 #define DYBIT_DW(BA, BW) launch_dw<BA, BW>(a, (size_t)lds_bytes, hs, (unsigned)blocks)
     switch (x_fmt.bits * 16 + w_fmt.bits) {
         case 0x22: DYBIT_DW(2, 2); break;  case 0x24: DYBIT_DW(2, 4); break;  case 0x28: DYBIT_DW(2, 8); break;

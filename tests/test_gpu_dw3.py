@@ -66,7 +66,7 @@ def test_images_past_the_first_grid_row():
 
 @pytest.mark.parametrize("stride", [1, 2])
 def test_image_of_2_30_bytes(stride):
-    """Such an image goes in bands of output rows: every row is what a slice of the image gives."""
+    """Such an image goes in bands of output rows, a launch each: every row is what a slice of the image gives."""
     H, W, C = 8192, 8192, 16
     g = torch.Generator(device="cuda").manual_seed(4)
     x = torch.randint(0, 256, (H, W * C), dtype=torch.uint8, device="cuda", generator=g)
