@@ -302,8 +302,8 @@ dybit_status dybit_dwconv2d_wb(int64_t B, int64_t H, int64_t W, int64_t C,
  * pixel and filter, i.e. (Cin / groups) * bits a multiple of 8 for both formats (DYBIT_ERR_ALIGNMENT).
  * w_scale [device]: 1 float, or Cout floats when w_per_channel is 1.  bias [device, may be NULL]: Cout floats.
  * residual [device, may be NULL]: like Y.  Y [device]: [B][Ho][Wo][Cout] floats.  y_absmax: as in dybit_conv2d_ex.
- * One launch where the filters are signed and a group's input channels are a multiple of 8 and whole 32-bit words of a pixel,
- * else one per group on its channel slices (groups = Cin = Cout is a depthwise convolution with the
+ * One launch where the filters are signed, a group's input channels are a multiple of 8 and whole 32-bit words of a pixel
+ * and that is the faster way, else one per group on its channel slices (groups = Cin = Cout is a depthwise convolution with the
  * filters laid out [C][kh][kw][1]; dybit_dwconv2d, with channel-innermost filters, is the fast form of that). */
 dybit_status dybit_group_conv2d(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t Cout,
                                 int32_t kh, int32_t kw, int32_t stride, int32_t pad, int32_t groups,

@@ -1,5 +1,5 @@
-// Argument marshalling of binding.py in native code: every C entry point of the library as a Python function that takes
-// tensors, (bits, signed) pairs, numbers and a stream in the order of its prototype and returns the status.
+// Argument marshalling of binding.py in native code: the C entry points that launch work as Python functions that take
+// tensors, (bits, signed) pairs, numbers and a stream in the order of their prototypes and return the status.
 //
 // A call through ctypes cost 6 to 7 us of argument conversion (a structure per format, a wrapper per pointer, the stream
 // object), more than most small kernels run for: scale, encode and product of 64 x 64 x 256 took 26.8 us, 16.6 us with this

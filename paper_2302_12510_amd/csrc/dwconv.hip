@@ -46,7 +46,6 @@ struct DwArgs {
     int *async_error;
     int B, H, W, C, Ho, Wo, kh, kw, stride, pad, relu;
     int a_bits, a_signed, w_bits, w_signed;
-    int in_h, in_w;                                // extent of the input patch, halo included
     int tiles_h, tiles_w, groups;
     int images, rows;                              // dw3_kernel: images of a grid row, output rows of a thread (tiles_h = strips, tiles_w = column groups)
     int pad_top;                                   // dw3_kernel: padding above the image (pad, but for the later bands of a large image)
@@ -487,7 +486,6 @@ static dybit_status dwconv_impl(int64_t B, int64_t H, int64_t W, int64_t C,
     a.B = (int)B; a.H = (int)H; a.W = (int)W; a.C = (int)C; a.Ho = (int)Ho; a.Wo = (int)Wo;
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad; a.relu = relu;
     a.a_bits = x_fmt.bits; a.a_signed = x_fmt.is_signed; a.w_bits = w_fmt.bits; a.w_signed = w_fmt.is_signed;
-    a.in_h = in_h; a.in_w = in_w;
     a.tiles_h = (int)((Ho + TH - 1) / TH); a.tiles_w = (int)((Wo + TW - 1) / TW); a.groups = (int)((C + CG - 1) / CG);
     const int64_t blocks = B * a.tiles_h * a.tiles_w * a.groups;
     if (blocks > 0x7fffffff || B > 0x7fffffff) return DYBIT_ERR_INVALID_ARG;

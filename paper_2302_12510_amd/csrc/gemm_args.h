@@ -17,7 +17,7 @@
 namespace dybit {
 
 // The builds of a kernel source, by what its epilogue writes: fp32 results; fp32 results and / or their DyBit codes;
-// codes only (codes_epilogue.h: the three kernel families that the codes-only chain runs on).
+// codes only (codes_epilogue.h).  Which source has which: at the launch functions below.
 enum : int { OUT_FP32 = 0, OUT_WRITE_BACK = 1, OUT_CODES = 2 };
 constexpr int kOut = DYBIT_WB;
 constexpr bool kWriteBack = DYBIT_WB != 0;
@@ -83,10 +83,10 @@ hipError_t take_hip_error();       // ... and this last: the first error noted s
 // Tiled MFMA kernels for 4- and 8-bit operands with signed weights: the large-tile kernel
 // (gemm_fast.hip, 256 x 256) and the mid-size-tile kernel (gemm_mid.hip, 128 x 128), one
 // translation unit per weight format.  a_bits is 4 or 8; signedness comes from g.
-// Every kernel source is compiled twice: plain, and with DYBIT_WB=1 as the write-back build whose
-// epilogue also encodes the results (g.q_out must then be set); those entry points end in _wb.  The
-// weight-stationary, 128 x 128 and e4m3 kernels are compiled a third time (DYBIT_WB=2, _co) for calls that want
-// codes only (codes_only() below).
+// Builds: plain; with DYBIT_WB=1 (_wb) the write-back build whose epilogue also encodes the results (g.q_out must then be
+// set); with DYBIT_WB=2 (_co) the build for calls that want codes only (codes_only() above).  The general, 256 x 256 and
+// small-output kernels have the first two, the weight-stationary, 128 x 128 and e4m3 kernels all three, the few-channel
+// convolution plain and _co, the grouped convolution the plain one.
 bool launch_gemm_fast_w0(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 4-bit signed
 bool launch_gemm_fast_w2(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 8-bit signed
 bool launch_gemm_fast_w4(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 6-bit signed

@@ -20,8 +20,9 @@ FORMATS = [(b, s) for b in (2, 4, 6, 8) for s in (True, False)]
 @pytest.mark.parametrize("groups,cin,cout", [(2, 128, 128), (4, 256, 64), (2, 96, 40), (3, 24, 9), (8, 64, 64), (1, 64, 70)])
 @pytest.mark.parametrize("geom", [(3, 1, 1), (1, 1, 0), (3, 2, 1)])
 def test_group_conv_matches_oracle(x_fmt, w_fmt, groups, cin, cout, geom):
-    """Groups of 64 / 128 channels (the tiled kernels on a channel slice of every pixel), of 48 (sixteen-code
-    vectors), of 8 (code by code); bias, shortcut, ReLU and the running maximum across the groups."""
+    """Groups of 64 / 128, 48, 32 and 8 channels on whichever kernel takes them (one launch where a group's channels are whole
+    words, else one per group; the tiled kernels on channel slices: test_gpu_group_rule); bias, shortcut, ReLU and the
+    running maximum across the groups."""
     k, stride, pad = geom
     cg = cin // groups
     if (cg * x_fmt[0]) % 8 or (cg * w_fmt[0]) % 8:
