@@ -88,7 +88,7 @@ __device__ __forceinline__ void load_run_bounded(const __amdgpu_buffer_rsrc_t rs
     w[4 * N - 1] = off & 3u;
 #pragma unroll
     for (int p = 0; p < N; ++p) raw[p] = u32x4{w[4 * p], w[4 * p + 1], w[4 * p + 2], w[4 * p + 3]};
-    join_last_bytes<BITS>(off, end, last, raw);
+    if (end - (off & ~3u) <= 4u * BITS) join_last_bytes<BITS>(off, end, last, raw);   // hardly any run: skipped by whole waves
 }
 
 // The run's words in place, as load_run() would have fetched them from an aligned address.  last: bytes to join to the extra word.
