@@ -417,7 +417,7 @@ dybit_status dybit_set_async_error_word(int32_t *device_word);
  *
  * dybit_set_option: overrides the automatic choice for the whole process, for tests and A/B
  * measurements.  name / value [host, NUL-terminated]:
- *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small" | "few"  -- takes the named kernel family whenever
+ *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small" | "few" | "patch"  -- takes the named kernel family whenever
  *                  the problem meets its preconditions (otherwise the automatic choice continues, which
  *                  dybit_last_gemm_kernel shows)
  *   "gemm_mfma"    "auto" | "f16"   -- "f16" keeps pairs of 4- and 2-bit operands off the e4m3 kernels
@@ -444,7 +444,9 @@ typedef enum {
     DYBIT_KERNEL_F16_SMALL = 12,     /* fp16 MFMA, 32-row tile, K split over the waves of a workgroup   */
     DYBIT_KERNEL_F16_GROUP = 13,     /* fp16 MFMA, weight-stationary grouped convolution                */
     DYBIT_KERNEL_F8_SMALL = 14,      /* e4m3 MFMA, 32-row tile, K split over the waves of a workgroup   */
-    DYBIT_KERNEL_F16_FEW = 15        /* fp16 MFMA, few-channel convolution, input decoded once          */
+    DYBIT_KERNEL_F16_FEW = 15,       /* fp16 MFMA, few-channel convolution, input decoded once          */
+    DYBIT_KERNEL_F16_PATCH = 16,     /* fp16 MFMA, convolution of 64 and more channels, input decoded once */
+    DYBIT_KERNEL_F8_PATCH = 17       /* e4m3 MFMA, the same                                             */
 } dybit_kernel_id;
 int32_t dybit_last_gemm_kernel(void);
 dybit_status dybit_set_option(const char *name, const char *value);

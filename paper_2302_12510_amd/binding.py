@@ -155,7 +155,7 @@ def _ptr(t) -> int | None:
 # ---- host-only --------------------------------------------------------------
 KERNEL_NAMES = ("none", "general", "f16_256", "f16_128_kg1", "f16_128_kg2", "f16_128_rows", "f16_ws",
                 "f8_256", "f8_128_kg1", "f8_128_kg2", "f8_64", "f8_ws", "f16_small",
-                "f16_group", "f8_small", "f16_few")
+                "f16_group", "f8_small", "f16_few", "f16_patch", "f8_patch")
 
 
 def dybit_last_gemm_kernel() -> str:

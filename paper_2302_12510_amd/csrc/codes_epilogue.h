@@ -219,11 +219,12 @@ __device__ __forceinline__ void shortcut_values(uint32_t t, const ShortcutFormat
     r[3] = shortcut_product(v1[1], f.s);
 }
 
-// The strip of 32 rows by 32 CB columns a wave holds.  RB: bits of the shortcut's codes (0: none).
-// cols: the factors stage_columns has left in LDS.  Returns the lane's maximum of |result|.
-template <int CB, int RB, int BITS>
+// The strip of 32 rows by 32 CB columns a wave holds or, STACKED, of 32 CB rows by 32 columns (block j is then rows 32 j ..
+// + 31).  RB: bits of the shortcut's codes (0: none).  cols: the factors stage_columns has left in LDS, for the strip's first
+// column on, the biases `staged` columns behind.  Returns the lane's maximum of |result|.
+template <int CB, int RB, int BITS, bool STACKED = false>
 __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast::f32x16 (&acc)[CB], const int64_t m_strip,
-                                                   const int64_t n0, const int rows, const float *cols, const OutScale os)
+                                                   const int64_t n0, const int rows, const float *cols, const OutScale os, const int staged = CB * 32)
 {
     static_assert(CB % 2 == 0, "column blocks are stored in pairs");
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -249,12 +250,13 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
 
     // the lane's own 32 shortcut codes of each block pair (lower half-wave: first block, upper: second)
     uint32_t rw[RB ? RB : 1];
-    auto block_base = [&](int jp) { return (uint32_t)(n0 + 64 * jp + 32 * kq); };
-    auto whole_pair = [&](int jp) { return n0 + 64 * (jp + 1) <= g.N; };                         // uniform
+    auto block_base = [&](int jp) { return (uint32_t)(STACKED ? n0 : n0 + 64 * jp + 32 * kq); };
+    auto whole_pair = [&](int jp) { return (STACKED ? n0 + 32 : n0 + 64 * (jp + 1)) <= g.N; };   // uniform
+    auto lane_row = [&](int jp) { return (uint32_t)(STACKED ? 64 * jp + 32 * kq + row : row); };
     auto request_shortcut = [&](int jp) {
         if constexpr (RB != 0) {
             const uint32_t at = block_base(jp) * RB / 8;
-            load_words<RB>(rres, at < rrow ? (uint32_t)row * rrow + at : fast::kOob, rw, whole_pair(jp), (int)rrow - (int)at);
+            load_words<RB>(rres, at < rrow ? lane_row(jp) * rrow + at : fast::kOob, rw, whole_pair(jp), (int)rrow - (int)at);
         }
     };
     request_shortcut(0);
@@ -282,8 +284,8 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int q = 2 * h + i;
-                    const f32x4 al = *reinterpret_cast<const f32x4 *>(cols + 32 * j + 8 * q + 4 * kq);
-                    const f32x4 bv = *reinterpret_cast<const f32x4 *>(cols + CB * 32 + 32 * j + 8 * q + 4 * kq);
+                    const f32x4 al = *reinterpret_cast<const f32x4 *>(cols + (STACKED ? 0 : 32 * j) + 8 * q + 4 * kq);
+                    const f32x4 bv = *reinterpret_cast<const f32x4 *>(cols + staged + (STACKED ? 0 : 32 * j) + 8 * q + 4 * kq);
                     float r[4];
                     if constexpr (RB != 0) shortcut_values<RB>(rt[jb][q], sf, r);
 #pragma unroll
@@ -293,7 +295,7 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
                         c[4 * i + u] = fmaxf(v, relu_floor);
                     }
                 }
-                if (track) {
+                if (track && (!STACKED || 32 * j + row < rows)) {
 #pragma unroll
                     for (int u = 0; u < 8; u += 2) mx = fmaxf(fmaxf(mx, fabsf(c[u])), fabsf(c[u + 1]));
                 }
@@ -350,10 +352,10 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
         }
         quads_to_words<BITS>(t, words);
         const uint32_t at = block_base(jp) * BITS / 8;
-        const uint32_t off = (rqp.ok && at < qrow) ? (uint32_t)row * qrow + at : fast::kOob;
+        const uint32_t off = (rqp.ok && at < qrow) ? lane_row(jp) * qrow + at : fast::kOob;
         store_words<BITS>(rq, off, words, whole_pair(jp), (int)qrow - (int)at);
     }
-    return row < rows ? mx : 0.0f;
+    return STACKED || row < rows ? mx : 0.0f;
 }
 
 // Picks the variant for the call's formats.  big: what stage_columns returned; acc is brought to scale here then.

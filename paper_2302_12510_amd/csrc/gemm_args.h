@@ -71,7 +71,7 @@ struct DispatchOptions {
     int mid_kgroups;   // 0 automatic, 1 or 2: k-groups of the 128 x 128 kernels
     int ws_off;        // 1: the weight-stationary kernel is left out of the automatic choice
 };
-enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5, DYBIT_FORCE_FEW = 6 };
+enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5, DYBIT_FORCE_FEW = 6, DYBIT_FORCE_PATCH = 7 };
 DispatchOptions dispatch_options();
 // Record of the kernel a launch function started, per host thread (dybit_last_gemm_kernel reads it),
 // and of a HIP error met on the way (hipFuncSetAttribute, ...), which the entry point then reports.
@@ -86,7 +86,7 @@ hipError_t take_hip_error();       // ... and this last: the first error noted s
 // Builds: plain; with DYBIT_WB=1 (_wb) the write-back build whose epilogue also encodes the results (g.q_out must then be
 // set); with DYBIT_WB=2 (_co) the build for calls that want codes only (codes_only() above).  The general, 256 x 256 and
 // small-output kernels have the first two, the weight-stationary, 128 x 128 and e4m3 kernels all three, the few-channel
-// convolution plain and _co, the grouped convolution the plain one.
+// and many-channel convolutions plain and _co, the grouped convolution the plain one.
 bool launch_gemm_fast_w0(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 4-bit signed
 bool launch_gemm_fast_w2(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 8-bit signed
 bool launch_gemm_fast_w4(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 6-bit signed
@@ -145,6 +145,17 @@ bool launch_conv_few_w0_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w2_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w4_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w6_co(const GemmArgs &g, int a_bits, hipStream_t st);
+
+// Convolution of 64 and more channels with its input decoded once (conv_patch.hip); plain and codes-only builds.  false: the
+// pixels of 128 outputs do not fit the LDS.
+bool launch_conv_patch_w0(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w2(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w4(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w6(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w0_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w2_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w4_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w6_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 
 // Grouped convolution in one launch (gemm_group.hip): g describes the whole layer (N of all groups, Cin and K of one).  false:
 // a group's channels are not whole words, or its weights do not fit the LDS of a compute unit.

@@ -33,7 +33,8 @@ bool apply_option(const char *name, const char *value)
     if (!strcmp(name, "gemm_kernel")) {
         const int v = is_auto ? 0 : !strcmp(value, "general") ? DYBIT_FORCE_GENERAL : !strcmp(value, "mid") ? DYBIT_FORCE_MID
                     : !strcmp(value, "large") ? DYBIT_FORCE_LARGE : !strcmp(value, "ws") ? DYBIT_FORCE_WS
-                    : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : !strcmp(value, "few") ? DYBIT_FORCE_FEW : -1;
+                    : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : !strcmp(value, "few") ? DYBIT_FORCE_FEW
+                    : !strcmp(value, "patch") ? DYBIT_FORCE_PATCH : -1;
         if (v < 0) return false;
         opt_kernel = v;
     } else if (!strcmp(name, "gemm_mfma")) {
@@ -179,6 +180,45 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
     }
 }
 
+// Whether the many-channel kernel is the faster one.  It decodes an input code once per tile, so it needs taps that share their
+// pixels (2 x 2 at stride 2, 63 x 49 x 49 x 128 to 256 channels: 14.9 -> 22.6 us).  Measured over 600 convolutions of 64 to 512
+// channels and 49 to 401408 outputs, 2 x 2 to 5 x 5 taps, all formats, fp32 and codes out (us, the kernel it replaces -> this one; 3 x 3):
+//   small-output kernel: a pair of 4- and 2-bit formats to the line of that kernel (3267 outputs, 256 to 64: 7.9 -> 10.5), others to 136
+//     tiles of 64 x 64 (15 x 23 x 23, 128 to 64, 124 tiles: 9.2 -> 10.8; 36 x 16 x 16, 144 tiles: 13.6 -> 11.9);
+//   weight-stationary kernel: at stride 1 with 4- and 2-bit weights everywhere (64 x 56 x 56, 64 to 64, 4-bit pair 25.7 -> 22.8, 6- by 4-bit
+//     35.8 -> 29.5); wider weights take a lane longer to decode, and at stride 2 a tile looks at four pixels per output, of which fewer fit the
+//     LDS: below 40960 outputs (25088: 11.6 -> 10.0 to 28.0 -> 18.0; 50176: 8-bit pair 11.9 -> 11.7, 8- by 6-bit 12.9 -> 14.6, stride 2
+//     11.4 -> 11.2 to 14.2 -> 20.3);
+//   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8);
+//   128 x 128 and 64 x 64 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
+static bool many_channels_pay(const GemmArgs &g, int w_bits, bool f8, bool large)
+{
+    if (g.kh * (int64_t)g.kw < 2 * (int64_t)g.stride * g.stride) return false;
+    if (small_output(g, false, f8) && (f8 || ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 136)) return false;
+    if (large && !f8 && w_bits > 4) return false;
+    const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
+    const bool stationary = g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024;
+    return !stationary || g.M < 40960 || (g.stride == 1 && w_bits <= 4);
+}
+
+// It takes a convolution with 64-code k groups inside one filter tap whose outputs look at consecutive pixels,
+// one after the other (no output reaches past the image with its first taps).
+static bool launch_conv_patch(const GemmArgs &g, int a_bits, int w_bits, bool low_pair, hipStream_t st)
+{
+    const bool codes = codes_only(g);
+    if (g.Cin % 64 || g.kh * (int64_t)g.kw < 2 || g.kh * (int64_t)g.kw > 30 || g.M > 0x7fffffff || g.N > 1 << 16 || (g.q_out && !codes)) return false;
+    if ((g.Ho - 1) * (int64_t)g.stride >= g.H || (g.Wo - 1) * (int64_t)g.stride >= g.Wd || g.pad >= g.kh || g.pad >= g.kw) return false;
+    if (codes ? g.q_row_bytes > 1 << 20 || (g.res_codes && g.res_row_bytes > 1 << 20) : g.ldc > 1 << 20) return false;
+    if (g.M / ((int64_t)g.Ho * g.Wo) * g.H * (int64_t)g.Wd > 0x3fffffff) return false;
+    switch (w_bits) {
+        case 4: return (codes ? launch_conv_patch_w0_co : launch_conv_patch_w0)(g, a_bits, low_pair, st);
+        case 8: return (codes ? launch_conv_patch_w2_co : launch_conv_patch_w2)(g, a_bits, low_pair, st);
+        case 6: return (codes ? launch_conv_patch_w4_co : launch_conv_patch_w4)(g, a_bits, low_pair, st);
+        case 2: return (codes ? launch_conv_patch_w6_co : launch_conv_patch_w6)(g, a_bits, low_pair, st);
+        default: return false;
+    }
+}
+
 bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hipStream_t st)
 {
     if (!g.w_signed) return false;                                  // every width 2, 4, 6, 8 has a decoder; weights are signed
@@ -199,15 +239,29 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     const bool wb = g.q_out != nullptr, codes = codes_only(g);
 #define DYBIT_BUILD_OF(name) (codes ? name##_co : wb ? name##_wb : name)
 
-    bool large;
     const bool low_pair = (a_bits == 4 || a_bits == 2) && (w_bits == 4 || w_bits == 2);
-    const int force = few ? 0 : opt.kernel;
+    const int force = few || opt.kernel == DYBIT_FORCE_PATCH ? 0 : opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
+    const bool f8 = low_pair && !opt.mfma_f16;
+
+    // Too few 256 x 256 tiles cannot fill 256 compute units, and a narrow N wastes most of a
+    // 256-wide tile.  With a short K the epilogue (the stores of C, the loads of the shortcut)
+    // dominates, and the 128 x 128 kernel with three workgroups per compute unit keeps more
+    // of those memory operations in flight: measured over M x N from 6272 x 2048 to
+    // 401408 x 256, it is 1.1 to 1.7 times faster up to K = 512, level at K = 1024 (fp16
+    // kernels) or K = 2048 (fp8 kernels), and 10 to 30 % slower beyond.
+    const int64_t tiles256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+    bool large = g.N > 128 && tiles256 >= 128 && g.K >= (low_pair ? 2048 : 1024);
+
+    // Convolution with its input decoded once per tile
+    const bool choose = !force && !opt.mid_tile && !opt.mid_kgroups && !opt.ws_off;
+    if (conv && (opt.kernel == DYBIT_FORCE_PATCH || (choose && many_channels_pay(g, w_bits, f8, large))) &&
+        launch_conv_patch(g, a_bits, w_bits, f8, st)) return true;
 
     // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.  That kernel counts the codes
     // of K and the bits of a row in 32 bits (its waves look up to 3072 codes ahead); longer rows go to the others.
     const bool short_rows = g.K < 0x7fff0000 / (a_bits > w_bits ? a_bits : w_bits);
-    if (!rows && short_rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, low_pair && !opt.mfma_f16)))) {
+    if (!rows && short_rows && (force == DYBIT_FORCE_SMALL || (!force && !opt.mid_tile && !opt.mid_kgroups && small_output(g, ragged, f8)))) {
         switch (w_bits) {
             case 4: (wb ? launch_gemm_small_w0_wb : launch_gemm_small_w0)(g, a_bits, conv, st); return true;
             case 8: (wb ? launch_gemm_small_w2_wb : launch_gemm_small_w2)(g, a_bits, conv, st); return true;
@@ -236,19 +290,10 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
         large = true;
     } else if (force == DYBIT_FORCE_MID) {
         large = false;
-    } else {
-        // Too few 256 x 256 tiles cannot fill 256 compute units, and a narrow N wastes most of a
-        // 256-wide tile.  With a short K the epilogue (the stores of C, the loads of the shortcut)
-        // dominates, and the 128 x 128 kernel with three workgroups per compute unit keeps more
-        // of those memory operations in flight: measured over M x N from 6272 x 2048 to
-        // 401408 x 256, it is 1.1 to 1.7 times faster up to K = 512, level at K = 1024 (fp16
-        // kernels) or K = 2048 (fp8 kernels), and 10 to 30 % slower beyond.
-        const int64_t tiles256 = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-        large = g.N > 128 && tiles256 >= 128 && g.K >= (low_pair ? 2048 : 1024);
     }
     // two operands of 4 or 2 bits: every value is exact in e4m3, so the fp8 matrix path (twice the
     // fp16 rate, byte decoders) takes them unless the "gemm_mfma" option asks for the fp16 kernels
-    if (low_pair && !rows && !ragged && !opt.mfma_f16) {
+    if (f8 && !rows && !ragged) {
         if (w_bits == 4) return DYBIT_BUILD_OF(launch_gemm_f8_w0)(g, a_bits, conv, large, st);
         return DYBIT_BUILD_OF(launch_gemm_f8_w6)(g, a_bits, conv, large, st);
     }
