@@ -10,8 +10,12 @@
 // columns of one block, so that a row's codes leave as 128-bit words (4-bit codes: one store instruction per
 // 2048 results, against 32 byte stores) and a shortcut given as codes arrives the same way; and a row past M
 // is a lane that stores nothing, so the running maximum needs no selection per value.
-// Per result: 11 vector-ALU instructions (20 there) and 1/32 of a store (2 there).  What bounds the layers that use it is
-// still vector-ALU issue: decode of A plus these.  Measured, batch 64 to 128, store_strip_wb -> here: first layer of a
+// Per result: 9 vector-ALU instructions for 4- and 6-bit codes, 11 for 8-bit ones (20 there), and 1/32 of a store (2 there).
+// What bounds the layers that use it is still vector-ALU issue: decode of A plus these.  The two instructions of difference are
+// the shift that tests a value for a decision point and the extraction of its code: with 16 fraction bits the first is a
+// minimum of half-words, the second is done by the byte permutes that pack (first layer below 57.0 -> 54.1 us with its encoder,
+// block 182.6 -> 177.6).  A variant per sign of the format would save one more; it doubled the variants, and what the compiler
+// keeps for all of them spilled 11 to 51 registers (first layer 60.4).  Measured, batch 64 to 128, store_strip_wb -> here: first layer of a
 // residual network (802816 x 64 x 256, 8-bit, 4-bit codes out) with its input encoding 104.5 -> 82.8 us; a bottleneck block
 // on 56 x 56 (401408 rows, 256 -> 64 -> 64 -> 256 channels, mixed widths, 6-bit codes out, 8-bit shortcut) 273 -> 186 us.
 //
@@ -245,7 +249,10 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
     uint32_t floor_bits = (uint32_t)__builtin_amdgcn_readfirstlane(g.relu ? 0 : 0x7fc00000);
     asm volatile("" : "+s"(floor_bits));                                // see store_strip_wb
     const float relu_floor = __uint_as_float(floor_bits);
-    const uint32_t mag_fields = ((1u << rqp.m) - 1u) * (BITS == 8 ? 0x01010101u : BITS == 6 ? 0x00041041u : 0x00001111u);
+    constexpr int GB = requant_fraction<BITS>();
+    constexpr uint32_t kOnes = BITS == 8 ? 0x01010101u : BITS == 6 ? 0x00041041u : 0x11111111u;   // a word's fields: four codes, 4-bit: eight
+    constexpr uint32_t kSign = kOnes << (BITS - 1), kMag = kSign - kOnes;
+    const uint32_t mag_fields = kOnes * ((1u << rqp.m) - 1u);
     float mx = 0.0f;
 
     // the lane's own 32 shortcut codes of each block pair (lower half-wave: first block, upper: second)
@@ -273,14 +280,14 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
             }
             if (jp + 1 < CB / 2) request_shortcut(jp + 1);
         }
-        uint32_t out[2][4];                                             // packed quads of the two blocks
+        uint32_t out[2][BITS == 4 ? 2 : 4];                             // packed quads of the two blocks
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
             const int j = 2 * jp + jb;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {                               // two quads at a time: fewer live registers
                 float c[8];
-                uint32_t zb[8], settle_key = 0xffffffffu;
+                uint32_t zb[8];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int q = 2 * h + i;
@@ -300,57 +307,91 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
                     for (int u = 0; u < 8; u += 2) mx = fmaxf(fmaxf(mx, fabsf(c[u])), fabsf(c[u + 1]));
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    zb[u] = requant_lower(c[u], rqp);
-                    settle_key = min(settle_key, requant_settle_key(zb[u]));
-                }
-                uint32_t comp[8];                                       // complements of the magnitude codes
+                for (int u = 0; u < 8; ++u) zb[u] = requant_lower<BITS>(c[u], rqp);
+                bool settle;                                            // whether some fraction reads zero
+                if constexpr (GB == 16) {
+                    uint16_t key = (uint16_t)zb[0];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) comp[u] = requant_complement(zb[u], rqp);
-                if (__builtin_amdgcn_ballot_w64(settle_key == 0u)) {    // some value on a decision point: the exact decision,
+                    for (int u = 1; u < 8; ++u) key = min(key, (uint16_t)zb[u]);
+                    settle = key == 0;
+                } else {
+                    uint32_t key = 0xffffffffu;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) key = min(key, zb[u] << (32 - GB));
+                    settle = key == 0;
+                }
+                if (__builtin_amdgcn_ballot_w64(settle)) {              // some value on a decision point: the exact decision,
                     uint32_t open = 0;                                  // a lane's values one after the other
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) open |= requant_needs_settling(zb[u]) ? 1u << u : 0u;
+                    for (int u = 0; u < 8; ++u) open |= (zb[u] << (32 - GB)) == 0u ? 1u << u : 0u;
                     while (__builtin_amdgcn_ballot_w64(open != 0u)) {
                         const uint32_t first = open & (0u - open);
                         float x = 0.0f;
                         uint32_t k = 0;
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
-                            if (first & (1u << u)) { x = c[u]; k = comp[u]; }
-                        const uint32_t top = (1u << rqp.m) - 1u, fixed = top - requant_settle(x, top + 1u - k, rqp);
+                            if (first & (1u << u)) { x = c[u]; k = requant_complement<BITS>(zb[u], rqp); }
+                        const uint32_t top = (1u << rqp.m) - 1u, fixed = (top - requant_settle(x, top + 1u - k, rqp)) << GB;
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) comp[u] = (first & (1u << u)) ? fixed : comp[u];
+                        for (int u = 0; u < 8; ++u) zb[u] = (first & (1u << u)) ? fixed : zb[u];
                         open &= open - 1u;
                     }
                 }
-                uint32_t w[2];                                          // four fields each
+                // the complements of the magnitude codes, packed: bytes 2 of the words, 8-bit codes by extraction
+                constexpr int PER = BITS == 4 ? 8 : 4, WORDS = 8 / PER;
+                uint32_t w[WORDS];
+                if constexpr (BITS == 4) {
+                    const uint32_t even = __builtin_amdgcn_perm(zb[2], zb[0], 0x0c0c0602u), even_up = __builtin_amdgcn_perm(zb[6], zb[4], 0x06020c0cu);
+                    const uint32_t odd = __builtin_amdgcn_perm(zb[3], zb[1], 0x0c0c0602u) | __builtin_amdgcn_perm(zb[7], zb[5], 0x06020c0cu);
+                    w[0] = (odd << 4 | even) | even_up;
+                } else if constexpr (BITS == 6) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i) w[i] = (((comp[4 * i + 3] << BITS | comp[4 * i + 2]) << BITS | comp[4 * i + 1]) << BITS) | comp[4 * i];
+                    for (int i = 0; i < 2; ++i) {
+                        const uint32_t even = __builtin_amdgcn_perm(zb[4 * i + 2], zb[4 * i], 0x0c060c02u), odd = __builtin_amdgcn_perm(zb[4 * i + 3], zb[4 * i + 1], 0x0c060c02u);
+                        const uint32_t pairs = odd << 6 | even;          // 12 bits in each half
+                        w[i] = (pairs & 0xfffu) | ((pairs >> 4) & ~0xfffu);
+                    }
+                } else {
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
+                    for (int i = 0; i < 2; ++i) {
+                        uint32_t k[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) k[u] = requant_complement<BITS>(zb[4 * i + u], rqp);
+                        w[i] = (((k[3] << BITS | k[2]) << BITS | k[1]) << BITS) | k[0];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < WORDS; ++i) {
                     w[i] ^= mag_fields;
                     if (rqp.is_signed) {                                // uniform
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) w[i] |= ((__float_as_uint(c[4 * i + u]) >> rqp.sign_shift) & rqp.sign_mask) << (u * BITS);
+                        for (int u = 0; u < PER; ++u) w[i] |= ((__float_as_uint(c[PER * i + u]) >> rqp.sign_shift) & rqp.sign_mask) << (u * BITS);
                         // a field whose magnitude is zero loses its sign
-                        constexpr uint32_t ones = BITS == 8 ? 0x01010101u : BITS == 6 ? 0x00041041u : 0x00001111u;
-                        constexpr uint32_t sign = ones << (BITS - 1), magm = sign - ones;
-                        const uint32_t t = w[i] & magm;
-                        w[i] = t | (w[i] & (t + magm) & sign);
+                        const uint32_t t = w[i] & kMag;
+                        w[i] = t | (w[i] & (t + kMag) & kSign);
                     }
-                    out[jb][2 * h + i] = w[i];
+                    out[jb][WORDS * h + i] = w[i];
                 }
             }
         }
-        uint32_t t[8], words[BITS];
+        uint32_t words[BITS];
+        if constexpr (BITS == 4) {                                      // out: two groups of four codes in a word
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            swap_halves(out[0][q], out[1][q]);                          // lower half: block 0, upper half: block 1
-            t[2 * q] = out[0][q];
-            t[2 * q + 1] = out[1][q];
+            for (int h = 0; h < 2; ++h) {
+                swap_halves(out[0][h], out[1][h]);                      // lower half: block 0, upper half: block 1
+                words[2 * h] = __builtin_amdgcn_perm(out[1][h], out[0][h], 0x05040100u);
+                words[2 * h + 1] = __builtin_amdgcn_perm(out[1][h], out[0][h], 0x07060302u);
+            }
+        } else {
+            uint32_t t[8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                swap_halves(out[0][q], out[1][q]);
+                t[2 * q] = out[0][q];
+                t[2 * q + 1] = out[1][q];
+            }
+            quads_to_words<BITS>(t, words);
         }
-        quads_to_words<BITS>(t, words);
         const uint32_t at = block_base(jp) * BITS / 8;
         const uint32_t off = (rqp.ok && at < qrow) ? lane_row(jp) * qrow + at : fast::kOob;
         store_words<BITS>(rq, off, words, whole_pair(jp), (int)qrow - (int)at);
@@ -358,7 +399,23 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
     return STACKED || row < rows ? mx : 0.0f;
 }
 
-// Picks the variant for the call's formats.  big: what stage_columns returned; acc is brought to scale here then.
+// Picks the variant for the call's formats.
+template <int CB, bool STACKED>
+__device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0, const int rows,
+                                             const float *cols, const OutScale os, const int staged)
+{
+#define DYBIT_CODES_STRIP(RB_) \
+    return g.q_bits == 4 ? store_strip_codes<CB, RB_, 4, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
+         : g.q_bits == 8 ? store_strip_codes<CB, RB_, 8, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
+                         : store_strip_codes<CB, RB_, 6, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged)
+    if (!g.res_codes) { DYBIT_CODES_STRIP(0); }
+    if (g.res_bits == 8) { DYBIT_CODES_STRIP(8); }
+    if (g.res_bits == 4) { DYBIT_CODES_STRIP(4); }
+    DYBIT_CODES_STRIP(6);
+#undef DYBIT_CODES_STRIP
+}
+
+// big: what stage_columns returned; acc is brought to scale here then.
 template <int CB, int ACC_EXP>
 __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0,
                                                       const float *cols, const bool big, const OutScale os)
@@ -371,15 +428,7 @@ __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][v] = acc_value<ACC_EXP>(acc[j][v]);
     }
-#define DYBIT_CODES_STRIP(RB_) \
-    return g.q_bits == 4 ? store_strip_codes<CB, RB_, 4>(g, acc, m_strip, n0, rows, cols, os) \
-         : g.q_bits == 8 ? store_strip_codes<CB, RB_, 8>(g, acc, m_strip, n0, rows, cols, os) \
-                         : store_strip_codes<CB, RB_, 6>(g, acc, m_strip, n0, rows, cols, os)
-    if (!g.res_codes) { DYBIT_CODES_STRIP(0); }
-    if (g.res_bits == 8) { DYBIT_CODES_STRIP(8); }
-    if (g.res_bits == 4) { DYBIT_CODES_STRIP(4); }
-    DYBIT_CODES_STRIP(6);
-#undef DYBIT_CODES_STRIP
+    return strip_codes<CB, false>(g, acc, m_strip, n0, rows, cols, os, CB * 32);
 }
 
 }  // namespace dybit

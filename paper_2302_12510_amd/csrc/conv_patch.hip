@@ -242,15 +242,7 @@ __device__ __forceinline__ float codes_of_pair(const GemmArgs &g, f32x16 (&acc)[
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][v] = acc_value<ACC>(acc[j][v]);
     }
-#define DYBIT_PATCH_CODES(RES_) \
-    return g.q_bits == 4 ? store_strip_codes<2, RES_, 4, true>(g, acc, m_first, n0, rows, cols, os, kMaxCols) \
-         : g.q_bits == 8 ? store_strip_codes<2, RES_, 8, true>(g, acc, m_first, n0, rows, cols, os, kMaxCols) \
-                         : store_strip_codes<2, RES_, 6, true>(g, acc, m_first, n0, rows, cols, os, kMaxCols)
-    if (!g.res_codes) { DYBIT_PATCH_CODES(0); }
-    if (g.res_bits == 8) { DYBIT_PATCH_CODES(8); }
-    if (g.res_bits == 4) { DYBIT_PATCH_CODES(4); }
-    DYBIT_PATCH_CODES(6);
-#undef DYBIT_PATCH_CODES
+    return strip_codes<2, true>(g, acc, m_first, n0, rows, cols, os, kMaxCols);
 }
 
 template <int FMT_W, bool F8, int OUT>

@@ -106,20 +106,27 @@ __device__ __forceinline__ uint32_t requant_magnitude(uint32_t zb, const Requant
     return __builtin_amdgcn_ubfe(Requant::kRound - zb, Requant::G, r.m);
 }
 
-// The same two halves for an epilogue that packs several codes before it complements them (codes_epilogue.h):
-// n = 2^m - c minus one half, on the magic number without the half, so that the bits above the G fraction bits are
-// floor(n - 1/2) = 2^m - 1 - c rounded half down: the complement of the code, in one bit-field extraction.  The fraction
-// bits are zero exactly where those of requant_rounded() are.  x is not negative where the format is unsigned.
+// The same first half for an epilogue that packs several codes before it complements them (codes_epilogue.h): n = 2^m - c minus
+// one half, on a magic number without the half, so that the bits above the GB fraction bits are floor(n - 1/2) = 2^m - 1 - c
+// rounded half down, the complement of the code.  The fraction bits are zero exactly where the fraction of c reads one half.
+// Codes of 4 and 6 bits keep GB = 16 fraction bits (n <= 64 fits beside them; the error of c, below 1.5 * 2^(m-24), stays under
+// half a unit): the complement is byte 2 of the word, where packing takes it without an extraction per value, and the fraction its
+// lower half.  x is not negative where the format is unsigned.
+template <int BITS> constexpr int requant_fraction() { return BITS == 8 ? Requant::G : 16; }
+template <int BITS>
 __device__ __forceinline__ uint32_t requant_lower(float x, const Requant &r)
 {
+    constexpr int GB = requant_fraction<BITS>();
     const float q = __builtin_amdgcn_fmed3f(fabsf(x) * r.rinv, 0.0f, r.vmax);
     const float qs = q * __uint_as_float(1u << 23);
     const float n = __uint_as_float(r.recip_sub - __float_as_uint(qs));
-    return __float_as_uint(n + __uint_as_float(Requant::kMagic - (1u << Requant::G)));
+    constexpr float magic = BITS == 8 ? 1.5f * (1 << (23 - GB)) - 0.5f : (float)(1 << (23 - GB)) - 0.5f;
+    return __float_as_uint(n + magic);
 }
+template <int BITS>
 __device__ __forceinline__ uint32_t requant_complement(uint32_t zb, const Requant &r)
 {
-    return __builtin_amdgcn_ubfe(zb, Requant::G, r.m);
+    return __builtin_amdgcn_ubfe(zb, requant_fraction<BITS>(), r.m);
 }
 
 // Exact decision at the midpoint between magnitude codes `code - 1` and `code`, for a value whose
