@@ -86,12 +86,16 @@ SOURCES = [
     ("conv_few.hip", "conv_few_w2", ["-DDYBIT_FEW_W=6"]),
     ("conv_few.hip", "conv_few_w2_co", ["-DDYBIT_FEW_W=6", "-DDYBIT_WB=2"]),
     ("conv_patch.hip", "conv_patch_w4", ["-DDYBIT_PATCH_W=0"]),
+    ("conv_patch.hip", "conv_patch_w4_wb", ["-DDYBIT_PATCH_W=0", "-DDYBIT_WB=1"]),
     ("conv_patch.hip", "conv_patch_w4_co", ["-DDYBIT_PATCH_W=0", "-DDYBIT_WB=2"]),
     ("conv_patch.hip", "conv_patch_w8", ["-DDYBIT_PATCH_W=2"]),
+    ("conv_patch.hip", "conv_patch_w8_wb", ["-DDYBIT_PATCH_W=2", "-DDYBIT_WB=1"]),
     ("conv_patch.hip", "conv_patch_w8_co", ["-DDYBIT_PATCH_W=2", "-DDYBIT_WB=2"]),
     ("conv_patch.hip", "conv_patch_w6", ["-DDYBIT_PATCH_W=4"]),
+    ("conv_patch.hip", "conv_patch_w6_wb", ["-DDYBIT_PATCH_W=4", "-DDYBIT_WB=1"]),
     ("conv_patch.hip", "conv_patch_w6_co", ["-DDYBIT_PATCH_W=4", "-DDYBIT_WB=2"]),
     ("conv_patch.hip", "conv_patch_w2", ["-DDYBIT_PATCH_W=6"]),
+    ("conv_patch.hip", "conv_patch_w2_wb", ["-DDYBIT_PATCH_W=6", "-DDYBIT_WB=1"]),
     ("conv_patch.hip", "conv_patch_w2_co", ["-DDYBIT_PATCH_W=6", "-DDYBIT_WB=2"]),
     ("diag.hip", "diag", []),
 ]

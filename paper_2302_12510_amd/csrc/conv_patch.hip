@@ -246,7 +246,7 @@ __device__ __forceinline__ float codes_of_pair(const GemmArgs &g, f32x16 (&acc)[
 }
 
 template <int FMT_W, bool F8, int OUT>
-__global__ __launch_bounds__(512, 2) void conv_patch_kernel(const GemmArgs g, const PatchArgs p)
+__global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, const PatchArgs p)
 {
     constexpr int PB = F8 ? 1 : 2;                       // LDS bytes per code
     constexpr int BW = Codec<FMT_W>::BITS, NW = (BW + 3) / 4, RUN_W = 4 * BW, ACC = F8 ? 0 : Codec<FMT_W>::ACC_EXP;
@@ -519,6 +519,13 @@ __global__ __launch_bounds__(512, 2) void conv_patch_kernel(const GemmArgs g, co
                 mx = fmaxf(mx, codes_of_pair<ACC>(reload_args(), pair, m_first + 32 * b, n0, cols + cwi * 32, big, os));
                 pair[0] = acc[2];
                 pair[1] = acc[3];
+            }
+        } else if constexpr (OUT == OUT_WRITE_BACK) {    // fp32 and codes: a block after the other
+            f32x16 one[1] = {acc[0]};
+#pragma unroll 1
+            for (int b = 0; b < blocks; ++b) {
+                mx = fmaxf(mx, epilogue_strip<1, true, false, ACC>(g, one, m_first + 32 * b, n0));
+                one[0] = b == 0 ? acc[1] : b == 1 ? acc[2] : acc[3];
             }
         } else {
             const bool relu = g.relu, track = g.absmax_bits != nullptr;

@@ -85,8 +85,8 @@ hipError_t take_hip_error();       // ... and this last: the first error noted s
 // translation unit per weight format.  a_bits is 4 or 8; signedness comes from g.
 // Builds: plain; with DYBIT_WB=1 (_wb) the write-back build whose epilogue also encodes the results (g.q_out must then be
 // set); with DYBIT_WB=2 (_co) the build for calls that want codes only (codes_only() above).  The general, 256 x 256 and
-// small-output kernels have the first two, the weight-stationary, 128 x 128 and e4m3 kernels all three, the few-channel
-// and many-channel convolutions plain and _co, the grouped convolution the plain one.
+// small-output kernels have the first two, the weight-stationary, 128 x 128 and e4m3 kernels and the many-channel convolution all three, the
+// few-channel convolution plain and _co, the grouped convolution the plain one.
 bool launch_gemm_fast_w0(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 4-bit signed
 bool launch_gemm_fast_w2(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 8-bit signed
 bool launch_gemm_fast_w4(const GemmArgs &g, int a_bits, bool conv, hipStream_t st);   // W 6-bit signed
@@ -146,12 +146,16 @@ bool launch_conv_few_w2_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w4_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w6_co(const GemmArgs &g, int a_bits, hipStream_t st);
 
-// Convolution of 64 and more channels with its input decoded once (conv_patch.hip); plain and codes-only builds.  false: the
+// Convolution of 64 and more channels with its input decoded once (conv_patch.hip), all three builds.  false: the
 // pixels of 128 outputs do not fit the LDS.
 bool launch_conv_patch_w0(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w2(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w4(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w6(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w0_wb(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w2_wb(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w4_wb(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
+bool launch_conv_patch_w6_wb(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w0_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w2_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w4_co(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);

@@ -205,16 +205,16 @@ static bool many_channels_pay(const GemmArgs &g, int w_bits, bool f8, bool large
 // one after the other (no output reaches past the image with its first taps).
 static bool launch_conv_patch(const GemmArgs &g, int a_bits, int w_bits, bool low_pair, hipStream_t st)
 {
-    const bool codes = codes_only(g);
-    if (g.Cin % 64 || g.kh * (int64_t)g.kw < 2 || g.kh * (int64_t)g.kw > 30 || g.M > 0x7fffffff || g.N > 1 << 16 || (g.q_out && !codes)) return false;
+    const bool codes = codes_only(g), wb = g.q_out != nullptr;
+    if (g.Cin % 64 || g.kh * (int64_t)g.kw < 2 || g.kh * (int64_t)g.kw > 30 || g.M > 0x7fffffff || g.N > 1 << 16) return false;
     if ((g.Ho - 1) * (int64_t)g.stride >= g.H || (g.Wo - 1) * (int64_t)g.stride >= g.Wd || g.pad >= g.kh || g.pad >= g.kw) return false;
-    if (codes ? g.q_row_bytes > 1 << 20 || (g.res_codes && g.res_row_bytes > 1 << 20) : g.ldc > 1 << 20) return false;
+    if (g.ldc > 1 << 20 || (g.q_out && g.q_row_bytes > 1 << 20) || (g.res_codes && g.res_row_bytes > 1 << 20)) return false;
     if (g.M / ((int64_t)g.Ho * g.Wo) * g.H * (int64_t)g.Wd > 0x3fffffff) return false;
     switch (w_bits) {
-        case 4: return (codes ? launch_conv_patch_w0_co : launch_conv_patch_w0)(g, a_bits, low_pair, st);
-        case 8: return (codes ? launch_conv_patch_w2_co : launch_conv_patch_w2)(g, a_bits, low_pair, st);
-        case 6: return (codes ? launch_conv_patch_w4_co : launch_conv_patch_w4)(g, a_bits, low_pair, st);
-        case 2: return (codes ? launch_conv_patch_w6_co : launch_conv_patch_w6)(g, a_bits, low_pair, st);
+        case 4: return (codes ? launch_conv_patch_w0_co : wb ? launch_conv_patch_w0_wb : launch_conv_patch_w0)(g, a_bits, low_pair, st);
+        case 8: return (codes ? launch_conv_patch_w2_co : wb ? launch_conv_patch_w2_wb : launch_conv_patch_w2)(g, a_bits, low_pair, st);
+        case 6: return (codes ? launch_conv_patch_w4_co : wb ? launch_conv_patch_w4_wb : launch_conv_patch_w4)(g, a_bits, low_pair, st);
+        case 2: return (codes ? launch_conv_patch_w6_co : wb ? launch_conv_patch_w6_wb : launch_conv_patch_w6)(g, a_bits, low_pair, st);
         default: return false;
     }
 }

@@ -58,6 +58,10 @@ def test_patch_kernel(patch, x_fmt, w_fmt, geom):
         assert bool((codes[-64:] == 0xA5).all()) and mx[0].item() == mx[1].item()
         want_codes = R.pack_rows(R.quantize(y.cpu().numpy().reshape(-1, Cout), s, *y_fmt), y_fmt[0])
         assert np.array_equal(codes[:-64].cpu().numpy(), want_codes.ravel())
+        both, codes = B.dybit_conv2d_wb(*args, y_fmt, scalar(s), dev(bias), None, True, mx[1:2].zero_())        # fp32 as well
+        assert B.dybit_last_gemm_kernel() == name
+        torch.cuda.synchronize()
+        assert torch.equal(both, y) and mx[0].item() == mx[1].item() and np.array_equal(codes.cpu().numpy().ravel(), want_codes.ravel())
         r_fmt = {4: (8, False), 6: (4, True), 8: (6, False)}[y_fmt[0]]
         if Cout * r_fmt[0] % 32:
             continue
