@@ -14,7 +14,8 @@
 // the LDS delivers) and, for 4-bit weights, 10 (e4m3) or 4 (fp16) vector instructions against 33 in gemm_f8.hip.  What bounds it:
 // of the 30000 cycles of 64 x 14 x 14 x 256 -> 256 with a 4-bit pair 15000 are the K loop (9200 matrix cycles per SIMD), the rest is
 // waiting for the first loads, decoding the patch, joining and storing; at N = 64 the encoder of the epilogue.  Loads of all
-// constants and the set-up of the lanes' outputs lie between the patch's loads and their use: 18.2 -> 15.5 us.
+// constants and the set-up of the lanes' outputs lie between the patch's loads and their use (18.2 -> 15.7 us), and nothing before those loads
+// waits twice for arguments, or for other loads (15.7 -> 15.2).
 // The kernels it replaces -> this one (us; fp32 or codes out): 64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5, 8-bit 25.4 -> 21.4;
 // 64 x 7 x 7 x 512 25.8 -> 15.6 and 41.3 -> 25.4; 64 x 28 x 28 x 128 19.8 -> 16.4 and 25.0 -> 22.0; 64 x 56 x 56 x 64 25.7 -> 22.9.
 #include <hip/hip_runtime.h>
@@ -59,7 +60,8 @@ struct PatchArgs {
     int rw, cw_log, kg_log;                              // waves of a workgroup: strips of 128 rows; of 32 columns and k-groups, as powers of two
     int tiles;
     int pitch, zero_at, cols_at;                         // LDS: bytes per pixel, the pixel of zeros, the columns' factors (and a word for the maximum)
-    int a_fmt;
+    int a_fmt, threads;
+    uint32_t run_bytes;                                  // of 32 codes of A
     uint32_t runs_magic;                                 // ceil(2^32 / runs of 32 codes per pixel)
     uint32_t row_bits;                                   // the first tap of every filter row
     Divisor wo, ho, tiles_n;
@@ -89,26 +91,25 @@ __device__ __forceinline__ u32 bit_range(int lo, int up) { return up > lo ? (1u 
 // workgroup's threads take in turn, kBatch at a time.
 constexpr int kBatch = 4;
 struct Runs {
-    int first, count, per_pixel;
-    u32 magic, pix_bytes;
+    int first, count, per_pixel, threads;
+    u32 magic, pix_bytes, bytes;                         // bytes: of a run
 };
-template <int BITS, int N>
+// One sequence of instructions for all formats, without branches around the loads: 16 bytes each, and the next 16 where the
+// format has them (what a 2- or 6-bit run reads too much stays unused, or is zero behind the tensor).  A variant per format
+// made the compiler wait for the weights' loads before the first of these (registers of the variant not taken).
+template <int N>
 __device__ __forceinline__ void load_batch(const __amdgpu_buffer_rsrc_t rsrcA, const Runs &q, const int r0, u32x4 (&raw)[kBatch][N])
 {
+    u32 off[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-        const int r = r0 + i * (int)blockDim.x, px = (int)__umulhi((u32)r, q.magic), at = q.first + px;
-        load_run<BITS>(rsrcA, r < q.count && at >= 0 ? (u32)at * q.pix_bytes + (u32)((r - px * q.per_pixel) * (4 * BITS)) : kOob, raw[i]);
+        const int r = r0 + i * q.threads, px = (int)__umulhi((u32)r, q.magic), at = q.first + px;
+        off[i] = ((u32)at * q.pix_bytes + (u32)(r - px * q.per_pixel) * q.bytes) | (r < q.count && at >= 0 ? 0u : kOob);
+        raw[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, off[i], 0, 0);
     }
-}
-template <bool F8, int N>
-__device__ __forceinline__ void load_first(const __amdgpu_buffer_rsrc_t rsrcA, const Runs &q, const int a_fmt, u32x4 (&raw)[kBatch][N])
-{
-    switch (a_fmt >> 1) {                                // uniform
-        case F4S >> 1: load_batch<4>(rsrcA, q, threadIdx.x, raw); break;
-        case F2S >> 1: load_batch<2>(rsrcA, q, threadIdx.x, raw); break;
-        case F8S >> 1: if constexpr (!F8) load_batch<8>(rsrcA, q, threadIdx.x, raw); break;
-        default: if constexpr (!F8) load_batch<6>(rsrcA, q, threadIdx.x, raw); break;
+    if (N == 2 && q.bytes > 16) {                        // uniform
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) raw[i][N - 1] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, off[i] + 16, 0, 0);
     }
 }
 // Decodes them into LDS; raw holds the thread's first batch.  fp16: values as they are, not on the 2^-14 scale of the arithmetic
@@ -116,12 +117,11 @@ __device__ __forceinline__ void load_first(const __amdgpu_buffer_rsrc_t rsrcA, c
 template <int FMT, bool F8, int N>
 __device__ __forceinline__ void fill(const __amdgpu_buffer_rsrc_t rsrcA, const Runs &q, const int pitch, char *lds, u32x4 (&raw)[kBatch][N])
 {
-    constexpr int BITS = Codec<FMT>::BITS;
-    const int threads = (int)blockDim.x;
+    const int threads = q.threads;
     for (int r0 = threadIdx.x; r0 < q.count; r0 += kBatch * threads) {
         u32x4 ahead[kBatch][N];
         const bool more = r0 - (int)threadIdx.x + kBatch * threads < q.count;   // uniform
-        if (more) load_batch<BITS>(rsrcA, q, r0 + kBatch * threads, ahead);
+        if (more) load_batch(rsrcA, q, r0 + kBatch * threads, ahead);
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
             const int r = r0 + i * threads, px = (int)__umulhi((u32)r, q.magic);
@@ -254,6 +254,10 @@ __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, co
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kq = lane >> 5;
+    // every argument that is needed before the first loads, read at once: the compiler otherwise reads them in five steps that wait for each other
+    asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.K), "s"(g.A), "s"(g.W), "s"(g.a_bytes), "s"(g.w_bytes), "s"(g.a_scale), "s"(g.w_scale), "s"(g.bias));
+    asm volatile("" ::"s"(g.H), "s"(g.Wd), "s"(g.Cin), "s"(g.Ho), "s"(g.Wo), "s"(g.kh), "s"(g.kw), "s"(g.stride), "s"(g.pad), "s"(g.pix_bytes), "s"(g.w_per_channel));
+    asm volatile("" ::"s"(p.threads), "s"(p.run_bytes), "s"(p.runs_magic), "s"(p.pitch), "s"(p.tiles), "s"(p.rw), "s"(p.cw_log), "s"(p.kg_log), "s"(p.second_step));
     const int cw = 1 << p.cw_log, kg = 1 << p.kg_log;
     const int cwi = wave & (cw - 1), kgp = (wave >> p.cw_log) & (kg - 1), rwi = wave >> (p.cw_log + p.kg_log);
     const int tile = xcd_contiguous_index();             // all column tiles of a strip of rows together
@@ -279,16 +283,16 @@ __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, co
     // ---- the image's pixels that the tile looks at: first codes requested
     const int64_t m_end = m0 + 32 * RB * p.rw < g.M ? m0 + 32 * RB * p.rw : g.M;
     const int first = origin(g, p, (u32)m0).pixel, pixels = origin(g, p, (u32)(m_end - 1)).pixel - first + (g.kh - 1) * g.Wd + g.kw;
-    const Runs runs{first, pixels * (g.Cin / 32), g.Cin / 32, p.runs_magic, (u32)g.pix_bytes};
+    const Runs runs{first, pixels * (g.Cin / 32), g.Cin / 32, p.threads, p.runs_magic, (u32)g.pix_bytes, p.run_bytes};
     const __amdgpu_buffer_rsrc_t rsrcA = code_descriptor(g.A, g.a_bytes);
     u32x4 raw[kBatch][F8 ? 1 : 2];
-    load_first<F8>(rsrcA, runs, p.a_fmt, raw);
+    load_batch(rsrcA, runs, tid, raw);
 
     // ---- factors and biases: of the lane's column, or (codes only) of the tile's columns, a thread each
     const int64_t n_own = OUT == OUT_CODES ? n_tile + tid : n_lane;
     const bool n_ok = n_own < g.N;
-    const float factor = n_ok ? (*g.a_scale) * g.w_scale[g.w_per_channel ? n_own : 0] : 0.0f;
-    const float bias = (g.bias && n_ok) ? g.bias[n_own] : 0.0f;
+    const float a_scale = scalar_scale(g.a_scale), w_scale = g.w_scale[g.w_per_channel && n_ok ? n_own : 0];   // no branch, used behind the set-up
+    const float bias_read = g.bias ? g.bias[n_ok ? n_own : 0] : 0.0f;
 
     // ---- the lane's outputs: where their first taps lie in LDS, and which taps lie inside the image
     const u32 lds_base = (u32)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
@@ -307,11 +311,14 @@ __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, co
     int tap = kgp ? p.second_tap : 0, block = kgp ? p.second_block : 0, fr = kgp ? p.second_fr : 0, fs = kgp ? p.second_fs : 0;   // the step whose A is read next
     const int steps = (n0 < g.N && m_wave < g.M) ? s1 - s0 : 0;
 
+    __builtin_amdgcn_sched_barrier(0);
+    const float factor = n_ok ? a_scale * w_scale : 0.0f, bias = n_ok ? bias_read : 0.0f;
+
     // ---- the pixels, decoded
     float *const cols = reinterpret_cast<float *>(lds + p.cols_at);
     u32 *const top = reinterpret_cast<u32 *>(lds + p.cols_at + (OUT == OUT_CODES ? kColumnBytes : 0));
     if (tid == 0) *top = 0;
-    for (int i = tid * 16; i < p.pitch; i += (int)blockDim.x * 16) *reinterpret_cast<u32x4 *>(lds + p.zero_at + i) = u32x4{0u, 0u, 0u, 0u};
+    for (int i = tid * 16; i < p.pitch; i += p.threads * 16) *reinterpret_cast<u32x4 *>(lds + p.zero_at + i) = u32x4{0u, 0u, 0u, 0u};
     switch (p.a_fmt) {                                   // uniform
         case F4S: fill<F4S, F8>(rsrcA, runs, p.pitch, lds, raw); break;
         case F4U: fill<F4U, F8>(rsrcA, runs, p.pitch, lds, raw); break;
@@ -606,6 +613,8 @@ static bool launch(const GemmArgs &g, int a_fmt, hipStream_t st)
     p.cw_log = cw == 8 ? 3 : cw == 4 ? 2 : cw == 2 ? 1 : 0;
     p.kg_log = kg - 1;
     p.a_fmt = a_fmt;
+    p.threads = 64 * waves;
+    p.run_bytes = a_fmt >= F2S ? 8 : a_fmt >= F6S ? 24 : a_fmt >= F8S ? 32 : 16;
     p.runs_magic = (uint32_t)((1ull << 32) / (unsigned)(g.Cin / 32) + 1);
     p.wo = divisor((uint32_t)g.Wo);
     p.ho = divisor((uint32_t)g.Ho);
