@@ -37,8 +37,14 @@ constexpr int kMaxWaves = 16;
 // instead of four, and decoders that emit bytes.  512 x 512 x 4096, 4-bit pair: fp16 form 9.2, this one 8.4 us.
 template <int FMT> constexpr bool low_format() { return FMT == F4S || FMT == F4U || FMT == F2S || FMT == F2U; }
 
+// The order of the tiles: l / per is one coordinate, l % per the other; mul and shift divide numbers below 2^31 by per.
+struct TileOrder {
+    uint32_t tiles, per, mul, shift;
+    int by_columns, waves;
+};
+
 template <int FMT_A, int FMT_W, int MODE, int CB, int OUT, bool E4M3>
-__global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_columns)
+__global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmArgs g, const TileOrder order)
 {
     using CA = Codec<FMT_A>;
     using CW = Codec<FMT_W>;
@@ -47,11 +53,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     extern __shared__ __attribute__((aligned(16))) float red[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int waves = (int)blockDim.x >> 6, kq = lane >> 5;
+    // every argument that the first loads need, read at once: the compiler otherwise reads them in steps that wait for each other
+    asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.K), "s"(g.A), "s"(g.W), "s"(g.a_bytes), "s"(g.w_bytes), "s"(g.a_scale), "s"(g.w_scale), "s"(g.bias));
+    if (MODE == CONVOLUTION) asm volatile("" ::"s"(g.H), "s"(g.Wd), "s"(g.Cin), "s"(g.Ho), "s"(g.Wo), "s"(g.kw), "s"(g.stride), "s"(g.pad), "s"(g.pix_bytes));
+    const int waves = order.waves, kq = lane >> 5;
     // neighbouring tiles, which share an operand strip, go to the same XCD: by columns when W is the larger operand
     const int l = xcd_contiguous_index();
-    if (l >= tiles_m * tiles_n) return;                              // uniform per workgroup
-    const int tile_m = by_columns ? l % tiles_m : l / tiles_n, tile_n = by_columns ? l / tiles_m : l % tiles_n;
+    if ((u32)l >= order.tiles) return;                               // uniform per workgroup
+    const int high = order.per == 1 ? l : (int)(__umulhi((u32)l, order.mul) >> order.shift), low = l - high * (int)order.per;
+    const int tile_m = order.by_columns ? low : high, tile_n = order.by_columns ? high : low;
     const int64_t m0 = (int64_t)tile_m * 32, n0 = (int64_t)tile_n * (32 * CB);
 
     const __amdgpu_buffer_rsrc_t rsrcA = MODE == RAGGED ? word_descriptor(g.A, g.a_bytes) : code_descriptor(g.A, g.a_bytes);
@@ -149,12 +159,22 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     u32x4 a0[NA], a1[NA], w0[CB][NW], w1[CB][NW];
     load(wave, a0, w0);
     load(wave + waves, a1, w1);
+    // the epilogue's scales and biases, requested now for its wave: its own loads then come out of the caches
+    u32 ahead[3] = {0, 0, 0};
+    if (wave == 0) {
+        const u32 n = (u32)(n0 + (lane & (32 * CB - 1))), n_in = n < (u32)g.N ? n : 0u;
+        ahead[0] = __builtin_amdgcn_raw_buffer_load_b32(code_descriptor(reinterpret_cast<const uint8_t *>(g.a_scale), 4), 0, 0, 0);
+        ahead[1] = __builtin_amdgcn_raw_buffer_load_b32(code_descriptor(reinterpret_cast<const uint8_t *>(g.w_scale), g.w_per_channel ? 4 * g.N : 4), g.w_per_channel ? 4u * n_in : 0u, 0, 0);
+        if (g.bias) ahead[2] = __builtin_amdgcn_raw_buffer_load_b32(code_descriptor(reinterpret_cast<const uint8_t *>(g.bias), 4 * g.N), 4u * n_in, 0, 0);
+    }
     for (int t = wave; t < steps; t += 2 * waves) {
         contract(t, a0, w0);
         load(t + 2 * waves, a0, w0);
         if (t + waves < steps) contract(t + waves, a1, w1);
         load(t + 3 * waves, a1, w1);
     }
+
+    asm volatile("" ::"v"(ahead[0]), "v"(ahead[1]), "v"(ahead[2]));
 
     // ---- add the waves' partial sums: in each round the upper half hands its sums to the lower half
     for (int half = waves >> 1; half > 0; half >>= 1) {
@@ -186,10 +206,15 @@ static void launch_one(const GemmArgs &g, hipStream_t st)
     int waves = 1;
     while (waves < kMaxWaves && waves * 2 <= steps && tiles * waves * 2 <= 4096) waves *= 2;
     const int lds_bytes = waves / 2 * CB * 16 * 64 * 4;
+    TileOrder order{(uint32_t)tiles, (uint32_t)(g.N > g.M ? tiles_m : tiles_n), 0, 0, g.N > g.M ? 1 : 0, waves};
+    int bits = 1;
+    while ((1ull << bits) < order.per) ++bits;
+    order.mul = (uint32_t)(((1ull << (31 + bits)) + order.per - 1) / order.per);
+    order.shift = (uint32_t)(bits - 1);
     auto k = gemm_small_kernel<FA, FW, MODE, CB, kOut, E4M3>;
     note_kernel(E4M3 ? DYBIT_KERNEL_F8_SMALL : DYBIT_KERNEL_F16_SMALL);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxWaves / 2 * CB * 16 * 64 * 4));
-    hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), lds_bytes, st, g, tiles_m, tiles_n, g.N > g.M ? 1 : 0);
+    hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), lds_bytes, st, g, order);
 }
 
 template <int FA, int FW, bool E4M3>
