@@ -115,3 +115,16 @@ def test_rule(cin, kh, kw, n, side, codes, takes):
     B.dybit_set_option("gemm_kernel", "auto")
     a, b = (t.double() if not codes else t.short().double() for t in (y, other))
     assert (a - b).abs().max() <= (1 if codes else 1e-5 * kh * kw * cin * 0.006 * 128 * 64)   # sums in another order: a code beside, 1e-5 of sum |a b|
+
+
+@pytest.mark.parametrize("width,takes", [(4552, True), (4554, False)])
+def test_lds_of_a_compute_unit(few, width, takes):
+    """Codes out, 4 x 8 taps of 4 channels: 4 rows of 8 bytes a column, 17920 for weights and columns and 256 of the kernel's own in 160 KiB."""
+    gen = torch.Generator(device="cuda").manual_seed(width)
+    x, w = (torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen) for n in (4 * width * 4, 64 * 4 * 8 * 4))
+    args = (1, 4, width, 4, 64, 4, 8, 2, 0, x, (8, False), scalar(0.3), w, (8, True), scalar(0.02), (8, False), scalar(1.0))
+    _, codes = B.dybit_conv2d_wb(*args, relu=True, fp32=False)
+    assert (B.dybit_last_gemm_kernel() == "f16_few") == takes
+    B.dybit_set_option("gemm_kernel", "general")
+    _, other = B.dybit_conv2d_wb(*args, relu=True, fp32=False)
+    assert (codes.short() - other.short()).abs().max() <= 1                        # sums of 128 products in another order: a code beside
