@@ -53,9 +53,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     extern __shared__ __attribute__((aligned(16))) float red[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // every argument that the first loads need, read at once: the compiler otherwise reads them in steps that wait for each other
-    asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.K), "s"(g.A), "s"(g.W), "s"(g.a_bytes), "s"(g.w_bytes), "s"(g.a_scale), "s"(g.w_scale), "s"(g.bias));
-    if (MODE == CONVOLUTION) asm volatile("" ::"s"(g.H), "s"(g.Wd), "s"(g.Cin), "s"(g.Ho), "s"(g.Wo), "s"(g.kw), "s"(g.stride), "s"(g.pad), "s"(g.pix_bytes));
+    // every argument that the first loads need, read at once: the compiler otherwise reads them in steps that wait for each other.  Not in
+    // the write-back build, whose epilogue has no scalar registers to spare (196 rows, three layers of a bottleneck block: 31.5 -> 32.6 us)
+    constexpr bool EARLY = OUT == OUT_FP32;
+    if (EARLY) asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.K), "s"(g.A), "s"(g.W), "s"(g.a_bytes), "s"(g.w_bytes), "s"(g.a_scale), "s"(g.w_scale), "s"(g.bias));
+    if (EARLY && MODE == CONVOLUTION) asm volatile("" ::"s"(g.H), "s"(g.Wd), "s"(g.Cin), "s"(g.Ho), "s"(g.Wo), "s"(g.kw), "s"(g.stride), "s"(g.pad), "s"(g.pix_bytes));
     const int waves = order.waves, kq = lane >> 5;
     // neighbouring tiles, which share an operand strip, go to the same XCD: by columns when W is the larger operand
     const int l = xcd_contiguous_index();
@@ -161,7 +163,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     load(wave + waves, a1, w1);
     // the epilogue's scales and biases, requested now for its wave: its own loads then come out of the caches
     u32 ahead[3] = {0, 0, 0};
-    if (wave == 0) {
+    if (EARLY && wave == 0) {
         const u32 n = (u32)(n0 + (lane & (32 * CB - 1))), n_in = n < (u32)g.N ? n : 0u;
         ahead[0] = __builtin_amdgcn_raw_buffer_load_b32(code_descriptor(reinterpret_cast<const uint8_t *>(g.a_scale), 4), 0, 0, 0);
         ahead[1] = __builtin_amdgcn_raw_buffer_load_b32(code_descriptor(reinterpret_cast<const uint8_t *>(g.w_scale), g.w_per_channel ? 4 * g.N : 4), g.w_per_channel ? 4u * n_in : 0u, 0, 0);
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
         load(t + 3 * waves, a1, w1);
     }
 
-    asm volatile("" ::"v"(ahead[0]), "v"(ahead[1]), "v"(ahead[2]));
+    if (EARLY) asm volatile("" ::"v"(ahead[0]), "v"(ahead[1]), "v"(ahead[2]));
 
     // ---- add the waves' partial sums: in each round the upper half hands its sums to the lower half
     for (int half = waves >> 1; half > 0; half >>= 1) {
