@@ -548,18 +548,6 @@ __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, co
     }
 }
 
-// Pixels from the first tap of a tile's first output to the last tap of its last one, at most: `rows` outputs advance rows - 1
-// times, by a pixel step each or, at an image row's or an image's end, by more.
-static int64_t most_pixels(const GemmArgs &g, int64_t rows)
-{
-    const int64_t steps = rows - 1, row_ends = (steps + g.Wo - 1) / g.Wo, image_ends = (steps + (int64_t)g.Ho * g.Wo - 1) / ((int64_t)g.Ho * g.Wo);
-    const int64_t row_step = (int64_t)g.stride * g.Wd - (int64_t)(g.Wo - 1) * g.stride;
-    const int64_t image_step = (int64_t)(g.H - (g.Ho - 1) * g.stride) * g.Wd - (int64_t)(g.Wo - 1) * g.stride;
-    const int64_t further = row_step > image_step ? row_step : image_step;
-    const int64_t inner = steps > row_ends ? steps - row_ends : 0;
-    return inner * g.stride + row_ends * row_step + image_ends * (further - row_step) + (int64_t)(g.kh - 1) * g.Wd + g.kw;
-}
-
 // The split of a workgroup for which the modelled time (cycles) is least.  A compute unit holds twelve waves (168 registers) and
 // the patches that fit its LDS; each round of workgroups it holds at once costs about 9000 cycles of launch, waiting for loads and
 // storing, the decoding of the patch, the K loop and the epilogue.  Sharing its SIMD a wave comes to 0.87 of the matrix rate (or
@@ -576,7 +564,7 @@ static bool plan(const GemmArgs &g, int pitch, Split &best)
     const double step = F8 ? 256 : 4 * (kDecode + 20) > 512 ? 4 * (kDecode + 20) : 512, steps = (double)g.K / 64;
     best.cycles = 0;
     for (int rw = 1; rw <= 2; ++rw) {
-        const int64_t rows = 32 * RB * rw, pixels = most_pixels(g, rows < g.M ? rows : g.M);
+        const int64_t rows = 32 * RB * rw, pixels = strip_pixels(g, rows < g.M ? rows : g.M);
         if ((pixels + 1) * pitch > kLds) break;
         for (int cw = 1; cw <= 8; cw *= 2)
             for (int kg = 1; kg <= 2; ++kg) {

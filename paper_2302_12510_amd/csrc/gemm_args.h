@@ -146,6 +146,20 @@ bool launch_conv_few_w2_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w4_co(const GemmArgs &g, int a_bits, hipStream_t st);
 bool launch_conv_few_w6_co(const GemmArgs &g, int a_bits, hipStream_t st);
 
+// Pixels from the first tap of a strip's first output to the last tap of its last one, at most: `rows` outputs advance rows - 1
+// times, by a pixel step each or, at an image row's or an image's end, by more (row_ends may count one too many, which must not
+// shorten the strip).  No output's first tap may reach past the image, which bounds every step by the image's pixels: with one
+// row of outputs every row's end is an image's, and with one column no step is a pixel step, whatever the stride.
+inline int64_t strip_pixels(const GemmArgs &g, int64_t rows)
+{
+    const int64_t steps = rows - 1, row_ends = (steps + g.Wo - 1) / g.Wo, image_ends = (steps + (int64_t)g.Ho * g.Wo - 1) / ((int64_t)g.Ho * g.Wo);
+    const int64_t back = (int64_t)(g.Wo - 1) * g.stride, image_step = (g.H - (int64_t)(g.Ho - 1) * g.stride) * g.Wd - back;
+    const int64_t row_step = g.Ho > 1 ? (int64_t)g.stride * g.Wd - back : g.Wo > 1 && g.stride > image_step ? g.stride : image_step;
+    const int64_t further = row_step > image_step ? row_step : image_step;
+    const int64_t inner = steps > row_ends ? steps - row_ends : 0;
+    return (g.Wo > 1 ? inner * g.stride : 0) + row_ends * row_step + image_ends * (further - row_step) + (int64_t)(g.kh - 1) * g.Wd + g.kw;
+}
+
 // Convolution of 64 and more channels with its input decoded once (conv_patch.hip), all three builds.  false: the
 // pixels of 128 outputs do not fit the LDS.
 bool launch_conv_patch_w0(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
