@@ -180,25 +180,36 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
     }
 }
 
-// Whether the many-channel kernel is the faster one.  It decodes an input code once per tile, so it needs taps that share their
-// pixels (2 x 2 at stride 2, 63 x 49 x 49 x 128 to 256 channels: 14.9 -> 22.6 us).  Measured over 600 convolutions of 64 to 512
-// channels and 49 to 401408 outputs, 2 x 2 to 5 x 5 taps, all formats, fp32 and codes out (us, the kernel it replaces -> this one; 3 x 3):
-//   small-output kernel: a pair of 4- and 2-bit formats to the line of that kernel (3267 outputs, 256 to 64: 7.9 -> 10.5), others to 136
-//     tiles of 64 x 64 (15 x 23 x 23, 128 to 64, 124 tiles: 9.2 -> 10.8; 36 x 16 x 16, 144 tiles: 13.6 -> 11.9);
+// Whether the many-channel kernel is the faster one.  It decodes an input code once per tile, so it lives on taps that share their
+// pixels: `share` of them look at a pixel of a strip of 128 outputs, on average (3 x 3 at stride 1: 8.0 on 7 x 7, 4.8 on 56 x 56, 1.2 on
+// 400 columns, where a strip looks at three image rows all along; at stride 2 on 56 x 56 1.8).  Measured over 4700 convolutions of 64 to
+// 1024 channels and 2 to 778752 outputs, 1 x 2 to 5 x 5 and 7 x 1 taps, all formats and outputs (us, the kernel it replaces -> this one):
+//   filters in two dimensions: share from 1.75 on (64 x 64 x 64, 192 to 160 at stride 2, 4-bit pair 44.7 -> 36.1; below, 400 x 400, 64 to 64,
+//     8- by 4-bit 22.0 -> 35.0, 4-bit pair 19.7 -> 32.8, and 2 x 2 at stride 2, 63 x 49 x 49, 128 to 256: 14.9 -> 22.6); in one from 3 on
+//     (1 x 3 of 384 channels, 69 x 75 x 32, to 128, 8-bit pair: 63.6 -> 81.6);
+//   K from 320 on: a shorter loop ends before the strip is decoded (2 taps of 64, 2 x 40 x 40, to 160, 8-bit pair: 5.6 -> 7.4);
+//   small-output kernel: not a pair of 4- and 2-bit formats to the line of that kernel (3267 outputs, 256 to 64: 7.9 -> 10.5), others from
+//     137 tiles of 64 x 64 on (15 x 23 x 23, 128 to 64, 124 tiles: 9.2 -> 10.8; 36 x 16 x 16, 144 tiles: 13.6 -> 11.9) and K from 512 on
+//     (2 x 2 taps of 64, 2 x 40 x 40, to 256: 6.4 -> 7.7);
 //   weight-stationary kernel: at stride 1 with 4- and 2-bit weights everywhere (64 x 56 x 56, 64 to 64, 4-bit pair 25.7 -> 22.8, 6- by 4-bit
 //     35.8 -> 29.5); wider weights take a lane longer to decode, and at stride 2 a tile looks at four pixels per output, of which fewer fit the
 //     LDS: below 40960 outputs (25088: 11.6 -> 10.0 to 28.0 -> 18.0; 50176: 8-bit pair 11.9 -> 11.7, 8- by 6-bit 12.9 -> 14.6, stride 2
 //     11.4 -> 11.2 to 14.2 -> 20.3);
 //   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8);
-//   128 x 128 and 64 x 64 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
+//   64 x 64 e4m3 kernel: at stride 1 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160: 11.9 -> 13.2), K from 512 on;
+//   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
 static bool many_channels_pay(const GemmArgs &g, int w_bits, bool f8, bool large)
 {
-    if (g.kh * (int64_t)g.kw < 2 * (int64_t)g.stride * g.stride) return false;
-    if (small_output(g, false, f8) && (f8 || ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 136)) return false;
+    if (g.K < 320) return false;
+    const int64_t strip = g.M < 128 ? g.M : 128;
+    const double share = (double)(g.kh * (int64_t)g.kw * strip) / (double)strip_pixels(g, strip);
+    if (share < (g.kh > 1 && g.kw > 1 ? 1.75 : 3.0)) return false;
+    if (small_output(g, false, f8) && (f8 || g.K < 512 || ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 136)) return false;
     if (large && !f8 && w_bits > 4) return false;
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
-    const bool stationary = g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024;
-    return !stationary || g.M < 40960 || (g.stride == 1 && w_bits <= 4);
+    if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return g.M < 40960 || (g.stride == 1 && w_bits <= 4);
+    const bool tiles_of_64 = f8 && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 128;   // see gemm_f8.hip
+    return !tiles_of_64 || (g.stride == 1 && g.K >= 512);
 }
 
 // It takes a convolution with 64-code k groups inside one filter tap whose outputs look at consecutive pixels,

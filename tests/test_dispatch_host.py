@@ -32,3 +32,17 @@ def test_stride_beyond_the_image(option):
     """Images of one row of one output, 2^20 pixels from one to the next: 127 of them never fit the LDS, however far 2^30 columns of stride reach
     (their product with the bytes of a pixel leaves 64 bits)."""
     assert not conv_kernel(127, 1, 1 << 20, 64, 8, 1, 2, 1 << 30, 0, 2, 4).endswith("_patch")
+
+
+#  B   H   W  Cin Cout kh kw s  p  A  W -> whether the many-channel kernel is taken
+@pytest.mark.parametrize("geom,takes", [
+    ((1, 400, 400, 64, 64, 3, 3, 1, 1, 8, 4), False), ((1, 400, 400, 64, 64, 3, 3, 1, 1, 4, 4), False), ((4, 112, 112, 64, 64, 3, 3, 1, 1, 4, 4), True),    # wide images
+    ((69, 75, 32, 384, 128, 1, 3, 1, 0, 8, 8), False), ((69, 75, 32, 384, 128, 1, 5, 1, 0, 8, 8), True),                                                    # filters of one row
+    ((64, 56, 56, 64, 128, 3, 3, 2, 1, 4, 4), False), ((64, 56, 56, 128, 256, 3, 3, 2, 1, 4, 4), True), ((32, 60, 90, 128, 256, 3, 3, 3, 0, 4, 4), False),   # strides
+    ((2, 40, 40, 64, 160, 1, 2, 1, 0, 8, 8), False), ((2, 40, 40, 64, 256, 2, 2, 1, 0, 6, 4), False), ((2, 40, 40, 128, 256, 2, 2, 1, 0, 6, 4), True),       # K
+    ((62, 8, 7, 64, 200, 1, 2, 1, 0, 8, 4), False), ((16, 64, 64, 64, 1024, 3, 1, 1, 0, 8, 4), False),
+    ((16, 39, 17, 256, 160, 3, 3, 2, 1, 4, 2), False), ((16, 39, 17, 256, 160, 3, 3, 1, 1, 4, 2), True)])                                                   # 64 x 64 tiles
+@pytest.mark.parametrize("out", ["fp32", "codes"])
+def test_taps_that_share_pixels(geom, takes, out):
+    """The kernel pays where a pixel that it decodes once serves several taps: not for wide images, long strides, two or three taps or a short K."""
+    assert conv_kernel(*geom, out=out).endswith("_patch") == takes
