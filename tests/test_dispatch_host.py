@@ -46,3 +46,14 @@ def test_stride_beyond_the_image(option):
 def test_taps_that_share_pixels(geom, takes, out):
     """The kernel pays where a pixel that it decodes once serves several taps: not for wide images, long strides, two or three taps or a short K."""
     assert conv_kernel(*geom, out=out).endswith("_patch") == takes
+
+
+@pytest.mark.parametrize("geom,takes", [
+    ((64, 7, 7, 512, 512, 3, 3, 1, 1, 8, 8), True), ((64, 7, 7, 512, 512, 3, 3, 1, 1, 4, 4), True),                                                  # tiles of 128; of 64, 392 of them
+    ((20, 16, 16, 64, 128, 3, 3, 1, 1, 2, 2), False), ((36, 16, 16, 128, 128, 3, 3, 1, 1, 4, 4), True),                                              # tiles of 64: 160 and 288
+    ((40, 14, 14, 128, 96, 3, 3, 1, 1, 8, 4), False), ((40, 14, 14, 128, 96, 3, 3, 1, 1, 8, 8), False), ((40, 14, 14, 192, 96, 3, 3, 1, 1, 8, 8), True),   # small outputs
+    ((13, 56, 56, 64, 64, 3, 3, 1, 1, 8, 4), False), ((64, 56, 56, 64, 64, 3, 3, 1, 1, 2, 2), False), ((13, 56, 56, 128, 64, 3, 3, 1, 1, 4, 4), True),     # stationary weights
+    ((13, 56, 56, 64, 96, 3, 3, 1, 1, 8, 4), True), ((32, 40, 40, 64, 160, 7, 1, 1, 0, 8, 8), False)])                                                # columns; K
+def test_both_outputs(geom, takes):
+    """Calls that write fp32 results and codes have the long epilogue: the kernel is taken less often for them."""
+    assert conv_kernel(*geom, out="both").endswith("_patch") == takes
