@@ -195,7 +195,8 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //     35.8 -> 29.5); wider weights take a lane longer to decode, and at stride 2 a tile looks at four pixels per output, of which fewer fit the
 //     LDS: below 40960 outputs (25088: 11.6 -> 10.0 to 28.0 -> 18.0; 50176: 8-bit pair 11.9 -> 11.7, 8- by 6-bit 12.9 -> 14.6, stride 2
 //     11.4 -> 11.2 to 14.2 -> 20.3);
-//   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8);
+//   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8), unless that kernel declines and
+//     leaves them to the 128 x 128 one (a 6- or 2-bit operand, 64 x 28 x 28, 192 to 192, 6-bit pair: 85.0 -> 51.7);
 //   64 x 64 e4m3 kernel: at stride 1 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160: 11.9 -> 13.2), K from 512 on;
 //   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
 // Calls that write fp32 results and codes have the long epilogue (20 vector instructions per result, a column per lane), which this kernel
@@ -204,7 +205,7 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 // 8- by 4-bit: 12.0 -> 13.2); against the 64 x 64 kernel from 264 tiles on (64 x 7 x 7 x 512, 4-bit pair 30.2 -> 20.4, but 20 x 16 x 16, 64 to
 // 128, 160 tiles, 2-bit pair 8.9 -> 10.3); against the weight-stationary kernel with more than 64 columns, for which that one holds twice the
 // weights, or K from 832 on (64 to 64, 13 x 56 x 56, 8- by 4-bit 14.2 -> 17.0, 64 x 56 x 56, 2-bit pair 25.4 -> 29.6).
-static bool many_channels_pay(const GemmArgs &g, int w_bits, bool f8, bool large)
+static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8, bool large)
 {
     if (g.K < 320) return false;
     const int64_t strip = g.M < 128 ? g.M : 128;
@@ -214,7 +215,8 @@ static bool many_channels_pay(const GemmArgs &g, int w_bits, bool f8, bool large
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (both && g.K < 512) return false;
     if (small_output(g, false, f8) && (f8 || g.K < 512 || tiles64 <= 136 || (both && (g.K < 1536 || w_bits <= 4)))) return false;
-    if (large && !f8 && w_bits > 4) return false;
+    const bool declines = (a_bits == 6 || a_bits == 2 || w_bits == 6) && g.Cin % 128 != 0;   // see gemm_fast.hip
+    if (large && !f8 && w_bits > 4 && !declines) return false;
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
     if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return (g.M < 40960 || (g.stride == 1 && w_bits <= 4)) && (!both || g.N > 64 || g.K >= 832);
     const bool tiles_of_64 = f8 && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 128;   // see gemm_f8.hip
@@ -275,7 +277,7 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 
     // Convolution with its input decoded once per tile
     const bool choose = !force && !opt.mid_tile && !opt.mid_kgroups && !opt.ws_off;
-    if (conv && (opt.kernel == DYBIT_FORCE_PATCH || (choose && many_channels_pay(g, w_bits, f8, large))) &&
+    if (conv && (opt.kernel == DYBIT_FORCE_PATCH || (choose && many_channels_pay(g, a_bits, w_bits, f8, large))) &&
         launch_conv_patch(g, a_bits, w_bits, f8, st)) return true;
 
     // Small outputs: so few 128 x 128 tiles that most compute units would idle through a serial K loop.  That kernel counts the codes

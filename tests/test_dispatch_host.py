@@ -57,3 +57,10 @@ def test_taps_that_share_pixels(geom, takes, out):
 def test_both_outputs(geom, takes):
     """Calls that write fp32 results and codes have the long epilogue: the kernel is taken less often for them."""
     assert conv_kernel(*geom, out="both").endswith("_patch") == takes
+
+
+@pytest.mark.parametrize("cin,a_bits,w_bits,takes", [(192, 6, 6, True), (192, 2, 8, True), (192, 8, 6, True), (192, 8, 8, False), (192, 4, 8, False), (256, 6, 6, False), (256, 8, 6, False)])
+@pytest.mark.parametrize("out", ["fp32", "codes", "both"])
+def test_what_the_large_tiles_decline(cin, a_bits, w_bits, takes, out):
+    """6- and 8-bit weights are left to the 256 x 256 kernel, but it takes 6- and 2-bit operands only with whole groups of 128 channels."""
+    assert conv_kernel(64, 28, 28, cin, 192, 3, 3, 1, 1, a_bits, w_bits, out).endswith("_patch") == takes
