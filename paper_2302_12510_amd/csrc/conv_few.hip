@@ -36,7 +36,6 @@ using namespace fast;
 
 constexpr int CB = 2;                                    // column blocks of 32: output channels of a workgroup
 constexpr int kMaxThreads = 512;
-constexpr int kLds = 160 * 1024 - (kOut == OUT_CODES ? 256 : 0);   // what a launch may ask for: __syncthreads_or holds 256 bytes itself
 
 struct FewArgs {
     int rows, units_per_image, units;                    // output rows of a unit; units of an image, of the call
@@ -211,16 +210,16 @@ static bool plan(const GemmArgs &g, FewArgs &f, int &waves, int &lds_bytes, int 
     int64_t in_cols = (int64_t)(g.Wo - 1) * g.stride + taps;
     const int64_t written = g.pad + ((int64_t)g.Wd * g.Cin + 31) / 32 * 32 / g.Cin;   // the last run of a row may reach past the image
     if (in_cols < written) in_cols = written;
-    if (in_cols * g.Cin * 2 > kLds) return false;               // no row fits the LDS (padding and stride reach 2^31)
+    if (in_cols * g.Cin * 2 > kLdsLimit) return false;               // no row fits the LDS (padding and stride reach 2^31)
     f.in_cols = (int)in_cols;
     f.pitch = (f.in_cols * g.Cin * 2 + 15) / 16 * 16;
     const int64_t fixed = (int64_t)CB * 32 * f.row_bytes + (kOut == OUT_CODES ? column_bytes<CB>() : 0);
     double best = 0;
     for (int r = 1; r <= 16 && r <= g.Ho; ++r) {
         const int64_t in_rows = (int64_t)(r - 1) * g.stride + g.kh, bytes = fixed + in_rows * f.pitch;
-        if (bytes > kLds) break;
+        if (bytes > kLdsLimit) break;
         for (int wv = 4; wv <= 8; ++wv) {
-            const int per_cu = (int)(kLds / bytes) < 16 / wv ? (int)(kLds / bytes) : 16 / wv;
+            const int per_cu = (int)(kLdsLimit / bytes) < 16 / wv ? (int)(kLdsLimit / bytes) : 16 / wv;
             const int rounds = ((r * g.Wo + 31) / 32 + wv - 1) / wv;
             const int64_t units = g.M / ((int64_t)g.Ho * g.Wo) * ((g.Ho + r - 1) / r) * f.parts;
             const double work = rounds * wv * 500.0 + (double)in_rows * f.in_cols * g.Cin / 32 * 130 / 64;
@@ -254,7 +253,7 @@ static bool launch(const GemmArgs &g, hipStream_t st)
     if (walkers > f.units) walkers = f.units;
     auto k = conv_few_kernel<FA, FW, kOut>;
     note_kernel(DYBIT_KERNEL_F16_FEW);
-    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)(walkers * f.parts)), dim3(64 * waves), lds_bytes, st, g, f);
     return true;
 }

@@ -68,7 +68,7 @@ struct PatchArgs {
     int second_step, second_tap, second_block, second_fr, second_fs;   // where the second k-group begins
 };
 constexpr int kColumnBytes = 2 * kMaxCols * 4;
-constexpr int kLds = 160 * 1024 - 256;                   // what a launch may ask for: the kernel itself holds 256 bytes (__syncthreads_or)
+constexpr int kLds = 160 * 1024 - 256;                   // what a launch may ask for: the codes-only kernels hold 256 bytes themselves (__syncthreads_or)
 
 // First tap of output pixel m (M and the image's pixels are below 2^31).
 struct Origin {
@@ -622,7 +622,7 @@ static bool launch(const GemmArgs &g, int a_fmt, hipStream_t st)
     p.second_fs = p.second_tap % g.kw;
     auto k = conv_patch_kernel<FMT_W, F8, kOut>;
     note_kernel(F8 ? DYBIT_KERNEL_F8_PATCH : DYBIT_KERNEL_F16_PATCH);
-    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, sp.lds_bytes));
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
     hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), sp.lds_bytes, st, g, p);
     return true;
 }

@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void dwconv_kernel(const DwArgs a)
 template <int BA, int BW>
 void launch_dw(const DwArgs &a, size_t lds_bytes, hipStream_t st, unsigned blocks)
 {
-    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(dwconv_kernel<BA, BW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(dwconv_kernel<BA, BW>), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
     hipLaunchKernelGGL((dwconv_kernel<BA, BW>), dim3(blocks), dim3(kThreads), lds_bytes, st, a);
 }
 

@@ -22,6 +22,11 @@ enum : int { OUT_FP32 = 0, OUT_WRITE_BACK = 1, OUT_CODES = 2 };
 constexpr int kOut = DYBIT_WB;
 constexpr bool kWriteBack = DYBIT_WB != 0;
 
+// The dynamic LDS that a launch may ask for: all of a compute unit's, less the 256 bytes that the codes-only kernels hold themselves
+// (__syncthreads_or).  Kernels of varying sizes set it as their limit with every launch: the limit is one per kernel and process, and with
+// the size of the call two threads could set it against each other.
+constexpr int kLdsLimit = 160 * 1024 - (kOut == OUT_CODES ? 256 : 0);
+
 struct GemmArgs {
     int64_t M, N, K;                 // conv: M = B*Ho*Wo, N = Cout, K = kh*kw*Cin
     const uint8_t *A, *W;            // packed codes, K-contiguous rows (conv: NHWC image / [Cout][kh][kw][Cin])

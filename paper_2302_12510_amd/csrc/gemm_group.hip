@@ -182,7 +182,7 @@ static bool launch_p(const GemmArgs &g, GroupArgs c, hipStream_t st)
     } else {
         const int64_t ktiles = (g.K + 63) / 64, row_bytes = ktiles * 128 + 16;
         const int64_t lds_bytes = CB * 32 * row_bytes + ktiles * 2 * (32 / P) * 8;
-        if (lds_bytes > 160 * 1024) return false;
+        if (lds_bytes > kLdsLimit) return false;
         c.ktiles = (int)ktiles;
         c.row_bytes = (int)row_bytes;
         c.parts = (c.Cog + 32 * CB - 1) / (32 * CB);
@@ -196,7 +196,7 @@ static bool launch_p(const GemmArgs &g, GroupArgs c, hipStream_t st)
         if (grid * kThreads > 0xffffffff) return false;               // a launch is less than 2^32 threads
         auto k = group_conv_kernel<FA, FW, P, CB>;
         note_kernel(DYBIT_KERNEL_F16_GROUP);
-        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+        note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
         hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kThreads), (int)lds_bytes, st, g, c);
         return true;
     }

@@ -458,7 +458,7 @@ static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds
     if (grid < 1) return false;
     auto k = gemm_ws8_kernel<FA, FW, CONV, CB, kOut>;
     note_kernel(DYBIT_KERNEL_F8_WS);
-    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
     return true;
 }
@@ -474,7 +474,7 @@ static bool launch_cb(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_
     if (grid < 1) return false;
     auto k = gemm_ws_kernel<FA, FW, CONV, CB, kOut>;
     note_kernel(DYBIT_KERNEL_F16_WS);
-    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
     return true;
 }
@@ -492,7 +492,7 @@ static bool launch(const GemmArgs &g, bool conv, hipStream_t st)
     // both operands 4- or 2-bit: the fp8 matrix path, unless the "gemm_mfma" option asks for fp16
     if constexpr (FA == F4S || FA == F4U || FA == F2S || FA == F2U) {
         const int row8 = (int)g.K + 16, lds8 = cb * 32 * row8 + extra;
-        if (!rows && !dispatch_options().mfma_f16 && lds8 <= 160 * 1024) {
+        if (!rows && !dispatch_options().mfma_f16 && lds8 <= kLdsLimit) {
             if (cb == 2) return conv ? launch_cb8<FA, FW, 1, 2>(g, st, row8, lds8) : launch_cb8<FA, FW, 0, 2>(g, st, row8, lds8);
             return conv ? launch_cb8<FA, FW, 1, 4>(g, st, row8, lds8) : launch_cb8<FA, FW, 0, 4>(g, st, row8, lds8);
         }
@@ -500,7 +500,7 @@ static bool launch(const GemmArgs &g, bool conv, hipStream_t st)
 #endif
     const int row_bytes = (int)g.K * 2 + 16;
     const int lds_bytes = cb * 32 * row_bytes + extra;
-    if (lds_bytes > 160 * 1024) return false;
+    if (lds_bytes > kLdsLimit) return false;
 #define DYBIT_WS_CB(C_) \
     return rows ? launch_cb<FA, FW, ROWS, C_>(g, st, row_bytes, lds_bytes) \
          : conv ? launch_cb<FA, FW, 1, C_>(g, st, row_bytes, lds_bytes) \

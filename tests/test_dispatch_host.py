@@ -1,6 +1,9 @@
 """Which kernel a call would start, seen without a GPU: the dispatcher runs on the host and notes the kernel before the launch, which then
 fails for want of a device.  Pointers are made up, so nothing here runs where there is a device."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -9,6 +12,7 @@ from paper_2302_12510_amd import binding as B
 
 pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="made-up pointers must never reach a device")
 P, NULL = C.c_void_p(0x10000), C.c_void_p(0)
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(params=["auto", "patch"])
@@ -24,7 +28,7 @@ def conv_kernel(Bn, H, W, cin, cout, kh, kw, stride, pad, a_bits, w_bits, out="f
     st = B.lib().dybit_conv2d_wb(Bn, H, W, cin, cout, kh, kw, stride, pad, P, B.fmt(a_bits, False), P, P, B.fmt(w_bits, True), P, NULL, NULL, 1,
                                  NULL if out == "codes" else P, NULL, B.fmt(4, False), P, NULL if out == "fp32" else P, None)
     assert B.lib().dybit_set_async_error_word(NULL) == B.OK
-    assert st == B.ERR_HIP
+    assert st in (B.OK, B.ERR_HIP)
     return B.dybit_last_gemm_kernel()
 
 
@@ -64,3 +68,62 @@ def test_both_outputs(geom, takes):
 def test_what_the_large_tiles_decline(cin, a_bits, w_bits, takes, out):
     """6- and 8-bit weights are left to the 256 x 256 kernel, but it takes 6- and 2-bit operands only with whole groups of 128 channels."""
     assert conv_kernel(64, 28, 28, cin, 192, 3, 3, 1, 1, a_bits, w_bits, out).endswith("_patch") == takes
+
+
+# Stands between the library and the runtime: prints what a call asks for and launches nothing.
+SHIM = """
+#include <cstdio>
+struct Dim { unsigned x, y, z; };
+extern "C" int hipFuncSetAttribute(const void *f, int what, int value) { std::printf("limit %p %d\\n", f, value); std::fflush(stdout); return 0; }
+extern "C" int __hipPushCallConfiguration(Dim grid, Dim block, size_t lds, void *) { std::printf("launch %u %u %zu\\n", grid.x, block.x, lds); std::fflush(stdout); return 1; }
+"""
+PRELUDE = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)                     # found before the runtime's own
+sys.path[:0] = [sys.argv[2], sys.argv[2] + "/tests"]
+import test_dispatch_host as T
+from paper_2302_12510_amd import binding as B
+P, f8 = T.P, B.fmt(8, True)
+"""
+
+
+@pytest.fixture
+def asked(tmp_path):
+    """Runs Python lines on a library that launches nothing; the words of every line printed."""
+    (tmp_path / "shim.cpp").write_text(SHIM)
+    shim = str(tmp_path / "shim.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(tmp_path / "shim.cpp"), "-o", shim], check=True)
+
+    def run(lines):
+        p = subprocess.run([sys.executable, "-c", PRELUDE + lines, shim, ROOT], capture_output=True, text=True)
+        assert p.returncode == 0, p.stderr
+        return [line.split() for line in p.stdout.splitlines()]
+    return run
+
+
+CALLS = """
+for out in ("fp32", "codes"):
+    for option, calls in (("patch", [(4, 14, 14, 64, 64, 3, 3, 1, 1, 8, 8), (4, 28, 28, 128, 64, 3, 3, 1, 1, 8, 8)]),
+                          ("few", [(64, 112, 112, 4, 64, 7, 7, 2, 3, 8, 8), (64, 224, 224, 4, 64, 7, 7, 2, 3, 8, 8), (64, 64, 64, 8, 64, 3, 3, 1, 1, 8, 8)]),
+                          ("ws", [(64, 28, 28, 64, 64, 3, 3, 1, 1, 4, 4), (64, 28, 28, 128, 64, 3, 3, 1, 1, 4, 4), (64, 28, 28, 64, 64, 3, 3, 1, 1, 8, 8), (64, 28, 28, 64, 64, 1, 1, 1, 0, 8, 8)])):
+        B.dybit_set_option("gemm_kernel", option)
+        for c in calls:
+            assert option in T.conv_kernel(*c, out=out)
+    B.dybit_set_option("gemm_kernel", "auto")
+for cin, cout, k in ((256, 256, 3), (512, 256, 3), (512, 256, 1)):
+    B.lib().dybit_group_conv2d(4, 14, 14, cin, cout, k, k, 1, k // 2, 8, P, f8, P, P, f8, P, 0, None, None, 0, P, None, None)
+for k, stride in ((5, 1), (5, 2), (7, 2)):
+    B.lib().dybit_dwconv2d(4, 28, 28, 32, k, k, stride, k // 2, P, f8, P, P, f8, P, None, 0, P, None, None)
+"""
+
+
+def test_lds_limits_are_constants(asked):
+    """The LDS limit of a kernel belongs to the whole process: every call sets the same one, or two threads with different sizes could
+    set it against each other between one's setting and its launch."""
+    limits, launches = {}, 0
+    for word, *rest in asked(CALLS):
+        if word == "limit":
+            limits.setdefault(rest[0], []).append(int(rest[1]))
+        launches += word == "launch"
+    assert launches == 24 and sum(map(len, limits.values())) == launches and len(limits) < launches
+    assert all(len(set(v)) == 1 and 64 * 1024 <= v[0] <= 160 * 1024 for v in limits.values()), limits
