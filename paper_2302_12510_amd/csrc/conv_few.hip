@@ -219,7 +219,7 @@ static bool plan(const GemmArgs &g, FewArgs &f, int &waves, int &lds_bytes, int 
         const int64_t in_rows = (int64_t)(r - 1) * g.stride + g.kh, bytes = fixed + in_rows * f.pitch;
         if (bytes > kLdsLimit) break;
         for (int wv = 4; wv <= 8; ++wv) {
-            const int per_cu = (int)(kLdsLimit / bytes) < 16 / wv ? (int)(kLdsLimit / bytes) : 16 / wv;
+            const int by_lds = (int)(160 * 1024 / (bytes + 160 * 1024 - kLdsLimit)), per_cu = by_lds < 16 / wv ? by_lds : 16 / wv;
             const int rounds = ((r * g.Wo + 31) / 32 + wv - 1) / wv;
             const int64_t units = g.M / ((int64_t)g.Ho * g.Wo) * ((g.Ho + r - 1) / r) * f.parts;
             const double work = rounds * wv * 500.0 + (double)in_rows * f.in_cols * g.Cin / 32 * 130 / 64;

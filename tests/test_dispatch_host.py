@@ -127,3 +127,13 @@ def test_lds_limits_are_constants(asked):
         launches += word == "launch"
     assert launches == 24 and sum(map(len, limits.values())) == launches and len(limits) < launches
     assert all(len(set(v)) == 1 and 64 * 1024 <= v[0] <= 160 * 1024 for v in limits.values()), limits
+
+
+@pytest.mark.parametrize("geom", [(8, 256, 708, 4, 64, 7, 7, 2, 3, 8, 8), (16, 250, 250, 16, 64, 2, 2, 1, 0, 8, 8), (4, 256, 736, 4, 64, 8, 8, 2, 3, 8, 8), (64, 224, 224, 4, 64, 7, 7, 2, 3, 8, 8)])
+def test_few_channel_walkers_fit_the_device(asked, geom):
+    """Its workgroups walk over the units of work, as many of them as 256 compute units hold at once: each has 256 bytes of LDS of its own beside
+    what the launch asks for (codes out)."""
+    lines = asked(f'B.dybit_set_option("gemm_kernel", "few")\nassert T.conv_kernel(*{geom}, out="codes") == "f16_few"')
+    (grid, threads, lds), = [map(int, rest) for word, *rest in lines if word == "launch"]
+    per_cu = min(160 * 1024 // (lds + 256), 1024 // threads)
+    assert grid <= 256 * per_cu
