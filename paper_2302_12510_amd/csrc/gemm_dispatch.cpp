@@ -201,10 +201,11 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
 // Calls that write fp32 results and codes have the long epilogue (20 vector instructions per result, a column per lane), which this kernel
 // has fewer waves to hide behind than the ones with small tiles.  They gain as above against tiles of 128 (64 x 7 x 7 x 512, 8-bit pair
-// 44.8 -> 28.2), but with K from 512 on; against the small-output kernel with 6- and 8-bit weights and K from 1536 on (40 x 14 x 14, 128 to 96,
-// 8- by 4-bit: 12.0 -> 13.2); against the 64 x 64 kernel from 264 tiles on (64 x 7 x 7 x 512, 4-bit pair 30.2 -> 20.4, but 20 x 16 x 16, 64 to
-// 128, 160 tiles, 2-bit pair 8.9 -> 10.3); against the weight-stationary kernel with more than 64 columns, for which that one holds twice the
-// weights, or K from 832 on (64 to 64, 13 x 56 x 56, 8- by 4-bit 14.2 -> 17.0, 64 x 56 x 56, 2-bit pair 25.4 -> 29.6).
+// 44.8 -> 28.2), but with K from 512 on; against the small-output kernel with 6-bit weights (40 x 14 x 14, 128 to 96, 6-bit pair 16.4 -> 15.2, 8-
+// by 4-bit 12.0 -> 13.2) and with 8-bit ones from K = 1536 on; against the 64 x 64 kernel from 264 tiles (64 x 7 x 7 x 512, 4-bit pair
+// 30.2 -> 20.4, but 20 x 16 x 16, 64 to 128, 160 tiles, 2-bit pair 8.9 -> 10.3) or K = 2560 on (5 x 5 of 256, 9 x 33 x 33, to 64, 25.9 -> 21.4);
+// against the weight-stationary kernel with more than 64 columns, for which that one holds twice the weights, or K from 832 on (64 to 64,
+// 13 x 56 x 56, 8- by 4-bit 14.2 -> 17.0, 64 x 56 x 56, 2-bit pair 25.4 -> 29.6).
 static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8, bool large)
 {
     if (g.K < 320) return false;
@@ -214,13 +215,13 @@ static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8
     const bool both = g.q_out && !codes_only(g);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (both && g.K < 512) return false;
-    if (small_output(g, false, f8) && (f8 || g.K < 512 || tiles64 <= 136 || (both && (g.K < 1536 || w_bits <= 4)))) return false;
+    if (small_output(g, false, f8) && (f8 || g.K < 512 || tiles64 <= 136 || (both && (w_bits <= 4 || (w_bits == 8 && g.K < 1536))))) return false;
     const bool declines = (a_bits == 6 || a_bits == 2 || w_bits == 6) && g.Cin % 128 != 0;   // see gemm_fast.hip
     if (large && !f8 && w_bits > 4 && !declines) return false;
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
     if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return (g.M < 40960 || (g.stride == 1 && w_bits <= 4)) && (!both || g.N > 64 || g.K >= 832);
     const bool tiles_of_64 = f8 && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 128;   // see gemm_f8.hip
-    return !tiles_of_64 || (g.stride == 1 && g.K >= 512 && (!both || tiles64 >= 264));
+    return !tiles_of_64 || (g.stride == 1 && g.K >= 512 && (!both || tiles64 >= 264 || g.K >= 2560));
 }
 
 // It takes a convolution with 64-code k groups inside one filter tap whose outputs look at consecutive pixels,

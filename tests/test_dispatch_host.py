@@ -55,6 +55,7 @@ def test_taps_that_share_pixels(geom, takes, out):
 @pytest.mark.parametrize("geom,takes", [
     ((64, 7, 7, 512, 512, 3, 3, 1, 1, 8, 8), True), ((64, 7, 7, 512, 512, 3, 3, 1, 1, 4, 4), True),                                                  # tiles of 128; of 64, 392 of them
     ((20, 16, 16, 64, 128, 3, 3, 1, 1, 2, 2), False), ((36, 16, 16, 128, 128, 3, 3, 1, 1, 4, 4), True),                                              # tiles of 64: 160 and 288
+    ((9, 33, 33, 256, 64, 5, 5, 1, 2, 4, 4), True), ((9, 33, 33, 256, 64, 3, 3, 1, 1, 4, 4), False), ((40, 14, 14, 128, 96, 3, 3, 1, 1, 8, 6), True),   # K
     ((40, 14, 14, 128, 96, 3, 3, 1, 1, 8, 4), False), ((40, 14, 14, 128, 96, 3, 3, 1, 1, 8, 8), False), ((40, 14, 14, 192, 96, 3, 3, 1, 1, 8, 8), True),   # small outputs
     ((13, 56, 56, 64, 64, 3, 3, 1, 1, 8, 4), False), ((64, 56, 56, 64, 64, 3, 3, 1, 1, 2, 2), False), ((13, 56, 56, 128, 64, 3, 3, 1, 1, 4, 4), True),     # stationary weights
     ((13, 56, 56, 64, 96, 3, 3, 1, 1, 8, 4), True), ((32, 40, 40, 64, 160, 7, 1, 1, 0, 8, 8), False)])                                                # columns; K
