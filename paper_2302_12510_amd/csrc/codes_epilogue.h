@@ -130,10 +130,8 @@ __device__ __forceinline__ void quads_to_words(const uint32_t (&t)[8], uint32_t 
     if constexpr (BITS == 8) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) w[i] = t[i];
-    } else if constexpr (BITS == 4) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = t[2 * i] | (t[2 * i + 1] << 16);
     } else {
+        static_assert(BITS == 6, "4-bit codes are packed by permutes");
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             w[3 * i] = t[4 * i] | (t[4 * i + 1] << 24);

@@ -44,18 +44,6 @@ constexpr int RB = 4;                                    // row blocks of 32 per
 constexpr int kMaxCols = 256;                            // columns of a workgroup, at most
 constexpr int kExchange = 2 * 16 * 64 * 4;               // LDS bytes a wave hands to its partner (two accumulators)
 
-// Division of numbers below 2^31 by a constant: the high word of a product, shifted.
-struct Divisor {
-    uint32_t d, mul, shift;
-};
-static Divisor divisor(uint32_t d)
-{
-    int l = 1;
-    while ((1ull << l) < d) ++l;
-    return Divisor{d, (uint32_t)(((1ull << (31 + l)) + d - 1) / d), (uint32_t)(l - 1)};
-}
-__device__ __forceinline__ u32 quotient(u32 n, const Divisor &d) { return d.d == 1 ? n : __umulhi(n, d.mul) >> d.shift; }
-
 struct PatchArgs {
     int rw, cw_log, kg_log;                              // waves of a workgroup: strips of 128 rows; of 32 columns and k-groups, as powers of two
     int tiles;

@@ -165,8 +165,8 @@ inline int64_t strip_pixels(const GemmArgs &g, int64_t rows)
     return (g.Wo > 1 ? inner * g.stride : 0) + row_ends * row_step + image_ends * (further - row_step) + (int64_t)(g.kh - 1) * g.Wd + g.kw;
 }
 
-// Convolution of 64 and more channels with its input decoded once (conv_patch.hip), all three builds.  false: the
-// pixels of 128 outputs do not fit the LDS.
+// Convolution of 64 and more channels with its input decoded once (conv_patch.hip), all three builds.  false: the pixels of 128 outputs
+// (up to 32 columns: of 256, which their four waves take together) do not fit the LDS.
 bool launch_conv_patch_w0(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w2(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);
 bool launch_conv_patch_w4(const GemmArgs &g, int a_bits, bool low_pair, hipStream_t st);

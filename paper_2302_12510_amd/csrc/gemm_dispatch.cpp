@@ -182,7 +182,7 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 
 // Whether the many-channel kernel is the faster one.  It decodes an input code once per tile, so it lives on taps that share their
 // pixels: `share` of them look at a pixel of a strip of 128 outputs, on average (3 x 3 at stride 1: 8.0 on 7 x 7, 4.8 on 56 x 56, 1.2 on
-// 400 columns, where a strip looks at three image rows all along; at stride 2 on 56 x 56 1.8).  Measured over 4700 convolutions of 64 to
+// 400 columns, where a strip looks at three image rows all along; at stride 2 on 56 x 56 1.8).  Measured over 5300 convolutions of 64 to
 // 1024 channels and 2 to 778752 outputs, 1 x 2 to 5 x 5 and 7 x 1 taps, all formats and outputs (us, the kernel it replaces -> this one):
 //   filters in two dimensions: share from 1.75 on (64 x 64 x 64, 192 to 160 at stride 2, 4-bit pair 44.7 -> 36.1; below, 400 x 400, 64 to 64,
 //     8- by 4-bit 22.0 -> 35.0, 4-bit pair 19.7 -> 32.8, and 2 x 2 at stride 2, 63 x 49 x 49, 128 to 256: 14.9 -> 22.6); in one from 3 on
@@ -197,7 +197,8 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //     11.4 -> 11.2 to 14.2 -> 20.3);
 //   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8), unless that kernel declines and
 //     leaves them to the 128 x 128 one (a 6- or 2-bit operand, 64 x 28 x 28, 192 to 192, 6-bit pair: 85.0 -> 51.7);
-//   64 x 64 e4m3 kernel: at stride 1 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160: 11.9 -> 13.2), K from 512 on;
+//   64 x 64 e4m3 kernel: K from 512 on, and 264 tiles, where that one needs a second round (64 x 14 x 14, 256 to 512 at stride 2, 392 tiles,
+//     coded shortcut: 20.3 -> 16.1), or stride 1 or a share of 2.5 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160, 135 tiles: 11.9 -> 13.2);
 //   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
 // Calls that write fp32 results and codes have the long epilogue (20 vector instructions per result, a column per lane), which this kernel
 // has fewer waves to hide behind than the ones with small tiles.  They gain as above against tiles of 128 (64 x 7 x 7 x 512, 8-bit pair
@@ -221,7 +222,7 @@ static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
     if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return (g.M < 40960 || (g.stride == 1 && w_bits <= 4)) && (!both || g.N > 64 || g.K >= 832);
     const bool tiles_of_64 = f8 && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 128;   // see gemm_f8.hip
-    return !tiles_of_64 || (g.stride == 1 && g.K >= 512 && (!both || tiles64 >= 264 || g.K >= 2560));
+    return !tiles_of_64 || (g.K >= 512 && (tiles64 >= 264 || (both ? g.K >= 2560 : g.stride == 1 || share >= 2.5)));
 }
 
 // It takes a convolution with 64-code k groups inside one filter tap whose outputs look at consecutive pixels,
@@ -337,12 +338,13 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 }
 
 // Whether a launch per group beats the one-launch kernel.  For a pair of 4- and 2-bit formats in groups of whole 64-channel k groups
-// the tiled kernels have e4m3 forms, the one-launch kernel is fp16; so with weights of some size (its own advantage on small ones is
+// the other kernels have e4m3 forms, the one-launch kernel is fp16; so with weights of some size (its own advantage on small ones is
 // that it fills the device), more columns than its 32-column form takes and enough multiply-adds per group for the number of
-// groups, they win.  One launch -> one per group (us), 3 x 3, 4-bit pair: 2 groups of 128 -> 128 channels, M = 50176: 44.3 -> 29.4,
-// 4 groups 88.9 -> 71.2; M = 200704, 2 groups 162 -> 111; but 64 -> 64 channels, 4 groups 88.6 <- 109.6, and at M = 12544 128 -> 128
-// channels, 2 groups 20.2 <- 24.1.  Of 700 geometries measured (64 to 512 channels, 1 x 1 to 3 x 3, 2 to 8 groups) the line leaves 30
-// more than 3 % slower than a launch per group (at most 1.34 times) and 17 than one launch (1.25 times).
+// groups, they win.  One launch -> one per group (us on the device, launches back to back), 3 x 3, 4-bit pair: 2 groups of
+// 128 -> 128 channels, M = 50176: 52.9 -> 30.1, 4 groups 81.5 -> 55.6; M = 200704, 2 groups 148.8 -> 78.1.  The line was drawn where the 128 x 128
+// kernels met the one-launch kernel; with 3 x 3 groups on the many-channel kernel it is on the safe side: of 531 geometries measured (64 to 512
+// channels, 1 x 1 to 3 x 3, 2 to 8 groups) two are up to 1.08 times slower than in one launch, and 79 that stay in one launch up to 1.38
+// times slower than a launch per group (128 -> 128 channels, 8 groups, M = 50176 152 against 115, 2 groups, M = 12544 19.0 against 16.5).
 static bool launch_per_group(const GemmArgs &g, int a_bits, int w_bits, int groups)
 {
     if (a_bits > 4 || w_bits > 4 || g.Cin % 64 || dispatch_options().mfma_f16) return false;

@@ -37,9 +37,10 @@ constexpr int kMaxWaves = 16;
 // instead of four, and decoders that emit bytes.  512 x 512 x 4096, 4-bit pair: fp16 form 9.2, this one 8.4 us.
 template <int FMT> constexpr bool low_format() { return FMT == F4S || FMT == F4U || FMT == F2S || FMT == F2U; }
 
-// The order of the tiles: l / per is one coordinate, l % per the other; mul and shift divide numbers below 2^31 by per.
+// The order of the tiles: l / per is one coordinate, l % per the other.
 struct TileOrder {
-    uint32_t tiles, per, mul, shift;
+    uint32_t tiles;
+    Divisor per;
     int by_columns, waves;
 };
 
@@ -53,8 +54,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     extern __shared__ __attribute__((aligned(16))) float red[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // every argument that the first loads need, read at once: the compiler otherwise reads them in steps that wait for each other.  Not in
-    // the write-back build, whose epilogue has no scalar registers to spare (196 rows, three layers of a bottleneck block: 31.5 -> 32.6 us)
+    // every argument that the first loads need, read at once, and the scales and biases requested before the K loop: the compiler otherwise
+    // reads them in steps that wait for each other.  Kernel times 1 to 7 % shorter (64 x 64 x 256, 4-bit pair 3.33 -> 3.10 us, 128 x 1000 x 2048,
+    // 8-bit 8.72 -> 8.55), a call that is waited for, with its absmax and encoder, 1 % (23.4 -> 23.2 and 32.7 -> 32.4).  Not in the
+    // write-back build, whose epilogue has no scalar registers to spare (196 rows, three layers of a bottleneck block: 31.5 -> 32.6 us)
     constexpr bool EARLY = OUT == OUT_FP32;
     if (EARLY) asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.K), "s"(g.A), "s"(g.W), "s"(g.a_bytes), "s"(g.w_bytes), "s"(g.a_scale), "s"(g.w_scale), "s"(g.bias));
     if (EARLY && MODE == CONVOLUTION) asm volatile("" ::"s"(g.H), "s"(g.Wd), "s"(g.Cin), "s"(g.Ho), "s"(g.Wo), "s"(g.kw), "s"(g.stride), "s"(g.pad), "s"(g.pix_bytes));
@@ -62,7 +65,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemm_small_kernel(const GemmAr
     // neighbouring tiles, which share an operand strip, go to the same XCD: by columns when W is the larger operand
     const int l = xcd_contiguous_index();
     if ((u32)l >= order.tiles) return;                               // uniform per workgroup
-    const int high = order.per == 1 ? l : (int)(__umulhi((u32)l, order.mul) >> order.shift), low = l - high * (int)order.per;
+    const int high = (int)quotient((u32)l, order.per), low = l - high * (int)order.per.d;
     const int tile_m = order.by_columns ? low : high, tile_n = order.by_columns ? high : low;
     const int64_t m0 = (int64_t)tile_m * 32, n0 = (int64_t)tile_n * (32 * CB);
 
@@ -208,11 +211,7 @@ static void launch_one(const GemmArgs &g, hipStream_t st)
     int waves = 1;
     while (waves < kMaxWaves && waves * 2 <= steps && tiles * waves * 2 <= 4096) waves *= 2;
     const int lds_bytes = waves / 2 * CB * 16 * 64 * 4;
-    TileOrder order{(uint32_t)tiles, (uint32_t)(g.N > g.M ? tiles_m : tiles_n), 0, 0, g.N > g.M ? 1 : 0, waves};
-    int bits = 1;
-    while ((1ull << bits) < order.per) ++bits;
-    order.mul = (uint32_t)(((1ull << (31 + bits)) + order.per - 1) / order.per);
-    order.shift = (uint32_t)(bits - 1);
+    const TileOrder order{(uint32_t)tiles, divisor((uint32_t)(g.N > g.M ? tiles_m : tiles_n)), g.N > g.M ? 1 : 0, waves};
     auto k = gemm_small_kernel<FA, FW, MODE, CB, kOut, E4M3>;
     note_kernel(E4M3 ? DYBIT_KERNEL_F8_SMALL : DYBIT_KERNEL_F16_SMALL);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxWaves / 2 * CB * 16 * 64 * 4));

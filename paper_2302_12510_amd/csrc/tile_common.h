@@ -51,6 +51,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t code_descriptor(const uint8_t 
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p), 0, (int)(bytes > 0x7fffffff ? 0x7fffffff : bytes), 0x00020000);
 }
 
+// Division of numbers below 2^31 by a number that the host knows: the high word of a product, shifted.
+struct Divisor {
+    uint32_t d, mul, shift;
+};
+inline Divisor divisor(uint32_t d)
+{
+    int l = 1;
+    while ((1ull << l) < d) ++l;
+    return Divisor{d, (uint32_t)(((1ull << (31 + l)) + d - 1) / d), (uint32_t)(l - 1)};
+}
+__device__ __forceinline__ uint32_t quotient(uint32_t n, const Divisor &d) { return d.d == 1 ? n : __umulhi(n, d.mul) >> d.shift; }
+
 // Output pixel m of a convolution: the image row and column of its filter tap (0, 0) (negative inside the
 // padding) and the pixel index of that tap in the NHWC image, (b H + hi0) Wd + wi0 (may be negative).
 struct PixelOrigin {

@@ -45,7 +45,7 @@ def test_stride_beyond_the_image(option):
     ((64, 56, 56, 64, 128, 3, 3, 2, 1, 4, 4), False), ((64, 56, 56, 128, 256, 3, 3, 2, 1, 4, 4), True), ((32, 60, 90, 128, 256, 3, 3, 3, 0, 4, 4), False),   # strides
     ((2, 40, 40, 64, 160, 1, 2, 1, 0, 8, 8), False), ((2, 40, 40, 64, 256, 2, 2, 1, 0, 6, 4), False), ((2, 40, 40, 128, 256, 2, 2, 1, 0, 6, 4), True),       # K
     ((62, 8, 7, 64, 200, 1, 2, 1, 0, 8, 4), False), ((16, 64, 64, 64, 1024, 3, 1, 1, 0, 8, 4), False),
-    ((16, 39, 17, 256, 160, 3, 3, 2, 1, 4, 2), False), ((16, 39, 17, 256, 160, 3, 3, 1, 1, 4, 2), True)])                                                   # 64 x 64 tiles
+    ((16, 39, 17, 256, 160, 3, 3, 2, 1, 4, 2), False), ((16, 39, 17, 256, 160, 3, 3, 1, 1, 4, 2), True), ((16, 39, 17, 64, 160, 5, 5, 2, 2, 4, 2), True), ((64, 14, 14, 256, 512, 3, 3, 2, 1, 4, 4), True)])                                                   # 64 x 64 tiles
 @pytest.mark.parametrize("out", ["fp32", "codes"])
 def test_taps_that_share_pixels(geom, takes, out):
     """The kernel pays where a pixel that it decodes once serves several taps: not for wide images, long strides, two or three taps or a short K."""
