@@ -38,9 +38,16 @@ PEAK_FP16_MFMA_TFLOPS = 2500.0   # MI355X dense fp16/bf16 matrix peak
 PEAK_FP8_MFMA_TFLOPS = 5000.0    # MI355X dense fp8 matrix peak (pairs of 4-bit formats run on it)
 PEAK_HBM_GBPS = 8000.0           # MI355X HBM3E peak
 
+# What dybit_last_gemm_kernel names, for the kernels the products and the convolution of this file can run on.
+KERNELS = {"f16_256": "dybit::fast::gemm_fast_kernel (256x256 tiles, fp16 MFMA)",
+           "f8_256": "dybit::f8::gemm_f8_kernel (256x256 tiles, e4m3 MFMA)",
+           "f8_128_kg2": "dybit::f8::gemm_f8_kernel (128x128 tiles, two k-groups, e4m3 MFMA)",
+           "f8_small": "dybit::small::gemm_small_kernel (32-row tiles, K split over the waves, e4m3 MFMA)",
+           "f8_patch": "dybit::patch::conv_patch_kernel (input decoded once per tile, e4m3 MFMA)"}
+
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (units of 2 KiB and 1 KiB on
 # this device, calibrated on a 1 GiB copy); the summaries are under profiles/.
-MEASURED_TRAFFIC = {"cfg5": 262303 * 2048 + 262222 * 1024, "cfg2": 2119 * 2048 + 12544 * 1024, "cfg1": None}
+MEASURED_TRAFFIC = {"cfg5": 262303 * 2048 + 262222 * 1024, "cfg2": 2126 * 2048 + 12544 * 1024, "cfg1": None}
 MEASURED_TRAFFIC_GEMM_4BIT = 196756 * 2048 + 262305 * 1024
 MEASURED_TRAFFIC_QUANTIZE4 = 524376 * 2048 + 131072 * 1024
 
@@ -486,6 +493,7 @@ def main():
     assert B.dybit_get_last_async_error() == B.OK
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     gemm_ms = float(np.mean([a.elapsed_time(b) for a, b in zip(g0, g1)]))
+    ran = B.dybit_last_gemm_kernel()
     flops = 2.0 * M * N * K
     value = flops / (ms_per_step * 1e-3) / 1e12
     gemm_tflops = flops / (gemm_ms * 1e-3) / 1e12
@@ -500,7 +508,7 @@ def main():
         "vs_baseline": None, "dtype": ("e4m3" if use_f8 else "f16") + " MFMA inputs (exact), f32 accumulate", "data": "synthetic",
         "config": {"workload": name, "M": M, "N": N, "K": K, "a_fmt": list(a_fmt), "w_fmt": list(w_fmt),
                    "step": "absmax + quantize activations + gemm; weights pre-quantized"},
-        "roofline": {"bound": "mfma", "kernel": {"cfg5": "dybit::fast::gemm_fast_kernel (256x256 tiles, fp16 MFMA)", "cfg2": "dybit::f8::gemm_f8_kernel (128x128 tiles, two k-groups, e4m3 MFMA)", "cfg1": "dybit::f8::gemm_f8_kernel (128x128 tiles, e4m3 MFMA)"}[args.workload], "achieved": round(gemm_tflops, 2),
+        "roofline": {"bound": "mfma", "kernel": KERNELS.get(ran, ran), "achieved": round(gemm_tflops, 2),
                      "peak": peak, "unit": "TFLOP/s",
                      "frac": round(gemm_tflops / peak, 4),
                      "kernel_ms": round(gemm_ms, 4), "traffic": MEASURED_TRAFFIC[args.workload]},
@@ -585,6 +593,7 @@ def main():
         C4 = torch.empty((M, N), dtype=torch.float32, device="cuda")
         g4_ms, _ = time_events(lambda: B.dybit_gemm(M, N, K, qa4, f4, sa4, qw, w_fmt, sw, out=C4), args.steps, args.warmup, torch)
         tf4 = flops / (g4_ms * 1e-3) / 1e12
+        ran4 = B.dybit_last_gemm_kernel()
         # the fp8 matrix cores alone on e4m3 bytes of these values (torch has the dtype; the library only times it)
         def sample8(q, s, need):
             v = B.dybit_dequantize(q[: need // 2], need, s, *f4) / s
@@ -592,7 +601,7 @@ def main():
         ops8 = torch.cat([sample8(qa4, sa4, 512 * 32), sample8(qw, sw, 8 * 512 * 32)]).contiguous()
         fl8 = B.dybit_diag_mfma_f8(ops8, 512, 1000, sink)
         m8_ms, _ = time_events(lambda: B.dybit_diag_mfma_f8(ops8, 512, 1000, sink), 5, 2, torch)
-        out["roofline_4bit_w_a"] = {"bound": "mfma", "kernel": "dybit::f8::gemm_f8_kernel (256x256 tiles, e4m3 MFMA)",
+        out["roofline_4bit_w_a"] = {"bound": "mfma", "kernel": KERNELS.get(ran4, ran4),
                                     "workload": "the same 8192^3 product with the activations quantized to 4-bit signed",
                                     "achieved": round(tf4, 2), "peak": PEAK_FP8_MFMA_TFLOPS, "unit": "TFLOP/s",
                                     "frac": round(tf4 / PEAK_FP8_MFMA_TFLOPS, 4), "kernel_ms": round(g4_ms, 4), "traffic": MEASURED_TRAFFIC_GEMM_4BIT,
@@ -614,9 +623,10 @@ def main():
         Y2 = torch.empty((Bn, H, Wd, Cout), dtype=torch.float32, device="cuda")
         conv2 = (Bn, H, Wd, Cin, Cout, kh, kw, c2["stride"], c2["pad"])
         c2_ms = time_batches(lambda: B.dybit_conv2d(*conv2, qx2, f_x, sx2, qw2, f_w, sw2, out=Y2), 25, 4, 5, torch)
+        ran2 = B.dybit_last_gemm_kernel()
         fl2 = 2.0 * Bn * H * Wd * Cout * kh * kw * Cin
         out["conv_4bit_w_a"] = {"workload": "cfg2 conv 3x3 256->256 on 14x14, batch 64, W 4-bit signed, A 4-bit unsigned",
-                                "kernel": "dybit::f8::gemm_f8_kernel (128x128 tiles, two k-groups, e4m3 MFMA)",
+                                "kernel": KERNELS.get(ran2, ran2),
                                 "kernel_ms": round(c2_ms, 4), "timing": "HIP events around batches of 25 back-to-back launches",
                                 "TFLOPs": round(fl2 / (c2_ms * 1e-3) / 1e12, 1),
                                 "frac_of_fp8_mfma_peak": round(fl2 / (c2_ms * 1e-3) / 1e12 / PEAK_FP8_MFMA_TFLOPS, 4)}
