@@ -199,7 +199,12 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //     leaves them to the 128 x 128 one (a 6- or 2-bit operand, 64 x 28 x 28, 192 to 192, 6-bit pair: 85.0 -> 51.7);
 //   64 x 64 e4m3 kernel: K from 512 on, and 264 tiles, where that one needs a second round (64 x 14 x 14, 256 to 512 at stride 2, 392 tiles,
 //     coded shortcut: 20.3 -> 16.1), or stride 1 or a share of 2.5 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160, 135 tiles: 11.9 -> 13.2);
-//   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5).
+//   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5);
+//   against these and the weight-stationary kernel, which have rounds enough from 513 tiles of 128 x 128 on to hide their fixed times, and a strip of
+//     more than 56 KiB, of which a compute unit holds one or two and each waits for its own loads: share from 2.5 on (53 x 90 x 90, 64 to 64, 8- by
+//     4-bit, codes 43.1 -> 73.2; 14 x 91 x 91, 128 to 64, 26.3 -> 40.4), with codes beside the fp32 results and more than 64 columns 3.5 (7 x 127 x 127,
+//     128 to 160, 2- by 4-bit 58.4 -> 75.6); 4-bit activations of a pair whose bytes decode faster: 2 up to 64 columns (73 x 20 x 128, 192 to 64, codes
+//     1.25 times as long), none beyond (64 x 56 x 56, 128 to 256 at stride 2 35.6 -> 31.8), nor for up to 32 columns of any pair (0.84 times).
 // Calls that write fp32 results and codes have the long epilogue (20 vector instructions per result, a column per lane), which this kernel
 // has fewer waves to hide behind than the ones with small tiles.  They gain as above against tiles of 128 (64 x 7 x 7 x 512, 8-bit pair
 // 44.8 -> 28.2), but with K from 512 on; against the small-output kernel with 6-bit weights (40 x 14 x 14, 128 to 96, 6-bit pair 16.4 -> 15.2, 8-
@@ -211,17 +216,23 @@ static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8
 {
     if (g.K < 320) return false;
     const int64_t strip = g.M < 128 ? g.M : 128;
-    const double share = (double)(g.kh * (int64_t)g.kw * strip) / (double)strip_pixels(g, strip);
+    const int64_t pixels = strip_pixels(g, strip);
+    const double share = (double)(g.kh * (int64_t)g.kw * strip) / (double)pixels;
     if (share < (g.kh > 1 && g.kw > 1 ? 1.75 : 3.0)) return false;
+    const int64_t strip_bytes = (pixels + 1) * (g.Cin * (f8 ? 1 : 2) + 16);
     const bool both = g.q_out && !codes_only(g);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (both && g.K < 512) return false;
     if (small_output(g, false, f8) && (f8 || g.K < 512 || tiles64 <= 136 || (both && (w_bits <= 4 || (w_bits == 8 && g.K < 1536))))) return false;
     const bool declines = (a_bits == 6 || a_bits == 2 || w_bits == 6) && g.Cin % 128 != 0;   // see gemm_fast.hip
-    if (large && !f8 && w_bits > 4 && !declines) return false;
+    const bool tiles_of_256 = large && (f8 || !declines);
+    if (tiles_of_256 && !f8 && w_bits > 4) return false;
+    const int64_t tiles128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    if (!tiles_of_256 && tiles128 > 512 && strip_bytes > 56 * 1024 && (!f8 || g.N > 32) &&
+        share < (both && g.N > 64 ? 3.5 : !f8 || a_bits == 2 ? 2.5 : g.N > 64 ? 0.0 : 2.0)) return false;
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
     if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return (g.M < 40960 || (g.stride == 1 && w_bits <= 4)) && (!both || g.N > 64 || g.K >= 832);
-    const bool tiles_of_64 = f8 && ((g.M + 127) / 128) * ((g.N + 127) / 128) <= 128;   // see gemm_f8.hip
+    const bool tiles_of_64 = f8 && tiles128 <= 128;   // see gemm_f8.hip
     return !tiles_of_64 || (g.K >= 512 && (tiles64 >= 264 || (both ? g.K >= 2560 : g.stride == 1 || share >= 2.5)));
 }
 

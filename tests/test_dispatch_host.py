@@ -64,6 +64,17 @@ def test_both_outputs(geom, takes):
     assert conv_kernel(*geom, out="both").endswith("_patch") == takes
 
 
+@pytest.mark.parametrize("geom,outs", [
+    ((53, 90, 90, 64, 64, 3, 3, 1, 0, 8, 4), ""), ((14, 91, 91, 128, 64, 3, 3, 1, 0, 8, 4), ""), ((64, 56, 56, 64, 64, 3, 3, 1, 1, 8, 4), "fp32 codes"),       # few taps a pixel; 4.8
+    ((7, 127, 127, 128, 160, 3, 3, 1, 0, 2, 4), ""), ((2, 127, 127, 128, 160, 3, 3, 1, 0, 2, 4), "fp32 codes both"),                                     # 856 tiles; 490
+    ((53, 90, 90, 64, 160, 3, 3, 1, 0, 2, 4), "fp32 codes both"), ((53, 90, 90, 128, 160, 3, 3, 1, 0, 2, 4), ""),                                        # strips of 39 KiB; of 70
+    ((64, 56, 56, 128, 256, 3, 3, 2, 1, 4, 4), "fp32 codes"), ((73, 20, 128, 192, 64, 3, 3, 1, 0, 4, 4), ""), ((30, 90, 90, 128, 64, 3, 3, 1, 0, 4, 4), "fp32 codes both"),   # 4-bit pair
+    ((30, 90, 90, 128, 32, 3, 3, 1, 0, 2, 4), "fp32 codes both"), ((30, 90, 90, 128, 40, 3, 3, 1, 0, 2, 4), "")])                                        # columns
+def test_many_tiles(geom, outs):
+    """Many tiles of long strips whose pixels serve few taps are left to the kernels with more workgroups a compute unit."""
+    assert [out for out in ("fp32", "codes", "both") if conv_kernel(*geom, out=out).endswith("_patch")] == outs.split()
+
+
 @pytest.mark.parametrize("cin,a_bits,w_bits,takes", [(192, 6, 6, True), (192, 2, 8, True), (192, 8, 6, True), (192, 8, 8, False), (192, 4, 8, False), (256, 6, 6, False), (256, 8, 6, False)])
 @pytest.mark.parametrize("out", ["fp32", "codes", "both"])
 def test_what_the_large_tiles_decline(cin, a_bits, w_bits, takes, out):
