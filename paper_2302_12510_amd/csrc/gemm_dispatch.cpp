@@ -183,14 +183,17 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 // Whether the many-channel kernel is the faster one.  It decodes an input code once per tile, so it lives on taps that share their
 // pixels: `share` of them look at a pixel of a strip of 128 outputs, on average (3 x 3 at stride 1: 8.0 on 7 x 7, 4.8 on 56 x 56, 1.2 on
 // 400 columns, where a strip looks at three image rows all along; at stride 2 on 56 x 56 1.8).  Measured over 5300 convolutions of 64 to
-// 1024 channels and 2 to 778752 outputs, 1 x 2 to 5 x 5 and 7 x 1 taps, all formats and outputs (us, the kernel it replaces -> this one):
+// 1024 channels and 2 to 778752 outputs, 1 x 2 to 5 x 5 and 7 x 1 taps, all formats and outputs, and over 24000 calls that it took on images of 4 to
+// 160 pixels a side (us, the kernel it replaces -> this one):
 //   filters in two dimensions: share from 1.75 on (64 x 64 x 64, 192 to 160 at stride 2, 4-bit pair 44.7 -> 36.1; below, 400 x 400, 64 to 64,
 //     8- by 4-bit 22.0 -> 35.0, 4-bit pair 19.7 -> 32.8, and 2 x 2 at stride 2, 63 x 49 x 49, 128 to 256: 14.9 -> 22.6); in one from 3 on
 //     (1 x 3 of 384 channels, 69 x 75 x 32, to 128, 8-bit pair: 63.6 -> 81.6);
 //   K from 320 on: a shorter loop ends before the strip is decoded (2 taps of 64, 2 x 40 x 40, to 160, 8-bit pair: 5.6 -> 7.4);
 //   small-output kernel: not a pair of 4- and 2-bit formats to the line of that kernel (3267 outputs, 256 to 64: 7.9 -> 10.5), others from
 //     137 tiles of 64 x 64 on (15 x 23 x 23, 128 to 64, 124 tiles: 9.2 -> 10.8; 36 x 16 x 16, 144 tiles: 13.6 -> 11.9) and K from 512 on
-//     (2 x 2 taps of 64, 2 x 40 x 40, to 256: 6.4 -> 7.7);
+//     (2 x 2 taps of 64, 2 x 40 x 40, to 256: 6.4 -> 7.7); fp32 results with 4- and 2-bit weights, whose decoding that kernel
+//     spreads over the most waves, only at stride 1 (16 x 22 x 22, 128 to 512 at stride 2, 6- by 4-bit 11.0 -> 13.2), and with 4-bit weights strips of more
+//     than 64 KiB only with a share from 4.5 on (2 x 7 x 129, 192 to 320, 8- by 4-bit 11.0 -> 13.6; 56 x 56, 256 to 256, 4.8, 15.6 -> 14.5);
 //   weight-stationary kernel: at stride 1 with 4- and 2-bit weights everywhere (64 x 56 x 56, 64 to 64, 4-bit pair 25.7 -> 22.8, 6- by 4-bit
 //     35.8 -> 29.5); wider weights take a lane longer to decode, and at stride 2 a tile looks at four pixels per output, of which fewer fit the
 //     LDS: below 40960 outputs (25088: 11.6 -> 10.0 to 28.0 -> 18.0; 50176: 8-bit pair 11.9 -> 11.7, 8- by 6-bit 12.9 -> 14.6, stride 2
@@ -198,7 +201,8 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //   256 x 256 kernel: not fp16 with 6- and 8-bit weights (64 x 28 x 28 x 256, 8-bit pair: 64.5 -> 69.8), unless that kernel declines and
 //     leaves them to the 128 x 128 one (a 6- or 2-bit operand, 64 x 28 x 28, 192 to 192, 6-bit pair: 85.0 -> 51.7);
 //   64 x 64 e4m3 kernel: K from 512 on, and 264 tiles, where that one needs a second round (64 x 14 x 14, 256 to 512 at stride 2, 392 tiles,
-//     coded shortcut: 20.3 -> 16.1), or stride 1 or a share of 2.5 (stride 2, 3 x 3, 16 x 39 x 17, 256 to 160, 135 tiles: 11.9 -> 13.2);
+//     coded shortcut: 20.3 -> 16.1), or a share of 3, codes only 2.5 (16 x 39 x 17, 256 to 160 at stride 2, 135 tiles: 11.9 -> 13.2; 6 x 26 x 72, 320
+//     to 40, 3 x 2 taps, 9.9 -> 12.0);
 //   128 x 128 kernels: everywhere (64 x 14 x 14 x 256, 4-bit pair 22.8 -> 15.5; 64 x 7 x 7 x 512, 6-bit pair 58.6 -> 31.5);
 //   against these and the weight-stationary kernel, which have rounds enough from 513 tiles of 128 x 128 on to hide their fixed times, and a strip of
 //     more than 56 KiB, of which a compute unit holds one or two and each waits for its own loads: share from 2.5 on (53 x 90 x 90, 64 to 64, 8- by
@@ -207,9 +211,10 @@ static bool launch_conv_few(const GemmArgs &g, int a_bits, int w_bits, bool forc
 //     1.25 times as long), none beyond (64 x 56 x 56, 128 to 256 at stride 2 35.6 -> 31.8), nor for up to 32 columns of any pair (0.84 times).
 // Calls that write fp32 results and codes have the long epilogue (20 vector instructions per result, a column per lane), which this kernel
 // has fewer waves to hide behind than the ones with small tiles.  They gain as above against tiles of 128 (64 x 7 x 7 x 512, 8-bit pair
-// 44.8 -> 28.2), but with K from 512 on; against the small-output kernel with 6-bit weights (40 x 14 x 14, 128 to 96, 6-bit pair 16.4 -> 15.2, 8-
-// by 4-bit 12.0 -> 13.2) and with 8-bit ones from K = 1536 on; against the 64 x 64 kernel from 264 tiles (64 x 7 x 7 x 512, 4-bit pair
-// 30.2 -> 20.4, but 20 x 16 x 16, 64 to 128, 160 tiles, 2-bit pair 8.9 -> 10.3) or K = 2560 on (5 x 5 of 256, 9 x 33 x 33, to 64, 25.9 -> 21.4);
+// 44.8 -> 28.2), but with K from 512 on; against the small-output kernel with 6-bit weights at stride 1 (40 x 14 x 14, 128 to 96, 6-bit pair
+// 16.4 -> 15.2, 8- by 4-bit 12.0 -> 13.2, 29 x 35 x 34, 64 to 64 at stride 2, 8- by 6-bit 12.0 -> 13.8) and with 8-bit ones from K = 1536 on; against the
+// 64 x 64 kernel from 264 tiles (64 x 7 x 7 x 512, 4-bit pair 30.2 -> 20.4, but 20 x 16 x 16, 64 to 128, 160 tiles, 2-bit pair 8.9 -> 10.3) or K = 2560
+// and a share of 4 on (5 x 5 of 256, 9 x 33 x 33, to 64, 25.9 -> 21.4, but 55 x 17 x 17, 512 to 64, 3 x 2 taps, 15.8 -> 18.6);
 // against the weight-stationary kernel with more than 64 columns, for which that one holds twice the weights, or K from 832 on (64 to 64,
 // 13 x 56 x 56, 8- by 4-bit 14.2 -> 17.0, 64 x 56 x 56, 2-bit pair 25.4 -> 29.6).
 static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8, bool large)
@@ -223,7 +228,11 @@ static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8
     const bool both = g.q_out && !codes_only(g);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (both && g.K < 512) return false;
-    if (small_output(g, false, f8) && (f8 || g.K < 512 || tiles64 <= 136 || (both && (w_bits <= 4 || (w_bits == 8 && g.K < 1536))))) return false;
+    if (small_output(g, false, f8)) {
+        if (f8 || g.K < 512 || tiles64 <= 136 || (both && (w_bits <= 4 || (w_bits == 8 && g.K < 1536)))) return false;
+        if (g.stride > 1 && (g.q_out ? both && w_bits == 6 : w_bits <= 4)) return false;
+        if (!g.q_out && w_bits == 4 && strip_bytes > 64 * 1024 && share < 4.5) return false;
+    }
     const bool declines = (a_bits == 6 || a_bits == 2 || w_bits == 6) && g.Cin % 128 != 0;   // see gemm_fast.hip
     const bool tiles_of_256 = large && (f8 || !declines);
     if (tiles_of_256 && !f8 && w_bits > 4) return false;
@@ -233,7 +242,7 @@ static bool many_channels_pay(const GemmArgs &g, int a_bits, int w_bits, bool f8
     const int64_t ws_bytes = (g.N <= 64 ? 64 : 128) * (g.K * (f8 ? 1 : 2) + 16);
     if (g.M >= 16384 && g.N <= 128 && ws_bytes <= 160 * 1024) return (g.M < 40960 || (g.stride == 1 && w_bits <= 4)) && (!both || g.N > 64 || g.K >= 832);
     const bool tiles_of_64 = f8 && tiles128 <= 128;   // see gemm_f8.hip
-    return !tiles_of_64 || (g.K >= 512 && (tiles64 >= 264 || (both ? g.K >= 2560 : g.stride == 1 || share >= 2.5)));
+    return !tiles_of_64 || (g.K >= 512 && (tiles64 >= 264 || (both ? g.K >= 2560 && share >= 4.0 : share >= (g.q_out ? 2.5 : 3.0))));
 }
 
 // It takes a convolution with 64-code k groups inside one filter tap whose outputs look at consecutive pixels,

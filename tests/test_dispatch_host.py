@@ -75,6 +75,16 @@ def test_many_tiles(geom, outs):
     assert [out for out in ("fp32", "codes", "both") if conv_kernel(*geom, out=out).endswith("_patch")] == outs.split()
 
 
+@pytest.mark.parametrize("geom,outs", [
+    ((16, 22, 22, 128, 512, 3, 3, 2, 1, 6, 4), "codes"), ((38, 26, 26, 128, 128, 3, 3, 2, 1, 8, 2), "codes"), ((29, 35, 34, 64, 64, 3, 3, 2, 1, 8, 6), "fp32 codes"),   # stride 2
+    ((1, 56, 56, 256, 256, 3, 3, 1, 1, 8, 4), "fp32 codes"), ((2, 7, 129, 192, 320, 3, 3, 1, 1, 8, 4), "codes"), ((2, 40, 40, 64, 160, 3, 3, 1, 0, 6, 6), "fp32 codes both"),   # share
+    ((6, 26, 72, 320, 40, 3, 2, 1, 0, 2, 4), ""), ((2, 60, 60, 64, 64, 3, 3, 1, 1, 4, 4), "fp32 codes"), ((2, 70, 70, 64, 64, 3, 3, 1, 0, 4, 4), "codes"),          # tiles of 64: share 1.8; 4.6; 2.8
+    ((55, 17, 17, 512, 64, 3, 2, 1, 0, 2, 4), "fp32 codes"), ((9, 33, 33, 256, 64, 5, 5, 1, 2, 4, 4), "fp32 codes both")])
+def test_few_tiles(geom, outs):
+    """Against the kernels for few tiles it needs more taps a pixel, and stride 1 where they decode with more waves."""
+    assert [out for out in ("fp32", "codes", "both") if conv_kernel(*geom, out=out).endswith("_patch")] == outs.split()
+
+
 @pytest.mark.parametrize("cin,a_bits,w_bits,takes", [(192, 6, 6, True), (192, 2, 8, True), (192, 8, 6, True), (192, 8, 8, False), (192, 4, 8, False), (256, 6, 6, False), (256, 8, 6, False)])
 @pytest.mark.parametrize("out", ["fp32", "codes", "both"])
 def test_what_the_large_tiles_decline(cin, a_bits, w_bits, takes, out):
