@@ -36,11 +36,14 @@ if ROOT not in sys.path:
 SETTLE_STEPS = 30          # untimed steps that always run before the timed region (clock settling)
 PEAK_FP16_MFMA_TFLOPS = 2500.0   # MI355X dense fp16/bf16 matrix peak
 PEAK_FP8_MFMA_TFLOPS = 5000.0    # MI355X dense fp8 matrix peak (pairs of 4-bit formats run on it)
+PEAK_FP6_MFMA_TFLOPS = 10000.0   # MI355X dense fp6 matrix peak (large products: operands split into one or two e3m2 planes)
 PEAK_HBM_GBPS = 8000.0           # MI355X HBM3E peak
 
 # What dybit_last_gemm_kernel names, for the kernels the products and the convolution of this file can run on.
 KERNELS = {"f16_256": "dybit::fast::gemm_fast_kernel (256x256 tiles, fp16 MFMA)",
            "f8_256": "dybit::f8::gemm_f8_kernel (256x256 tiles, e4m3 MFMA)",
+           "f6_256": "dybit::six::split_kernel + product_kernel (256x256 tiles, e3m2 MFMA on exactly split operands)",
+           "f6_128": "dybit::six::split_kernel + product_kernel (128x128 tiles, e3m2 MFMA on exactly split operands)",
            "f8_128_kg2": "dybit::f8::gemm_f8_kernel (128x128 tiles, two k-groups, e4m3 MFMA)",
            "f8_small": "dybit::small::gemm_small_kernel (32-row tiles, K split over the waves, e4m3 MFMA)",
            "f8_patch": "dybit::patch::conv_patch_kernel (input decoded once per tile, e4m3 MFMA)"}
@@ -500,12 +503,16 @@ def main():
 
     use_f8 = a_fmt[0] == 4 and w_fmt[0] == 4       # pairs of 4-bit formats run on the fp8 matrix path
     peak = PEAK_FP8_MFMA_TFLOPS if use_f8 else PEAK_FP16_MFMA_TFLOPS
+    dtype = "e4m3" if use_f8 else "f16"
+    if ran.startswith("f6"):                       # one matrix instruction per plane of the activations
+        planes = 2 if a_fmt[0] > 4 else 1
+        peak, dtype = PEAK_FP6_MFMA_TFLOPS / planes, "e3m2" if planes == 1 else "e3m2 + e3m2"
     out = {
         "metric": "DyBit GEMM effective TOPS at 4-bit W/A (+ quantize GB/s), % of roofline",
         "value": round(value, 3), "unit": "TOPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "settle_steps": max(args.warmup, SETTLE_STEPS),
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": ("e4m3" if use_f8 else "f16") + " MFMA inputs (exact), f32 accumulate", "data": "synthetic",
+        "vs_baseline": None, "dtype": dtype + " MFMA inputs (exact), f32 accumulate", "data": "synthetic",
         "config": {"workload": name, "M": M, "N": N, "K": K, "a_fmt": list(a_fmt), "w_fmt": list(w_fmt),
                    "step": "absmax + quantize activations + gemm; weights pre-quantized"},
         "roofline": {"bound": "mfma", "kernel": KERNELS.get(ran, ran), "achieved": round(gemm_tflops, 2),
@@ -535,6 +542,7 @@ def main():
     wgs = 256 * 2
     fl = diag(ops, wgs, iters, sink)
     mf_ms, _ = time_events(lambda: diag(ops, wgs, iters, sink), 5, 2, torch)
+    out["roofline"]["mfma_only_instruction"] = "e4m3" if use_f8 else "f16"
     out["roofline"]["mfma_only_measured_TFLOPs"] = round(fl / (mf_ms * 1e-3) / 1e12, 1)
     out["roofline"]["frac_of_mfma_only_measured"] = round(gemm_tflops / (fl / (mf_ms * 1e-3) / 1e12), 4)
 
@@ -594,6 +602,7 @@ def main():
         g4_ms, _ = time_events(lambda: B.dybit_gemm(M, N, K, qa4, f4, sa4, qw, w_fmt, sw, out=C4), args.steps, args.warmup, torch)
         tf4 = flops / (g4_ms * 1e-3) / 1e12
         ran4 = B.dybit_last_gemm_kernel()
+        peak4 = PEAK_FP6_MFMA_TFLOPS if ran4.startswith("f6") else PEAK_FP8_MFMA_TFLOPS
         # the fp8 matrix cores alone on e4m3 bytes of these values (torch has the dtype; the library only times it)
         def sample8(q, s, need):
             v = B.dybit_dequantize(q[: need // 2], need, s, *f4) / s
@@ -603,8 +612,8 @@ def main():
         m8_ms, _ = time_events(lambda: B.dybit_diag_mfma_f8(ops8, 512, 1000, sink), 5, 2, torch)
         out["roofline_4bit_w_a"] = {"bound": "mfma", "kernel": KERNELS.get(ran4, ran4),
                                     "workload": "the same 8192^3 product with the activations quantized to 4-bit signed",
-                                    "achieved": round(tf4, 2), "peak": PEAK_FP8_MFMA_TFLOPS, "unit": "TFLOP/s",
-                                    "frac": round(tf4 / PEAK_FP8_MFMA_TFLOPS, 4), "kernel_ms": round(g4_ms, 4), "traffic": MEASURED_TRAFFIC_GEMM_4BIT,
+                                    "achieved": round(tf4, 2), "peak": peak4, "unit": "TFLOP/s",
+                                    "frac": round(tf4 / peak4, 4), "kernel_ms": round(g4_ms, 4), "mfma_only_instruction": "e4m3", "traffic": MEASURED_TRAFFIC_GEMM_4BIT,
                                     "mfma_only_measured_TFLOPs": round(fl8 / (m8_ms * 1e-3) / 1e12, 1),
                                     "frac_of_mfma_only_measured": round(tf4 / (fl8 / (m8_ms * 1e-3) / 1e12), 4)}
         out["value_4bit_w_a"] = {"value": round(tf4, 2), "unit": "TOPS", "what": "the same product at 4-bit W / 4-bit A, kernel alone"}

@@ -114,6 +114,17 @@ dybit_status dybit_gemm(int64_t M, int64_t N, int64_t K,
                         const float *bias, int32_t relu,
                         float *C, int64_t ldc, dybit_stream stream);
 
+/* dybit_gemm with device memory to work in: large products split their operands into 6-bit floats there, which multiply on
+ * a faster matrix path (results as dybit_gemm's, in another order of summation).  workspace [device]: 16-byte aligned, its
+ * contents do not matter before or after.  dybit_gemm_workspace_bytes: how much the product would use, 0 if it is one that
+ * runs as in dybit_gemm; with less (or NULL) it does as well. */
+size_t dybit_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, dybit_fmt a_fmt, dybit_fmt w_fmt);
+dybit_status dybit_gemm_work(int64_t M, int64_t N, int64_t K,
+                             const uint8_t *A_codes, dybit_fmt a_fmt, const float *a_scale,
+                             const uint8_t *W_codes, dybit_fmt w_fmt, const float *w_scale,
+                             const float *bias, int32_t relu,
+                             float *C, int64_t ldc, uint8_t *workspace, size_t workspace_bytes, dybit_stream stream);
+
 /* Convolution mapped onto the same matrix product (Sec. IV, "GEMM systolic array"), without
  * materialising the patch matrix: row = (b, ho, wo), column = cout, k = (r, s, cin).
  * X_codes [device]: [B][H][W][Cin] packed along Cin (pixel stride Cin*x_fmt.bits/8 bytes).
@@ -417,11 +428,11 @@ dybit_status dybit_set_async_error_word(int32_t *device_word);
  *
  * dybit_set_option: overrides the automatic choice for the whole process, for tests and A/B
  * measurements.  name / value [host, NUL-terminated]:
- *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small" | "few" | "patch"  -- takes the named kernel family whenever
+ *   "gemm_kernel"  "auto" | "general" | "mid" | "large" | "ws" | "small" | "few" | "patch" | "six"  -- takes the named kernel family whenever
  *                  the problem meets its preconditions (otherwise the automatic choice continues, which
  *                  dybit_last_gemm_kernel shows)
  *   "gemm_mfma"    "auto" | "f16"   -- "f16" keeps pairs of 4- and 2-bit operands off the e4m3 kernels
- *   "mid_tile"     "auto" | "64" | "128"   -- tile of the e4m3 kernel when it is not the 256 x 256 one
+ *   "mid_tile"     "auto" | "64" | "128"   -- tile of the e4m3 kernel when it is not the 256 x 256 one, and of "six" ("128", else 256 x 256)
  *   "mid_kgroups"  "auto" | "1" | "2"      -- k-groups per workgroup of the 128 x 128 kernels
  *   "gemm_ws"      "auto" | "off"   -- "off" leaves the weight-stationary kernel out of the automatic choice
  * Initial values come from the environment, read once when the library is first used (DYBIT_GEMM_KERNEL,
@@ -446,7 +457,9 @@ typedef enum {
     DYBIT_KERNEL_F8_SMALL = 14,      /* e4m3 MFMA, 32-row tile, K split over the waves of a workgroup   */
     DYBIT_KERNEL_F16_FEW = 15,       /* fp16 MFMA, few-channel convolution, input decoded once          */
     DYBIT_KERNEL_F16_PATCH = 16,     /* fp16 MFMA, convolution of 64 and more channels, input decoded once */
-    DYBIT_KERNEL_F8_PATCH = 17       /* e4m3 MFMA, the same                                             */
+    DYBIT_KERNEL_F8_PATCH = 17,      /* e4m3 MFMA, the same                                             */
+    DYBIT_KERNEL_F6_256 = 18,        /* e3m2 MFMA on split operands, 256 x 256 tile                     */
+    DYBIT_KERNEL_F6_128 = 19         /* e3m2 MFMA on split operands, 128 x 128 tile                     */
 } dybit_kernel_id;
 int32_t dybit_last_gemm_kernel(void);
 dybit_status dybit_set_option(const char *name, const char *value);

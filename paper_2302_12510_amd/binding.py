@@ -91,6 +91,9 @@ def lib() -> C.CDLL:
         L.dybit_dequantize.argtypes = [vp, sz, Fmt, vp, vp, vp]
         L.dybit_quantize_absmax.argtypes = [vp, sz, Fmt, vp, vp, vp, vp]
         L.dybit_gemm.argtypes = [i64, i64, i64, vp, Fmt, vp, vp, Fmt, vp, vp, i32, vp, i64, vp]
+        L.dybit_gemm_work.argtypes = L.dybit_gemm.argtypes[:-1] + [vp, sz, vp]
+        L.dybit_gemm_workspace_bytes.argtypes = [i64, i64, i64, Fmt, Fmt]
+        L.dybit_gemm_workspace_bytes.restype = sz
         L.dybit_conv2d.argtypes = [i64] * 5 + [i32] * 4 + [vp, Fmt, vp, vp, Fmt, vp, vp, i32, vp, vp]
         L.dybit_gemm_ex.argtypes = [i64, i64, i64, vp, Fmt, vp, vp, Fmt, vp, vp, vp, i32, vp, i64, vp, vp]
         L.dybit_conv2d_ex.argtypes = [i64] * 5 + [i32] * 4 + [vp, Fmt, vp, vp, Fmt, vp, vp, vp, i32, vp, vp, vp]
@@ -155,7 +158,7 @@ def _ptr(t) -> int | None:
 # ---- host-only --------------------------------------------------------------
 KERNEL_NAMES = ("none", "general", "f16_256", "f16_128_kg1", "f16_128_kg2", "f16_128_rows", "f16_ws",
                 "f8_256", "f8_128_kg1", "f8_128_kg2", "f8_64", "f8_ws", "f16_small",
-                "f16_group", "f8_small", "f16_few", "f16_patch", "f8_patch")
+                "f16_group", "f8_small", "f16_few", "f16_patch", "f8_patch", "f6_256", "f6_128")
 
 
 def dybit_last_gemm_kernel() -> str:
@@ -290,7 +293,8 @@ def dybit_dequantize(codes: torch.Tensor, n: int, scale: torch.Tensor, bits: int
 
 def dybit_gemm(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fmt, w_scale,
                bias=None, relu: bool = False, out: torch.Tensor | None = None, ldc: int | None = None, stream=None):
-    """C [M][N] float32 = sA sW A W^T (+bias)(ReLU); a_fmt / w_fmt are (bits, signed) pairs."""
+    """C [M][N] float32 = sA sW A W^T (+bias)(ReLU); a_fmt / w_fmt are (bits, signed) pairs.  On the current stream
+    (stream None) the native module gives a large product a workspace (dybit_gemm_work)."""
     if out is None:
         out = _n().empty(a_scale, True, M, N)
     if ldc is None:

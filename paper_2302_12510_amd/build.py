@@ -21,6 +21,7 @@ SOURCES = [
     ("search.cpp", "search", []),
     ("gemm.hip", "gemm", []),
     ("gemm_dispatch.cpp", "gemm_dispatch", []),
+    ("gemm_six.hip", "gemm_six", []),
     ("gemm_fast.hip", "gemm_fast_w4", ["-DDYBIT_FAST_W=0"]),
     ("gemm_fast.hip", "gemm_fast_w8", ["-DDYBIT_FAST_W=2"]),
     ("gemm_fast.hip", "gemm_fast_w6", ["-DDYBIT_FAST_W=4"]),

@@ -109,16 +109,17 @@ template <class T> T argument(PyObject *o)
 
 template <auto F> struct Entry;
 template <class... A, dybit_status (*F)(A...)> struct Entry<F> {
-    template <size_t... I>
-    static dybit_status run(PyObject *const *args, std::index_sequence<I...>)
+    template <class G, size_t... I>
+    static dybit_status run(G g, PyObject *const *args, std::index_sequence<I...>)
     {
         const std::tuple<A...> a{argument<A>(args[I])...};               // braces: left to right
         dybit_status st;
         Py_BEGIN_ALLOW_THREADS
-        st = std::apply(F, a);
+        st = std::apply(g, a);
         Py_END_ALLOW_THREADS
         return st;
     }
+    template <class G> static dybit_status with(G g, PyObject *const *args) { return run(g, args, std::index_sequence_for<A...>{}); }
     static PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n)
     {
         HANDLE_TH_ERRORS
@@ -127,13 +128,38 @@ template <class... A, dybit_status (*F)(A...)> struct Entry<F> {
             return nullptr;
         }
         try {
-            return PyLong_FromLong((long)run(args, std::index_sequence_for<A...>{}));
+            return PyLong_FromLong((long)with(F, args));
         } catch (const PythonError &) {
             return nullptr;
         }
         END_HANDLE_TH_ERRORS
     }
 };
+
+// dybit_gemm: on the current stream, whose allocator the workspace comes from, a product that uses one gets it (dybit_gemm_work).
+template <size_t... I>
+dybit_status gemm_with_workspace(PyObject *const *args, const at::Tensor &work, std::index_sequence<I...>)
+{
+    return Entry<&dybit_gemm>::with([&](auto... a) {
+        const std::tuple<decltype(a)...> t{a...};
+        return dybit_gemm_work(std::get<I>(t)..., (uint8_t *)work.data_ptr(), (size_t)work.numel(), std::get<sizeof...(I)>(t));
+    }, args);
+}
+PyObject *gemm(PyObject *self, PyObject *const *args, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 14 || args[13] != Py_None || !is_plain_tensor(args[11])) return Entry<&dybit_gemm>::call(self, args, n);
+    try {
+        const size_t need = dybit_gemm_workspace_bytes(integer(args[0]), integer(args[1]), integer(args[2]), format(args[4]), format(args[7]));
+        const at::Tensor &out = THPVariable_Unpack(args[11]);
+        if (!need || !out.is_cuda()) return Entry<&dybit_gemm>::call(self, args, n);
+        const at::Tensor work = at::empty({(int64_t)need}, at::TensorOptions().device(out.device()).dtype(at::kByte));
+        return PyLong_FromLong((long)gemm_with_workspace(args, work, std::make_index_sequence<13>{}));
+    } catch (const PythonError &) {
+        return nullptr;
+    }
+    END_HANDLE_TH_ERRORS
+}
 
 // empty(like, floats, *sizes): an uninitialised tensor of float32 (or, floats false, bytes) on the device of `like`.
 PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n)
@@ -170,7 +196,7 @@ PyMethodDef methods[] = {
     DYBIT_ENTRY(dybit_quantize), DYBIT_ENTRY(dybit_quantize_absmax), DYBIT_ENTRY(dybit_quantize_pad),
     DYBIT_ENTRY(dybit_quantize_rows), DYBIT_ENTRY(dybit_quantize_cols), DYBIT_ENTRY(dybit_dequantize),
     DYBIT_ENTRY(dybit_fake_quant), DYBIT_ENTRY(dybit_fake_quant_bwd), DYBIT_ENTRY(dybit_rmse),
-    DYBIT_ENTRY(dybit_gemm), DYBIT_ENTRY(dybit_gemm_ex), DYBIT_ENTRY(dybit_gemm_wb), DYBIT_ENTRY(dybit_gemm_wb_rc), DYBIT_ENTRY(dybit_gemm_pc),
+    {"dybit_gemm", (PyCFunction)(void (*)(void))gemm, METH_FASTCALL, nullptr}, DYBIT_ENTRY(dybit_gemm_ex), DYBIT_ENTRY(dybit_gemm_wb), DYBIT_ENTRY(dybit_gemm_wb_rc), DYBIT_ENTRY(dybit_gemm_pc),
     DYBIT_ENTRY(dybit_conv2d), DYBIT_ENTRY(dybit_conv2d_ex), DYBIT_ENTRY(dybit_conv2d_wb), DYBIT_ENTRY(dybit_conv2d_wb_rc), DYBIT_ENTRY(dybit_conv2d_pc),
     DYBIT_ENTRY(dybit_dwconv2d), DYBIT_ENTRY(dybit_dwconv2d_wb), DYBIT_ENTRY(dybit_group_conv2d), DYBIT_ENTRY(dybit_maxpool2d_codes),
     {"dybit_packed_bytes", (PyCFunction)(void (*)(void))packed_bytes, METH_FASTCALL, nullptr},

@@ -512,7 +512,7 @@ dybit_status check_codes_out(const Epilogue &e, int64_t N, int64_t ldc)
 dybit_status gemm_impl(int64_t M, int64_t N, int64_t K,
                        const uint8_t *A_codes, dybit_fmt a_fmt, const float *a_scale,
                        const uint8_t *W_codes, dybit_fmt w_fmt, const float *w_scale,
-                       const Epilogue &e, float *C, int64_t ldc, dybit_stream stream)
+                       const Epilogue &e, float *C, int64_t ldc, dybit_stream stream, uint8_t *workspace = nullptr, size_t workspace_bytes = 0)
 {
     clear_call_record();
     dybit_status st = check_fmt(a_fmt);
@@ -531,6 +531,13 @@ dybit_status gemm_impl(int64_t M, int64_t N, int64_t K,
     if ((st = set_epilogue(g, e, C, ldc)) != DYBIT_OK) return st;
     g.a_bytes = M * (K * a_fmt.bits / 8);
     g.w_bytes = N * (K * w_fmt.bits / 8);
+    if (workspace && ldc < (1 << 23) && aligned16(workspace) && aligned16(A_codes) && aligned16(W_codes)) {
+        const size_t need = dybit_gemm_workspace_bytes(M, N, K, a_fmt, w_fmt);
+        if (need && need <= workspace_bytes) {
+            launch_gemm_six(g, a_fmt.bits, w_fmt.bits, gemm_six_tile(M, N, K, a_fmt.bits, w_fmt.bits), workspace, (hipStream_t)stream);
+            return launch_status();
+        }
+    }
     if (launch_gemm_tiled(g, a_fmt.bits, w_fmt.bits, false, (hipStream_t)stream)) return launch_status();
     const int mode = (K % UNIT == 0) && aligned16(A_codes) && aligned16(W_codes) ? 1 : 0;   // VEC : ELEMS
     (g.q_out ? launch_gemm_general_wb : launch_gemm_general)(g, a_fmt.bits, w_fmt.bits, false, mode, (hipStream_t)stream);
@@ -606,6 +613,23 @@ extern "C" dybit_status dybit_gemm(int64_t M, int64_t N, int64_t K,
     Epilogue e;
     e.bias = bias; e.relu = relu;
     return gemm_impl(M, N, K, A_codes, a_fmt, a_scale, W_codes, w_fmt, w_scale, e, C, ldc, stream);
+}
+
+extern "C" size_t dybit_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, dybit_fmt a_fmt, dybit_fmt w_fmt)
+{
+    if (check_fmt(a_fmt) != DYBIT_OK || check_fmt(w_fmt) != DYBIT_OK || !gemm_six_tile(M, N, K, a_fmt.bits, w_fmt.bits)) return 0;
+    return (size_t)gemm_six_bytes(M, N, K, a_fmt.bits, a_fmt.is_signed, w_fmt.bits, w_fmt.is_signed);
+}
+
+extern "C" dybit_status dybit_gemm_work(int64_t M, int64_t N, int64_t K,
+                                        const uint8_t *A_codes, dybit_fmt a_fmt, const float *a_scale,
+                                        const uint8_t *W_codes, dybit_fmt w_fmt, const float *w_scale,
+                                        const float *bias, int32_t relu,
+                                        float *C, int64_t ldc, uint8_t *workspace, size_t workspace_bytes, dybit_stream stream)
+{
+    Epilogue e;
+    e.bias = bias; e.relu = relu;
+    return gemm_impl(M, N, K, A_codes, a_fmt, a_scale, W_codes, w_fmt, w_scale, e, C, ldc, stream, workspace, workspace_bytes);
 }
 
 extern "C" dybit_status dybit_gemm_ex(int64_t M, int64_t N, int64_t K,

@@ -76,7 +76,7 @@ struct DispatchOptions {
     int mid_kgroups;   // 0 automatic, 1 or 2: k-groups of the 128 x 128 kernels
     int ws_off;        // 1: the weight-stationary kernel is left out of the automatic choice
 };
-enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5, DYBIT_FORCE_FEW = 6, DYBIT_FORCE_PATCH = 7 };
+enum { DYBIT_FORCE_GENERAL = 1, DYBIT_FORCE_MID = 2, DYBIT_FORCE_LARGE = 3, DYBIT_FORCE_WS = 4, DYBIT_FORCE_SMALL = 5, DYBIT_FORCE_FEW = 6, DYBIT_FORCE_PATCH = 7, DYBIT_FORCE_SIX = 8 };
 DispatchOptions dispatch_options();
 // Record of the kernel a launch function started, per host thread (dybit_last_gemm_kernel reads it),
 // and of a HIP error met on the way (hipFuncSetAttribute, ...), which the entry point then reports.
@@ -196,6 +196,12 @@ bool launch_gemm_f8_w0_wb(const GemmArgs &g, int a_bits, bool conv, bool large, 
 bool launch_gemm_f8_w6_wb(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 bool launch_gemm_f8_w0_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
 bool launch_gemm_f8_w6_co(const GemmArgs &g, int a_bits, bool conv, bool large, hipStream_t st);
+
+// Large products on split operands (gemm_six.hip).  Bytes of scratch (0: the kernel does not take the product), the tile it is faster
+// with than the other kernels (0: none; gemm_dispatch.cpp), and the launch (`scratch` holds so many bytes).
+int64_t gemm_six_bytes(int64_t M, int64_t N, int64_t K, int a_bits, int a_signed, int w_bits, int w_signed);
+int gemm_six_tile(int64_t M, int64_t N, int64_t K, int a_bits, int w_bits);
+void launch_gemm_six(const GemmArgs &g, int a_bits, int w_bits, int tile, uint8_t *scratch, hipStream_t st);
 
 // General kernel (gemm.hip): any format pair and shape.  mode: 0 operands fetched code by code;
 // 1 operands are 16-byte aligned and K (convolution: Cin) is a multiple of 16; 2 (convolution

@@ -34,7 +34,7 @@ bool apply_option(const char *name, const char *value)
         const int v = is_auto ? 0 : !strcmp(value, "general") ? DYBIT_FORCE_GENERAL : !strcmp(value, "mid") ? DYBIT_FORCE_MID
                     : !strcmp(value, "large") ? DYBIT_FORCE_LARGE : !strcmp(value, "ws") ? DYBIT_FORCE_WS
                     : !strcmp(value, "small") ? DYBIT_FORCE_SMALL : !strcmp(value, "few") ? DYBIT_FORCE_FEW
-                    : !strcmp(value, "patch") ? DYBIT_FORCE_PATCH : -1;
+                    : !strcmp(value, "patch") ? DYBIT_FORCE_PATCH : !strcmp(value, "six") ? DYBIT_FORCE_SIX : -1;
         if (v < 0) return false;
         opt_kernel = v;
     } else if (!strcmp(name, "gemm_mfma")) {
@@ -284,7 +284,7 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 #define DYBIT_BUILD_OF(name) (codes ? name##_co : wb ? name##_wb : name)
 
     const bool low_pair = (a_bits == 4 || a_bits == 2) && (w_bits == 4 || w_bits == 2);
-    const int force = few || opt.kernel == DYBIT_FORCE_PATCH ? 0 : opt.kernel;
+    const int force = few || opt.kernel == DYBIT_FORCE_PATCH || opt.kernel == DYBIT_FORCE_SIX ? 0 : opt.kernel;
     if (force == DYBIT_FORCE_GENERAL) return false;
     const bool f8 = low_pair && !opt.mfma_f16;
 
@@ -355,6 +355,40 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
     if (w_bits == 2) return DYBIT_BUILD_OF(launch_gemm_mid_w6)(g, a_bits, conv, st);
     return DYBIT_BUILD_OF(launch_gemm_mid_w2)(g, a_bits, conv, st);
 #undef DYBIT_BUILD_OF
+}
+
+// The tile with which the product on split operands (gemm_six.hip) is faster than the kernel that launch_gemm_tiled would take, or 0.
+// That kernel's matrix time is half of fp16's (two planes: an operand of 6 or 8 bits) or of e4m3's (one), and rows that start at any byte cost
+// it only a slower split; but the operands go through memory once more, and its tiles have the longer fill.  Measured over 9000 products
+// (M, N from 96 and K from 200 to 9000, all formats it takes; us, the kernel before -> this one, the split included); of the 2078 taken, 0.63 times
+// the time in the geometric mean, 12 more than the same, at most 1.05 times:
+//   more than 256 tiles of 128 x 128: two planes with K from 1024 on (8192^3, 8- by 4-bit 830 -> 500; 5203 x 3732 x 1144 68.1 -> 51.5, but
+//     5351 x 2368 x 320 20.3 -> 22.3); one plane where the e4m3 kernels have their 256 x 256 tile or K from 3072 on (8192^3, 4-bit
+//     pair 404 -> 273; 4657 x 4891 x 3968 139 -> 76, but 2196 x 2672 x 960 14.2 -> 16.5); one plane and ragged rows, which have no e4m3 form
+//     there, with K from 512 on (2368 x 6144 x 1740, 2-bit pair 70.4 -> 33.7);
+//   from there down to the line of the small-output kernel: one plane and ragged rows, K from 1536 on (3281 x 800 x 3004, 4-bit pair 0.5 to 0.9
+//     times); two planes, K from 2560 and both sides from 768 on (1874 x 1024 x 8584 75.5 -> 59.2; with one short side the split is most of
+//     the work: 7473 x 226 x 8768 68.4 -> 77.7), with a 6-bit operand, whose decoding costs the fp16 kernels most, K from 2048 on or one
+//     short side and K from 3072 on (5442 x 193 x 6592 59.9 -> 53.0).
+// The 256 x 256 tile where its rounds over the compute units are at most 0.35 times those of 128 x 128: of the faster one of both 1.004 times
+// on average, at most 1.26.
+int gemm_six_tile(int64_t M, int64_t N, int64_t K, int a_bits, int w_bits)
+{
+    const DispatchOptions opt = dispatch_options();
+    if (opt.kernel == DYBIT_FORCE_SIX) return opt.mid_tile == 128 ? 128 : 256;
+    if (opt.kernel || opt.mfma_f16 || opt.mid_tile || opt.mid_kgroups || opt.ws_off) return 0;
+    if (M < 1 || N < 1 || K < 512 || M > 1 << 24 || N > 1 << 24 || (M >= 16384 && N <= 128)) return 0;
+    GemmArgs g{};
+    g.M = M; g.N = N; g.K = K;
+    const bool one = a_bits <= 4 && w_bits <= 4, ragged = K % 64 != 0, six = a_bits == 6 || w_bits == 6;
+    if (small_output(g, ragged, one)) return 0;
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles256 = ((M + 255) / 256) * ((N + 255) / 256), shorter = M < N ? M : N;
+    bool pays;
+    if (tiles128 > 256) pays = one ? ragged || K >= 3072 || (K >= 2048 && N > 128 && tiles256 >= 128) : K >= 1024;
+    else if (one) pays = ragged && K >= 1536;
+    else pays = shorter >= 768 ? K >= (six ? 2048 : 2560) : six && K >= 3072;
+    if (!pays) return 0;
+    return 20 * ((tiles256 + 255) / 256) <= 7 * ((tiles128 + 255) / 256) ? 256 : 128;
 }
 
 // Whether a launch per group beats the one-launch kernel.  For a pair of 4- and 2-bit formats in groups of whole 64-channel k groups
