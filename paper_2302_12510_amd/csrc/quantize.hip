@@ -16,12 +16,14 @@ __device__ int g_async_error = 0;
 constexpr int kThreads = 256;
 // Tuning knobs of the quantize pass (swept on the device, from 2^20 to 2^28 elements: four 128-bit loads
 // in flight per lane and a grid that is not capped below about 128 workgroups per compute unit run
-// closest to the HBM rate -- 2 to 9 % faster than eight loads; tensors of under 2^23 elements (most
-// activation tensors of the networks) have too few workgroups then and take two loads per lane).
+// closest to the HBM rate -- 2 to 9 % faster than eight loads).  Tensors of under 2^23 elements (most
+// activation tensors of the networks) have too few workgroups then: they take one load per lane, and two with the least arithmetic
+// (us, cold caches, two loads requested after the scale had come -> one requested before it: 2^18 floats to 4 bits 4.9 -> 4.7, 2^21 7.1 -> 5.7,
+// 3.2 M to 8 bits 8.3 -> 6.8, 8.4 M 12.8 -> 11.5; 2 bits, 8.4 M in warm ones: one load 8.2, two 7.0).
 #ifndef DYBIT_QUANT_UNROLL
 #define DYBIT_QUANT_UNROLL 4
 #endif
-#define DYBIT_QUANT_UNROLL_SMALL 2
+constexpr int quant_unroll_small(int bits) { return bits == 2 ? 2 : 1; }
 // Fake-quant up to this size takes one load per lane: more workgroups.  Kernel times in a graph, four loads -> one (us): 2^14 floats
 // at 8 bits 5.0 -> 2.4, 2^20 9.4 -> 5.2, 2^22 9.2 -> 8.2, at 4 bits 7.8 -> 6.9, but 6.3 M at 4 bits 8.6 -> 9.6.  The 2-bit form, which
 // computes least, turns earlier: 2.4 M 4.9 -> 4.3, 3.1 M 4.9 -> 5.6.
@@ -325,6 +327,20 @@ __device__ __forceinline__ ScaleInfo load_scale(const float *scale, float inv_vm
     return si;
 }
 
+// A workgroup's chunk of UNROLL x kThreads 128-bit words from `base` on; zeros past the end.
+template <int UNROLL>
+__device__ __forceinline__ void load_chunk(const f32x4 *__restrict__ x4, size_t n4, size_t base, f32x4 (&v)[UNROLL])
+{
+    const size_t i = base + threadIdx.x;
+    if (base + (size_t)kThreads * UNROLL <= n4) {                       // uniform: a whole chunk
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kThreads);
+    } else {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) v[u] = (i + u * kThreads < n4) ? __builtin_nontemporal_load(x4 + i + u * kThreads) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
 // 4 consecutive elements per lane per load (coalesced float4), UNROLL loads in flight; a workgroup works
 // on contiguous chunks of UNROLL x kThreads loads.  Whole chunks run without bounds checks.
 // Output per load: 4*BITS bits, stored as one 8/16/32-bit word.  BITS in {2, 4, 8}.
@@ -335,12 +351,15 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
 {
     using word_t = typename std::conditional<BITS == 8, uint32_t,
                    typename std::conditional<BITS == 4, uint16_t, uint8_t>::type>::type;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    f32x4 v[UNROLL];
+    size_t base = (size_t)blockIdx.x * kThreads * UNROLL;
+    load_chunk(x4, n4, base, v);                                         // on its way while the scale is
     const ScaleInfo si = load_scale(scale, inv_vmax, scale_out);
     if (!si.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
         return;
     }
-    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     word_t *o = reinterpret_cast<word_t *>(out);
     auto encode = [&](const f32x4 v) -> uint32_t {
         const float e[4] = {v.x, v.y, v.z, v.w};
@@ -354,24 +373,20 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
         return w;
     };
     constexpr size_t per_block = (size_t)kThreads * UNROLL;
-    for (size_t base = (size_t)blockIdx.x * per_block; base < n4; base += (size_t)gridDim.x * per_block) {
+    while (base < n4) {
         const size_t i = base + threadIdx.x;
-        f32x4 v[UNROLL];
         if (base + per_block <= n4) {                                  // uniform: a whole chunk
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kThreads);
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) __builtin_nontemporal_store((word_t)encode(v[u]), o + i + u * kThreads);
         } else {
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                v[u] = (i + u * kThreads < n4) ? __builtin_nontemporal_load(x4 + i + u * kThreads) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
                 const uint32_t w = encode(v[u]);
                 if (i + u * kThreads < n4) __builtin_nontemporal_store((word_t)w, o + i + u * kThreads);
             }
         }
+        base += (size_t)gridDim.x * per_block;
+        if (base < n4) load_chunk(x4, n4, base, v);                    // uniform
     }
 }
 
@@ -384,22 +399,18 @@ __global__ __launch_bounds__(kThreads) void quantize6_kernel(const float *__rest
                                                              const float *__restrict__ scale,
                                                              uint8_t *__restrict__ out, float inv_vmax, float *scale_out, int *err)
 {
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    f32x4 v[UNROLL];
+    size_t base = (size_t)blockIdx.x * kThreads * UNROLL;
+    load_chunk(x4, n4, base, v);                                         // as above
     const ScaleInfo si = load_scale(scale, inv_vmax, scale_out);
     if (!si.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
         return;
     }
-    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     uint32_t *o = reinterpret_cast<uint32_t *>(out);
     const int k = threadIdx.x & 3;
-    const size_t per_block = (size_t)kThreads * UNROLL;
-    for (size_t base = (size_t)blockIdx.x * per_block; base < n4; base += (size_t)gridDim.x * per_block) {
-        f32x4 v[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const size_t i = base + (size_t)u * kThreads + threadIdx.x;
-            v[u] = (i < n4) ? __builtin_nontemporal_load(x4 + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    while (base < n4) {
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const size_t i = base + (size_t)u * kThreads + threadIdx.x;
@@ -415,6 +426,8 @@ __global__ __launch_bounds__(kThreads) void quantize6_kernel(const float *__rest
             const uint32_t w = (own >> (8 * k)) | (right << (24 - 8 * k));
             if (k < 3 && i < n4) __builtin_nontemporal_store(w, o + (i >> 2) * 3 + k);
         }
+        base += (size_t)gridDim.x * kThreads * UNROLL;
+        if (base < n4) load_chunk(x4, n4, base, v);                      // uniform
     }
 }
 
@@ -431,22 +444,19 @@ template <int BITS, bool SIGNED, int UNROLL>
 __global__ __launch_bounds__(kThreads) void fake_quant_kernel(const float *__restrict__ x, size_t n,
                                                               const float *__restrict__ scale, float *__restrict__ y, int *err)
 {
+    const size_t n4 = n >> 2;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    f32x4 v[UNROLL];
+    const size_t per_block = (size_t)kThreads * UNROLL;
+    size_t base = (size_t)blockIdx.x * per_block;
+    load_chunk(x4, n4, base, v);                                         // on its way while the scale is
     const ScaleInfo si = load_scale(scale);
     if (!si.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
         return;
     }
-    const size_t n4 = n >> 2;
-    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     f32x4 *y4 = reinterpret_cast<f32x4 *>(y);
-    const size_t per_block = (size_t)kThreads * UNROLL;
-    for (size_t base = (size_t)blockIdx.x * per_block; base < n4; base += (size_t)gridDim.x * per_block) {
-        f32x4 v[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const size_t i = base + (size_t)u * kThreads + threadIdx.x;
-            v[u] = (i < n4) ? __builtin_nontemporal_load(x4 + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    while (base < n4) {
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const size_t i = base + (size_t)u * kThreads + threadIdx.x;
@@ -467,6 +477,8 @@ __global__ __launch_bounds__(kThreads) void fake_quant_kernel(const float *__res
                                code_to_value<BITS, SIGNED>(c[2], si.s), code_to_value<BITS, SIGNED>(c[3], si.s)};
             if (i < n4) __builtin_nontemporal_store(out, y4 + i);
         }
+        base += (size_t)gridDim.x * per_block;
+        if (base < n4) load_chunk(x4, n4, base, v);                      // uniform
     }
     if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {                      // remainder: exact path
         const size_t j = (n4 << 2) + threadIdx.x;
@@ -621,6 +633,12 @@ template <int BITS, bool SIGNED>
 __global__ __launch_bounds__(kThreads) void quantize_pad3_kernel(const float *__restrict__ x, int64_t rows, const float *__restrict__ scale,
                                                                  uint8_t *__restrict__ out, int *err)
 {
+    const int64_t r0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    f32x4 a{}, b{}, c{};
+    if (r0 + 4 <= rows) {                                              // on their way while the scale is
+        const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x + r0 * 3);
+        a = x4[0]; b = x4[1]; c = x4[2];
+    }
     const ScaleInfo si = load_scale(scale);
     if (!si.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
@@ -637,10 +655,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pad3_kernel(const float *__
         }
         return w;
     };
-    const int64_t r0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
     if (r0 + 4 <= rows) {
-        const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x + r0 * 3);
-        const f32x4 a = x4[0], b = x4[1], c = x4[2];
         const uint32_t w0 = encode(a.x, a.y, a.z), w1 = encode(a.w, b.x, b.y), w2 = encode(b.z, b.w, c.x), w3 = encode(c.y, c.z, c.w);
         uint32_t *o = reinterpret_cast<uint32_t *>(out + r0 * (BITS / 2));           // 4 rows are 2 BITS bytes
         if constexpr (BITS == 8) *reinterpret_cast<uint4 *>(o) = make_uint4(w0, w1, w2, w3);
@@ -662,6 +677,14 @@ __global__ __launch_bounds__(kThreads) void fake_quant_bwd_kernel(const float *_
                                                                   const float *__restrict__ scale, float vmax, int is_signed,
                                                                   float *__restrict__ out, int *err)
 {
+    const size_t n4 = n >> 2;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x), *g4 = reinterpret_cast<const f32x4 *>(grad);
+    f32x4 *o4 = reinterpret_cast<f32x4 *>(out);
+    constexpr size_t per_block = (size_t)kThreads * 2;
+    size_t base = (size_t)blockIdx.x * per_block;
+    f32x4 a[2], b[2];                                                  // four loads in flight, the first ones while the scale is on its way
+    load_chunk(x4, n4, base, a);
+    load_chunk(g4, n4, base, b);
     const float s = *scale;
     if (!(s > 0.0f) || ((__float_as_uint(s) >> 23) & 0xffu) == 255u) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
@@ -669,26 +692,25 @@ __global__ __launch_bounds__(kThreads) void fake_quant_bwd_kernel(const float *_
     }
     // s * 2^(m-1) is exact; should it overflow, every finite x is inside and +Inf is not
     const float hi = fminf(s * vmax, __uint_as_float(0x7f7fffffu)), lo = is_signed ? -hi : 0.0f;
-    const size_t n4 = n >> 2;
-    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x), *g4 = reinterpret_cast<const f32x4 *>(grad);
-    f32x4 *o4 = reinterpret_cast<f32x4 *>(out);
     auto mask = [&](f32x4 xv, f32x4 gv) {
         f32x4 r;
 #pragma unroll
         for (int k = 0; k < 4; ++k) r[k] = (xv[k] >= lo && xv[k] <= hi) ? gv[k] : 0.0f;
         return r;
     };
-    constexpr size_t per_block = (size_t)kThreads * 2;
-    for (size_t base = (size_t)blockIdx.x * per_block; base < n4; base += (size_t)gridDim.x * per_block) {
+    while (base < n4) {
         const size_t i = base + threadIdx.x;
-        if (base + per_block <= n4) {                                  // uniform: a whole chunk, four loads in flight
-            const f32x4 a0 = __builtin_nontemporal_load(x4 + i), a1 = __builtin_nontemporal_load(x4 + i + kThreads);
-            const f32x4 b0 = __builtin_nontemporal_load(g4 + i), b1 = __builtin_nontemporal_load(g4 + i + kThreads);
-            __builtin_nontemporal_store(mask(a0, b0), o4 + i);
-            __builtin_nontemporal_store(mask(a1, b1), o4 + i + kThreads);
+        if (base + per_block <= n4) {                                  // uniform: a whole chunk
+            __builtin_nontemporal_store(mask(a[0], b[0]), o4 + i);
+            __builtin_nontemporal_store(mask(a[1], b[1]), o4 + i + kThreads);
         } else {
             for (int u = 0; u < 2; ++u)
-                if (i + u * kThreads < n4) o4[i + u * kThreads] = mask(x4[i + u * kThreads], g4[i + u * kThreads]);
+                if (i + u * kThreads < n4) o4[i + u * kThreads] = mask(a[u], b[u]);
+        }
+        base += (size_t)gridDim.x * per_block;
+        if (base < n4) {                                               // uniform
+            load_chunk(x4, n4, base, a);
+            load_chunk(g4, n4, base, b);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {
@@ -798,7 +820,7 @@ template <int BITS, bool SIGNED>
 static void launch_quantize(const float *x, size_t n, const float *scale, uint8_t *out, hipStream_t st,
                             float inv_vmax = 0.0f, float *scale_out = nullptr)
 {
-    if (n / 4 < kQuantSmall) launch_quantize_u<BITS, SIGNED, DYBIT_QUANT_UNROLL_SMALL>(x, n, scale, out, st, inv_vmax, scale_out);
+    if (n / 4 < kQuantSmall) launch_quantize_u<BITS, SIGNED, quant_unroll_small(BITS)>(x, n, scale, out, st, inv_vmax, scale_out);
     else launch_quantize_u<BITS, SIGNED, DYBIT_QUANT_UNROLL>(x, n, scale, out, st, inv_vmax, scale_out);
 }
 
