@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "dybit_device.h"
@@ -110,21 +111,62 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
     }
 }
 
-// With a workspace: every workgroup leaves its maximum in a word of its own, and one workgroup makes the scale of
-// them -- two launches instead of three, nothing to clear and no atomics.  Kernel times in a graph, three launches -> these
-// two: 2^18 floats 6.2 -> 4.1 us, 2.4 M 13.3 -> 4.7, 2^24 21.0 -> 14.2, 2^26 43.4 -> 42.9.
+// With a workspace: one launch.  A workgroup leaves its maximum there, and the last one of the grid, dispatched behind all
+// others, waits for them and makes the scale.  Nobody has cleared the workspace and the result must not depend on what it holds, so
+// a maximum comes as two words, each with half of a 64-bit number that belongs to this launch, and counts when both
+// have come and agree; a word is stored and read as a whole, past the caches that are not shared.  The last workgroup clears what
+// it has read: a replayed graph, whose number is always the same, finds no words of its last replay.
+// A launch for the maxima and one that joined them -> this (us; calls, which the host's launches bound, and in a graph): 2^17 floats 8.1 -> 5.6 and
+// 4.0 -> 3.5, 2.4 M 8.0 -> 5.6 and 5.0 -> 3.9, 2^23 8.2 -> 5.6 and 6.4 -> 4.8, 2^26 42.1 -> 40.3, 2^28 155 both.  256 workgroups of 16 waves:
+// as many as wait for one another in one round, each with contiguous words, 64 KiB of loads in flight.  STREAM: see kStreamBytes.
+constexpr int kJoinThreads = 1024, kJoinBlocks = DYBIT_ABSMAX_WORKSPACE / 4;   // four floats a workgroup
 template <bool STREAM>
-__global__ __launch_bounds__(kThreads) void absmax_partial_kernel(const float *__restrict__ x, size_t n, float *__restrict__ partial)
+__global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float *__restrict__ x, size_t n, size_t span, float *scale_out, float inv_vmax,
+                                                                     uint64_t *words, uint32_t tag0, uint32_t tag1)
 {
-    const float mx = absmax_of_chunks<STREAM>(x, n);
-    if (threadIdx.x == 0) partial[blockIdx.x] = mx;
-}
-
-__global__ __launch_bounds__(kThreads) void absmax_join_kernel(const float *__restrict__ partial, int count, float *scale_out, float inv_vmax)
-{
+    const size_t n4 = n >> 2, first = (size_t)blockIdx.x * span, end = first + span < n4 ? first + span : n4;   // in 128-bit words
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     float mx = 0.0f;
-    for (int i = threadIdx.x; i < count; i += kThreads) mx = fmaxf(mx, partial[i]);
-    mx = workgroup_max<kThreads>(mx);
+    for (size_t base = first; base < end; base += 4 * kJoinThreads) {
+        f32x4 v[4];
+        const size_t i = base + threadIdx.x;
+        if (base + 4 * kJoinThreads <= end) {                              // uniform: a whole chunk
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = STREAM ? __builtin_nontemporal_load(x4 + i + u * kJoinThreads) : x4[i + u * kJoinThreads];
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = (i + u * kJoinThreads < end) ? x4[i + u * kJoinThreads] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+    }
+    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) mx = fmaxf(mx, fabsf(x[(n4 << 2) + threadIdx.x]));
+    mx = workgroup_max<kJoinThreads>(mx);
+    const unsigned others = gridDim.x - 1;
+    if (blockIdx.x < others) {
+        if (threadIdx.x == 0) {
+            const uint64_t value = __float_as_uint(mx);
+            __hip_atomic_store(words + 2 * blockIdx.x, value | (uint64_t)tag0 << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(words + 2 * blockIdx.x + 1, value | (uint64_t)tag1 << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
+    if (threadIdx.x >= kJoinBlocks) return;                                // whole waves: the barrier below is one of those left
+    if (threadIdx.x != 0) mx = 0.0f;
+    if (threadIdx.x < others) {
+        uint64_t a, b;
+        for (;;) {
+            a = __hip_atomic_load(words + 2 * threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            b = __hip_atomic_load(words + 2 * threadIdx.x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t)(a >> 32) == tag0 && (uint32_t)(b >> 32) == tag1 && (uint32_t)a == (uint32_t)b) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __hip_atomic_store(words + 2 * threadIdx.x, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(words + 2 * threadIdx.x + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mx = fmaxf(mx, __uint_as_float((uint32_t)a));
+    }
+    mx = workgroup_max<kJoinBlocks>(mx);
     if (threadIdx.x == 0) *scale_out = scale_of_max(mx, inv_vmax);
 }
 
@@ -840,13 +882,16 @@ static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *sc
         hipLaunchKernelGGL(absmax_small_kernel, dim3(1), dim3(kSmallThreads), 0, hs, x, (int)n, scale_out, inv_vmax);
         return launch_status();
     }
-    const int blocks = grid_for(n / 4 + 1, kThreads * 4, DYBIT_ABSMAX_WORKSPACE);
     const bool stream_past = n * sizeof(float) > kStreamBytes;
-    if (workspace) {
-        hipLaunchKernelGGL(stream_past ? absmax_partial_kernel<true> : absmax_partial_kernel<false>, dim3(blocks), dim3(kThreads), 0, hs,
-                           x, n, workspace);
-        hipLaunchKernelGGL(absmax_join_kernel, dim3(1), dim3(kThreads), 0, hs, workspace, blocks, scale_out, inv_vmax);
+    if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+        const size_t n4 = n / 4, span = ((n4 + kJoinBlocks - 1) / kJoinBlocks + kJoinThreads - 1) / kJoinThreads * kJoinThreads;
+        static std::atomic<uint64_t> launches{0};
+        uint64_t tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;   // odd factor: all different
+        tag ^= tag >> 32;                                                  // one to one: still all different, and 0 for none
+        hipLaunchKernelGGL(stream_past ? absmax_joined_kernel<true> : absmax_joined_kernel<false>, dim3((unsigned)((n4 + span - 1) / span)), dim3(kJoinThreads), 0, hs, x, n, span, scale_out, inv_vmax,
+                           reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32));
     } else {
+        const int blocks = grid_for(n / 4 + 1, kThreads * 4, 1024);
         hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, hs, scale_out);
         hipLaunchKernelGGL(stream_past ? absmax_kernel<true> : absmax_kernel<false>, dim3(blocks), dim3(kThreads), 0, hs, x, n, scale_out);
         hipLaunchKernelGGL(absmax_finish_kernel, dim3(1), dim3(1), 0, hs, scale_out, inv_vmax);

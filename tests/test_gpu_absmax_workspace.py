@@ -1,0 +1,75 @@
+"""Max-abs scale with a workspace: one launch whose last workgroup waits for the others.  Parity: bit-equal to the oracle's rule
+(an exact division of the maximum by a power of two), wherever the maximum lies and whatever the workspace holds."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dybit_ref as R
+from paper_2302_12510_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SMALL, CHUNK, ONE_EACH = 1 << 16, 4 * 1024, 256 * 4 * 1024       # floats: one-workgroup kernel, of 1024 lanes, a chunk for every workgroup
+
+
+def scale_of(x, work):
+    out = torch.empty(1, device="cuda")
+    assert B._n().dybit_absmax_scale_ws(x, x.numel(), (8, True), out, work, None) == B.OK
+    return out
+
+
+@pytest.mark.parametrize("n", [SMALL + 1, SMALL + CHUNK - 1, SMALL + CHUNK + 2, ONE_EACH - 1, ONE_EACH, ONE_EACH + 5, 4 * ONE_EACH + CHUNK + 3, (1 << 26) + 6])
+def test_wherever_the_maximum_lies(n):
+    x = torch.rand(n, device="cuda")
+    work = torch.full((1024,), float("nan"), device="cuda")
+    for at in (0, CHUNK - 1, CHUNK, n // 2, n - CHUNK, n - 4, n - 1):
+        old = x[at].item()
+        x[at] = -3.0 - at % 5
+        want = R.absmax_scale(np.float32([-3.0 - at % 5]), 8, True)
+        assert scale_of(x, work).item() == want                  # the workspace keeps what the last call left there
+        x[at] = old
+    x.fill_(float("nan"))
+    assert scale_of(x, work).item() == 1.0                         # nothing but NaN: as no values at all
+
+
+def test_workspace_of_any_content_and_alignment():
+    x = torch.rand(200003, device="cuda")
+    want = x.max().item() / 64
+    whole = torch.randint(-2 ** 31, 2 ** 31 - 1, (1032,), device="cuda", dtype=torch.int32).view(torch.float32)
+    for first in (0, 1, 2, 3):                                     # every word of it at 4-byte alignment
+        assert scale_of(x, whole[first:first + 1024]).item() == want
+
+
+def test_replays_see_their_own_values():
+    """A graph's launch always has the same number: values of an earlier replay must not count."""
+    x = torch.rand(3 * ONE_EACH, device="cuda")
+    out = torch.empty(1, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        B.dybit_absmax_scale(x, 8, True)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(3):
+                B.dybit_absmax_scale(x, 8, True, out=out)
+    for peak in (64.0, 8.0, 32.0, 2.0):                            # falling maxima: a stale word would win
+        x.clamp_(max=1.0)[7 * ONE_EACH // 4] = peak
+        graph.replay()
+        eager = B.dybit_absmax_scale(x, 8, True)
+        torch.cuda.synchronize()
+        assert out.item() == eager.item() == peak / 64
+
+
+def test_streams_side_by_side():
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    xs = [torch.rand(ONE_EACH + 4 * i, device="cuda") * (i + 1) for i in range(4)]
+    want = [x.max().item() / 64 for x in xs]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(20):
+        for s, x in zip(streams, xs):
+            with torch.cuda.stream(s):
+                got.append(B.dybit_absmax_scale(x, 8, True))
+    torch.cuda.synchronize()
+    assert [g.item() for g in got] == want * 20
