@@ -591,14 +591,17 @@ dybit_status conv2d_impl(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t C
         *launched = launch_group_conv(g, x_fmt.bits, w_fmt.bits, all_groups, (hipStream_t)stream);
         return *launched ? launch_status() : DYBIT_OK;
     }
-    if (launch_gemm_tiled(g, x_fmt.bits, w_fmt.bits, true, (hipStream_t)stream)) return launch_status();
+    // One tap per output on the output's own pixel: the image is the matrix A, and no kernel needs to find pixels (two divisions per
+    // row) or step through taps.
+    const bool conv = !(dense && kh == 1 && kw == 1 && stride == 1 && pad == 0);
+    if (launch_gemm_tiled(g, x_fmt.bits, w_fmt.bits, conv, (hipStream_t)stream)) return launch_status();
     // operand access of the general kernel: whole 16-channel vectors, runs of neighbouring taps
     // when there are few channels (the first layer of an image network), else code by code
     const bool aligned = aligned16(X_codes) && aligned16(Wt_codes);
     int mode = 0;
     if (aligned && Cin % UNIT == 0) mode = 1;
-    else if (aligned && dense && UNIT % Cin == 0 && ((int64_t)kw * Cin) % UNIT == 0 && g.a_bytes < 0x7fffffff && g.a_bytes % 4 == 0) mode = 2;
-    (g.q_out ? launch_gemm_general_wb : launch_gemm_general)(g, x_fmt.bits, w_fmt.bits, true, mode, (hipStream_t)stream);
+    else if (conv && aligned && dense && UNIT % Cin == 0 && ((int64_t)kw * Cin) % UNIT == 0 && g.a_bytes < 0x7fffffff && g.a_bytes % 4 == 0) mode = 2;
+    (g.q_out ? launch_gemm_general_wb : launch_gemm_general)(g, x_fmt.bits, w_fmt.bits, conv, mode, (hipStream_t)stream);
     return launch_status();
 }
 
