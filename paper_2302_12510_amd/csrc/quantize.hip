@@ -25,10 +25,10 @@ constexpr int kThreads = 256;
 #define DYBIT_QUANT_UNROLL 4
 #endif
 constexpr int quant_unroll_small(int bits) { return bits == 2 ? 2 : 1; }
-// Fake-quant up to this size takes one load per lane: more workgroups.  Kernel times in a graph, four loads -> one (us): 2^14 floats
-// at 8 bits 5.0 -> 2.4, 2^20 9.4 -> 5.2, 2^22 9.2 -> 8.2, at 4 bits 7.8 -> 6.9, but 6.3 M at 4 bits 8.6 -> 9.6.  The 2-bit form, which
-// computes least, turns earlier: 2.4 M 4.9 -> 4.3, 3.1 M 4.9 -> 5.6.
-constexpr size_t fake_quant_small(int bits) { return bits == 2 ? (size_t)5 << 19 : (size_t)1 << 22; }
+// Fake-quant up to this size takes one load per lane (the 2-bit form, which computes least, two): more workgroups.  Four loads requested after
+// the scale had come -> this, cold caches, in a graph (us): 4.3 M floats at 4 bits 10.8 -> 9.5, 6.3 M 13.1 -> 11.9, 8.3 M 16.3 -> 14.8; at
+// 2 bits 2.4 M 5.4 -> 4.6 (one load: 5.2), 8.3 M 13.1 -> 12.2.
+constexpr size_t kFakeQuantSmall = (size_t)1 << 23;
 constexpr size_t kQuantSmall = (size_t)1 << 21;     // in groups of four elements
 #ifndef DYBIT_QUANT_BLOCKS_PER_CU
 #define DYBIT_QUANT_BLOCKS_PER_CU 128
@@ -118,24 +118,33 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
 // it has read: a replayed graph, whose number is always the same, finds no words of its last replay.
 // A launch for the maxima and one that joined them -> this (us; calls, which the host's launches bound, and in a graph): 2^17 floats 8.1 -> 5.6 and
 // 4.0 -> 3.5, 2.4 M 8.0 -> 5.6 and 5.0 -> 3.9, 2^23 8.2 -> 5.6 and 6.4 -> 4.8, 2^26 42.1 -> 40.3, 2^28 155 both.  256 workgroups of 16 waves:
-// as many as wait for one another in one round, each with contiguous words, 64 KiB of loads in flight.  STREAM: see kStreamBytes.
+// as many as wait for one another in one round, 64 KiB of loads in flight.  STREAM: see kStreamBytes.
+// 1 << shift: the 16-byte words that a workgroup of the pass that quantizes x next takes at a time (quantize_kernel, fake_quant_kernel).  A
+// workgroup here takes the same ones and every gridDim-th piece after, so that with the grid a multiple of 8 both read a
+// piece on one XCD and the second pass finds it in that L2 (fake_quant_kernel after it, 14 M floats: 20.6 -> 18.1 us, 9 M 15.2 -> 13.1).
 constexpr int kJoinThreads = 1024, kJoinBlocks = DYBIT_ABSMAX_WORKSPACE / 4;   // four floats a workgroup
 template <bool STREAM>
-__global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float *__restrict__ x, size_t n, size_t span, float *scale_out, float inv_vmax,
+__global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float *__restrict__ x, size_t n, int shift, float *scale_out, float inv_vmax,
                                                                      uint64_t *words, uint32_t tag0, uint32_t tag1)
 {
-    const size_t n4 = n >> 2, first = (size_t)blockIdx.x * span, end = first + span < n4 ? first + span : n4;   // in 128-bit words
+    const size_t n4 = n >> 2;
     const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     float mx = 0.0f;
-    for (size_t base = first; base < end; base += 4 * kJoinThreads) {
+    const auto index = [&](size_t l) { return (((l >> shift) * gridDim.x + blockIdx.x) << shift) + (l & (((size_t)1 << shift) - 1)); };
+    for (size_t l = 0; l * gridDim.x < n4; l += 4 * kJoinThreads) {            // l: of the words of this workgroup; 4 * kJoinThreads is whole pieces
         f32x4 v[4];
-        const size_t i = base + threadIdx.x;
-        if (base + 4 * kJoinThreads <= end) {                              // uniform: a whole chunk
+        if ((l + 4 * kJoinThreads) * gridDim.x <= n4) {                        // uniform: no workgroup passes the end
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = STREAM ? __builtin_nontemporal_load(x4 + i + u * kJoinThreads) : x4[i + u * kJoinThreads];
+            for (int u = 0; u < 4; ++u) {
+                const f32x4 *p = x4 + index(l + u * kJoinThreads + threadIdx.x);
+                v[u] = STREAM ? __builtin_nontemporal_load(p) : *p;
+            }
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = (i + u * kJoinThreads < end) ? x4[i + u * kJoinThreads] : f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < 4; ++u) {
+                const size_t i = index(l + u * kJoinThreads + threadIdx.x);
+                v[u] = i < n4 ? x4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -488,15 +497,23 @@ __global__ __launch_bounds__(kThreads) void fake_quant_kernel(const float *__res
 {
     const size_t n4 = n >> 2;
     const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
-    f32x4 v[UNROLL];
     const size_t per_block = (size_t)kThreads * UNROLL;
     size_t base = (size_t)blockIdx.x * per_block;
-    load_chunk(x4, n4, base, v);                                         // on its way while the scale is
+    f32x4 v[UNROLL];
+    const auto load = [&] {                                              // bounds by the lane: load_chunk, 67 M floats at 4 bits, 94.7 -> 95.6 us
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const size_t i = base + (size_t)u * kThreads + threadIdx.x;
+            v[u] = (i < n4) ? __builtin_nontemporal_load(x4 + i) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    if constexpr (UNROLL < 4) load();                                    // on its way while the scale is; four loads gain nothing by it
     const ScaleInfo si = load_scale(scale);
     if (!si.ok) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *err = DYBIT_ERR_BAD_SCALE;
         return;
     }
+    if constexpr (UNROLL >= 4) load();
     f32x4 *y4 = reinterpret_cast<f32x4 *>(y);
     while (base < n4) {
 #pragma unroll
@@ -520,7 +537,7 @@ __global__ __launch_bounds__(kThreads) void fake_quant_kernel(const float *__res
             if (i < n4) __builtin_nontemporal_store(out, y4 + i);
         }
         base += (size_t)gridDim.x * per_block;
-        if (base < n4) load_chunk(x4, n4, base, v);                      // uniform
+        if (base < n4) load();                      // uniform
     }
     if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {                      // remainder: exact path
         const size_t j = (n4 << 2) + threadIdx.x;
@@ -884,11 +901,13 @@ static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *sc
     }
     const bool stream_past = n * sizeof(float) > kStreamBytes;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
-        const size_t n4 = n / 4, span = ((n4 + kJoinBlocks - 1) / kJoinBlocks + kJoinThreads - 1) / kJoinThreads * kJoinThreads;
+        const int u = n / 4 < kQuantSmall ? quant_unroll_small(f.bits) : DYBIT_QUANT_UNROLL, shift = u == 1 ? 8 : u == 2 ? 9 : 10;
+        const unsigned grid = (unsigned)(grid_for(n / 4, kJoinThreads, kJoinBlocks) + 7) & ~7u;
         static std::atomic<uint64_t> launches{0};
         uint64_t tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;   // odd factor: all different
         tag ^= tag >> 32;                                                  // one to one: still all different, and 0 for none
-        hipLaunchKernelGGL(stream_past ? absmax_joined_kernel<true> : absmax_joined_kernel<false>, dim3((unsigned)((n4 + span - 1) / span)), dim3(kJoinThreads), 0, hs, x, n, span, scale_out, inv_vmax,
+        hipLaunchKernelGGL(stream_past ? absmax_joined_kernel<true> : absmax_joined_kernel<false>, dim3(grid), dim3(kJoinThreads), 0, hs, x, n, shift,
+                           scale_out, inv_vmax,
                            reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32));
     } else {
         const int blocks = grid_for(n / 4 + 1, kThreads * 4, 1024);
@@ -1074,12 +1093,12 @@ extern "C" dybit_status dybit_fake_quant(const float *x, size_t n, dybit_fmt f, 
     if (!aligned16(x) || !aligned16(y_out)) return DYBIT_ERR_ALIGNMENT;
     if (n == 0) return DYBIT_OK;
     hipStream_t hs = (hipStream_t)stream;
-    const bool small = n <= fake_quant_small(f.bits);
-    const int grid = grid_for(n / 4 + 1, kThreads * (small ? 1 : 4), 256 * DYBIT_QUANT_BLOCKS_PER_CU);
+    const bool small = n <= kFakeQuantSmall;
+    const int grid = grid_for(n / 4 + 1, kThreads * (small ? quant_unroll_small(f.bits) : 4), 256 * DYBIT_QUANT_BLOCKS_PER_CU);
     int *err = async_error_word();
     if (!err) return DYBIT_ERR_HIP;
 #define DYBIT_FQ(B, S) \
-    if (small) hipLaunchKernelGGL((fake_quant_kernel<B, S, 1>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err); \
+    if (small) hipLaunchKernelGGL((fake_quant_kernel<B, S, quant_unroll_small(B)>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err); \
     else hipLaunchKernelGGL((fake_quant_kernel<B, S, 4>), dim3(grid), dim3(kThreads), 0, hs, x, n, scale, y_out, err)
     switch (f.bits * 2 + f.is_signed) {
         case 4: DYBIT_FQ(2, false); break;   case 5: DYBIT_FQ(2, true); break;
