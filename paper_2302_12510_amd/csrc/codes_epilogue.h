@@ -10,7 +10,9 @@
 // columns of one block, so that a row's codes leave as 128-bit words (4-bit codes: one store instruction per
 // 2048 results, against 32 byte stores) and a shortcut given as codes arrives the same way; and a row past M
 // is a lane that stores nothing, so the running maximum needs no selection per value.
-// Per result: 9 vector-ALU instructions for 4- and 6-bit codes, 11 for 8-bit ones (20 there), and 1/32 of a store (2 there).
+// Per result: 9 vector-ALU instructions for 4- and 6-bit codes, 11 for 8-bit ones (20 there), and 1/32 of a store (2 there); a
+// shortcut adds 6.  Maximum without a branch, shortcut product as one mixed-precision instruction, and three halves a minimum: 3 fewer per
+// result with a shortcut than before (last layer below 24.9 -> 23.6 with its K loop, 84.4 -> 83.0 us; block 169.9 -> 168.7).
 // What bounds the layers that use it is still vector-ALU issue: decode of A plus these.  The two instructions of difference are
 // the shift that tests a value for a decision point and the extraction of its code: with 16 fraction bits the first is a
 // minimum of half-words, the second is done by the byte permutes that pack (first layer below 57.0 -> 54.1 us with its encoder,
@@ -198,10 +200,11 @@ __device__ __forceinline__ ShortcutFormat shortcut_format(const GemmArgs &g)
     f.s = scalar_scale(g.res_scale);
     return f;
 }
+// One instruction (v_fma_mix_f32 takes the half as it is); adding zero rounds nothing, and only a product of -0 comes out as +0,
+// which neither a code nor the maximum shows.
 __device__ __forceinline__ float shortcut_product(_Float16 v, float s)
 {
-#pragma clang fp contract(off)
-    return (float)v * s;                             // rounded here, before it is added
+    return __builtin_fmaf((float)v, s, 0.0f);        // rounded here, before it is added
 }
 template <int RB>
 __device__ __forceinline__ void shortcut_values(uint32_t t, const ShortcutFormat &f, float (&r)[4])
@@ -219,6 +222,16 @@ __device__ __forceinline__ void shortcut_values(uint32_t t, const ShortcutFormat
     r[1] = shortcut_product(v1[0], f.s);
     r[2] = shortcut_product(v0[1], f.s);
     r[3] = shortcut_product(v1[1], f.s);
+}
+
+// The least of eight lower halves.
+__device__ __forceinline__ uint16_t lower_halves_min(const uint32_t (&z)[8])
+{
+    uint32_t a, b, c;                                // the compiler's own form pairs them up with permutes: eight instructions
+    asm("v_min3_u16 %0, %1, %2, %3" : "=v"(a) : "v"(z[0]), "v"(z[1]), "v"(z[2]));
+    asm("v_min3_u16 %0, %1, %2, %3" : "=v"(b) : "v"(z[3]), "v"(z[4]), "v"(z[5]));
+    asm("v_min3_u16 %0, %1, %2, %3" : "=v"(c) : "v"(a), "v"(z[6]), "v"(z[7]));
+    return min((uint16_t)b, (uint16_t)c);
 }
 
 // The strip of 32 rows by 32 CB columns a wave holds or, STACKED, of 32 CB rows by 32 columns (block j is then rows 32 j ..
@@ -243,7 +256,6 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
     if (!rqp.ok && m_strip == 0 && n0 == 0 && lane == 0) *g.async_error = DYBIT_ERR_BAD_SCALE;   // no codes, flag the call
     ShortcutFormat sf{};
     if (RB) sf = shortcut_format(g);
-    const bool track = g.absmax_bits != nullptr;
     uint32_t floor_bits = (uint32_t)__builtin_amdgcn_readfirstlane(g.relu ? 0 : 0x7fc00000);
     asm volatile("" : "+s"(floor_bits));                                // see store_strip_wb
     const float relu_floor = __uint_as_float(floor_bits);
@@ -282,6 +294,7 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
             const int j = 2 * jp + jb;
+            float block_max = 0.0f;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {                               // two quads at a time: fewer live registers
                 float c[8];
@@ -300,18 +313,14 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
                         c[4 * i + u] = fmaxf(v, relu_floor);
                     }
                 }
-                if (track && (!STACKED || 32 * j + row < rows)) {
-#pragma unroll
-                    for (int u = 0; u < 8; u += 2) mx = fmaxf(fmaxf(mx, fabsf(c[u])), fabsf(c[u + 1]));
-                }
+                float &top = STACKED ? block_max : mx;                  // kept whether asked for or not: behind a branch the magnitudes
+#pragma unroll                                                          // would be computed by themselves, two instructions against one
+                for (int u = 0; u < 8; u += 2) top = fmaxf(fmaxf(top, fabsf(c[u])), fabsf(c[u + 1]));
 #pragma unroll
                 for (int u = 0; u < 8; ++u) zb[u] = requant_lower<BITS>(c[u], rqp);
                 bool settle;                                            // whether some fraction reads zero
                 if constexpr (GB == 16) {
-                    uint16_t key = (uint16_t)zb[0];
-#pragma unroll
-                    for (int u = 1; u < 8; ++u) key = min(key, (uint16_t)zb[u]);
-                    settle = key == 0;
+                    settle = lower_halves_min(zb) == 0;
                 } else {
                     uint32_t key = 0xffffffffu;
 #pragma unroll
@@ -371,6 +380,7 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
                     out[jb][WORDS * h + i] = w[i];
                 }
             }
+            if (STACKED) mx = fmaxf(mx, 32 * j + row < rows ? block_max : 0.0f);
         }
         uint32_t words[BITS];
         if constexpr (BITS == 4) {                                      // out: two groups of four codes in a word
