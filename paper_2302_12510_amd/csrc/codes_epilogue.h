@@ -407,8 +407,8 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
     return STACKED || row < rows ? mx : 0.0f;
 }
 
-// Picks the variant for the call's formats.
-template <int CB, bool STACKED>
+// Picks the variant for the call's formats.  Q: bits of the codes in a kernel that was compiled for calls without a shortcut, 0: any.
+template <int CB, bool STACKED, int Q = 0>
 __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0, const int rows,
                                              const float *cols, const OutScale os, const int staged)
 {
@@ -416,6 +416,7 @@ __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x
     return g.q_bits == 4 ? store_strip_codes<CB, RB_, 4, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
          : g.q_bits == 8 ? store_strip_codes<CB, RB_, 8, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
                          : store_strip_codes<CB, RB_, 6, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged)
+    if constexpr (Q != 0) return store_strip_codes<CB, 0, Q, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged);
     if (!g.res_codes) { DYBIT_CODES_STRIP(0); }
     if (g.res_bits == 8) { DYBIT_CODES_STRIP(8); }
     if (g.res_bits == 4) { DYBIT_CODES_STRIP(4); }
@@ -424,7 +425,7 @@ __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x
 }
 
 // big: what stage_columns returned; acc is brought to scale here then.
-template <int CB, int ACC_EXP>
+template <int CB, int ACC_EXP, int Q = 0>
 __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0,
                                                       const float *cols, const bool big, const OutScale os)
 {
@@ -436,7 +437,7 @@ __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][v] = acc_value<ACC_EXP>(acc[j][v]);
     }
-    return strip_codes<CB, false>(g, acc, m_strip, n0, rows, cols, os, CB * 32);
+    return strip_codes<CB, false, Q>(g, acc, m_strip, n0, rows, cols, os, CB * 32);
 }
 
 }  // namespace dybit

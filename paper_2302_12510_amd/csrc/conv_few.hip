@@ -10,13 +10,15 @@
 //
 // What bounds it then: LDS reads (1.5 KiB per matrix instruction, 64 KiB per strip with the epilogue's factors) and the
 // epilogue's vector instructions, which the barriers around a unit keep from overlapping fully.  64 x 112 x 112 x 64 from
-// 224 x 224, 8-bit operands: codes out 74.4 -> 50.6 us, fp32 out 79.3 -> 65.6 us (weight-stationary kernel -> this one).
+// 224 x 224, 8-bit operands: codes out 74.4 -> 50.6 us (46.9 with a kernel per width of the codes), fp32 out 79.3 -> 65.6 us (weight-stationary kernel -> this one).
 //
 // Decoding is cheap only in whole runs: a thread takes 32 codes of an image row (a group of eight per thread spent 150
 // instructions on where it lies, and the kernel was no faster than decoding every tap), written at the padded column with
 // the codes in their natural order, so that runs can start at the image's edge and fragments at the padding's.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "codes_epilogue.h"
 #include "dybit_codec.h"
@@ -53,7 +55,7 @@ __device__ __forceinline__ u32x4 decode_eight_in_order(const u32x4 *raw, int q)
                  __builtin_amdgcn_perm(d[3], d[2], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u)};
 }
 
-template <int FMT_A, int FMT_W, int OUT>
+template <int FMT_A, int FMT_W, int OUT, int Q>
 __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs g, const FewArgs f)
 {
     using CA = Codec<FMT_A>;
@@ -159,25 +161,26 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
             const char *a = patch + y * g.stride * f.pitch + x * g.stride * g.Cin * 2 + kq * 16;
             const char *w = lds + rdW;
             f32x16 acc[CB];
-#pragma unroll
-            for (int j = 0; j < CB; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
-            for (int fr = 0; fr < g.kh; ++fr, a += f.pitch, w += 64) {
+            auto filter_row = [&](auto first) {                        // the first adds to a constant zero
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {                          // 16 codes of the filter row
                     const f16x8 fa = *reinterpret_cast<const f16x8 *>(a + h * 32);
 #pragma unroll
                     for (int j = 0; j < CB; ++j) {
                         const f16x8 fw = *reinterpret_cast<const f16x8 *>(w + h * 32 + j * 32 * f.row_bytes);
-                        acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw, fa, acc[j], 0, 0, 0)
-                                                  : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fw, acc[j], 0, 0, 0);
+                        const f32x16 c = decltype(first)::value && h == 0 ? f32x16{} : acc[j];
+                        acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw, fa, c, 0, 0, 0)
+                                                  : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fw, c, 0, 0, 0);
                     }
                 }
-            }
-            GemmArgs ge = OUT == OUT_CODES ? reload_args() : g;
+                a += f.pitch;
+                w += 64;
+            };
+            filter_row(std::true_type{});
+            for (int fr = 1; fr < g.kh; ++fr) filter_row(std::false_type{});
+            GemmArgs ge = OUT == OUT_CODES && Q == 0 ? reload_args() : g;
             ge.M = m_unit + outputs;                                   // the epilogue stores no row past the unit
-            if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, ACC>(ge, acc, m_unit + s, n0, cols, big, os));
+            if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, ACC, Q>(ge, acc, m_unit + s, n0, cols, big, os));
             else run_max = fmaxf(run_max, epilogue_strip<CB, false, false, ACC>(ge, acc, m_unit + s, n0));
         }
     }
@@ -251,7 +254,11 @@ static bool launch(const GemmArgs &g, hipStream_t st)
     int walkers = resident / f.parts;
     if (walkers < 1) walkers = 1;
     if (walkers > f.units) walkers = f.units;
-    auto k = conv_few_kernel<FA, FW, kOut>;
+    // codes without a shortcut: a kernel per width of the codes.  The one with all forms computes the uniform values of each of them
+    // and keeps them in vector registers: 64 x 224 x 224 at 8 bits to 4-bit codes 31.1 -> 27.4 us
+    auto k = conv_few_kernel<FA, FW, kOut, 0>;
+    if constexpr (kOut == OUT_CODES)
+        if (!g.res_codes) k = g.q_bits == 4 ? conv_few_kernel<FA, FW, kOut, 4> : g.q_bits == 8 ? conv_few_kernel<FA, FW, kOut, 8> : conv_few_kernel<FA, FW, kOut, 6>;
     note_kernel(DYBIT_KERNEL_F16_FEW);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)(walkers * f.parts)), dim3(64 * waves), lds_bytes, st, g, f);
