@@ -25,6 +25,8 @@
 #ifndef DYBIT_CODES_EPILOGUE_H
 #define DYBIT_CODES_EPILOGUE_H
 
+#include <type_traits>
+
 #include "../../include/dybit.h"
 #include "dybit_codec.h"
 #include "gemm_args.h"
@@ -407,8 +409,9 @@ __device__ __forceinline__ float store_strip_codes(const GemmArgs &g, const fast
     return STACKED || row < rows ? mx : 0.0f;
 }
 
-// Picks the variant for the call's formats.  Q: bits of the codes in a kernel that was compiled for calls without a shortcut, 0: any.
-template <int CB, bool STACKED, int Q = 0>
+// Picks the variant for the call's formats.  Q and R: bits of the codes and of the shortcut's codes (0: none) in a kernel that was
+// compiled for them; Q = 0: any.
+template <int CB, bool STACKED, int Q = 0, int R = 0>
 __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0, const int rows,
                                              const float *cols, const OutScale os, const int staged)
 {
@@ -416,7 +419,7 @@ __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x
     return g.q_bits == 4 ? store_strip_codes<CB, RB_, 4, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
          : g.q_bits == 8 ? store_strip_codes<CB, RB_, 8, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged) \
                          : store_strip_codes<CB, RB_, 6, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged)
-    if constexpr (Q != 0) return store_strip_codes<CB, 0, Q, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged);
+    if constexpr (Q != 0) return store_strip_codes<CB, R, Q, STACKED>(g, acc, m_strip, n0, rows, cols, os, staged);
     if (!g.res_codes) { DYBIT_CODES_STRIP(0); }
     if (g.res_bits == 8) { DYBIT_CODES_STRIP(8); }
     if (g.res_bits == 4) { DYBIT_CODES_STRIP(4); }
@@ -424,8 +427,18 @@ __device__ __forceinline__ float strip_codes(const GemmArgs &g, const fast::f32x
 #undef DYBIT_CODES_STRIP
 }
 
+// The kernel for a call's formats: what f(Q, R) returns, with strip_codes' Q and R as constants.
+template <int V> using Bits = std::integral_constant<int, V>;
+template <typename F> inline auto kernel_for_codes(const GemmArgs &g, F f)
+{
+    auto with_shortcut = [&](auto q) {
+        return !g.res_codes ? f(q, Bits<0>{}) : g.res_bits == 8 ? f(q, Bits<8>{}) : g.res_bits == 4 ? f(q, Bits<4>{}) : f(q, Bits<6>{});
+    };
+    return g.q_bits == 4 ? with_shortcut(Bits<4>{}) : g.q_bits == 8 ? with_shortcut(Bits<8>{}) : with_shortcut(Bits<6>{});
+}
+
 // big: what stage_columns returned; acc is brought to scale here then.
-template <int CB, int ACC_EXP, int Q = 0>
+template <int CB, int ACC_EXP, int Q = 0, int R = 0>
 __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f32x16 (&acc)[CB], const int64_t m_strip, const int64_t n0,
                                                       const float *cols, const bool big, const OutScale os)
 {
@@ -437,7 +450,7 @@ __device__ __forceinline__ float epilogue_strip_codes(const GemmArgs &g, fast::f
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][v] = acc_value<ACC_EXP>(acc[j][v]);
     }
-    return strip_codes<CB, false, Q>(g, acc, m_strip, n0, rows, cols, os, CB * 32);
+    return strip_codes<CB, false, Q, R>(g, acc, m_strip, n0, rows, cols, os, CB * 32);
 }
 
 }  // namespace dybit

@@ -218,7 +218,7 @@ __device__ __forceinline__ float store_rows(const Rows &o, const f32x16 (&acc)[R
 }
 
 // Codes of 64 rows x 32 columns (two blocks, one above the other).
-template <int ACC>
+template <int ACC, int Q, int R>
 __device__ __forceinline__ float codes_of_pair(const GemmArgs &g, f32x16 (&acc)[2], const int64_t m_first, const int64_t n0,
                                                const float *cols, const bool big, const OutScale os)
 {
@@ -230,10 +230,10 @@ __device__ __forceinline__ float codes_of_pair(const GemmArgs &g, f32x16 (&acc)[
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][v] = acc_value<ACC>(acc[j][v]);
     }
-    return strip_codes<2, true>(g, acc, m_first, n0, rows, cols, os, kMaxCols);
+    return strip_codes<2, true, Q, R>(g, acc, m_first, n0, rows, cols, os, kMaxCols);
 }
 
-template <int FMT_W, bool F8, int OUT>
+template <int FMT_W, bool F8, int OUT, int Q, int R>
 __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, const PatchArgs p)
 {
     constexpr int PB = F8 ? 1 : 2;                       // LDS bytes per code
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(512, 3) void conv_patch_kernel(const GemmArgs g, co
             f32x16 pair[2] = {acc[0], acc[1]};
 #pragma unroll 1
             for (int b = 0; b < blocks; b += 2) {
-                mx = fmaxf(mx, codes_of_pair<ACC>(reload_args(), pair, m_first + 32 * b, n0, cols + cwi * 32, big, os));
+                mx = fmaxf(mx, codes_of_pair<ACC, Q, R>(g, pair, m_first + 32 * b, n0, cols + cwi * 32, big, os));
                 pair[0] = acc[2];
                 pair[1] = acc[3];
             }
@@ -608,7 +608,10 @@ static bool launch(const GemmArgs &g, int a_fmt, hipStream_t st)
     p.second_block = p.second_step % per_tap;
     p.second_fr = p.second_tap / g.kw;
     p.second_fs = p.second_tap % g.kw;
-    auto k = conv_patch_kernel<FMT_W, F8, kOut>;
+    auto k = [&] {
+        if constexpr (kOut == OUT_CODES) return kernel_for_codes(g, [](auto q, auto r) { return conv_patch_kernel<FMT_W, F8, kOut, q(), r()>; });
+        else return conv_patch_kernel<FMT_W, F8, kOut, 0, 0>;
+    }();
     note_kernel(F8 ? DYBIT_KERNEL_F8_PATCH : DYBIT_KERNEL_F16_PATCH);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
     hipLaunchKernelGGL(k, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * waves), sp.lds_bytes, st, g, p);
