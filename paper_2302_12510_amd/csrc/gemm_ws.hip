@@ -98,7 +98,7 @@ inline int grid_for_groups(int slabs, int groups, int resident)
 // workgroups share a compute unit (four waves per SIMD) when their weight tiles both fit its LDS.
 constexpr int ROWS = 2;
 
-template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
+template <int FMT_A, int FMT_W, int CONV, int CB, int OUT, int Q, int R>
 __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
     const int THREADS = OUT == OUT_CODES ? (int)blockDim.x : 64 * waves_of<CB, OUT>(), SLAB = THREADS / 2;
@@ -116,6 +116,113 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
 
     // ROWS reads aligned words; the dispatcher takes it only for tensors of a whole number of words
     const __amdgpu_buffer_rsrc_t rsrcA = code_descriptor(g.A, g.a_bytes), rsrcW = code_descriptor(g.W, g.w_bytes);
+
+    const int a_row_bytes = (int)(g.K * CA::BITS / 8);
+    const int pix_bytes = CONV ? g.pix_bytes : 0;
+    const u32 rdW = (u32)(lane & 31) * (u32)row_bytes + (u32)kq * 64;   // K step adds 128 B, block kk 16 B, column block j 32 rows
+
+    // ---- A: the lane's own row of a slab, the 32 codes kq of every K step
+    u32 offA = kOob;
+    int hi0 = 0, wi0 = 0;
+    bool okA = false;
+    u32 row_keep[CONV == ROWS ? WORDS_A : 1];                        // ROWS: bits of a run that belong to taps inside the image
+    // position of the next K step to load: first k, and for a convolution its filter row, filter
+    // column and first channel (uniform over the wave), counted up from step to step
+    int a_k0 = 0;
+    TapCounter tap;
+    auto locate = [&](int slab) {
+        const int64_t m = (int64_t)slab * SLAB + wave * 32 + (lane & 31);
+        okA = m < g.M;
+        if (CONV) {
+            // M fits 31 bits (checked at launch): 32-bit divisions, a fraction of the cost of 64-bit ones,
+            // and this set-up runs once per slab, which for a short K is as much work as the K loop
+            const u32 mm = okA ? (u32)m : 0u;
+            const u32 plane = (u32)g.Ho * (u32)g.Wo;
+            const int b = (int)(mm / plane);
+            const int rem = (int)(mm - (u32)b * plane);
+            const int ho = (int)((u32)rem / (u32)g.Wo), wo = rem - ho * g.Wo;
+            hi0 = ho * g.stride - g.pad;
+            wi0 = wo * g.stride - g.pad;
+            if (CONV == ROWS) {
+                offA = (u32)(((b * g.H + hi0) * g.Wd + wi0) * pix_bytes);   // first byte of filter row 0 (may be negative); the image is under 2 GiB
+                const int taps = g.kw, tap_bits = g.Cin * CA::BITS;                       // kw * Cin = 32
+                const int t_lo = max(0, -wi0), t_hi = max(min(taps, g.Wd - wi0), t_lo);
+#pragma unroll
+                for (int i = 0; i < WORDS_A; ++i) {
+                    // bits [lo, up) of word i, 0 <= lo <= up <= 32
+                    const int lo = min(max(t_lo * tap_bits - 32 * i, 0), 32), up = min(max(t_hi * tap_bits - 32 * i, 0), 32);
+                    const u32 below_up = up >= 32 ? ~0u : (1u << up) - 1u, below_lo = lo >= 32 ? ~0u : (1u << lo) - 1u;
+                    row_keep[i] = below_up & ~below_lo;
+                }
+            } else {
+                offA = (u32)(((b * g.H + hi0) * g.Wd + wi0) * pix_bytes + kq * RUN_A);   // the image is under 2 GiB
+            }
+        } else {
+            offA = okA ? (u32)(m * a_row_bytes + kq * RUN_A) : kOob;
+        }
+    };
+    auto load_A = [&](u32x4 *raw) {
+        if constexpr (CONV == ROWS) {
+            const int fr = (a_k0 >> 5) + kq;
+            const int hi = hi0 + fr;
+            const bool in = okA && a_k0 < g.K && (unsigned)hi < (unsigned)g.H;
+            const int byte_off = (int)offA + fr * g.Wd * pix_bytes;
+            const int shift = byte_off & 3, base = byte_off - shift;
+            u32 w[NA * 4];
+#pragma unroll
+            for (int j = 0; j < NA * 4; ++j) w[j] = 0;
+#pragma unroll
+            for (int j = 0; j <= WORDS_A; ++j) {
+                const int o = base + 4 * j;                  // a word before the tensor is "outside" explicitly
+                w[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrcA, (in && o >= 0) ? (u32)o : kOob, 0, 0);
+            }
+            w[NA * 4 - 1] = (u32)shift;                      // travels with the words to the decoder
+#pragma unroll
+            for (int p = 0; p < NA; ++p) raw[p] = u32x4{w[4 * p], w[4 * p + 1], w[4 * p + 2], w[4 * p + 3]};
+            a_k0 += 64;
+            return;
+        }
+        u32 off;
+        if (CONV) {
+            const bool in = okA && a_k0 < g.K && tap.inside(g, hi0, wi0);
+            off = in ? offA + (u32)tap.byte_offset(g, pix_bytes, CA::BITS) : kOob;   // padding reads code 0
+        } else {
+            off = a_k0 < g.K ? offA + (u32)(a_k0 * CA::BITS / 8) : kOob;
+        }
+        load_run<CA::BITS>(rsrcA, off, raw);
+        a_k0 += 64;
+        if (CONV == 1) {
+            tap.advance(64, g);
+        }
+    };
+    auto decode_A = [&](const u32x4 *raw, int q) -> f16x8 {
+        u32 d[4];
+        if constexpr (CONV == ROWS) {
+            const u32 shift = raw[NA - 1].w;
+            u32x4 t[2] = {u32x4{0u, 0u, 0u, 0u}, u32x4{0u, 0u, 0u, 0u}};
+#pragma unroll
+            for (int i = 0; i < WORDS_A; ++i)
+                t[i >> 2][i & 3] = __builtin_amdgcn_alignbyte(raw[(i + 1) >> 2][(i + 1) & 3], raw[i >> 2][i & 3], shift) & row_keep[i];
+            decode_eight<FMT_A>(t, q, d);
+        } else {
+            decode_eight<FMT_A>(raw, q, d);
+        }
+        return __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]});
+    };
+
+    // AHEAD: the first two K steps of a slab are requested before the epilogue of the slab in front of it, which hides their way, and the
+    // first products add to a constant zero.  Codes only (401408 x 256 x 64 with a shortcut 77.4 -> 73.9 us; 83.0 with the epilogues of all
+    // widths in one kernel); the other builds and the convolutions of two blocks have no registers for it (12 to 40 spilled).
+    constexpr bool AHEAD = OUT == OUT_CODES && (CB == 4 || CONV == 0);
+    u32x4 rawA[2][NA];
+    auto request = [&](int slab) {
+        locate(slab);
+        a_k0 = 0;
+        tap = TapCounter();
+        load_A(rawA[0]);
+        if (ktiles > 1) load_A(rawA[1]);                             // uniform
+    };
+    if constexpr (AHEAD) request(cg.walker);
 
     // ---- W: every run of 32 codes is decoded once and stays.  Row n of the tile is K halves plus 16
     // bytes of padding (fragment reads of 32 consecutive rows then fall into different banks); rows
@@ -146,118 +253,20 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
         __syncthreads();
     }
 
-    const int a_row_bytes = (int)(g.K * CA::BITS / 8);
-    const int pix_bytes = CONV ? g.pix_bytes : 0;
-    const u32 rdW = (u32)(lane & 31) * (u32)row_bytes + (u32)kq * 64;   // K step adds 128 B, block kk 16 B, column block j 32 rows
-
     float run_max = 0.0f;                                            // max |C| over every strip this lane stores
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below
-        // ---- A: the lane's own row, the 32 codes kq of every K step
-        u32 offA;
-        int hi0 = 0, wi0 = 0;
-        bool okA;
-        u32 row_keep[CONV == ROWS ? WORDS_A : 1];                    // ROWS: bits of a run that belong to taps inside the image
-        {
-            const int64_t m = m_strip + (lane & 31);
-            okA = m < g.M;
-            if (CONV) {
-                // M fits 31 bits (checked at launch): 32-bit divisions, a fraction of the cost of 64-bit ones,
-                // and this set-up runs once per slab, which for a short K is as much work as the K loop
-                const u32 mm = okA ? (u32)m : 0u;
-                const u32 plane = (u32)g.Ho * (u32)g.Wo;
-                const int b = (int)(mm / plane);
-                const int rem = (int)(mm - (u32)b * plane);
-                const int ho = (int)((u32)rem / (u32)g.Wo), wo = rem - ho * g.Wo;
-                hi0 = ho * g.stride - g.pad;
-                wi0 = wo * g.stride - g.pad;
-                if (CONV == ROWS) {
-                    offA = (u32)(((b * g.H + hi0) * g.Wd + wi0) * pix_bytes);   // first byte of filter row 0 (may be negative); the image is under 2 GiB
-                    const int taps = g.kw, tap_bits = g.Cin * CA::BITS;                       // kw * Cin = 32
-                    const int t_lo = max(0, -wi0), t_hi = max(min(taps, g.Wd - wi0), t_lo);
-#pragma unroll
-                    for (int i = 0; i < WORDS_A; ++i) {
-                        // bits [lo, up) of word i, 0 <= lo <= up <= 32
-                        const int lo = min(max(t_lo * tap_bits - 32 * i, 0), 32), up = min(max(t_hi * tap_bits - 32 * i, 0), 32);
-                        const u32 below_up = up >= 32 ? ~0u : (1u << up) - 1u, below_lo = lo >= 32 ? ~0u : (1u << lo) - 1u;
-                        row_keep[i] = below_up & ~below_lo;
-                    }
-                } else {
-                    offA = (u32)(((b * g.H + hi0) * g.Wd + wi0) * pix_bytes + kq * RUN_A);   // the image is under 2 GiB
-                }
-            } else {
-                offA = okA ? (u32)(m * a_row_bytes + kq * RUN_A) : kOob;
-            }
-        }
-        // position of the next K step to load: first k, and for a convolution its filter row, filter
-        // column and first channel (uniform over the wave), counted up from step to step
-        int a_k0 = 0;
-        TapCounter tap;
-        auto load_A = [&](u32x4 *raw) {
-            if constexpr (CONV == ROWS) {
-                const int fr = (a_k0 >> 5) + kq;
-                const int hi = hi0 + fr;
-                const bool in = okA && a_k0 < g.K && (unsigned)hi < (unsigned)g.H;
-                const int byte_off = (int)offA + fr * g.Wd * pix_bytes;
-                const int shift = byte_off & 3, base = byte_off - shift;
-                u32 w[NA * 4];
-#pragma unroll
-                for (int j = 0; j < NA * 4; ++j) w[j] = 0;
-#pragma unroll
-                for (int j = 0; j <= WORDS_A; ++j) {
-                    const int o = base + 4 * j;                  // a word before the tensor is "outside" explicitly
-                    w[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrcA, (in && o >= 0) ? (u32)o : kOob, 0, 0);
-                }
-                w[NA * 4 - 1] = (u32)shift;                      // travels with the words to the decoder
-#pragma unroll
-                for (int p = 0; p < NA; ++p) raw[p] = u32x4{w[4 * p], w[4 * p + 1], w[4 * p + 2], w[4 * p + 3]};
-                a_k0 += 64;
-                return;
-            }
-            u32 off;
-            if (CONV) {
-                const bool in = okA && a_k0 < g.K && tap.inside(g, hi0, wi0);
-                off = in ? offA + (u32)tap.byte_offset(g, pix_bytes, CA::BITS) : kOob;   // padding reads code 0
-            } else {
-                off = a_k0 < g.K ? offA + (u32)(a_k0 * CA::BITS / 8) : kOob;
-            }
-            load_run<CA::BITS>(rsrcA, off, raw);
-            a_k0 += 64;
-            if (CONV == 1) {
-                tap.advance(64, g);
-            }
-        };
-        auto decode_A = [&](const u32x4 *raw, int q) -> f16x8 {
-            u32 d[4];
-            if constexpr (CONV == ROWS) {
-                const u32 shift = raw[NA - 1].w;
-                u32x4 t[2] = {u32x4{0u, 0u, 0u, 0u}, u32x4{0u, 0u, 0u, 0u}};
-#pragma unroll
-                for (int i = 0; i < WORDS_A; ++i)
-                    t[i >> 2][i & 3] = __builtin_amdgcn_alignbyte(raw[(i + 1) >> 2][(i + 1) & 3], raw[i >> 2][i & 3], shift) & row_keep[i];
-                decode_eight<FMT_A>(t, q, d);
-            } else {
-                decode_eight<FMT_A>(raw, q, d);
-            }
-            return __builtin_bit_cast(f16x8, u32x4{d[0], d[1], d[2], d[3]});
-        };
-
+        if (m_strip >= g.M) break;                                   // uniform per wave; no barriers below
+        if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
-#pragma unroll
-        for (int j = 0; j < CB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
-
-        u32x4 rawA[2][NA];
-        load_A(rawA[0]);
-        load_A(rawA[1]);
         f16x8 fa = decode_A(rawA[0], 0);
 
         // One K step: four k blocks of CB MFMAs; the A fragment of the next block is decoded while
-        // this block's MFMAs run, the codes of K step kt + 2 are requested once step kt's are decoded.
-        auto step = [&](int kt, auto stage_tag) {
+        // this block's MFMAs run, the codes of K step kt + 2 are requested once step kt's are decoded.  The first block adds to
+        // a constant zero; an only step has no next one.
+        auto step = [&](int kt, auto stage_tag, auto first_tag, auto only_tag) {
             constexpr int s = decltype(stage_tag)::value;
+            constexpr bool first = decltype(first_tag)::value, only = decltype(only_tag)::value;
             const char *wk = lds + rdW + kt * 128;
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
@@ -265,20 +274,40 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
                 f16x8 fw[CB];
 #pragma unroll
                 for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const f16x8 *>(wk + kk * 16 + j * 32 * row_bytes);
-                fa = kk < 3 ? decode_A(rawA[s], kk + 1) : decode_A(rawA[s ^ 1], 0);
+                if (kk < 3) fa = decode_A(rawA[s], kk + 1);
+                else if (!only) fa = decode_A(rawA[s ^ 1], 0);
 #pragma unroll
-                for (int j = 0; j < CB; ++j)
-                    acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[j], fa_cur, acc[j], 0, 0, 0)
-                                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], acc[j], 0, 0, 0);
-                if (kk == 3) load_A(rawA[s]);
+                for (int j = 0; j < CB; ++j) {
+                    const f32x16 c = first && kk == 0 ? f32x16{} : acc[j];
+                    acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[j], fa_cur, c, 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa_cur, fw[j], c, 0, 0, 0);
+                }
+                if (kk == 3 && !only) load_A(rawA[s]);
             }
         };
-        for (int kt = 0; kt < ktiles; kt += 2) {
-            step(kt, std::integral_constant<int, 0>{});
-            if (kt + 1 < ktiles) step(kt + 1, std::integral_constant<int, 1>{});
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        int kt = 0;
+        if constexpr (!AHEAD) {
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
+        } else if (ktiles == 1) {                                    // uniform
+            step(0, even, std::true_type{}, std::true_type{});
+            kt = 1;
+        } else {
+            step(0, even, std::true_type{}, std::false_type{});
+            step(1, odd, std::false_type{}, std::false_type{});
+            kt = 2;
         }
+        for (; kt < ktiles; kt += 2) {
+            step(kt, even, std::false_type{}, std::false_type{});
+            if (kt + 1 < ktiles) step(kt + 1, odd, std::false_type{}, std::false_type{});
+        }
+        if constexpr (AHEAD) request(slab + cg.walkers);
         if constexpr (OUT == OUT_CODES)
-            run_max = fmaxf(run_max, epilogue_strip_codes<CB, CA::ACC_EXP + CW::ACC_EXP>(reload_args(), acc, m_strip, cg.n0, cols, big, os));
+            run_max = fmaxf(run_max, epilogue_strip_codes<CB, CA::ACC_EXP + CW::ACC_EXP, Q, R>(g, acc, m_strip, cg.n0, cols, big, os));
         else
             run_max = fmaxf(run_max, epilogue_strip<CB, OUT != OUT_FP32, false, CA::ACC_EXP + CW::ACC_EXP>(g, acc, m_strip, cg.n0));
     }
@@ -312,7 +341,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
 // CONV: 0 matrix product, 1 convolution with Cin a multiple of 64.
 // ---------------------------------------------------------------------------
 #if DYBIT_WS_W == 0 || DYBIT_WS_W == 6
-template <int FMT_A, int FMT_W, int CONV, int CB, int OUT>
+template <int FMT_A, int FMT_W, int CONV, int CB, int OUT, int Q, int R>
 __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_WRITE_BACK ? 3 : 4) : 2)) void gemm_ws8_kernel(const GemmArgs g, const int slabs, const int row_bytes, const int groups)
 {
     const int THREADS = OUT == OUT_CODES ? (int)blockDim.x : 64 * waves_of<CB, OUT>(), SLAB = THREADS / 2;
@@ -334,6 +363,46 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
             return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
         }
     };
+
+    const int a_row_bytes = (int)(g.K * BA / 8);
+    const int pix_bytes = CONV ? g.pix_bytes : 0;
+    const u32 rdW = (u32)(lane & 31) * (u32)row_bytes + (u32)kq * 32;   // K step adds 64 B, column block j 32 rows
+
+    u32 offA = kOob;
+    int hi0 = 0, wi0 = 0, a_k0 = 0;
+    bool okA = false;
+    TapCounter tap;
+    auto load_A = [&]() -> u32x4 {
+        u32 off;
+        if (CONV) {
+            const bool in = okA && a_k0 < g.K && tap.inside(g, hi0, wi0);
+            off = in ? offA + (u32)tap.byte_offset(g, pix_bytes, BA) : kOob;   // padding reads code 0
+            tap.advance(64, g);
+        } else {
+            off = a_k0 < g.K ? offA + (u32)(a_k0 * BA / 8) : kOob;
+        }
+        a_k0 += 64;
+        return load_run8(rsrcA, off, std::integral_constant<int, BA>{});
+    };
+    constexpr bool AHEAD = OUT == OUT_CODES;                         // see the fp16 form
+    u32x4 rawA[2];
+    auto request = [&](int slab) {                                   // a slab's first two K steps, see the fp16 form
+        const int64_t m = (int64_t)slab * SLAB + wave * 32 + (lane & 31);
+        okA = m < g.M;
+        if (CONV) {
+            const PixelOrigin o = pixel_origin(g, okA ? m : 0);
+            hi0 = o.hi0;
+            wi0 = o.wi0;
+            offA = (u32)(o.first_pixel * pix_bytes + kq * RUN_A);    // the image is under 2 GiB
+        } else {
+            offA = okA ? (u32)(m * a_row_bytes + kq * RUN_A) : kOob;
+        }
+        a_k0 = 0;
+        tap = TapCounter();
+        rawA[0] = load_A();
+        rawA[1] = load_A();
+    };
+    if constexpr (AHEAD) request(cg.walker);
 
     // ---- W: every run of 32 codes is decoded once into 32 bytes and stays.  Row n of the tile is K bytes plus
     // 16 bytes of padding; rows N .. 32 CB - 1 hold zeros (fetched from the out-of-range offset).
@@ -358,55 +427,18 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
         __syncthreads();
     }
 
-    const int a_row_bytes = (int)(g.K * BA / 8);
-    const int pix_bytes = CONV ? g.pix_bytes : 0;
-    const u32 rdW = (u32)(lane & 31) * (u32)row_bytes + (u32)kq * 32;   // K step adds 64 B, column block j 32 rows
-
     float run_max = 0.0f;
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below
-        u32 offA;
-        int hi0 = 0, wi0 = 0;
-        const int64_t m = m_strip + (lane & 31);
-        const bool okA = m < g.M;
-        if (CONV) {
-            const PixelOrigin o = pixel_origin(g, okA ? m : 0);
-            hi0 = o.hi0;
-            wi0 = o.wi0;
-            offA = (u32)(o.first_pixel * pix_bytes + kq * RUN_A);    // the image is under 2 GiB
-        } else {
-            offA = okA ? (u32)(m * a_row_bytes + kq * RUN_A) : kOob;
-        }
-        int a_k0 = 0;
-        TapCounter tap;
-        auto load_A = [&]() -> u32x4 {
-            u32 off;
-            if (CONV) {
-                const bool in = okA && a_k0 < g.K && tap.inside(g, hi0, wi0);
-                off = in ? offA + (u32)tap.byte_offset(g, pix_bytes, BA) : kOob;   // padding reads code 0
-                tap.advance(64, g);
-            } else {
-                off = a_k0 < g.K ? offA + (u32)(a_k0 * BA / 8) : kOob;
-            }
-            a_k0 += 64;
-            return load_run8(rsrcA, off, std::integral_constant<int, BA>{});
-        };
-
+        if (m_strip >= g.M) break;                                   // uniform per wave; no barriers below
+        if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
-#pragma unroll
-        for (int j = 0; j < CB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
-
-        u32x4 rawA[2];
-        rawA[0] = load_A();
-        rawA[1] = load_A();
         i32x8 fa = f8::decode_fragment<FMT_A, true>(rawA[0]);
         // One K step: CB MFMAs on the fragment decoded during the previous step; the codes of step kt + 2 are
-        // requested once step kt + 1's are decoded.
-        auto step = [&](int kt, auto stage_tag) {
+        // requested once step kt + 1's are decoded.  The first adds to a constant zero.
+        auto step = [&](int kt, auto stage_tag, auto first_tag) {
             constexpr int s = decltype(stage_tag)::value;
+            constexpr bool first = decltype(first_tag)::value;
             const char *wk = lds + rdW + kt * 64;
             const i32x8 fa_cur = fa;
             i32x8 fw[CB];
@@ -418,16 +450,32 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
             }
             fa = f8::decode_fragment<FMT_A, true>(rawA[s ^ 1]);
 #pragma unroll
-            for (int j = 0; j < CB; ++j)
-                acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[j], fa_cur, acc[j], 0, 0, 0, 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[j], acc[j], 0, 0, 0, 0, 0, 0);
+            for (int j = 0; j < CB; ++j) {
+                const f32x16 c = first ? f32x16{} : acc[j];
+                acc[j] = OUT == OUT_CODES ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[j], fa_cur, c, 0, 0, 0, 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa_cur, fw[j], c, 0, 0, 0, 0, 0, 0);
+            }
             rawA[s] = load_A();
         };
-        for (int kt = 0; kt < ktiles; kt += 2) {
-            step(kt, std::integral_constant<int, 0>{});
-            if (kt + 1 < ktiles) step(kt + 1, std::integral_constant<int, 1>{});
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        int kt = 0;
+        if constexpr (!AHEAD) {
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
+        } else {
+            step(0, even, std::true_type{});
+            if (ktiles > 1) step(1, odd, std::false_type{});
+            kt = 2;
         }
-        if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, 0>(reload_args(), acc, m_strip, cg.n0, cols, false, os));
+        for (; kt < ktiles; kt += 2) {
+            step(kt, even, std::false_type{});
+            if (kt + 1 < ktiles) step(kt + 1, odd, std::false_type{});
+        }
+        if constexpr (AHEAD) request(slab + cg.walkers);
+        if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, 0, Q, R>(g, acc, m_strip, cg.n0, cols, false, os));
         else run_max = fmaxf(run_max, epilogue_strip<CB, OUT != OUT_FP32, false, 0>(g, acc, m_strip, cg.n0));
     }
 
@@ -456,7 +504,10 @@ static bool launch_cb8(const GemmArgs &g, hipStream_t st, int row_bytes, int lds
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));
     if (grid < 1) return false;
-    auto k = gemm_ws8_kernel<FA, FW, CONV, CB, kOut>;
+    auto k = [&] {
+        if constexpr (kOut == OUT_CODES) return kernel_for_codes(g, [](auto q, auto r) { return gemm_ws8_kernel<FA, FW, CONV, CB, kOut, q(), r()>; });
+        else return gemm_ws8_kernel<FA, FW, CONV, CB, kOut, 0, 0>;
+    }();
     note_kernel(DYBIT_KERNEL_F8_WS);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
@@ -472,7 +523,10 @@ static bool launch_cb(const GemmArgs &g, hipStream_t st, int row_bytes, int lds_
     const int groups = (int)((g.N + CB * 32 - 1) / (CB * 32));
     const int grid = grid_for_groups(slabs, groups, 256 * workgroups_per_cu<CB>(lds_bytes));
     if (grid < 1) return false;
-    auto k = gemm_ws_kernel<FA, FW, CONV, CB, kOut>;
+    auto k = [&] {
+        if constexpr (kOut == OUT_CODES) return kernel_for_codes(g, [](auto q, auto r) { return gemm_ws_kernel<FA, FW, CONV, CB, kOut, q(), r()>; });
+        else return gemm_ws_kernel<FA, FW, CONV, CB, kOut, 0, 0>;
+    }();
     note_kernel(DYBIT_KERNEL_F16_WS);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, g, slabs, row_bytes, groups);
