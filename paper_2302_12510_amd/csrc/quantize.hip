@@ -122,6 +122,7 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
 // 1 << shift: the 16-byte words that a workgroup of the pass that quantizes x next takes at a time (quantize_kernel, fake_quant_kernel).  A
 // workgroup here takes the same ones and every gridDim-th piece after, so that with the grid a multiple of 8 both read a
 // piece on one XCD and the second pass finds it in that L2 (fake_quant_kernel after it, 14 M floats: 20.6 -> 18.1 us, 9 M 15.2 -> 13.1).
+// Past kStreamBytes nothing stays for it: a workgroup's 64 KiB are one piece then (2^28 floats 161.5 -> 155.9).
 constexpr int kJoinThreads = 1024, kJoinBlocks = DYBIT_ABSMAX_WORKSPACE / 4;   // four floats a workgroup
 template <bool STREAM>
 __global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float *__restrict__ x, size_t n, int shift, float *scale_out, float inv_vmax,
@@ -901,7 +902,7 @@ static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *sc
     }
     const bool stream_past = n * sizeof(float) > kStreamBytes;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
-        const int u = n / 4 < kQuantSmall ? quant_unroll_small(f.bits) : DYBIT_QUANT_UNROLL, shift = u == 1 ? 8 : u == 2 ? 9 : 10;
+        const int u = n / 4 < kQuantSmall ? quant_unroll_small(f.bits) : DYBIT_QUANT_UNROLL, shift = stream_past ? 12 : u == 1 ? 8 : u == 2 ? 9 : 10;
         const unsigned grid = (unsigned)(grid_for(n / 4, kJoinThreads, kJoinBlocks) + 7) & ~7u;
         static std::atomic<uint64_t> launches{0};
         uint64_t tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;   // odd factor: all different
