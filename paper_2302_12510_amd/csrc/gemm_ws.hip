@@ -212,8 +212,9 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
 
     // AHEAD: the first two K steps of a slab are requested before the epilogue of the slab in front of it, which hides their way, and the
     // first products add to a constant zero.  Codes only (401408 x 256 x 64 with a shortcut 77.4 -> 73.9 us; 83.0 with the epilogues of all
-    // widths in one kernel); the other builds and the convolutions of two blocks have no registers for it (12 to 40 spilled).
-    constexpr bool AHEAD = OUT == OUT_CODES && (CB == 4 || CONV == 0);
+    // widths in one kernel); the other builds and the convolutions of two blocks have no registers for it (12 to 40 spilled), and a
+    // convolution finds its next outputs by divisions, whose time in front of the epilogue it does not win back (ResNet-18 chain 378.1, with it 379.2).
+    constexpr bool AHEAD = OUT == OUT_CODES && CONV == 0;
     u32x4 rawA[2][NA];
     auto request = [&](int slab) {
         locate(slab);
@@ -384,7 +385,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
         a_k0 += 64;
         return load_run8(rsrcA, off, std::integral_constant<int, BA>{});
     };
-    constexpr bool AHEAD = OUT == OUT_CODES;                         // see the fp16 form
+    constexpr bool AHEAD = OUT == OUT_CODES && CONV == 0;            // see the fp16 form
     u32x4 rawA[2];
     auto request = [&](int slab) {                                   // a slab's first two K steps, see the fp16 form
         const int64_t m = (int64_t)slab * SLAB + wave * 32 + (lane & 31);
