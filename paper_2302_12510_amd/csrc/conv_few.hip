@@ -176,8 +176,17 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
                 a += f.pitch;
                 w += 64;
             };
-            filter_row(std::true_type{});
-            for (int fr = 1; fr < g.kh; ++fr) filter_row(std::false_type{});
+            int fr = 0;
+            if constexpr (OUT == OUT_CODES && Q == 0) {                // all epilogues: a second copy of the loop's body spills 13 more registers
+#pragma unroll
+                for (int j = 0; j < CB; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
+            } else {
+                filter_row(std::true_type{});
+                fr = 1;
+            }
+            for (; fr < g.kh; ++fr) filter_row(std::false_type{});
             GemmArgs ge = OUT == OUT_CODES && Q == 0 ? reload_args() : g;
             ge.M = m_unit + outputs;                                   // the epilogue stores no row past the unit
             if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, ACC, Q>(ge, acc, m_unit + s, n0, cols, big, os));
