@@ -509,6 +509,19 @@ dybit_status check_codes_out(const Epilogue &e, int64_t N, int64_t ldc)
     return DYBIT_OK;
 }
 
+// The tile of the product on split operands and the bytes it works in (both 0: not taken).  Asked for once per call: the rule reads
+// options that another thread may change before a second answer.
+struct SixPlan {
+    int tile = 0;
+    size_t bytes = 0;
+};
+SixPlan plan_six(int64_t M, int64_t N, int64_t K, dybit_fmt a_fmt, dybit_fmt w_fmt)
+{
+    const int tile = gemm_six_tile(M, N, K, a_fmt.bits, w_fmt.bits);
+    const int64_t bytes = tile ? gemm_six_bytes(M, N, K, a_fmt.bits, a_fmt.is_signed, w_fmt.bits, w_fmt.is_signed) : 0;
+    return bytes ? SixPlan{tile, (size_t)bytes} : SixPlan{};
+}
+
 dybit_status gemm_impl(int64_t M, int64_t N, int64_t K,
                        const uint8_t *A_codes, dybit_fmt a_fmt, const float *a_scale,
                        const uint8_t *W_codes, dybit_fmt w_fmt, const float *w_scale,
@@ -532,9 +545,9 @@ dybit_status gemm_impl(int64_t M, int64_t N, int64_t K,
     g.a_bytes = M * (K * a_fmt.bits / 8);
     g.w_bytes = N * (K * w_fmt.bits / 8);
     if (workspace && ldc < (1 << 23) && aligned16(workspace) && aligned16(A_codes) && aligned16(W_codes)) {
-        const size_t need = dybit_gemm_workspace_bytes(M, N, K, a_fmt, w_fmt);
-        if (need && need <= workspace_bytes) {
-            launch_gemm_six(g, a_fmt.bits, w_fmt.bits, gemm_six_tile(M, N, K, a_fmt.bits, w_fmt.bits), workspace, (hipStream_t)stream);
+        const SixPlan six = plan_six(M, N, K, a_fmt, w_fmt);
+        if (six.tile && six.bytes <= workspace_bytes) {
+            launch_gemm_six(g, a_fmt.bits, w_fmt.bits, six.tile, workspace, (hipStream_t)stream);
             return launch_status();
         }
     }
@@ -620,8 +633,7 @@ extern "C" dybit_status dybit_gemm(int64_t M, int64_t N, int64_t K,
 
 extern "C" size_t dybit_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, dybit_fmt a_fmt, dybit_fmt w_fmt)
 {
-    if (check_fmt(a_fmt) != DYBIT_OK || check_fmt(w_fmt) != DYBIT_OK || !gemm_six_tile(M, N, K, a_fmt.bits, w_fmt.bits)) return 0;
-    return (size_t)gemm_six_bytes(M, N, K, a_fmt.bits, a_fmt.is_signed, w_fmt.bits, w_fmt.is_signed);
+    return check_fmt(a_fmt) == DYBIT_OK && check_fmt(w_fmt) == DYBIT_OK ? plan_six(M, N, K, a_fmt, w_fmt).bytes : 0;
 }
 
 extern "C" dybit_status dybit_gemm_work(int64_t M, int64_t N, int64_t K,
