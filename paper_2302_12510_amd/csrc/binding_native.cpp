@@ -109,26 +109,28 @@ template <class T> T argument(PyObject *o)
 
 template <auto F> struct Entry;
 template <class... A, dybit_status (*F)(A...)> struct Entry<F> {
-    template <class G, size_t... I>
-    static dybit_status run(G g, PyObject *const *args, std::index_sequence<I...>)
+    static constexpr Py_ssize_t kCount = sizeof...(A);
+    using Arguments = std::tuple<A...>;
+    template <size_t... I>
+    static Arguments convert(PyObject *const *args, std::index_sequence<I...>) { return Arguments{argument<A>(args[I])...}; }   // braces: left to right
+    static Arguments arguments(PyObject *const *args) { return convert(args, std::index_sequence_for<A...>{}); }
+    static dybit_status run(const Arguments &a)
     {
-        const std::tuple<A...> a{argument<A>(args[I])...};               // braces: left to right
         dybit_status st;
         Py_BEGIN_ALLOW_THREADS
-        st = std::apply(g, a);
+        st = std::apply(F, a);
         Py_END_ALLOW_THREADS
         return st;
     }
-    template <class G> static dybit_status with(G g, PyObject *const *args) { return run(g, args, std::index_sequence_for<A...>{}); }
     static PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n)
     {
         HANDLE_TH_ERRORS
-        if (n != (Py_ssize_t)sizeof...(A)) {
-            PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", (Py_ssize_t)sizeof...(A), n);
+        if (n != kCount) {
+            PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", kCount, n);
             return nullptr;
         }
         try {
-            return PyLong_FromLong((long)with(F, args));
+            return PyLong_FromLong((long)run(arguments(args)));
         } catch (const PythonError &) {
             return nullptr;
         }
@@ -138,23 +140,24 @@ template <class... A, dybit_status (*F)(A...)> struct Entry<F> {
 
 // dybit_gemm: on the current stream, whose allocator the workspace comes from, a product that uses one gets it (dybit_gemm_work).
 template <size_t... I>
-dybit_status gemm_with_workspace(PyObject *const *args, const at::Tensor &work, std::index_sequence<I...>)
+std::tuple<std::tuple_element_t<I, Entry<&dybit_gemm>::Arguments>...> front(const Entry<&dybit_gemm>::Arguments &a, std::index_sequence<I...>)
 {
-    return Entry<&dybit_gemm>::with([&](auto... a) {
-        const std::tuple<decltype(a)...> t{a...};
-        return dybit_gemm_work(std::get<I>(t)..., (uint8_t *)work.data_ptr(), (size_t)work.numel(), std::get<sizeof...(I)>(t));
-    }, args);
+    return {std::get<I>(a)...};
 }
 PyObject *gemm(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
+    using Gemm = Entry<&dybit_gemm>;
+    constexpr size_t kStream = Gemm::kCount - 1, kOut = 11;
     HANDLE_TH_ERRORS
-    if (n != 14 || args[13] != Py_None || !is_plain_tensor(args[11])) return Entry<&dybit_gemm>::call(self, args, n);
+    if (n != Gemm::kCount || args[kStream] != Py_None || !is_plain_tensor(args[kOut])) return Gemm::call(self, args, n);
     try {
-        const size_t need = dybit_gemm_workspace_bytes(integer(args[0]), integer(args[1]), integer(args[2]), format(args[4]), format(args[7]));
-        const at::Tensor &out = THPVariable_Unpack(args[11]);
-        if (!need || !out.is_cuda()) return Entry<&dybit_gemm>::call(self, args, n);
-        const at::Tensor work = at::empty({(int64_t)need}, at::TensorOptions().device(out.device()).dtype(at::kByte));
-        return PyLong_FromLong((long)gemm_with_workspace(args, work, std::make_index_sequence<13>{}));
+        const Gemm::Arguments a = Gemm::arguments(args);
+        const size_t need = dybit_gemm_workspace_bytes(std::get<0>(a), std::get<1>(a), std::get<2>(a), std::get<4>(a), std::get<7>(a));
+        if (!need) return PyLong_FromLong((long)Gemm::run(a));
+        const at::Tensor work = at::empty({(int64_t)need}, at::TensorOptions().device(THPVariable_Unpack(args[kOut]).device()).dtype(at::kByte));
+        const auto with_work = std::tuple_cat(front(a, std::make_index_sequence<kStream>{}),
+                                              std::tuple<uint8_t *, size_t, dybit_stream>{(uint8_t *)work.data_ptr(), need, std::get<kStream>(a)});
+        return PyLong_FromLong((long)Entry<&dybit_gemm_work>::run(with_work));
     } catch (const PythonError &) {
         return nullptr;
     }

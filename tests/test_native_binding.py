@@ -77,6 +77,28 @@ def test_without_the_native_module(without_native):
     assert n.dybit_packed_bytes((6, True), 9) == 7
 
 
+def test_arguments_are_converted_once():
+    """Also by the product's wrapper, which looks at some of them itself."""
+    seen = []
+
+    class Index:
+        def __init__(self, name, value):
+            self.name, self.value = name, value
+
+        def __index__(self):
+            seen.append(self.name)
+            return self.value
+
+    class Bits(Index):
+        def __int__(self):
+            return self.__index__()
+
+    with pytest.raises(ValueError, match="expected a device tensor"):
+        NATIVE.dybit_gemm(Index("M", 64), Index("N", 64), Index("K", 256), None, (Bits("a", 4), True), None, None, (Bits("w", 4), True), None,
+                          None, False, CPU, 64, None)
+    assert seen == ["M", "N", "K", "a", "w"]
+
+
 @pytest.mark.gpu
 @pytest.mark.filterwarnings("ignore:the native argument marshalling")
 def test_results_without_the_native_module(without_native):
