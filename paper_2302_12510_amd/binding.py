@@ -294,7 +294,9 @@ def dybit_dequantize(codes: torch.Tensor, n: int, scale: torch.Tensor, bits: int
 def dybit_gemm(M: int, N: int, K: int, a_codes, a_fmt, a_scale, w_codes, w_fmt, w_scale,
                bias=None, relu: bool = False, out: torch.Tensor | None = None, ldc: int | None = None, stream=None):
     """C [M][N] float32 = sA sW A W^T (+bias)(ReLU); a_fmt / w_fmt are (bits, signed) pairs.  On the current stream
-    (stream None) the native module gives a large product a workspace (dybit_gemm_work)."""
+    (stream None) the native module gives a large product a workspace (dybit_gemm_work) where there is memory for it:
+    0.75 bytes a value and plane of either operand, 150 MB for 8192^3 at 8- by 4-bit, back with torch's allocator after the call, and with the
+    graph's memory for as long as the graph lives where the call is captured."""
     if out is None:
         out = _n().empty(a_scale, True, M, N)
     if ldc is None:

@@ -8,7 +8,9 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/Allocator.h>
 #include <c10/hip/HIPStream.h>
+#include <c10/util/Exception.h>
 
 #include <tuple>
 #include <type_traits>
@@ -138,7 +140,18 @@ template <class... A, dybit_status (*F)(A...)> struct Entry<F> {
     }
 };
 
-// dybit_gemm: on the current stream, whose allocator the workspace comes from, a product that uses one gets it (dybit_gemm_work).
+// Memory of the current device that later work on its current stream may reuse once the result is gone; empty where there is not enough:
+// what is only faster with a workspace does without one then.
+c10::DataPtr scratch(size_t bytes)
+{
+    try {
+        return c10::GetAllocator(c10::DeviceType::CUDA)->allocate(bytes);
+    } catch (const c10::OutOfMemoryError &) {
+        return {};
+    }
+}
+
+// dybit_gemm: on the current stream a product that uses a workspace gets it (dybit_gemm_work).
 template <size_t... I>
 std::tuple<std::tuple_element_t<I, Entry<&dybit_gemm>::Arguments>...> front(const Entry<&dybit_gemm>::Arguments &a, std::index_sequence<I...>)
 {
@@ -147,16 +160,16 @@ std::tuple<std::tuple_element_t<I, Entry<&dybit_gemm>::Arguments>...> front(cons
 PyObject *gemm(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
     using Gemm = Entry<&dybit_gemm>;
-    constexpr size_t kStream = Gemm::kCount - 1, kOut = 11;
+    constexpr size_t kStream = Gemm::kCount - 1;
     HANDLE_TH_ERRORS
-    if (n != Gemm::kCount || args[kStream] != Py_None || !is_plain_tensor(args[kOut])) return Gemm::call(self, args, n);
+    if (n != Gemm::kCount || args[kStream] != Py_None) return Gemm::call(self, args, n);
     try {
         const Gemm::Arguments a = Gemm::arguments(args);
         const size_t need = dybit_gemm_workspace_bytes(std::get<0>(a), std::get<1>(a), std::get<2>(a), std::get<4>(a), std::get<7>(a));
-        if (!need) return PyLong_FromLong((long)Gemm::run(a));
-        const at::Tensor work = at::empty({(int64_t)need}, at::TensorOptions().device(THPVariable_Unpack(args[kOut]).device()).dtype(at::kByte));
+        const c10::DataPtr work = need ? scratch(need) : c10::DataPtr();
+        if (!work) return PyLong_FromLong((long)Gemm::run(a));
         const auto with_work = std::tuple_cat(front(a, std::make_index_sequence<kStream>{}),
-                                              std::tuple<uint8_t *, size_t, dybit_stream>{(uint8_t *)work.data_ptr(), need, std::get<kStream>(a)});
+                                              std::tuple<uint8_t *, size_t, dybit_stream>{(uint8_t *)work.get(), need, std::get<kStream>(a)});
         return PyLong_FromLong((long)Entry<&dybit_gemm_work>::run(with_work));
     } catch (const PythonError &) {
         return nullptr;

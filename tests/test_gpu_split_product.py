@@ -104,3 +104,30 @@ def test_one_stream_after_another_and_capture():
     assert not B.dybit_last_gemm_kernel().startswith("f6")
     side.synchronize()
     assert torch.allclose(out, want, rtol=1e-5, atol=1e-2)
+
+
+def test_no_memory_for_a_workspace():
+    """A product whose workspace the allocator refuses runs as without one."""
+    import torch
+    M, N, K, a_fmt, w_fmt = 4096, 4096, 4096, (8, True), (4, True)
+    need = B.lib().dybit_gemm_workspace_bytes(M, N, K, B.fmt(*a_fmt), B.fmt(*w_fmt))
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    args = (M, N, K, torch.randint(0, 256, (M * K,), dtype=torch.uint8, device="cuda", generator=gen), a_fmt, scalar(0.5),
+            torch.randint(0, 256, (N * K // 2,), dtype=torch.uint8, device="cuda", generator=gen), w_fmt, scalar(0.25))
+    want, out = B.dybit_gemm(*args), torch.zeros(M, N, device="cuda")
+    assert B.dybit_last_gemm_kernel() == "f6_256"
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + need // 4) / total)
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty(need, dtype=torch.uint8, device="cuda")
+        assert B.dybit_gemm(*args, out=out) is out
+        assert B.dybit_last_gemm_kernel() == "f16_256"
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    # the same products in another order of summation: 2^-24 of sum |a b| for each of the K / 16 steps that add into a result, at most
+    bound = (K / 16 + 1) * 2.0 ** -24 * 0.125 * K * 64 * 4
+    assert (out - want).abs().max().item() <= bound
+    assert B.dybit_gemm(*args).equal(want) and B.dybit_last_gemm_kernel() == "f6_256"
