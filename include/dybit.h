@@ -70,7 +70,10 @@ dybit_status dybit_absmax_scale(const float *x, size_t n, dybit_fmt f, float *sc
                                 dybit_stream stream);
 
 /* The same with a workspace of DYBIT_ABSMAX_WORKSPACE floats [device] that is the call's own until it has run; its
- * contents do not matter before or after.  One launch fewer for tensors of more than a few ten thousand floats. */
+ * contents do not matter before or after.  One launch instead of three for tensors of more than 65536 floats, where the workspace is 8-byte
+ * aligned.  Two calls must not use one workspace at the same time: one of them, or both, then end only after some 15 seconds of waiting
+ * on the device (option "absmax_looks"), with *scale_out = NaN and the asynchronous error flag set; where that was a captured call, the
+ * workspace has to be cleared before the graph is replayed. */
 #define DYBIT_ABSMAX_WORKSPACE 1024
 dybit_status dybit_absmax_scale_ws(const float *x, size_t n, dybit_fmt f, float *scale_out,
                                    float *workspace, dybit_stream stream);
@@ -407,7 +410,8 @@ dybit_status dybit_search(int32_t n_layers, const double *lat, const double *rms
 
 /* Waits for `stream`, then reports and clears the asynchronous error flag of the current
  * device: *flag_out [host] is DYBIT_OK or DYBIT_ERR_BAD_SCALE (a dybit_quantize kernel since the
- * last call, or a write-back epilogue, found an unusable scale and wrote no codes). */
+ * last call, or a write-back epilogue, found an unusable scale and wrote no codes, or a dybit_absmax_scale_ws
+ * lost its workspace to another call and made no scale). */
 dybit_status dybit_get_last_async_error(int32_t *flag_out, dybit_stream stream);
 
 /* A caller-owned error word for the calling host thread (for callers that run several streams at once and
@@ -434,6 +438,7 @@ dybit_status dybit_set_async_error_word(int32_t *device_word);
  *   "gemm_mfma"    "auto" | "f16"   -- "f16" keeps pairs of 4- and 2-bit operands off the e4m3 kernels
  *   "mid_tile"     "auto" | "64" | "128"   -- tile of the e4m3 kernel when it is not the 256 x 256 one, and of "six" ("128", else 256 x 256)
  *   "mid_kgroups"  "auto" | "1" | "2"      -- k-groups per workgroup of the 128 x 128 kernels
+ *   "absmax_looks" "auto" | "1" to "67108864" (auto)   -- how often dybit_absmax_scale_ws looks for a workgroup's maximum
  *   "gemm_ws"      "auto" | "off"   -- "off" leaves the weight-stationary kernel out of the automatic choice
  * Initial values come from the environment, read once when the library is first used (DYBIT_GEMM_KERNEL,
  * DYBIT_GEMM_MFMA, DYBIT_MID_TILE, DYBIT_MID_KGROUPS, DYBIT_GEMM_WS=0).  DYBIT_ERR_NULL for a NULL

@@ -17,6 +17,9 @@ inline dybit_status check_fmt(dybit_fmt f)
 // (dybit_set_async_error_word) or the library's flag on the current device; NULL on a HIP failure (quantize.hip).
 int *async_error_word();
 
+// Option "absmax_looks" (gemm_dispatch.cpp).
+unsigned absmax_looks();
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // A HIP error that a launch function met before its launch (gemm_dispatch.cpp keeps it per host thread).

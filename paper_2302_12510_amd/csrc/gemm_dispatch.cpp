@@ -23,6 +23,9 @@ namespace dybit {
 namespace {
 
 std::atomic<int> opt_kernel{0}, opt_mfma_f16{0}, opt_mid_tile{0}, opt_mid_kgroups{0}, opt_ws_off{0};
+// A look of the max-abs kernel's last workgroup takes 0.2 us (100000 of them 23 ms): some 15 s, where a launch ends within milliseconds.
+constexpr unsigned kAbsmaxLooks = 1u << 26;
+std::atomic<unsigned> opt_absmax_looks{kAbsmaxLooks};
 thread_local int last_kernel = DYBIT_KERNEL_NONE;
 thread_local hipError_t pending_hip_error = hipSuccess;
 
@@ -51,6 +54,11 @@ bool apply_option(const char *name, const char *value)
     } else if (!strcmp(name, "gemm_ws")) {
         if (!is_auto && strcmp(value, "off")) return false;
         opt_ws_off = is_auto ? 0 : 1;
+    } else if (!strcmp(name, "absmax_looks")) {
+        char *end = nullptr;
+        const unsigned long v = is_auto ? kAbsmaxLooks : strtoul(value, &end, 10);
+        if (v < 1 || v > kAbsmaxLooks || (end && *end)) return false;
+        opt_absmax_looks = (unsigned)v;
     } else {
         return false;
     }
@@ -81,6 +89,8 @@ DispatchOptions dispatch_options()
     options_from_environment();
     return DispatchOptions{opt_kernel.load(), opt_mfma_f16.load(), opt_mid_tile.load(), opt_mid_kgroups.load(), opt_ws_off.load()};
 }
+
+unsigned absmax_looks() { return opt_absmax_looks.load(); }
 
 void note_kernel(int id) { last_kernel = id; }
 void note_hip(hipError_t e)

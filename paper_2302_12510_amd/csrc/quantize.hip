@@ -111,11 +111,13 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
     }
 }
 
-// With a workspace: one launch.  A workgroup leaves its maximum there, and the last one of the grid, dispatched behind all
-// others, waits for them and makes the scale.  Nobody has cleared the workspace and the result must not depend on what it holds, so
-// a maximum comes as two words, each with half of a 64-bit number that belongs to this launch, and counts when both
+// With a workspace: one launch.  A workgroup leaves its maximum there, and the last one of the grid waits for the others and makes the
+// scale; the others wait for nobody, so they end in whatever order they are dispatched.  Nobody has cleared the workspace and the result must not
+// depend on what it holds, so a maximum comes as two words, each with half of a 64-bit number that belongs to this launch, and counts when both
 // have come and agree; a word is stored and read as a whole, past the caches that are not shared.  The last workgroup clears what
-// it has read: a replayed graph, whose number is always the same, finds no words of its last replay.
+// it has read: a replayed graph, whose number is always the same, finds no words of its last replay.  Another call that uses the workspace at the
+// same time takes words away that then never come: the wait ends after `looks` of them, with NaN for a scale and the error word set.
+// (Without a wait, every workgroup looking through all words once its own has arrived: 2.4 M floats, in a graph, 4.4 -> 15 us.)
 // A launch for the maxima and one that joined them -> this (us; calls, which the host's launches bound, and in a graph): 2^17 floats 8.1 -> 5.6 and
 // 4.0 -> 3.5, 2.4 M 8.0 -> 5.6 and 5.0 -> 3.9, 2^23 8.2 -> 5.6 and 6.4 -> 4.8, 2^26 42.1 -> 40.3, 2^28 155 both.  256 workgroups of 16 waves:
 // as many as wait for one another in one round, 64 KiB of loads in flight.  STREAM: see kStreamBytes.
@@ -126,8 +128,10 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(const float *__restric
 constexpr int kJoinThreads = 1024, kJoinBlocks = DYBIT_ABSMAX_WORKSPACE / 4;   // four floats a workgroup
 template <bool STREAM>
 __global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float *__restrict__ x, size_t n, int shift, float *scale_out, float inv_vmax,
-                                                                     uint64_t *words, uint32_t tag0, uint32_t tag1)
+                                                                     uint64_t *words, uint32_t tag0, uint32_t tag1, unsigned looks, int *err)
 {
+    __shared__ int missing;
+    if (threadIdx.x == 0) missing = 0;                                     // the first maximum's barrier is behind it
     const size_t n4 = n >> 2;
     const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
     float mx = 0.0f;
@@ -166,18 +170,27 @@ __global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float
     if (threadIdx.x != 0) mx = 0.0f;
     if (threadIdx.x < others) {
         uint64_t a, b;
-        for (;;) {
+        bool here;
+        for (;; --looks) {
             a = __hip_atomic_load(words + 2 * threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             b = __hip_atomic_load(words + 2 * threadIdx.x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)(a >> 32) == tag0 && (uint32_t)(b >> 32) == tag1 && (uint32_t)a == (uint32_t)b) break;
+            here = (uint32_t)(a >> 32) == tag0 && (uint32_t)(b >> 32) == tag1 && (uint32_t)a == (uint32_t)b;
+            if (here || looks <= 1) break;
             __builtin_amdgcn_s_sleep(1);
         }
-        __hip_atomic_store(words + 2 * threadIdx.x, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(words + 2 * threadIdx.x + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        mx = fmaxf(mx, __uint_as_float((uint32_t)a));
+        if (here) {
+            __hip_atomic_store(words + 2 * threadIdx.x, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(words + 2 * threadIdx.x + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mx = fmaxf(mx, __uint_as_float((uint32_t)a));
+        } else {
+            missing = 1;
+        }
     }
     mx = workgroup_max<kJoinBlocks>(mx);
-    if (threadIdx.x == 0) *scale_out = scale_of_max(mx, inv_vmax);
+    if (threadIdx.x == 0) {
+        *scale_out = missing ? __uint_as_float(0x7fc00000u) : scale_of_max(mx, inv_vmax);
+        if (missing) *err = DYBIT_ERR_BAD_SCALE;
+    }
 }
 
 // Small tensors: one workgroup, one launch.  Eight 128-bit loads in flight per lane, 128 KiB in all.  16384 floats 2.7 us,
@@ -907,9 +920,11 @@ static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *sc
         static std::atomic<uint64_t> launches{0};
         uint64_t tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;   // odd factor: all different
         tag ^= tag >> 32;                                                  // one to one: still all different, and 0 for none
+        int *err = async_error_word();
+        if (!err) return DYBIT_ERR_HIP;
         hipLaunchKernelGGL(stream_past ? absmax_joined_kernel<true> : absmax_joined_kernel<false>, dim3(grid), dim3(kJoinThreads), 0, hs, x, n, shift,
                            scale_out, inv_vmax,
-                           reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32));
+                           reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32), absmax_looks(), err);
     } else {
         const int blocks = grid_for(n / 4 + 1, kThreads * 4, 1024);
         hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, hs, scale_out);

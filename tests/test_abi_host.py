@@ -255,3 +255,9 @@ def test_code_chain_argument_errors_without_gpu():
     assert pool(x=null) == B.ERR_NULL and pool(y=null) == B.ERR_NULL
     assert L.dybit_set_async_error_word(C.c_void_p(0x1002)) == B.ERR_ALIGNMENT
     assert L.dybit_set_async_error_word(null) == B.OK
+
+
+def test_number_options():
+    for value, ok in (("1", True), ("67108864", True), ("auto", True), ("0", False), ("67108865", False), ("", False), ("2x", False), ("-1", False), ("many", False)):
+        assert (B.lib().dybit_set_option(b"absmax_looks", value.encode()) == B.OK) == ok, value
+    B.dybit_set_option("absmax_looks", "auto")
