@@ -59,6 +59,89 @@ def test_largest_and_smallest_products_meet(tile, a_fmt, w_fmt):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("larger", ["+++", "++-", "++", "+-"])
+@pytest.mark.parametrize("a_fmt,w_fmt", PAIRS)
+def test_several_largest_products_beside_a_smaller_one(tile, a_fmt, w_fmt, larger):
+    """Every code of A times every code of W in one group of four k with two or three products of the largest values, of either sign: the
+    instruction adds a group at the place of its largest product, and nothing of the smaller one may go."""
+    top_a, top_w = (1 << (a_fmt[0] - a_fmt[1])) - 1, (1 << (w_fmt[0] - 1)) - 1
+    M, N, K = 4 << a_fmt[0], 1 << w_fmt[0], 64
+    qa, qw = np.zeros((M, K), np.uint8), np.zeros((N, K), np.uint8)
+    for p in range(4):                                           # a group for each position of the smaller product; a row of A uses one of them
+        group = [16 * p + 4 + j for j in range(4)]
+        small = group.pop(p)
+        qa[p::4, small], qw[:, small] = np.arange(1 << a_fmt[0]), np.arange(N)
+        for k, sign in zip(group, larger):
+            qa[p::4, k], qw[:, k] = top_a, top_w | (1 << (w_fmt[0] - 1) if sign == "-" else 0)
+    got = product(M, N, K, qa, a_fmt, qw, w_fmt).cpu().numpy()
+    assert B.dybit_last_gemm_kernel() == tile
+    want, _ = R.gemm(qa, a_fmt, 1.0, qw, w_fmt, 1.0)
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("a_fmt,w_fmt", [((8, True), (4, True)), ((6, False), (4, True)), ((4, True), (8, True)), ((4, False), (4, True)), ((2, False), (2, True))])
+def test_long_sums_of_positive_products(tile, a_fmt, w_fmt):
+    """Nothing cancels and the sum outgrows its terms by 2^15: what the fp32 sums round, which is within the product's tolerance."""
+    M, N, K = 130, 70, 1 << 15
+    rng = np.random.default_rng(K + a_fmt[0])
+    qa, qw = rng.integers(1, 1 << (a_fmt[0] - a_fmt[1]), (M, K)).astype(np.uint8), rng.integers(1, 1 << (w_fmt[0] - 1), (N, K)).astype(np.uint8)
+    got = product(M, N, K, qa, a_fmt, qw, w_fmt).cpu().numpy()
+    assert B.dybit_last_gemm_kernel() == tile
+    want, den = R.gemm(qa, a_fmt, 1.0, qw, w_fmt, 1.0)
+    assert_within(got, want, den)
+
+
+def work_call(M, N, K, a, a_fmt, w, w_fmt, out, work, work_bytes, scale):
+    assert B.lib().dybit_gemm_work(M, N, K, a.data_ptr(), B.fmt(*a_fmt), scale.data_ptr(), w.data_ptr(), B.fmt(*w_fmt), scale.data_ptr(), None, 0,
+                                   out.data_ptr(), out.shape[1], work, work_bytes, B._stream(None)) == B.OK
+    return B.dybit_last_gemm_kernel()
+
+
+def test_entry_point_with_a_workspace():
+    """dybit_gemm_work itself: what it does with less memory than it asks for, none, or some that does not begin on 16 bytes, with rows of results too
+    far apart, and that it keeps to the bytes it asks for."""
+    import torch
+    M, N, K, a_fmt, w_fmt = 3000, 2000, 1532, (8, True), (4, True)
+    need = int(B.lib().dybit_gemm_workspace_bytes(M, N, K, B.fmt(*a_fmt), B.fmt(*w_fmt)))
+    rng = np.random.default_rng(8)
+    a, w = pack_rows_dev(rng.integers(0, 256, (M, K)).astype(np.uint8), 8), pack_rows_dev(rng.integers(0, 16, (N, K)).astype(np.uint8), 4)
+    one, out = scalar(1.0), torch.empty(M, N, device="cuda")
+    args = (M, N, K, a, a_fmt, w, w_fmt)
+    guard = 4096
+    memory = torch.full((need + 2 * guard,), 0xa5, dtype=torch.uint8, device="cuda")
+    at = memory.data_ptr() + guard
+    assert at % 16 == 0
+    assert work_call(*args, out, at, need, one) == "f6_128"
+    assert (memory[:guard] == 0xa5).all() and (memory[guard + need:] == 0xa5).all() and not (memory[guard:guard + need] == 0xa5).all()
+    memory.fill_(0xff)                                           # no contents matter
+    again = torch.empty_like(out)
+    assert work_call(*args, again, at, need + guard, one) == "f6_128" and torch.equal(out, again)
+    memory.fill_(0xa5)
+    for pointer, size in ((at, need - 1), (at, 0), (None, need), (at + 8, need), (at + 1, need)):
+        other = torch.empty_like(out)
+        assert work_call(*args, other, pointer, size, one).startswith("f16_128")
+        assert torch.equal(other, out)                           # integers below 2^24 steps of 2^-8: exact on either kernel
+    assert (memory == 0xa5).all()
+
+
+def test_rows_of_results_too_far_apart():
+    import torch
+    M, N, K, a_fmt, w_fmt, ldc = 130, 200, 2048, (8, True), (4, True), 1 << 23
+    rng = np.random.default_rng(9)
+    qa, qw = rng.integers(0, 256, (M, K)).astype(np.uint8), rng.integers(0, 16, (N, K)).astype(np.uint8)
+    a, w, one = pack_rows_dev(qa, 8), pack_rows_dev(qw, 4), scalar(1.0)
+    out = torch.empty(M, ldc, device="cuda")                     # 4.4 GB
+    memory = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    B.dybit_set_option("gemm_kernel", "six")
+    try:
+        need = int(B.lib().dybit_gemm_workspace_bytes(M, N, K, B.fmt(*a_fmt), B.fmt(*w_fmt)))
+        assert 0 < need <= memory.numel()
+        assert not work_call(M, N, K, a, a_fmt, w, w_fmt, out, memory.data_ptr(), need, one).startswith("f6")
+    finally:
+        B.dybit_set_option("gemm_kernel", "auto")
+    want, den = R.gemm(qa, a_fmt, 1.0, qw, w_fmt, 1.0)
+    assert_within(out[:, :N].cpu().numpy(), want, den)
+
 @pytest.mark.parametrize("ldc_extra", [0, 3])
 @pytest.mark.parametrize("relu", [False, True])
 def test_bias_relu_and_row_pitch(tile, relu, ldc_extra):
