@@ -48,10 +48,14 @@ KERNELS = {"f16_256": "dybit::fast::gemm_fast_kernel (256x256 tiles, fp16 MFMA)"
            "f8_small": "dybit::small::gemm_small_kernel (32-row tiles, K split over the waves, e4m3 MFMA)",
            "f8_patch": "dybit::patch::conv_patch_kernel (input decoded once per tile, e4m3 MFMA)"}
 
-# HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (units of 2 KiB and 1 KiB on
-# this device, calibrated on a 1 GiB copy); the summaries are under profiles/.
-MEASURED_TRAFFIC = {"cfg5": 262303 * 2048 + 262222 * 1024, "cfg2": 2126 * 2048 + 12544 * 1024, "cfg1": None}
-MEASURED_TRAFFIC_GEMM_4BIT = 196756 * 2048 + 262305 * 1024
+# HBM bytes per call at the default sizes from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (units of 2 KiB and 1 KiB on
+# this device, calibrated on a 1 GiB copy); the summaries are under profiles/.  By workload and the kernel that ran: a call on
+# another one reports none.
+MEASURED_TRAFFIC = {("cfg5", "f16_256"): 262303 * 2048 + 262222 * 1024,
+                    ("cfg5", "f6_256"): (49292 + 393290) * 2048 + (147456 + 262234) * 1024,          # split + product
+                    ("cfg5 4-bit", "f8_256"): 196756 * 2048 + 262305 * 1024,
+                    ("cfg5 4-bit", "f6_256"): (32824 + 294994) * 2048 + (98304 + 262277) * 1024,
+                    ("cfg2", "f8_patch"): 2126 * 2048 + 12544 * 1024}
 MEASURED_TRAFFIC_QUANTIZE4 = 524376 * 2048 + 131072 * 1024
 
 
@@ -104,6 +108,65 @@ def time_batches(fn, launches, batches, warmup, torch):
         torch.cuda.synchronize()
         ts.append(s.elapsed_time(e) / launches)
     return float(np.mean(ts))
+
+
+def e3m2_magnitudes():
+    """The 32 non-negative e3m2 values, by code."""
+    return np.array([(m / 16.0) if e == 0 else (1.0 + m / 4.0) * 2.0 ** (e - 3) for e in range(8) for m in range(4)], dtype=np.float64)
+
+
+def e3m2(v):
+    """(codes, values) of the e3m2 numbers nearest to v; of two as near the one with the even code."""
+    mags = e3m2_magnitudes()
+    x = np.abs(v)
+    up = np.clip(np.searchsorted(mags, x), 1, 31)
+    below, above = x - mags[up - 1], mags[up] - x
+    code = np.where((above < below) | ((above == below) & (up % 2 == 0)), up, up - 1)
+    return (code | np.where(v < 0, 32, 0)).astype(np.uint8), np.where(v < 0, -mags[code], mags[code])
+
+
+def e3m2_lanes(codes):
+    """32 codes a lane as its 192 bits, in 32 bytes."""
+    bits = (codes.reshape(-1, 32, 1) >> np.arange(6, dtype=np.uint8)) & 1
+    packed = np.packbits(bits.reshape(-1, 192), axis=1, bitorder="little")
+    return np.pad(packed, ((0, 0), (0, 8)))
+
+
+def split_planes(v, fmt):
+    """Codes of the e3m2 planes of decoded values (one for 2- and 4-bit formats; rounded and the rest for 6- and 8-bit ones, on the
+    powers of two that make both exact)."""
+    if fmt[0] <= 4:
+        return [e3m2(v)[0]]
+    hi, lo = {(8, True): (4.0, 0.25), (6, False): (2.0, 0.5), (6, True): (1.0, 1.0)}[tuple(fmt)]
+    code, value = e3m2(v / hi)
+    rest, left = e3m2((v - value * hi) / lo)
+    assert np.array_equal(value * hi + left * lo, v)
+    return [code, rest]
+
+
+def matrix_cores_alone(ran, low_pair, a, a_fmt, w, w_fmt, sink, B, torch):
+    """(instruction, TFLOP/s) of a loop of the matrix instruction that kernel `ran` uses, on decoded values of its operands (a, w: functions
+    of a number of values); for split operands, whose products are one instruction per pair of planes, per product."""
+    lanes = 512 * 32
+    if ran.startswith("f6"):
+        assert w_fmt[0] <= 4
+        planes = split_planes(a(lanes).double().cpu().numpy(), a_fmt)
+        halves = [e3m2_lanes(p).reshape(-1)[i * lanes // len(planes): (i + 1) * lanes // len(planes)] for i, p in enumerate(planes)]   # waves by plane
+        ops = np.concatenate([*halves, e3m2_lanes(split_planes(w(8 * lanes).double().cpu().numpy(), w_fmt)[0]).reshape(-1)])
+        ops, name, n = torch.from_numpy(ops).cuda(), "e3m2" if len(planes) == 1 else "e3m2, two for a product", len(planes)
+        diag, iters = B.dybit_diag_mfma_f6, 2000
+    elif low_pair:
+        ops, name, n = torch.cat([a(lanes), w(8 * lanes)]).to(torch.float8_e4m3fn).view(torch.uint8).contiguous(), "e4m3", 1
+        diag, iters = B.dybit_diag_mfma_f8, 1000
+    else:
+        def as_decoded(v, fmt):                    # the fp16 kernels decode 6- and 8-bit operands on this scale
+            return v * 2.0 ** -14 if fmt[0] in (6, 8) else v
+        ops, name, n = torch.cat([as_decoded(a(512 * 8), a_fmt), as_decoded(w(8 * 512 * 8), w_fmt)]).to(torch.float16).contiguous(), "f16", 1
+        diag, iters = B.dybit_diag_mfma_f16, 2000
+    wgs = 256 * 2
+    flops = diag(ops, wgs, iters, sink)
+    ms, _ = time_events(lambda: diag(ops, wgs, iters, sink), 5, 2, torch)
+    return name, flops / (ms * 1e-3) / 1e12 / n
 
 
 def network_roofline(work, ms):
@@ -501,7 +564,7 @@ def main():
     value = flops / (ms_per_step * 1e-3) / 1e12
     gemm_tflops = flops / (gemm_ms * 1e-3) / 1e12
 
-    use_f8 = a_fmt[0] == 4 and w_fmt[0] == 4       # pairs of 4-bit formats run on the fp8 matrix path
+    use_f8 = a_fmt[0] == 4 and w_fmt[0] == 4       # pairs of 4-bit formats run on the fp8 matrix path, but for large products
     peak = PEAK_FP8_MFMA_TFLOPS if use_f8 else PEAK_FP16_MFMA_TFLOPS
     dtype = "e4m3" if use_f8 else "f16"
     if ran.startswith("f6"):                       # one matrix instruction per plane of the activations
@@ -518,33 +581,25 @@ def main():
         "roofline": {"bound": "mfma", "kernel": KERNELS.get(ran, ran), "achieved": round(gemm_tflops, 2),
                      "peak": peak, "unit": "TFLOP/s",
                      "frac": round(gemm_tflops / peak, 4),
-                     "kernel_ms": round(gemm_ms, 4), "traffic": MEASURED_TRAFFIC[args.workload]},
+                     "kernel_ms": round(gemm_ms, 4), "traffic": MEASURED_TRAFFIC.get((args.workload, ran)) if args.size == 8192 else None},
     }
 
     # ---------------- the matrix cores alone, on decoded values of this workload ------------
     # (the sustained clock of an MFMA-bound kernel depends on the operand values: the A operand of
     # the instruction gets activation values, the B operands weight values, as in the product)
-    def sample(q, fmt, s, need):
-        n = min(need, q.numel() * 8 // fmt[0])
-        v = B.dybit_dequantize(q[: n * fmt[0] // 8], n, s, *fmt) / s
-        if not use_f8 and fmt[0] in (6, 8):
-            v = v * 2.0 ** -14                     # the fp16 kernels decode 6- and 8-bit operands on this scale
-        return v.repeat((need + n - 1) // n)[:need]
+    one = torch.ones(1, dtype=torch.float32, device="cuda")
+
+    def sample(q, fmt):
+        def values(need):
+            n = min(need, q.numel() * 8 // fmt[0])
+            v = B.dybit_dequantize(q[: n * fmt[0] // 8], n, one, *fmt)
+            return v.repeat((need + n - 1) // n)[:need]
+        return values
     sink = torch.zeros(1, dtype=torch.float32, device="cuda")
-    per_lane = 32 if use_f8 else 8                 # operand elements per lane of one instruction
-    ops = torch.cat([sample(qa, a_fmt, sa, 512 * per_lane), sample(qw, w_fmt, sw, 8 * 512 * per_lane)])
-    if use_f8:
-        ops = ops.to(torch.float8_e4m3fn).view(torch.uint8).contiguous()
-        diag, iters = B.dybit_diag_mfma_f8, 1000
-    else:
-        ops = ops.to(torch.float16).contiguous()
-        diag, iters = B.dybit_diag_mfma_f16, 2000
-    wgs = 256 * 2
-    fl = diag(ops, wgs, iters, sink)
-    mf_ms, _ = time_events(lambda: diag(ops, wgs, iters, sink), 5, 2, torch)
-    out["roofline"]["mfma_only_instruction"] = "e4m3" if use_f8 else "f16"
-    out["roofline"]["mfma_only_measured_TFLOPs"] = round(fl / (mf_ms * 1e-3) / 1e12, 1)
-    out["roofline"]["frac_of_mfma_only_measured"] = round(gemm_tflops / (fl / (mf_ms * 1e-3) / 1e12), 4)
+    instruction, alone = matrix_cores_alone(ran, use_f8, sample(qa, a_fmt), a_fmt, sample(qw, w_fmt), w_fmt, sink, B, torch)
+    out["roofline"]["mfma_only_instruction"] = instruction
+    out["roofline"]["mfma_only_measured_TFLOPs"] = round(alone, 1)
+    out["roofline"]["frac_of_mfma_only_measured"] = round(gemm_tflops / alone, 4)
 
     # ---------------- activation-side passes of the step, timed alone --------------------
     nA = A.numel()
@@ -593,7 +648,7 @@ def main():
         del x, y
 
     # ---------------- the same product with 4-bit activations (4-bit W / 4-bit A) -----------
-    # Two 4-bit operands are exact in e4m3 and run on the fp8 matrix path: its peak is the roofline.
+    # Two 4-bit operands are exact in e3m2 (and e4m3): the matrix peak of the path it ran on is the roofline.
     if args.workload == "cfg5" and not args.no_quantize:
         f4 = (4, True)
         sa4 = B.dybit_absmax_scale(A, *f4)
@@ -603,19 +658,14 @@ def main():
         tf4 = flops / (g4_ms * 1e-3) / 1e12
         ran4 = B.dybit_last_gemm_kernel()
         peak4 = PEAK_FP6_MFMA_TFLOPS if ran4.startswith("f6") else PEAK_FP8_MFMA_TFLOPS
-        # the fp8 matrix cores alone on e4m3 bytes of these values (torch has the dtype; the library only times it)
-        def sample8(q, s, need):
-            v = B.dybit_dequantize(q[: need // 2], need, s, *f4) / s
-            return v.to(torch.float8_e4m3fn).view(torch.uint8)
-        ops8 = torch.cat([sample8(qa4, sa4, 512 * 32), sample8(qw, sw, 8 * 512 * 32)]).contiguous()
-        fl8 = B.dybit_diag_mfma_f8(ops8, 512, 1000, sink)
-        m8_ms, _ = time_events(lambda: B.dybit_diag_mfma_f8(ops8, 512, 1000, sink), 5, 2, torch)
+        instruction4, alone4 = matrix_cores_alone(ran4, True, sample(qa4, f4), f4, sample(qw, w_fmt), w_fmt, sink, B, torch)
         out["roofline_4bit_w_a"] = {"bound": "mfma", "kernel": KERNELS.get(ran4, ran4),
                                     "workload": "the same 8192^3 product with the activations quantized to 4-bit signed",
                                     "achieved": round(tf4, 2), "peak": peak4, "unit": "TFLOP/s",
-                                    "frac": round(tf4 / peak4, 4), "kernel_ms": round(g4_ms, 4), "mfma_only_instruction": "e4m3", "traffic": MEASURED_TRAFFIC_GEMM_4BIT,
-                                    "mfma_only_measured_TFLOPs": round(fl8 / (m8_ms * 1e-3) / 1e12, 1),
-                                    "frac_of_mfma_only_measured": round(tf4 / (fl8 / (m8_ms * 1e-3) / 1e12), 4)}
+                                    "frac": round(tf4 / peak4, 4), "kernel_ms": round(g4_ms, 4), "mfma_only_instruction": instruction4,
+                                    "traffic": MEASURED_TRAFFIC.get(("cfg5 4-bit", ran4)) if args.size == 8192 else None,
+                                    "mfma_only_measured_TFLOPs": round(alone4, 1),
+                                    "frac_of_mfma_only_measured": round(tf4 / alone4, 4)}
         out["value_4bit_w_a"] = {"value": round(tf4, 2), "unit": "TOPS", "what": "the same product at 4-bit W / 4-bit A, kernel alone"}
         del C4, qa4
 

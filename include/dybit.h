@@ -483,6 +483,11 @@ dybit_status dybit_diag_mfma_f16(const void *operands, int32_t workgroups, int32
 dybit_status dybit_diag_mfma_f8(const void *operands, int32_t workgroups, int32_t iters,
                                 float *sink, double *flops_out, dybit_stream stream);
 
+/* The same for the fp6 (e3m2) MFMA instruction of the split products.  operands as above; of each 32 bytes the first
+ * 24 hold 32 values of 6 bits. */
+dybit_status dybit_diag_mfma_f6(const void *operands, int32_t workgroups, int32_t iters,
+                                float *sink, double *flops_out, dybit_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -122,6 +122,7 @@ def lib() -> C.CDLL:
         L.dybit_set_option.argtypes = [C.c_char_p, C.c_char_p]
         L.dybit_diag_mfma_f16.argtypes = [vp, i32, i32, vp, C.POINTER(C.c_double), vp]
         L.dybit_diag_mfma_f8.argtypes = [vp, i32, i32, vp, C.POINTER(C.c_double), vp]
+        L.dybit_diag_mfma_f6.argtypes = [vp, i32, i32, vp, C.POINTER(C.c_double), vp]
         _lib = L
     return _lib
 
@@ -595,4 +596,12 @@ def dybit_diag_mfma_f8(operands: torch.Tensor, workgroups: int, iters: int, sink
     flops = C.c_double(0.0)
     _check(lib().dybit_diag_mfma_f8(_ptr(operands), workgroups, iters, _ptr(sink), C.byref(flops), _stream(stream)),
            "dybit_diag_mfma_f8")
+    return float(flops.value)
+
+
+def dybit_diag_mfma_f6(operands: torch.Tensor, workgroups: int, iters: int, sink: torch.Tensor, stream=None) -> float:
+    """The same for the fp6 (e3m2) instruction; of each 32 bytes of `operands` the first 24 hold 32 values."""
+    flops = C.c_double(0.0)
+    _check(lib().dybit_diag_mfma_f6(_ptr(operands), workgroups, iters, _ptr(sink), C.byref(flops), _stream(stream)),
+           "dybit_diag_mfma_f6")
     return float(flops.value)
