@@ -165,7 +165,8 @@ PyObject *gemm(PyObject *self, PyObject *const *args, Py_ssize_t n)
     if (n != Gemm::kCount || args[kStream] != Py_None) return Gemm::call(self, args, n);
     try {
         const Gemm::Arguments a = Gemm::arguments(args);
-        const size_t need = dybit_gemm_workspace_bytes(std::get<0>(a), std::get<1>(a), std::get<2>(a), std::get<4>(a), std::get<7>(a));
+        const bool results = std::get<11>(a) != nullptr;                 // else the call is refused
+        const size_t need = results ? dybit_gemm_workspace_bytes(std::get<0>(a), std::get<1>(a), std::get<2>(a), std::get<4>(a), std::get<7>(a)) : 0;
         const c10::DataPtr work = need ? scratch(need) : c10::DataPtr();
         if (!work) return PyLong_FromLong((long)Gemm::run(a));
         const auto with_work = std::tuple_cat(front(a, std::make_index_sequence<kStream>{}),

@@ -203,12 +203,15 @@ def test_no_memory_for_a_workspace():
     torch.cuda.empty_cache()
     total = torch.cuda.get_device_properties(0).total_memory
     torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + need // 4) / total)
+    taken = []
     try:
-        with pytest.raises(torch.cuda.OutOfMemoryError):
-            torch.empty(need, dtype=torch.uint8, device="cuda")
+        with pytest.raises(torch.cuda.OutOfMemoryError):         # what other tests have left in the allocator's segments as well
+            while True:
+                taken.append(torch.empty(need, dtype=torch.uint8, device="cuda"))
         assert B.dybit_gemm(*args, out=out) is out
         assert B.dybit_last_gemm_kernel() == "f16_256"
     finally:
+        taken.clear()
         torch.cuda.set_per_process_memory_fraction(1.0)
     # the same products in another order of summation: 2^-24 of sum |a b| for each of the K / 16 steps that add into a result, at most
     bound = (K / 16 + 1) * 2.0 ** -24 * 0.125 * K * 64 * 4
