@@ -13,6 +13,9 @@
 namespace dybit {
 
 __device__ int g_async_error = 0;
+namespace {
+thread_local int *tl_error_word = nullptr;        // caller-owned word of this host thread, or NULL: the library's
+}
 
 constexpr int kThreads = 256;
 // Tuning knobs of the quantize pass (swept on the device, from 2^20 to 2^28 elements: four 128-bit loads
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(kJoinThreads) void absmax_joined_kernel(const float
     mx = workgroup_max<kJoinBlocks>(mx);
     if (threadIdx.x == 0) {
         *scale_out = missing ? __uint_as_float(0x7fc00000u) : scale_of_max(mx, inv_vmax);
-        if (missing) *err = DYBIT_ERR_BAD_SCALE;
+        if (missing) *(err ? err : &g_async_error) = DYBIT_ERR_BAD_SCALE;
     }
 }
 
@@ -920,11 +923,9 @@ static dybit_status absmax_impl(const float *x, size_t n, dybit_fmt f, float *sc
         static std::atomic<uint64_t> launches{0};
         uint64_t tag = (launches.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;   // odd factor: all different
         tag ^= tag >> 32;                                                  // one to one: still all different, and 0 for none
-        int *err = async_error_word();
-        if (!err) return DYBIT_ERR_HIP;
         hipLaunchKernelGGL(stream_past ? absmax_joined_kernel<true> : absmax_joined_kernel<false>, dim3(grid), dim3(kJoinThreads), 0, hs, x, n, shift,
                            scale_out, inv_vmax,
-                           reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32), absmax_looks(), err);
+                           reinterpret_cast<uint64_t *>(workspace), (uint32_t)tag, (uint32_t)(tag >> 32), absmax_looks(), tl_error_word);   // NULL: the library's, which the kernel knows
     } else {
         const int blocks = grid_for(n / 4 + 1, kThreads * 4, 1024);
         hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, hs, scale_out);
@@ -1146,9 +1147,6 @@ extern "C" dybit_status dybit_dequantize(const uint8_t *codes, size_t n, dybit_f
 }
 
 namespace dybit {
-namespace {
-thread_local int *tl_error_word = nullptr;        // caller-owned word of this host thread, or NULL: the library's
-}
 // Device word that receives asynchronous errors of the calls this host thread makes: the caller's
 // (dybit_set_async_error_word), else the library's own on the current device (each device has its copy;
 // the address is looked up once per device).
