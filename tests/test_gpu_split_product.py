@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import dybit_ref as R
-from gpu_util import assert_within, dev, pack_rows_dev, scalar
+from gpu_util import assert_within, dev, oracle_codes, pack_rows_dev, scalar
 from paper_2302_12510_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -142,6 +142,7 @@ def test_rows_of_results_too_far_apart():
     want, den = R.gemm(qa, a_fmt, 1.0, qw, w_fmt, 1.0)
     assert_within(out[:, :N].cpu().numpy(), want, den)
 
+
 @pytest.mark.parametrize("ldc_extra", [0, 3])
 @pytest.mark.parametrize("relu", [False, True])
 def test_bias_relu_and_row_pitch(tile, relu, ldc_extra):
@@ -217,3 +218,26 @@ def test_no_memory_for_a_workspace():
     bound = (K / 16 + 1) * 2.0 ** -24 * 0.125 * K * 64 * 4
     assert (out - want).abs().max().item() <= bound
     assert B.dybit_gemm(*args).equal(want) and B.dybit_last_gemm_kernel() == "f6_256"
+
+
+@pytest.mark.parametrize("a_bits,before", [(8, "f16_256"), (4, "f8_256")])
+def test_8192_cubed_on_either_kernel(a_bits, before):
+    """The benchmark's 8192^3 products: as a call takes them, and on the kernel that callers without a workspace get; the oracle evaluates a
+    sample of rows and columns exactly."""
+    import torch
+    from paper_2302_12510_amd import synth
+    size, a_fmt, w_fmt = 8192, (a_bits, True), (4, True)
+    cfg = synth.config5a(size=size)
+    (sa, qa), (sw, qw) = oracle_codes(cfg["A"], a_fmt), oracle_codes(cfg["W"], w_fmt)
+    a, w = pack_rows_dev(qa, a_bits), pack_rows_dev(qw, 4)
+    rng = np.random.default_rng(a_bits)
+    rows, cols = (np.unique(np.concatenate([[0, 127, 128, 255, 256, size - 1], rng.integers(0, size, n)])) for n in (60, 508))
+    want, den = R.gemm(qa[rows], a_fmt, sa, qw[cols], w_fmt, sw)
+    for option, kernel in (("auto", "f6_256"), ("large", before)):
+        B.dybit_set_option("gemm_kernel", option)
+        try:
+            c = B.dybit_gemm(size, size, size, a, a_fmt, scalar(sa), w, w_fmt, scalar(sw))
+        finally:
+            B.dybit_set_option("gemm_kernel", "auto")
+        assert B.dybit_last_gemm_kernel() == kernel
+        assert_within(c[torch.from_numpy(rows).cuda()][:, torch.from_numpy(cols).cuda()].cpu().numpy(), want, den)
