@@ -221,7 +221,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
         a_k0 = 0;
         tap = TapCounter();
         load_A(rawA[0]);
-        if (ktiles > 1) load_A(rawA[1]);                             // uniform
+        if (!AHEAD || ktiles > 1) load_A(rawA[1]);                   // uniform; a condition would keep rawA alive from slab to slab
     };
     if constexpr (AHEAD) request(cg.walker);
 
@@ -257,7 +257,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
     float run_max = 0.0f;                                            // max |C| over every strip this lane stores
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) break;                                   // uniform per wave; no barriers below
+        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below; `break` spills more scalars
         if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
         f16x8 fa = decode_A(rawA[0], 0);
@@ -431,7 +431,7 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
     float run_max = 0.0f;
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) break;                                   // uniform per wave; no barriers below
+        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below
         if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
         i32x8 fa = f8::decode_fragment<FMT_A, true>(rawA[0]);
