@@ -51,8 +51,8 @@ def spills(tmp_path_factory):
 
 def test_weight_stationary_fp32(spills):
     """Template arguments: formats of A and W, convolution (0: product), blocks of 32 columns, outputs (0: fp32).  What the accumulators, two K
-    steps of codes and the epilogue need is 6 to 10 registers more than four waves per SIMD have, for a convolution up to 33."""
+    steps of codes and the epilogue need is 6 to 12 registers more than four waves per SIMD have, for a convolution up to 33."""
     kernels = {tuple(map(int, re.findall(r"Li(\d+)E", name))): n for name, n in spills.items() if "14gemm_ws_kernelI" in name}
     kernels = {a: n for a, n in kernels.items() if a[4] == 0}
     assert len(kernels) == 8 * 4 * 3 * 2
-    assert {a: n for a, n in kernels.items() if n > (0 if a[3] == 4 else 10 if a[2] == 0 else 33)} == {}
+    assert {a: n for a, n in kernels.items() if n > (0 if a[3] == 4 else 12 if a[2] == 0 else 33)} == {}
