@@ -55,7 +55,7 @@ __device__ __forceinline__ u32x4 decode_eight_in_order(const u32x4 *raw, int q)
                  __builtin_amdgcn_perm(d[3], d[2], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u)};
 }
 
-template <int FMT_A, int FMT_W, int OUT, int Q>
+template <int FMT_A, int FMT_W, int OUT, int Q, int R>
 __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs g, const FewArgs f)
 {
     using CA = Codec<FMT_A>;
@@ -187,9 +187,9 @@ __global__ __launch_bounds__(kMaxThreads, 4) void conv_few_kernel(const GemmArgs
                     for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
             }
             for (; fr < g.kh; ++fr) filter_row(std::false_type{});
-            GemmArgs ge = OUT == OUT_CODES && Q == 0 ? reload_args() : g;
+            GemmArgs ge = OUT == OUT_CODES && R != 0 ? reload_args() : g;   // kept over the loop, a shortcut's fill the scalar registers
             ge.M = m_unit + outputs;                                   // the epilogue stores no row past the unit
-            if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, ACC, Q>(ge, acc, m_unit + s, n0, cols, big, os));
+            if constexpr (OUT == OUT_CODES) run_max = fmaxf(run_max, epilogue_strip_codes<CB, ACC, Q, R>(ge, acc, m_unit + s, n0, cols, big, os));
             else run_max = fmaxf(run_max, epilogue_strip<CB, false, false, ACC>(ge, acc, m_unit + s, n0));
         }
     }
@@ -263,11 +263,13 @@ static bool launch(const GemmArgs &g, hipStream_t st)
     int walkers = resident / f.parts;
     if (walkers < 1) walkers = 1;
     if (walkers > f.units) walkers = f.units;
-    // codes without a shortcut: a kernel per width of the codes.  The one with all forms computes the uniform values of each of them
-    // and keeps them in vector registers: 64 x 224 x 224 at 8 bits to 4-bit codes 31.1 -> 27.4 us
-    auto k = conv_few_kernel<FA, FW, kOut, 0>;
-    if constexpr (kOut == OUT_CODES)
-        if (!g.res_codes) k = g.q_bits == 4 ? conv_few_kernel<FA, FW, kOut, 4> : g.q_bits == 8 ? conv_few_kernel<FA, FW, kOut, 8> : conv_few_kernel<FA, FW, kOut, 6>;
+    // codes: a kernel per form of them.  One with all forms computes the uniform values of each of them
+    // and keeps them in vector registers: 64 x 224 x 224 at 8 bits to 4-bit codes 31.1 -> 27.4 us; with a shortcut, 77 calls, 0.94 times the time
+    // (and 0.96 of that with the arguments read again for each strip: 25088 outputs, 4 x 4 taps of 4 to 128, 19.0 -> 15.8)
+    auto k = [&] {
+        if constexpr (kOut == OUT_CODES) return kernel_for_codes(g, [](auto q, auto r) { return conv_few_kernel<FA, FW, kOut, q(), r()>; });
+        else return conv_few_kernel<FA, FW, kOut, 0, 0>;
+    }();
     note_kernel(DYBIT_KERNEL_F16_FEW);
     note_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit));
     hipLaunchKernelGGL(k, dim3((unsigned)(walkers * f.parts)), dim3(64 * waves), lds_bytes, st, g, f);
