@@ -257,7 +257,10 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
     float run_max = 0.0f;                                            // max |C| over every strip this lane stores
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below; `break` spills more scalars
+        if (m_strip >= g.M) {                                        // uniform per wave; no barriers below
+            if constexpr (OUT == OUT_CODES) break;                   // the later slabs are past the end too
+            else continue;                                           // `break` spills up to 6 more scalar registers here
+        }
         if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
         f16x8 fa = decode_A(rawA[0], 0);
@@ -431,7 +434,10 @@ __global__ __launch_bounds__((64 * waves_of<CB, OUT>()), (CB == 2 ? (OUT == OUT_
     float run_max = 0.0f;
     for (int slab = cg.walker; slab < slabs; slab += cg.walkers) {
         const int64_t m_strip = (int64_t)slab * SLAB + wave * 32;
-        if (m_strip >= g.M) continue;                                // uniform per wave; no barriers below
+        if (m_strip >= g.M) {                                        // see the fp16 form
+            if constexpr (OUT == OUT_CODES) break;
+            else continue;
+        }
         if constexpr (!AHEAD) request(slab);
         f32x16 acc[CB];
         i32x8 fa = f8::decode_fragment<FMT_A, true>(rawA[0]);
