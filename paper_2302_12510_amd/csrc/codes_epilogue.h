@@ -65,9 +65,9 @@ __device__ __forceinline__ bool stage_columns(const GemmArgs &g, const int64_t n
     return any;
 }
 
-// The kernel's arguments, read again from the kernel-argument segment by each call: the persistent loop's epilogue has a
-// variant per format of its codes, and the compiler otherwise computes the uniform values of all of them once, before the
-// loop, where they exceed the scalar registers (157 spilled, each a v_readlane per slab) -- the scalar loads are cheaper.
+// The kernel's arguments, read again from the kernel-argument segment by each call: a persistent loop's uniform values are otherwise
+// computed once, before the loop, and where they exceed the scalar registers (the few-channel kernel with a shortcut: 73 to 84
+// spilled, each a v_readlane per strip) the scalar loads are cheaper.
 __device__ __forceinline__ GemmArgs reload_args()
 {
     struct Words { uint64_t w[sizeof(GemmArgs) / 8]; } words;

@@ -372,9 +372,9 @@ bool launch_gemm_tiled(const GemmArgs &g, int a_bits, int w_bits, bool conv, hip
 // it only a slower split; but the operands go through memory once more, and its tiles have the longer fill.  Measured over 9000 products
 // (M, N from 96 and K from 200 to 9000, all formats it takes; us, the kernel before -> this one, the split included); of the 2078 taken, 0.63 times
 // the time in the geometric mean, 12 more than the same, at most 1.05 times:
-//   more than 256 tiles of 128 x 128: two planes with K from 1024 on (8192^3, 8- by 4-bit 830 -> 500; 5203 x 3732 x 1144 68.1 -> 51.5, but
+//   more than 256 tiles of 128 x 128: two planes with K from 1024 on (8192^3, 8- by 4-bit 775 to 840 -> 470 to 510 over cards; 5203 x 3732 x 1144 68.1 -> 51.5, but
 //     5351 x 2368 x 320 20.3 -> 22.3); one plane where the e4m3 kernels have their 256 x 256 tile or K from 3072 on (8192^3, 4-bit
-//     pair 404 -> 273; 4657 x 4891 x 3968 139 -> 76, but 2196 x 2672 x 960 14.2 -> 16.5); one plane and ragged rows, which have no e4m3 form
+//     pair 400 to 415 -> 267 to 288; 4657 x 4891 x 3968 139 -> 76, but 2196 x 2672 x 960 14.2 -> 16.5); one plane and ragged rows, which have no e4m3 form
 //     there, with K from 512 on (2368 x 6144 x 1740, 2-bit pair 70.4 -> 33.7);
 //   from there down to the line of the small-output kernel: one plane and ragged rows, K from 1536 on (3281 x 800 x 3004, 4-bit pair 0.5 to 0.9
 //     times); two planes, K from 2560 and both sides from 768 on (1874 x 1024 x 8584 75.5 -> 59.2; with one short side the split is most of

@@ -17,9 +17,10 @@
 // it, more than the matrix instructions leave room for; here it is done once, and the loop of the product holds nothing but loads
 // to LDS, fragment reads and matrix instructions.
 //
-// What bounds it, 8192^3: 8- by 4-bit (455 us, 35 of the split before it; fp16 kernel 790 to 840) the device's power: matrix cores busy 73 % of the
-// time at 1.57 GHz, where a loop of the same instruction alone on such values holds 1.6 to 1.65; a 4-bit pair (250 us; e4m3 kernel 400) the
-// loads to LDS, 24 KiB per 64 k of a tile.  For 128 x 128 tiles these are twice as many per matrix instruction.
+// What bounds it, 8192^3: 8- by 4-bit (470 to 510 us over cards, 39 of the split before it; fp16 kernel 775 to 840) the device's power: matrix
+// cores busy 76 % of the time at 1.59 GHz, 0.82 of the rate of a loop of the same instruction alone on such values, which holds 1.48 GHz; a 4-bit
+// pair (267 to 288 us, 25 of the split; e4m3 kernel 400 to 415; busy 66 %, 0.68 of its loop's rate) the loads to LDS, 24 KiB per 64 k of a
+// tile.  For 128 x 128 tiles these are twice as many per matrix instruction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
