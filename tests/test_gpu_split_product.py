@@ -241,3 +241,35 @@ def test_8192_cubed_on_either_kernel(a_bits, before):
             B.dybit_set_option("gemm_kernel", "auto")
         assert B.dybit_last_gemm_kernel() == kernel
         assert_within(c[torch.from_numpy(rows).cuda()][:, torch.from_numpy(cols).cuda()].cpu().numpy(), want, den)
+
+
+@pytest.mark.parametrize("a_fmt,w_fmt", [((8, True), (4, True)), ((4, True), (8, True)), ((2, False), (8, True))])
+@pytest.mark.parametrize("K", [32768, 32772])
+def test_tiles_of_128_keep_two_sums(a_fmt, w_fmt, K):
+    """Sums of positive products that outgrow 2^24 steps of theirs, but no half of them does: the halves (128 k in turn) are exact, as the two
+    k-groups of the kernel such products ran on are, and the result is their sum rounded once."""
+    M, N = 70, 130
+    a_bits, w_bits = a_fmt[0] - a_fmt[1], w_fmt[0] - 1
+    step = 2.0 ** (1 - a_bits) * 2.0 ** (1 - w_bits)
+    rng = np.random.default_rng(K + a_fmt[0])
+    qa, qw = (rng.integers(0, 1 << b, s) for b, s in ((a_bits, (M, K)), (w_bits, (N, K))))
+    value_a, value_w = (R.codebook(*f)[:1 << b].astype(np.float64) for f, b in ((a_fmt, a_bits), (w_fmt, w_bits)))
+    mean = K * value_a.mean() * value_w.mean() / step
+    if mean < 1.4 * 2 ** 24:                                     # more of the largest codes, until the mean is 1.4 * 2^24 steps
+        top = value_a[-1] * value_w[-1] * K / step
+        share = (1.4 * 2 ** 24 - mean) / (top - mean)
+        k = rng.random(K) < share
+        qa[:, k], qw[:, k] = (1 << a_bits) - 1, (1 << w_bits) - 1
+    qa, qw = qa.astype(np.uint8), qw.astype(np.uint8)
+    turn = np.arange(K) // 128 % 2
+    halves = [np.asarray(R.gemm(qa[:, turn == t], a_fmt, 1.0, qw[:, turn == t], w_fmt, 1.0)[0], dtype=np.float64) for t in (0, 1)]
+    assert max(h.max() for h in halves) < 2 ** 24 * step < (halves[0] + halves[1]).min()
+    B.dybit_set_option("gemm_kernel", "six")
+    B.dybit_set_option("mid_tile", "128")
+    try:
+        got = product(M, N, K, qa, a_fmt, qw, w_fmt).cpu().numpy()
+    finally:
+        B.dybit_set_option("gemm_kernel", "auto")
+        B.dybit_set_option("mid_tile", "auto")
+    assert B.dybit_last_gemm_kernel() == "f6_128"
+    assert np.array_equal(got, (halves[0] + halves[1]).astype(np.float32))
